@@ -165,8 +165,8 @@ hipError_t launch_prefill_attention(const AttnArgs& a, hipStream_t st);
 // Up to SB_PREFILL_PASSES passes of one layer go into one launch (a "super-pass"), so
 // that the passes' thread blocks meet on the same weights in the caches.  Activations
 // come as bf16 planes xs [2][plane_rows][K] (high parts, then low parts; row r of pass p
-// is row p * SB_PREFILL_ROWS + r); the product is left as k-split partial sums
-// part [n_pass][S][SB_PREFILL_ROWS][rows] for the epilogue that follows.
+// is row p * pass_rows + r); the product is left as k-split partial sums
+// part [n_pass][S][pass_rows][rows] for the epilogue that follows.
 #define SB_PREFILL_PASSES 16
 struct GemmArgs {
     const void* Wp;      // packed weights [rows][K]
@@ -175,6 +175,7 @@ struct GemmArgs {
     int32_t plane_rows;
     int32_t M;           // live rows over all passes
     int32_t n_pass;      // ceil(M / SB_PREFILL_ROWS)
+    int32_t pass_rows;   // set by launch_prefill_gemm: rows per pass, the M rows in n_pass equal parts of whole 16-row tiles
     float* part;
     int32_t S;           // partial-sum slots per row block, from gemm_splits()
     // Tail done by the GEMM itself for the row blocks (256 weight rows) whose whole k range one thread
@@ -191,7 +192,7 @@ struct GemmArgs {
     float* y;            // STORE: [M][ldy]
     int32_t ldy;
 };
-int gemm_splits(int32_t rows, int32_t K, int32_t n_pass);
+int gemm_splits(int32_t rows, int32_t K, int32_t n_pass, bool gate_up = false);  // gate_up: the fused SwiGLU tail
 hipError_t launch_prefill_gemm(const GemmArgs& a, hipStream_t st);
 
 // Sums the k splits in order, applies the RMSNorm scale of the input row (from the

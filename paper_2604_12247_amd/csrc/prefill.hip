@@ -20,30 +20,36 @@ namespace sb {
 
 namespace {
 constexpr int PM = SB_PREFILL_ROWS;
+constexpr int WPB = 8;                     // waves per thread block, one thread block per CU
 constexpr int ROWB = 288;                  // LDS bytes per staged row: 128 bf16 + 32 bytes of padding (16-byte operand
                                            // reads at rows 272 bytes apart measure as 2-way bank conflicts, at 288 as none)
-constexpr int STAGE = 2 * PM * ROWB;       // one k block of both planes
-constexpr int WPB = 8;                     // waves per thread block (one block per CU: two LDS stages take 144 KB)
-constexpr int LDS_BYTES = 2 * STAGE + PM * 4;  // two stages + the rows' scales
-constexpr int BLOCK_ROWS = 256;            // weight rows of a row block: 8 row groups x 2 tiles of 16
+constexpr int stage_bytes(int ct) { return 2 * ct * 16 * ROWB; }            // one k block of both planes
+constexpr int lds_bytes(int ct) { return 2 * stage_bytes(ct) + PM * 4; }    // two stages + the rows' scales
 }  // namespace
 
-// Work decomposition: the (row block, k block) pairs are numbered row block first and
-// cut into equal contiguous ranges, one per thread block, so that every block streams
-// the same number of weight bytes whatever the shape (a plain k split leaves a ragged
-// last round of blocks on 256 CUs).  A range may end in the middle of a row block: each
-// thread block that touches a row block leaves one partial sum for it, in slot
-// (range index - first range of that row block).
+// Work decomposition: the rows of the super-pass are cut into equal passes of at most PM rows
+// (whole 16-row column tiles), the weight rows into row blocks (8 waves x rt tiles of 16).  Per pass,
+// the (row block, k block) pairs are numbered row block first and cut into equal contiguous
+// ranges, one per thread block, so that every block streams the same number of weight bytes
+// whatever the shape (a plain k split leaves a ragged last round of blocks on 256 CUs).  A range
+// may end in the middle of a row block: each thread block that touches a row block leaves one
+// partial sum for it, in slot (range index - first range of that row block).  rt, q and grid depend on
+// the weights' shape and the number of passes only, so a row's sums do not depend on the rows beside
+// it within a launch of as many passes.
 struct GemmPlan {
-    int nb;      // row blocks
-    int q;       // (row block, k block) pairs per thread block
-    int grid;    // thread blocks
-    int smax;    // most partial sums a row block can get
+    int rt;          // 16-row weight tiles per wave
+    int block_rows;  // weight rows of a row block
+    int nb;          // row blocks
+    int q;           // (row block, k block) pairs per thread block
+    int grid;        // thread blocks per pass
+    int smax;        // most partial sums a row block can get
 };
-static GemmPlan gemm_plan(int32_t rows, int32_t K, int32_t n_pass) {
+static GemmPlan gemm_plan_rt(int32_t rows, int32_t K, int32_t n_pass, int rt) {
     GemmPlan p;
     const int KB = K >> 7;
-    p.nb = (rows + BLOCK_ROWS - 1) / BLOCK_ROWS;
+    p.rt = rt;
+    p.block_rows = WPB * rt * 16;
+    p.nb = (rows + p.block_rows - 1) / p.block_rows;
     const long total = (long)p.nb * KB;
     // resident thread blocks: one per CU (LDS), shared out among the passes of the launch --
     // every pass gets the same cut, so the blocks of different passes that work on the same
@@ -57,200 +63,207 @@ static GemmPlan gemm_plan(int32_t rows, int32_t K, int32_t n_pass) {
     if (p.smax > KB) p.smax = KB;
     return p;
 }
-int gemm_splits(int32_t rows, int32_t K, int32_t n_pass) { return gemm_plan(rows, K, n_pass).smax; }
+// Tiles per wave.  A wave reads the pass's activations from LDS once per tile set: with two tiles these reads
+// alone keep the LDS as busy as the matrix cores are, with four half as busy ([28672 x 4096] at 1999 rows: 821
+// and 739 us), but twice the weight rows per thread block leave twice the partial sums: four where
+// a thread block still gets half a row block's k range or more (measured about even below it: [12288 x 4096] at
+// 512 rows 120 and 126 us with their epilogues, [4096 x 11008] at 1024 rows 183 and 196).  A single pass is bound
+// by the weight stream: small matrices take one tile, so that a thread block's range is long and its partial
+// sums few ([12288 x 4096] at 45 rows 22 and 28 us, [5120 x 13824] at 128 rows 60 and 43: the line lies between).
+static GemmPlan gemm_plan(int32_t rows, int32_t K, int32_t n_pass, bool gate_up) {
+    const int KB = K >> 7;
+    if (n_pass == 1) {
+        const GemmPlan p = gemm_plan_rt(rows, K, 1, 1);
+        return p.q <= 12 && !gate_up ? p : gemm_plan_rt(rows, K, 1, 2);   // (gate and up tiles meet in one wave)
+    }
+    const GemmPlan p = gemm_plan_rt(rows, K, n_pass, 4);
+    return 2 * p.q >= KB ? p : gemm_plan_rt(rows, K, n_pass, 2);
+}
+int gemm_splits(int32_t rows, int32_t K, int32_t n_pass, bool gate_up) { return gemm_plan(rows, K, n_pass, gate_up).smax; }
+// Rows of a pass: the super-pass in n_pass equal parts, rounded up to whole column tiles.
+static int gemm_pass_rows(int32_t M, int32_t n_pass) { return ((M + n_pass - 1) / n_pass + 15) / 16 * 16; }
 
 // ---- pieces of the GEMM kernel (all inlined; register arrays are passed by reference) ----
 struct GemmCtx {
-    const uint16_t* W;      // packed weights + this lane's 16 bytes
-    const uint16_t* bsrc0;  // this thread's first staging unit in the activation planes
-    int bdst0;              // ... and in an LDS stage
-    int K, KB, n_tiles, it1, wr, wt, li, lq;  // wr: the wave's row group, wt: its share of the pass's rows
-    int lo_off;             // rows from a high-plane row to its low-plane row
-    int Mp, cid, pass;      // live rows of this pass, range index, pass
-    int n_out_tiles;        // fused gate/up: 16-column groups of the output (gate tile j pairs with up tile n_out_tiles + j)
+    int KB, n_tiles, it1, wr;          // wr: the wave's row group
+    int Mp, cid, pass, row0;           // live rows of this pass, range index, pass, its first row
+    int n_out_tiles;                   // fused gate/up: 16-column groups of the output (gate tile j pairs with up tile n_out_tiles + j)
 };
 
-// Weights of half a pair: half-step h = 2 * pair + (0 | 1) covers MFMA steps 2 (h & 1) and
-// 2 (h & 1) + 1 of the pair's k block.  (Clamped to the block's range: a re-read of the last
-// half keeps the steady-state loop free of conditional loads, whose completion could only be
-// waited for conservatively.)  STREAM: the weights are read once by this launch (a single
-// pass), so the loads carry the streaming hint; with several passes the other passes' blocks
-// read the same lines and they are left to the caches.
 // Weight tile t of this wave in row block b; -1 past the end.  Gate/up with the fused tail: the
-// wave's two tiles are the gate and the up tile of one group of 16 outputs.
-template <int RT, int RG, int FE>
+// wave's tiles are the gate tiles of RT / 2 groups of 16 outputs, then their up tiles.
+template <int RT, bool SWI>
 __device__ __forceinline__ int gemm_tile(const GemmCtx& c, int b, int t) {
-    if (FE == 1 + EPI_SWIGLU) {
-        const int j = b * RG + c.wr;
-        return j < c.n_out_tiles ? (t == 0 ? j : c.n_out_tiles + j) : -1;
+    if (SWI) {
+        const int j = (b * WPB + c.wr) * (RT / 2) + t % (RT / 2);
+        return j < c.n_out_tiles ? (t < RT / 2 ? j : c.n_out_tiles + j) : -1;
     }
-    const int tile = (b * RG + c.wr) * RT + t;
+    const int tile = (b * WPB + c.wr) * RT + t;
     return tile < c.n_tiles ? tile : -1;
 }
-template <int RT, bool STREAM, int RG, int FE>
-__device__ __forceinline__ void gemm_load_a(uint4 (&ar)[RT][2], const GemmCtx& c, int h_) {
-    const int h = h_ < 2 * c.it1 ? h_ : 2 * c.it1 - 1;
-    const int it = h >> 1, b = it / c.KB, kb = it - b * c.KB;
-#pragma unroll
-    for (int t = 0; t < RT; ++t) {
-        int tile = gemm_tile<RT, RG, FE>(c, b, t);
-        if (tile < 0) tile = c.n_tiles - 1;  // a tile past the end re-reads the last one (not stored)
-        const uint16_t* wp = c.W + ((size_t)tile * c.KB + kb) * 2048 + (h & 1) * 1024;
-#pragma unroll
-        for (int u = 0; u < 2; ++u)
-            ar[t][u] = STREAM ? ld_weights_packed(wp + u * 512) : *reinterpret_cast<const uint4*>(wp + u * 512);
-    }
-}
-// Staging map: 2 planes x PM rows x 16 segments of 16 bytes, NBU per thread; unit i of a
-// thread lies RPI rows below unit i - 1 (same segment), first in the high plane, then in
-// the low plane.  Rows past the live ones are read too, from the planes' unused rows:
-// whatever they hold only reaches result columns that are never stored.
-constexpr int NBU = 2 * PM * 16 / (64 * WPB);
-constexpr int RPI = 4 * WPB;
-__device__ __forceinline__ void gemm_load_b(u32x4 (&br)[NBU], const GemmCtx& c, int it_) {
-    const int it = it_ < c.it1 ? it_ : c.it1 - 1;
-    const int kb = it % c.KB;
-#pragma unroll
-    for (int i = 0; i < NBU; ++i) {
-        const int row = i * RPI < PM ? i * RPI : c.lo_off + i * RPI - PM;  // high plane, then low plane
-        br[i] = *reinterpret_cast<const u32x4*>(c.bsrc0 + (size_t)row * c.K + (size_t)kb * 128);
-    }
-}
-__device__ __forceinline__ void gemm_store_b(unsigned char* dst, const u32x4 (&br)[NBU], const GemmCtx& c) {
-#pragma unroll
-    for (int i = 0; i < NBU; ++i) *reinterpret_cast<u32x4*>(dst + c.bdst0 + i * RPI * ROWB) = br[i];
-}
-// A wave multiplies its RT weight tiles with the CTW column tiles (16 rows each) of its share of
-// the pass: one LDS operand read serves RT MFMAs.  All column tiles are always multiplied, so
-// the block of LDS reads and MFMAs stays free of branches.
-template <int RT, int CTW>
-__device__ __forceinline__ void gemm_mma(f32x4 (&acc)[RT][CTW], const uint4 (&ar)[RT][2], const unsigned char* src,
-                                         const GemmCtx& c, int uhalf) {
-#pragma unroll
-    for (int uu = 0; uu < 2; ++uu) {
-#pragma unroll
-        for (int ct = 0; ct < CTW; ++ct) {
-            const unsigned char* rp = src + ((c.wt * CTW + ct) * 16 + c.li) * ROWB + (uhalf * 2 + uu) * 64 + c.lq * 16;
-            const bf16x8 bh = *reinterpret_cast<const bf16x8*>(rp);
-            const bf16x8 bl = *reinterpret_cast<const bf16x8*>(rp + PM * ROWB);
-#pragma unroll
-            for (int t = 0; t < RT; ++t)
-                acc[t][ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, ar[t][uu]), bh, acc[t][ct],
-                                                                     0, 0, 0);
-#pragma unroll
-            for (int t = 0; t < RT; ++t)
-                acc[t][ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, ar[t][uu]), bl, acc[t][ct],
-                                                                     0, 0, 0);
-        }
-    }
-    // issue order for the compiler's scheduler: two operand reads, 2 RT MFMAs, and so on (1 % faster
-    // than its own choice)
-#pragma unroll
-    for (int i = 0; i < 2 * CTW; ++i) {
-        __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-        __builtin_amdgcn_sched_group_barrier(0x008, 2 * RT, 0);
-    }
-}
-// Partial sum of row block b (C layout: lane (j = li, g = lq), register r -> weight row 4g + r
-// of the tile, activation row j), then zero for the next row block.
-template <int RT, int RG, int CTW, int FE>
-__device__ __forceinline__ void gemm_flush(f32x4 (&acc)[RT][CTW], const GemmArgs& a, const GemmCtx& c, int b, int q,
-                                           const float* s_inv) {
-    const int first = (b * c.KB) / q;
-    const bool whole = first == ((b + 1) * c.KB - 1) / q;  // the row block's whole k range was this thread block's
-    if (FE == 1 + EPI_STORE && whole) {
+
+// Where the weights of a (row block, k block) pair begin, one pointer per tile of the wave: wave-uniform
+// (scalar registers).  Past the block's range it stays on the last pair: a re-read keeps the
+// steady-state loop free of conditional loads.
+template <int RT, bool SWI>
+struct GemmWeights {
+    const char* p[RT];
+    int it, b, kb;
+    __device__ __forceinline__ void base(const GemmCtx& c, const void* W) {
 #pragma unroll
         for (int t = 0; t < RT; ++t) {
-            const int tile = gemm_tile<RT, RG, FE>(c, b, t);
-#pragma unroll
-            for (int ct = 0; ct < CTW; ++ct) {
-                const int m = (c.wt * CTW + ct) * 16 + c.li;
-                if (tile >= 0 && m < c.Mp) {
-                    const float inv = s_inv[m];
-                    *reinterpret_cast<float4*>(a.y + (size_t)(c.pass * PM + m) * a.ldy + tile * 16 + 4 * c.lq) =
-                        make_float4(acc[t][ct][0] * inv, acc[t][ct][1] * inv, acc[t][ct][2] * inv, acc[t][ct][3] * inv);
-                }
-                acc[t][ct] = f32x4{0.f, 0.f, 0.f, 0.f};
-            }
+            int tile = gemm_tile<RT, SWI>(c, b, t);
+            if (tile < 0) tile = c.n_tiles - 1;  // a tile past the end re-reads the last one (not stored)
+            p[t] = reinterpret_cast<const char*>(W) + ((size_t)tile * c.KB + kb) * 4096;
         }
-        return;
     }
-    if (FE == 1 + EPI_SWIGLU && whole) {
-        // register r of lane (li, lq): output 16 j + 4 lq + r of row li of the column tile, gate in tile 0, up in tile 1
-        const int j = b * RG + c.wr;
+    __device__ __forceinline__ void init(const GemmCtx& c, const void* W, int it_) {
+        it = it_;
+        b = it / c.KB;
+        kb = it - b * c.KB;
+        base(c, W);
+    }
+    __device__ __forceinline__ void next(const GemmCtx& c, const void* W) {
+        if (it + 1 >= c.it1) return;
+        ++it;
+        if (++kb == c.KB) {
+            kb = 0;
+            ++b;
+            base(c, W);
+        } else {
 #pragma unroll
-        for (int ct = 0; ct < CTW; ++ct) {
-            const int m = (c.wt * CTW + ct) * 16 + c.li;
-            if (j < c.n_out_tiles && m < c.Mp) {
-                const float inv = s_inv[m];
-                const float4 v = make_float4(silu_mul(acc[0][ct][0] * inv, acc[RT - 1][ct][0] * inv), silu_mul(acc[0][ct][1] * inv, acc[RT - 1][ct][1] * inv),
-                                             silu_mul(acc[0][ct][2] * inv, acc[RT - 1][ct][2] * inv), silu_mul(acc[0][ct][3] * inv, acc[RT - 1][ct][3] * inv));
-                split_store4(a.ys, a.N, a.plane_rows, c.pass * PM + m, j * 16 + 4 * c.lq, v);
-            }
-#pragma unroll
-            for (int t = 0; t < RT; ++t) acc[t][ct] = f32x4{0.f, 0.f, 0.f, 0.f};
+            for (int t = 0; t < RT; ++t) p[t] += 4096;
         }
-        return;
     }
-    const int slot = c.cid - first;
-    float* part = a.part + (size_t)(c.pass * a.S + slot) * PM * a.rows;
+};
+// MFMA step u (32 k) of every tile.  STREAM: the weights are read once by this launch (a single pass),
+// so the loads carry the streaming hint; with several passes the other passes' blocks read the same
+// lines and they are left to the caches.
+template <int RT, bool STREAM, bool SWI>
+__device__ __forceinline__ void gemm_load_a(uint4 (&ar)[RT], const GemmWeights<RT, SWI>& w, int u, uint32_t lane_off) {
 #pragma unroll
     for (int t = 0; t < RT; ++t) {
-        const int tile = gemm_tile<RT, RG, FE>(c, b, t);
+        const uint16_t* wp = reinterpret_cast<const uint16_t*>(w.p[t] + u * 1024 + lane_off);
+        ar[t] = STREAM ? ld_weights_packed(wp) : *reinterpret_cast<const uint4*>(wp);
+    }
+}
+
+// Staging map: 2 planes x 16 CT rows x 16 segments of 16 bytes, CT per thread; unit i of a thread
+// lies 32 rows below unit i - 1 (same segment), first in the high plane, then in the low plane.
+// Rows past the live ones are read too, from the planes' unused rows: whatever they hold only
+// reaches result columns that are never stored.
+template <int CT>
+struct GemmStage {
+    const char* base;      // the pass's first row in the high plane
+    uint32_t off;          // this thread's byte offset at unit 0
+    size_t off_mid;        // ... at the unit that holds the last rows of the high and the first of the low plane (odd CT)
+    int row_bytes, lo_off, dst;
+    __device__ __forceinline__ void init(const GemmArgs& a, const GemmCtx& c, int tid) {
+        row_bytes = a.K * 2;
+        lo_off = a.plane_rows;
+        base = reinterpret_cast<const char*>(a.xs + (size_t)c.row0 * a.K);
+        const int r = tid >> 4, seg = (tid & 15) * 16;
+        off = (uint32_t)(r * row_bytes + seg);
+        const int rm = (CT / 2) * 32 + r;
+        off_mid = (size_t)(rm < CT * 16 ? rm : lo_off + rm - CT * 16) * row_bytes + seg;
+        dst = r * ROWB + seg;
+    }
+    template <int I0, int I1, int N>
+    __device__ __forceinline__ void load(u32x4 (&br)[N], int kb) const {
+        const char* p = base + (size_t)kb * 256;
 #pragma unroll
-        for (int ct = 0; ct < CTW; ++ct) {
-            const int m = (c.wt * CTW + ct) * 16 + c.li;
-            if (tile >= 0 && m < c.Mp)
-                *reinterpret_cast<f32x4*>(part + (size_t)m * a.rows + tile * 16 + 4 * c.lq) = acc[t][ct];
-            acc[t][ct] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int i = I0; i < I1; ++i) {
+            if (CT % 2 && i == CT / 2) {
+                br[i - I0] = *reinterpret_cast<const u32x4*>(p + off_mid);
+            } else {
+                const int row = i * 32 < CT * 16 ? i * 32 : lo_off + i * 32 - CT * 16;  // high plane, then low plane
+                br[i - I0] = *reinterpret_cast<const u32x4*>(p + (size_t)row * row_bytes + off);
+            }
         }
     }
-}
-
-// Half a pair.  First half (P = 0): request the next pair's activations; both halves: request
-// the weights two half-steps ahead, multiply the current half; second half (P = 1): leave the
-// row block's partial sum if it ends here and publish the next activations (the stage they go
-// to was last read before the barrier that ended the previous pair).  Loads complete in issue
-// order and the activations are requested before the weights of the same half-step, so
-// waiting for them leaves the newest weight loads in flight.
-template <int RT, bool STREAM, int P, int RG, int CTW, int FE>
-__device__ __forceinline__ void gemm_half(f32x4 (&acc)[RT][CTW], const uint4 (&acur)[RT][2], uint4 (&afar)[RT][2],
-                                          u32x4 (&breg)[NBU], unsigned char* bt, int& buf, const GemmArgs& a,
-                                          const GemmCtx& c, int h, int q) {
-    const int cur = h >> 1;
-    if (P == 0) gemm_load_b(breg, c, cur + 1);
-    gemm_load_a<RT, STREAM, RG, FE>(afar, c, h + 2);
-    gemm_mma<RT, CTW>(acc, acur, bt + buf * STAGE, c, P);
-    if (P == 1) {
-        const int b = cur / c.KB;
-        if (cur + 1 >= c.it1 || (cur + 1) / c.KB != b) gemm_flush<RT, RG, CTW, FE>(acc, a, c, b, q, reinterpret_cast<const float*>(bt + 2 * STAGE));
-        buf ^= 1;
-        gemm_store_b(bt + buf * STAGE, breg, c);
-        __syncthreads();
+    template <int I0, int I1, int N>
+    __device__ __forceinline__ void store(unsigned char* stage, const u32x4 (&br)[N]) const {
+#pragma unroll
+        for (int i = I0; i < I1; ++i) *reinterpret_cast<u32x4*>(stage + dst + i * 32 * ROWB) = br[i - I0];
     }
+};
+
+// Partial sum of row block b, or the finished tail where the row block's whole k range was this thread
+// block's; then zero for the next row block.  C layout: register r of lane l is weight row 4 (l / 16) + r
+// of the tile, activation row l % 16.
+template <int RT, int CT, bool SWI>
+__device__ __forceinline__ void gemm_flush(f32x4 (&acc)[RT][CT], const GemmArgs& a, const GemmCtx& c, int b, int q,
+                                           const float* s_inv, int lane) {
+    const int first = (b * c.KB) / q;
+    const bool whole = first == ((b + 1) * c.KB - 1) / q;
+    const int li = lane & 15, sub = 4 * (lane >> 4);
+    if (SWI && whole) {
+#pragma unroll
+        for (int t = 0; t < RT / 2; ++t) {
+            const int j = gemm_tile<RT, SWI>(c, b, t);
+#pragma unroll
+            for (int ct = 0; ct < CT; ++ct) {
+                const int m = ct * 16 + li;
+                if (j >= 0 && m < c.Mp) {
+                    const float inv = s_inv[m];
+                    const f32x4 g = acc[t][ct], u = acc[RT / 2 + t][ct];
+                    split_store4(a.ys, a.N, a.plane_rows, c.row0 + m, j * 16 + sub,
+                                 make_float4(silu_mul(g[0] * inv, u[0] * inv), silu_mul(g[1] * inv, u[1] * inv),
+                                             silu_mul(g[2] * inv, u[2] * inv), silu_mul(g[3] * inv, u[3] * inv)));
+                }
+            }
+        }
+    } else {
+        const bool store = !SWI && a.fused && whole;
+        const int slot = c.cid - first;
+        float* const y = store ? a.y + (size_t)c.row0 * a.ldy : a.part + (size_t)(c.pass * a.S + slot) * a.pass_rows * a.rows;
+        const int ld = store ? a.ldy : a.rows;
+#pragma unroll
+        for (int t = 0; t < RT; ++t) {
+            const int tile = gemm_tile<RT, SWI>(c, b, t);
+#pragma unroll
+            for (int ct = 0; ct < CT; ++ct) {
+                const int m = ct * 16 + li;
+                if (tile >= 0 && m < c.Mp) {
+                    const float f = store ? s_inv[m] : 1.0f;
+                    const f32x4 v = acc[t][ct];
+                    *reinterpret_cast<float4*>(y + (size_t)m * ld + tile * 16 + sub) = make_float4(v[0] * f, v[1] * f, v[2] * f, v[3] * f);
+                }
+            }
+        }
+    }
+#pragma unroll
+    for (int t = 0; t < RT; ++t)
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct) acc[t][ct] = f32x4{0.f, 0.f, 0.f, 0.f};
 }
 
-// 512 threads = RG row groups x (8 / RG) splits of the pass's 128 rows; a wave has RT 16-row weight
-// tiles (of the block's 16 RG RT weight rows) and 16 RG of the pass's rows.  Used with RG = 8, RT = 2:
-// 256 weight rows per block, a 32 x 128 tile of the result per wave, every wave loading weights of
-// its own.  (Four row groups x two halves of the pass, a 64 x 64 tile per wave, read every weight
-// tile in two waves: the vector memory path was busy 64 % of the time instead of 46 %, the launches
-// took 4-5 % longer on the wide projections and 20 % longer on the narrow ones at 16 passes.)
-// Weights: a ring of three register half-stages, requested two half-steps (one pair) ahead;
-// activations: one pair ahead through LDS.
-template <int RT, bool STREAM, int RG, int FE>
+// 512 threads; a wave multiplies its RT weight tiles (16 rows each, registers) with all CT column
+// tiles (16 of the pass's rows, bf16 high and low parts, LDS): a 16 RT x 16 CT tile of the result.
+//   weights      a ring of D register stages, 32 k each, requested D - 1 steps ahead
+//   activations  a k block (128 k) ahead through registers into the other LDS stage; one barrier per k block
+//   operands     read from LDS PD column tiles before the MFMAs that take them
+// What bounds it: a long prompt the power the card gives the matrix cores (random operands: an MFMA-only loop
+// reaches 1.81 PFLOP/s, this kernel 1.27 on [28672 x 4096] at 1999 rows; with zeros it reaches 1.69 and the loop
+// 2.25), a short one the weight stream.  Operand reads that wait right before their MFMAs, and two tiles per wave
+// throughout, took 819 us there against 739; multiplying all 128 rows of a pass whatever it holds took 82 us on
+// [27648 x 5120] at 45 rows against 55 (5.1 TB/s) with only the live column tiles.  32 x 32 x 16 MFMAs, which the
+// MFMA-only loop prefers by 4 %, were 5 % slower here.
+template <int RT, int CT, int D, int PD, bool STREAM, bool SWI>
 __global__ __launch_bounds__(64 * WPB) void prefill_gemm_kernel(GemmArgs a, int q, int xa) {
-    static_assert(WPB == 8 && (RG == 4 || RG == 8), "row groups x splits of the pass's rows");
-    constexpr int CTW = PM / 16 / (WPB / RG);  // column tiles (16 of the pass's rows) per wave
+    constexpr int STAGE = stage_bytes(CT), UB = D / 4;   // UB: k blocks per turn of the ring
+    // staging units requested at the start of a k block; the rest half way
+    constexpr int H0 = CT > 4 ? (CT + 1) / 2 : CT, H1 = CT > H0 ? CT - H0 : 1;
+    static_assert(D % 4 == 0 && D >= 4, "the ring turns over in whole k blocks");
+    static_assert(!SWI || RT % 2 == 0, "gate and up tiles in one wave");
     extern __shared__ __attribute__((aligned(16))) unsigned char bt[];  // [2][STAGE], then PM floats: the rows' RMSNorm scales (fused tails)
     const int tid = threadIdx.x, lane = tid & 63;
+    const uint32_t lane_off = lane * 16;
     GemmCtx c;
-    c.wr = (tid >> 6) % RG; c.wt = (tid >> 6) / RG; c.li = lane & 15; c.lq = lane >> 4;
-    c.K = a.K; c.KB = a.K >> 7; c.n_tiles = a.rows >> 4;
-    constexpr bool SWI = FE == 1 + EPI_SWIGLU;
-    static_assert(!SWI || RT == 2, "a gate and an up tile per wave");
+    c.wr = __builtin_amdgcn_readfirstlane(tid >> 6);
+    c.KB = a.K >> 7; c.n_tiles = a.rows >> 4;
     c.n_out_tiles = SWI ? a.N >> 4 : 0;
-    const int nb = SWI ? (c.n_out_tiles + RG - 1) / RG : (c.n_tiles + RG * RT - 1) / (RG * RT);
+    const int nb = (c.n_tiles + WPB * RT - 1) / (WPB * RT);
     const int total = nb * c.KB;  // (checked on the host to fit an int)
     // Thread blocks go to the 8 XCDs round-robin by index.  The blocks that share a range of the
     // weights (same range index, different passes) are given indices of one residue mod 8, so that
@@ -263,105 +276,168 @@ __global__ __launch_bounds__(64 * WPB) void prefill_gemm_kernel(GemmArgs a, int 
     c.pass = (j % npb) * xb + xcd / xa;
     c.cid = (j / npb) * xa + xcd % xa;
     if (c.pass >= a.n_pass) return;
-    c.Mp = a.M - c.pass * PM < PM ? a.M - c.pass * PM : PM;
-    c.lo_off = a.plane_rows;
+    c.row0 = c.pass * a.pass_rows;
+    c.Mp = a.M - c.row0 < a.pass_rows ? a.M - c.row0 : a.pass_rows;
     const int it0 = c.cid * q;
     c.it1 = it0 + q < total ? it0 + q : total;
     if (it0 >= c.it1) return;
-    c.W = reinterpret_cast<const uint16_t*>(a.Wp) + lane * 8;
-    c.bsrc0 = a.xs + (size_t)(c.pass * PM + (tid >> 4)) * a.K + (tid & 15) * 8;
-    c.bdst0 = (tid >> 4) * ROWB + (tid & 15) * 16;
-
-    f32x4 acc[RT][CTW];
+    f32x4 acc[RT][CT];
 #pragma unroll
     for (int t = 0; t < RT; ++t)
 #pragma unroll
-        for (int ct = 0; ct < CTW; ++ct) acc[t][ct] = f32x4{0.f, 0.f, 0.f, 0.f};
-    uint4 ah[3][RT][2];  // ring of weight half-stages
-    u32x4 breg[NBU];     // (a native vector type: the compiler keeps such an array in registers)
-
-    gemm_load_b(breg, c, it0);
-    gemm_load_a<RT, STREAM, RG, FE>(ah[0], c, 2 * it0);
-    gemm_load_a<RT, STREAM, RG, FE>(ah[1], c, 2 * it0 + 1);
-    gemm_store_b(bt, breg, c);
-    if (FE != 0) {  // 1 / rms of this pass's input rows, from the partial sums of squares their producer left
+        for (int ct = 0; ct < CT; ++ct) acc[t][ct] = f32x4{0.f, 0.f, 0.f, 0.f};
+    uint4 ar[D][RT];
+    GemmStage<CT> sg;
+    sg.init(a, c, tid);
+    GemmWeights<RT, SWI> w;  // the pair whose step 3 is requested at the first step of a k block; then the pair after it
+    w.init(c, a.Wp, it0);
+    int b = w.b, kb = w.kb;  // the pair being multiplied
+    {
+        u32x4 br[CT];
+        sg.template load<0, CT>(br, kb);
+#pragma unroll
+        for (int s = 0; s < D - 1; ++s) {
+            gemm_load_a<RT, STREAM, SWI>(ar[s], w, s & 3, lane_off);
+            if ((s & 3) == 3) w.next(c, a.Wp);
+        }
+        sg.template store<0, CT>(bt, br);
+    }
+    float* const s_inv = reinterpret_cast<float*>(bt + 2 * STAGE);
+    if (a.fused) {  // 1 / rms of this pass's input rows, from the partial sums of squares their producer left
         const int m = tid >> 2, part = tid & 3;
         float t = 0.f;
         if (a.ssq_in && m < c.Mp)
-            for (int i = part; i < a.ssq_nb; i += 4) t += a.ssq_in[(size_t)(c.pass * PM + m) * a.ssq_ld + i];
+            for (int i = part; i < a.ssq_nb; i += 4) t += a.ssq_in[(size_t)(c.row0 + m) * a.ssq_ld + i];
         t += __shfl_xor(t, 1, 64);
         t += __shfl_xor(t, 2, 64);
-        if (part == 0) reinterpret_cast<float*>(bt + 2 * STAGE)[m] = a.ssq_in ? 1.0f / sqrtf(t / (float)a.K + a.eps) : 1.0f;
+        if (part == 0) s_inv[m] = a.ssq_in ? 1.0f / sqrtf(t / (float)a.K + a.eps) : 1.0f;
     }
     __syncthreads();
-    int buf = 0;  // LDS stage that holds the current pair's activations
+    const unsigned char* const rd0 = bt + (lane & 15) * ROWB + (lane >> 4) * 16;
+    int buf = 0;  // LDS stage that holds the current k block's activations
+
+    auto k_block = [&](auto phase, int it) {
+        constexpr int P = decltype(phase)::value * 4;   // ring position of the k block's first step
+        const unsigned char* const src = rd0 + buf * STAGE;
+        unsigned char* const dst = bt + (buf ^ 1) * STAGE;
+        int kbn = kb + 1 < c.KB ? kb + 1 : 0;            // k block of the next pair (re-read past the range)
+        u32x4 br0[H0], br1[H1];
+        bf16x8 bh[PD + 1], bl[PD + 1];
+        auto read = [&](int n) {                         // operands of column tile n % CT of step n / CT
+            const unsigned char* rp = src + (n % CT) * 16 * ROWB + (n / CT) * 64;
+            bh[n % (PD + 1)] = *reinterpret_cast<const bf16x8*>(rp);
+            bl[n % (PD + 1)] = *reinterpret_cast<const bf16x8*>(rp + CT * 16 * ROWB);
+        };
+#pragma unroll
+        for (int n = 0; n < PD; ++n) read(n);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            if (u == 0) sg.template load<0, H0>(br0, kbn);
+            if (CT > H0 && u == 2) {
+                sg.template store<0, H0>(dst, br0);
+                sg.template load<H0, CT>(br1, kbn);
+            }
+            gemm_load_a<RT, STREAM, SWI>(ar[(P + u + D - 1) % D], w, (u + 3) & 3, lane_off);
+            if (u == 0) w.next(c, a.Wp);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int n = u * CT; n < (u + 1) * CT; ++n) {
+                const int ct = n % CT;
+                if (n + PD < 4 * CT) read(n + PD);
+                const bf16x8 xh = bh[n % (PD + 1)], xl = bl[n % (PD + 1)];
+#pragma unroll
+                for (int t = 0; t < RT; ++t)
+                    acc[t][ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, ar[(P + u) % D][t]), xh, acc[t][ct], 0, 0, 0);
+#pragma unroll
+                for (int t = 0; t < RT; ++t)
+                    acc[t][ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, ar[(P + u) % D][t]), xl, acc[t][ct], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        if (it + 1 >= c.it1 || kb + 1 == c.KB) gemm_flush<RT, CT, SWI>(acc, a, c, b, q, s_inv, lane);
+        if (CT > H0) sg.template store<H0, CT>(dst, br1);
+        else sg.template store<0, H0>(dst, br0);
+        if (++kb == c.KB) { kb = 0; ++b; }
+        buf ^= 1;
+        __syncthreads();
+    };
     int it = it0;
-    // steady state: three pairs = six half-steps, every ring index a constant
-    for (; it + 3 <= c.it1; it += 3) {
-        gemm_half<RT, STREAM, 0, RG, CTW, FE>(acc, ah[0], ah[2], breg, bt, buf, a, c, 2 * it, q);
-        gemm_half<RT, STREAM, 1, RG, CTW, FE>(acc, ah[1], ah[0], breg, bt, buf, a, c, 2 * it + 1, q);
-        gemm_half<RT, STREAM, 0, RG, CTW, FE>(acc, ah[2], ah[1], breg, bt, buf, a, c, 2 * it + 2, q);
-        gemm_half<RT, STREAM, 1, RG, CTW, FE>(acc, ah[0], ah[2], breg, bt, buf, a, c, 2 * it + 3, q);
-        gemm_half<RT, STREAM, 0, RG, CTW, FE>(acc, ah[1], ah[0], breg, bt, buf, a, c, 2 * it + 4, q);
-        gemm_half<RT, STREAM, 1, RG, CTW, FE>(acc, ah[2], ah[1], breg, bt, buf, a, c, 2 * it + 5, q);
+    for (; it + UB <= c.it1; it += UB) {
+        k_block(std::integral_constant<int, 0>{}, it);
+        if constexpr (UB > 1) k_block(std::integral_constant<int, 1>{}, it + 1);
+        if constexpr (UB > 2) k_block(std::integral_constant<int, 2>{}, it + 2);
+        if constexpr (UB > 3) k_block(std::integral_constant<int, 3>{}, it + 3);
     }
-    if (it < c.it1) {
-        gemm_half<RT, STREAM, 0, RG, CTW, FE>(acc, ah[0], ah[2], breg, bt, buf, a, c, 2 * it, q);
-        gemm_half<RT, STREAM, 1, RG, CTW, FE>(acc, ah[1], ah[0], breg, bt, buf, a, c, 2 * it + 1, q);
-    }
-    if (it + 1 < c.it1) {
-        gemm_half<RT, STREAM, 0, RG, CTW, FE>(acc, ah[2], ah[1], breg, bt, buf, a, c, 2 * it + 2, q);
-        gemm_half<RT, STREAM, 1, RG, CTW, FE>(acc, ah[0], ah[2], breg, bt, buf, a, c, 2 * it + 3, q);
-    }
+    if constexpr (UB > 1) if (it < c.it1) k_block(std::integral_constant<int, 0>{}, it);
+    if constexpr (UB > 2) if (it + 1 < c.it1) k_block(std::integral_constant<int, 1>{}, it + 1);
+    if constexpr (UB > 3) if (it + 2 < c.it1) k_block(std::integral_constant<int, 2>{}, it + 2);
 }
 
-hipError_t launch_prefill_gemm(const GemmArgs& a, hipStream_t st) {
+template <int RT, int CT, int D, int PD, bool STREAM, bool SWI>
+static hipError_t launch_gemm_t(const GemmArgs& a, int q, int xa, int grid, hipStream_t st) {
+    constexpr int LDS = lds_bytes(CT);
+    static bool attr_set = false;
+    if (!attr_set) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&prefill_gemm_kernel<RT, CT, D, PD, STREAM, SWI>),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
+        if (e != hipSuccess) return e;
+        attr_set = true;
+    }
+    prefill_gemm_kernel<RT, CT, D, PD, STREAM, SWI><<<grid, 64 * WPB, LDS, st>>>(a, q, xa);
+    return hipGetLastError();
+}
+// D and PD by measurement (45 and 128 rows, 7B to 13B shapes): one tile per wave keeps seven steps in flight
+// ([4096 x 4096], 45 rows: 9.6 us), two or four tiles three; reading two operands ahead instead of one
+// takes [22016 x 4096] at 512 rows from 200 to 173 us with two tiles, with four tiles it only costs registers.
+template <int RT, int CT, bool STREAM>
+static hipError_t launch_gemm_ct(const GemmArgs& a, int q, int xa, int grid, hipStream_t st) {
+    constexpr int D = RT == 1 ? 8 : 4, PD = RT == 4 ? 1 : 2;
+    if constexpr (RT > 1)
+        if (a.fused == 1 + EPI_SWIGLU) return launch_gemm_t<RT, CT, D, PD, STREAM, true>(a, q, xa, grid, st);
+    return launch_gemm_t<RT, CT, D, PD, STREAM, false>(a, q, xa, grid, st);
+}
+
+hipError_t launch_prefill_gemm(const GemmArgs& a_, hipStream_t st) {
+    GemmArgs a = a_;
     if (a.rows < 16 || a.rows % 16 || a.K < 128 || a.K % 128 || a.M < 1 || a.n_pass < 1 || a.n_pass > SB_PREFILL_PASSES ||
         a.n_pass != (a.M + PM - 1) / PM || a.plane_rows < a.n_pass * PM)
         return hipErrorInvalidValue;
-    const GemmPlan p = gemm_plan(a.rows, a.K, a.n_pass);
+    const GemmPlan p = gemm_plan(a.rows, a.K, a.n_pass, a.fused == 1 + EPI_SWIGLU);
+    a.pass_rows = gemm_pass_rows(a.M, a.n_pass);
     if (a.S != p.smax || (long)p.nb * (a.K >> 7) > 0x3fffffffL) return hipErrorInvalidValue;
     if (a.fused != 0 && a.fused != 1 + EPI_STORE && a.fused != 1 + EPI_SWIGLU) return hipErrorInvalidValue;
     if (a.fused == 1 + EPI_SWIGLU && (a.rows != 2 * a.N || a.N % 16 || !a.ys)) return hipErrorInvalidValue;
     if (a.fused == 1 + EPI_STORE && (a.rows != a.N || !a.y || a.ldy < a.N || a.ldy % 4)) return hipErrorInvalidValue;
     if (a.fused && a.ssq_in && (a.ssq_nb < 1 || a.ssq_ld < a.ssq_nb)) return hipErrorInvalidValue;
-    static bool attr_set = false;
-    if (!attr_set) {
-        const void* fns[6] = {reinterpret_cast<const void*>(&prefill_gemm_kernel<2, false, 8, 0>),
-                              reinterpret_cast<const void*>(&prefill_gemm_kernel<2, true, 8, 0>),
-                              reinterpret_cast<const void*>(&prefill_gemm_kernel<2, false, 8, 1 + EPI_STORE>),
-                              reinterpret_cast<const void*>(&prefill_gemm_kernel<2, true, 8, 1 + EPI_STORE>),
-                              reinterpret_cast<const void*>(&prefill_gemm_kernel<2, false, 8, 1 + EPI_SWIGLU>),
-                              reinterpret_cast<const void*>(&prefill_gemm_kernel<2, true, 8, 1 + EPI_SWIGLU>)};
-        for (const void* fn : fns) {
-            hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES);
-            if (e != hipSuccess) return e;
-        }
-        attr_set = true;
-    }
     // XCD array shape, by measurement at the 7B shapes: with few passes the weights dominate what the
     // L2s fetch (one L2 per range: 8 % faster than every L2 fetching everything at 4 passes); with many
     // passes the activations weigh as much and 2 x 4 is 2 % ahead of both 8 x 1 and 1 x 8
     const int xa = a.n_pass >= 8 ? 2 : (a.n_pass >= 5 ? 4 : 8);
     const int xb = 8 / xa;
     const int grid = 8 * ((a.n_pass + xb - 1) / xb) * ((p.grid + xa - 1) / xa);
-    const bool stream = a.n_pass == 1;
-    const dim3 g3(grid), b3(64 * WPB);
-    if (a.fused == 1 + EPI_SWIGLU) {
-        if (stream) prefill_gemm_kernel<2, true, 8, 1 + EPI_SWIGLU><<<g3, b3, LDS_BYTES, st>>>(a, p.q, xa);
-        else prefill_gemm_kernel<2, false, 8, 1 + EPI_SWIGLU><<<g3, b3, LDS_BYTES, st>>>(a, p.q, xa);
-    } else if (a.fused == 1 + EPI_STORE) {
-        if (stream) prefill_gemm_kernel<2, true, 8, 1 + EPI_STORE><<<g3, b3, LDS_BYTES, st>>>(a, p.q, xa);
-        else prefill_gemm_kernel<2, false, 8, 1 + EPI_STORE><<<g3, b3, LDS_BYTES, st>>>(a, p.q, xa);
+    const int ct = a.pass_rows / 16;
+    if (a.n_pass == 1) {
+        switch (ct * 4 + p.rt) {
+#define SB_GEMM_CASE(CT) \
+    case CT * 4 + 1: return launch_gemm_ct<1, CT, true>(a, p.q, xa, grid, st); \
+    case CT * 4 + 2: return launch_gemm_ct<2, CT, true>(a, p.q, xa, grid, st);
+            SB_GEMM_CASE(1) SB_GEMM_CASE(2) SB_GEMM_CASE(3) SB_GEMM_CASE(4) SB_GEMM_CASE(5) SB_GEMM_CASE(6) SB_GEMM_CASE(7) SB_GEMM_CASE(8)
+#undef SB_GEMM_CASE
+        }
     } else {
-        if (stream) prefill_gemm_kernel<2, true, 8, 0><<<g3, b3, LDS_BYTES, st>>>(a, p.q, xa);
-        else prefill_gemm_kernel<2, false, 8, 0><<<g3, b3, LDS_BYTES, st>>>(a, p.q, xa);
+        switch (ct * 8 + p.rt) {   // (more than PM / 2 rows per pass)
+#define SB_GEMM_CASE(CT) \
+    case CT * 8 + 2: return launch_gemm_ct<2, CT, false>(a, p.q, xa, grid, st); \
+    case CT * 8 + 4: return launch_gemm_ct<4, CT, false>(a, p.q, xa, grid, st);
+            SB_GEMM_CASE(5) SB_GEMM_CASE(6) SB_GEMM_CASE(7) SB_GEMM_CASE(8)
+#undef SB_GEMM_CASE
+        }
     }
-    return hipGetLastError();
+    return hipErrorInvalidValue;
 }
 
 // Partial sums that row block b received: thread blocks first..last of the plan.
-struct GemmSplitMap { int rows_per_block, KB, q; };
+struct GemmSplitMap { int rows_per_block, KB, q, pass_rows; };
 __device__ __forceinline__ int splits_of(const GemmSplitMap& mp, int n) {
     const int b = n / mp.rows_per_block;
     const int first = (int)(((long)b * mp.KB) / mp.q), last = (int)(((long)(b + 1) * mp.KB - 1) / mp.q);
@@ -401,12 +477,12 @@ __global__ __launch_bounds__(256) void prefill_epilogue_kernel(GemmEpiArgs a, Ge
         }
         inv = 1.0f / sqrtf(t / (float)a.K + a.eps);
     }
-    const size_t plane = (size_t)PM * a.rows;
-    const float* p = a.part + ((size_t)(m / PM) * a.S * PM + m % PM) * a.rows;
+    const size_t plane = (size_t)mp.pass_rows * a.rows;
+    const float* p = a.part + ((size_t)(m / mp.pass_rows) * a.S * mp.pass_rows + m % mp.pass_rows) * a.rows;
     float sq = 0.f;
     if (n < a.N) {
         if (EPI == EPI_SWIGLU && a.fused) {
-            // (row blocks are 128 outputs: gate and up tiles side by side; one partial = finished by the GEMM)
+            // (a row block holds gate and up tiles side by side; one partial = finished by the GEMM)
             const int sp = splits_of(mp, n);
             if (sp > 1) {
                 const float4 g = sum_splits4(p + n, plane, sp);
@@ -451,10 +527,11 @@ hipError_t launch_prefill_epilogue(const GemmEpiArgs& a, hipStream_t st) {
     if (a.ssq_out && (a.N + 255) / 256 > a.ssq_ld) return hipErrorInvalidValue;
     if (a.N % 4 || a.ldy % 4) return hipErrorInvalidValue;
     dim3 grid((a.N + 255) / 256, (a.M + 3) / 4);
-    const GemmPlan pl = gemm_plan(a.rows, a.K, a.n_pass);
+    const GemmPlan pl = gemm_plan(a.rows, a.K, a.n_pass, a.fused == 1 + EPI_SWIGLU);
     if (a.S != pl.smax) return hipErrorInvalidValue;
     if (a.fused && a.fused != 1 + a.epi) return hipErrorInvalidValue;
-    const GemmSplitMap mp{a.epi == EPI_SWIGLU && a.fused ? BLOCK_ROWS / 2 : BLOCK_ROWS, a.K >> 7, pl.q};
+    const GemmSplitMap mp{a.epi == EPI_SWIGLU && a.fused ? pl.block_rows / 2 : pl.block_rows, a.K >> 7, pl.q,
+                          gemm_pass_rows(a.M, a.n_pass)};
     switch (a.epi) {
         case EPI_STORE: prefill_epilogue_kernel<EPI_STORE><<<grid, 256, 0, st>>>(a, mp); break;
         case EPI_RESID: prefill_epilogue_kernel<EPI_RESID><<<grid, 256, 0, st>>>(a, mp); break;

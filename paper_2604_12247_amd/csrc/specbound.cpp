@@ -127,9 +127,10 @@ WsLayout ws_layout(const sb_config* c) {
         L.p_us = take(2 * RS * f * 2);
         size_t pe = 0;  // largest set of k-split partials: any projection, any number of passes
         const size_t shapes[4][2] = {{qkv_rows, d}, {d, hq}, {2 * f, d}, {d, f}};
-        for (auto& sh : shapes)
+        for (int i = 0; i < 4; ++i)
             for (int np = 1; np <= (int)(RS / PM); ++np) {
-                size_t e = (size_t)np * gemm_splits((int32_t)sh[0], (int32_t)sh[1], np) * PM * sh[0];
+                const size_t* sh = shapes[i];
+                size_t e = (size_t)np * gemm_splits((int32_t)sh[0], (int32_t)sh[1], np, i == 2) * PM * sh[0];
                 if (e > pe) pe = e;
             }
         L.p_part = take(pe * 4);
@@ -397,7 +398,7 @@ int prefill_proj(sb_session* s, const void* Wp, int rows, int K, const uint16_t*
     GemmArgs g{};
     g.Wp = Wp; g.rows = rows; g.K = K; g.xs = xs; g.plane_rows = s->L.p_rows; g.M = R;
     g.n_pass = (R + SB_PREFILL_ROWS - 1) / SB_PREFILL_ROWS;
-    g.part = wsp<float>(s, s->L.p_part); g.S = gemm_splits(rows, K, g.n_pass);
+    g.part = wsp<float>(s, s->L.p_part); g.S = gemm_splits(rows, K, g.n_pass, e.epi == EPI_SWIGLU);
     e.part = g.part; e.S = g.S; e.rows = rows; e.M = R; e.n_pass = g.n_pass; e.plane_rows = s->L.p_rows;
     e.K = K; e.eps = s->m->cfg.rms_eps; e.ssq_ld = s->L.p_ssq_ld;
     if (e.epi == EPI_SWIGLU || e.epi == EPI_STORE) {  // the GEMM finishes the row blocks it owns whole

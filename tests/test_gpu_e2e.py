@@ -439,6 +439,27 @@ def test_long_prompt_goes_through_128_row_passes(sb, name, n_prompt):
     assert pst.stats()["layer_sweeps"] == shape.n_layers * ((n_prompt + super_rows - 1) // super_rows)
 
 
+# passes of a super-pass are equal parts of the prompt: 2 of 65 (80 staged), 90 (96), 104 (112) and 128 rows, 3 of 100
+@pytest.mark.parametrize("n_prompt", [9, 49, 129, 180, 208, 256, 300])
+@pytest.mark.parametrize("deep", [False, True])   # four weight tiles per wave, or two (k ranges cut in more than two)
+def test_prompt_pass_heights(sb, deep, n_prompt):
+    """Cached keys and values of the second layer (which every projection of the first one reaches) against the
+    oracle, at every position."""
+    kw = dict(d_model=1024, n_heads=8, n_kv_heads=8, head_dim=128, d_ffn=2048) if deep else {}
+    shape = si.tiny_shape(n_layers=2, n_exit_heads=1, **dict(_variants(sb)["bf16-mfma-packed"][0], **kw))
+    w = si.make_weights(shape, 67, gain_jitter=0.1)
+    om, gm = Oracle(shape, w, 320), gpu_model(shape, w, 320)
+    prompt = si.make_prompt(shape.vocab, n_prompt, 73)
+    osn, gsn = om.session(), gm.session()
+    osn.prefill(prompt)
+    gsn.prefill(prompt)
+    for pos in range(n_prompt):
+        (ko, vo), (kg, vg) = osn.kv_read(1, pos), gsn.debug_kv(1, pos)
+        # one bf16 unit of the largest value (the keys and values are rounded to bf16 on both sides)
+        assert np.max(np.abs(kg - ko)) <= 2.0 ** -7 * max(1.0, np.max(np.abs(ko))), pos
+        assert np.max(np.abs(vg - vo)) <= 2.0 ** -7 * max(1.0, np.max(np.abs(vo))), pos
+
+
 @pytest.mark.parametrize("tau", [0.3, 0.7])
 def test_easy_token_fixture_accepts_computed_drafts_like_the_oracle(sb, tau):
     """The structured fixture (aliased, peaked heads; deep layers fading out): computed exits

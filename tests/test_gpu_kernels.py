@@ -109,6 +109,21 @@ def test_prompt_pass_gemm(T, N, K, M):
         assert np.array_equal(y3, y[:3])
 
 
+# every height of a pass (1 to 8 column tiles, odd ones straddle the two planes in the staging), one and two weight
+# tiles per wave ([4096 x 1024] and [20480 x 2560]), a last row block that is not full ([20496 x ...])
+@pytest.mark.parametrize("N,K", [(4096, 1024), (20496, 2560)])
+@pytest.mark.parametrize("M", [1, 16, 17, 40, 64, 70, 96, 97, 113, 128])
+def test_prompt_pass_gemm_heights(T, N, K, M):
+    import paper_2604_12247_amd as sb
+    g = np.random.default_rng(N + M)
+    W = T.from_numpy(_rand_w(g, N, K, True).view(np.int16)).cuda()
+    x = T.from_numpy(g.standard_normal((M, K)).astype(np.float32)).cuda()
+    y = sb.op_gemm(sb.op_repack(W), x).double()
+    ref = x.double() @ W.view(T.bfloat16).double().t()
+    # 16 mantissa bits per activation: 2^-17 a term, fp32 sums over K <= 2560
+    assert float((y - ref).abs().max()) <= 3e-5 * float(ref.abs().max())
+
+
 GATE_UP_SHAPES = [(64, 256, 3), (11008, 4096, 1), (11008, 4096, 6), (14336, 4096, 8)]
 GATE_UP_CASES = [(k, *c) for k in ("valu", "mfma", "mfma_packed") for c in GATE_UP_SHAPES] + [("valu", 1000, 512, 5)]
 
