@@ -591,6 +591,17 @@ hipError_t launch_prefill_split(const float* x, uint16_t* xs, int32_t plane_rows
 }
 
 // ---------------------------------------------------------------- prompt attention
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+// maximum / sum over a lane and its counterpart in the other half of the wave
+__device__ __forceinline__ float half_max(float v) {
+    const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return fmaxf(__uint_as_float(s[0]), __uint_as_float(s[1]));
+}
+__device__ __forceinline__ float half_add(float v) {
+    const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return __uint_as_float(s[0]) + __uint_as_float(s[1]);
+}
+
 // The prompt's attention for a bf16 cache: first the keys and values of all rows of the
 // super-pass go into the cache (rotary embedding on the keys, both rounded to bf16; V
 // transposed per page, as everywhere), then one launch computes every row's attention with
@@ -663,132 +674,202 @@ __global__ __launch_bounds__(256) void prefill_kv_append_kernel(AttnArgs a) {
     }
 }
 
-// grid (n_kv_heads, ceil(M G / (64 QT))), 256 threads.  A wave owns QT tiles of 16 queries and
-// is independent of the other waves but for the K/V chunk (64 keys) the block stages in LDS.
-// Scores are computed transposed, S^T = K Q^T, so a lane holds, for ONE query (its column),
-// the scores of 4 keys per key tile: the running maximum, sum and rescaling are per-lane
-// scalars, and the exponentials -- 4 keys of tile 2s, then 4 of tile 2s+1 -- are already the
-// B operand of O^T += V^T P^T when the 32 keys of a k step are taken in that order, which is
-// the order the A operand is read in from the transposed V page (two 8-byte runs per lane).
-template <int HD, int QT>
-__global__ __launch_bounds__(256, 2) void prefill_attn_kernel(AttnArgs a) {
-    constexpr int CH = 64, KT = CH / 16, HALF = HD / 2;
-    constexpr int KSQ = HD / 32;             // k steps (32 dims) of the score product
-    constexpr int DTN = HD / 16;             // 16-dim tiles of the output
+// ---- pieces of the prompt attention kernels
+// The query (row x head of kv head g's group) of this lane; past the end: zeros, nothing masked, never stored.
+struct AttnQuery { int row, head, pos; bool valid; };
+__device__ __forceinline__ AttnQuery attn_query(const AttnArgs& a, int g, int qq, int nq_total) {
+    const int G = a.n_heads / a.kv.n_kv_heads;
+    AttnQuery q;
+    q.valid = qq < nq_total;
+    q.row = q.valid ? qq / G : 0;
+    q.head = g * G + (q.valid ? qq - q.row * G : 0);
+    q.pos = q.valid ? a.pos0 + q.row : 0x7fffffff;
+    return q;
+}
+// Its rotated values as hi + lo B operands, scores in units of log 2: this lane has dims 16 ks + 8 lh ..; steps
+// ks and ks + HD / 32 are the two ends of the rotation's pairs.
+template <int HD>
+__device__ __forceinline__ void attn_load_query(const AttnArgs& a, const AttnQuery& qi, int lh, bf16x8 (&qh)[HD / 16], bf16x8 (&ql)[HD / 16]) {
+    constexpr int HALF = HD / 2, KS = HD / 16;
+    const float* qp = a.q + (size_t)qi.row * a.qkv_rows + (size_t)qi.head * HD + lh * 8;
+    const float* cp = a.rope_cos + (size_t)(a.pos0 + qi.row) * HALF + lh * 8;
+    const float* sp = a.rope_sin + (size_t)(a.pos0 + qi.row) * HALF + lh * 8;
+    const float c2 = 1.4426950408889634f / sqrtf((float)HD);
+#pragma unroll
+    for (int ks = 0; ks < KS / 2; ++ks) {
+        uint32_t h[2][4], l[2][4];
+#pragma unroll
+        for (int e4 = 0; e4 < 8; e4 += 4) {
+            const float4 x = *reinterpret_cast<const float4*>(qp + ks * 16 + e4);
+            const float4 y = *reinterpret_cast<const float4*>(qp + ks * 16 + HALF + e4);
+            const float4 c = *reinterpret_cast<const float4*>(cp + ks * 16 + e4);
+            const float4 sn = *reinterpret_cast<const float4*>(sp + ks * 16 + e4);
+            const float xs4[4] = {x.x, x.y, x.z, x.w}, ys4[4] = {y.x, y.y, y.z, y.w};
+            const float cs4[4] = {c.x, c.y, c.z, c.w}, sn4[4] = {sn.x, sn.y, sn.z, sn.w};
+            float u[2][4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float ua = (xs4[e] * cs4[e] - ys4[e] * sn4[e]) * c2, ub = (ys4[e] * cs4[e] + xs4[e] * sn4[e]) * c2;
+                u[0][e] = qi.valid ? ua : 0.f;
+                u[1][e] = qi.valid ? ub : 0.f;
+            }
+#pragma unroll
+            for (int o = 0; o < 2; ++o)
+#pragma unroll
+                for (int e = 0; e < 4; e += 2) {
+                    const uint32_t hp = pack_bf16(u[o][e], u[o][e + 1]);
+                    h[o][(e4 + e) / 2] = hp;
+                    l[o][(e4 + e) / 2] = pack_bf16(u[o][e] - __uint_as_float(hp << 16), u[o][e + 1] - __uint_as_float(hp & 0xffff0000u));
+                }
+        }
+#pragma unroll
+        for (int o = 0; o < 2; ++o) {
+            qh[ks + o * (KS / 2)] = __builtin_bit_cast(bf16x8, make_uint4(h[o][0], h[o][1], h[o][2], h[o][3]));
+            ql[ks + o * (KS / 2)] = __builtin_bit_cast(bf16x8, make_uint4(l[o][0], l[o][1], l[o][2], l[o][3]));
+        }
+    }
+}
+// Running soft-max over KT key tiles of this lane's query (masked scores are -inf): exponentials as hi + lo B
+// operands, a page's 16 keys each, this lane's part of their sum, the output rescaled where needed.
+// The reference point follows the maximum only when that has grown by more than 2^8: until then the
+// exponentials stay below 2^8 and nothing has to be rescaled (any reference point gives the same
+// quotient; sums and products are float, the bf16 pairs relative).
+template <int KT, int DT>
+__device__ __forceinline__ void attn_softmax(const f32x16 (&st)[KT], f32x16 (&o)[DT], float& m_run, float& l_run, bf16x8 (&ph)[2 * KT], bf16x8 (&pl)[2 * KT]) {
+    float mx = -__builtin_inff();
+#pragma unroll
+    for (int kt = 0; kt < KT; ++kt)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) mx = fmaxf(mx, st[kt][r]);
+    mx = half_max(mx);
+    const float m_new = mx > m_run + 8.0f ? mx : m_run;
+    if (__builtin_amdgcn_ballot_w64(m_new != m_run) != 0) {
+        const float alpha = m_new == m_run ? 1.0f : __builtin_amdgcn_exp2f(m_run - m_new);
+        l_run *= alpha;
+        m_run = m_new;
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) o[dt][r] *= alpha;
+    }
+    const float ref = m_new == -__builtin_inff() ? 0.f : m_new;   // (a tile none of whose keys the query sees, before any it does)
+    float sum0 = 0.f, sum1 = 0.f;
+#pragma unroll
+    for (int s = 0; s < KT * 2; ++s) {   // the 16 keys of a page: 8 of them in this lane
+        uint32_t hw[4], lw[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const float p0 = __builtin_amdgcn_exp2f(st[s >> 1][(s & 1) * 8 + 2 * e] - ref);
+            const float p1 = __builtin_amdgcn_exp2f(st[s >> 1][(s & 1) * 8 + 2 * e + 1] - ref);
+            sum0 += p0;
+            sum1 += p1;
+            hw[e] = pack_bf16(p0, p1);
+            lw[e] = pack_bf16(p0 - __uint_as_float(hw[e] << 16), p1 - __uint_as_float(hw[e] & 0xffff0000u));
+        }
+        ph[s] = __builtin_bit_cast(bf16x8, make_uint4(hw[0], hw[1], hw[2], hw[3]));
+        pl[s] = __builtin_bit_cast(bf16x8, make_uint4(lw[0], lw[1], lw[2], lw[3]));
+    }
+    l_run += sum0 + sum1;
+}
+
+// grid (n_kv_heads, ceil(M G / (32 W))), 64 W threads.  A wave owns 32 queries and is independent of the
+// other waves but for the K/V chunk (64 keys) the block stages in LDS.  Scores are computed transposed,
+// S^T = K Q^T in 32 x 32 tiles, so a lane holds, for ONE query (its column), 16 keys of every key tile: the
+// running maximum, sum and rescaling are per-lane scalars, completed across the two halves of the wave
+// only.  The rows of a key tile are taken in the order (bits 2 and 3 of the key swapped) that leaves a lane
+// the exponentials of 8 neighbouring keys in neighbouring registers: they are the B operand of
+// O^T += V^T P^T as they stand, and the A operand is one 16-byte piece of the transposed V page.
+//
+// What bounds it: the matrix cores and, beside them, about 300 vector instructions and 32 quarter-rate
+// exponentials per 64 MFMAs; two waves per SIMD cover for each other.  2048 rows behind 2048, 32 heads x 128:
+// 189 us, 1.09 PFLOP/s of MFMAs; 300 us as 16 x 16 x 32 tiles of two query tiles per wave, whose operand reads
+// were waited for one by one, with 480 vector instructions per chunk and spills.
+constexpr int ATTN_CH = 64;   // keys per chunk
+
+template <int HD, int W>
+__global__ __launch_bounds__(64 * W, 2) void prefill_attn_kernel(AttnArgs a) {
+    constexpr int CH = ATTN_CH, NT = 64 * W;
+    constexpr int KT = CH / 32;              // key tiles of a chunk
+    constexpr int KS = HD / 16;              // k steps (16 dims) of the score product
+    constexpr int DT = HD / 32;              // 32-dim tiles of the output
     constexpr int PPK = HD / 8;              // 16-byte pieces of a key
     constexpr int SLAB = SB_KV_BLOCK * HD;   // one head's part of a page
-    constexpr int NL = KT * SLAB / (256 * 8);  // 16-byte pieces per thread, operand and chunk
+    constexpr int NPG = CH / SB_KV_BLOCK;    // pages of a chunk
+    constexpr int NL = NPG * SLAB / (NT * 8);  // 16-byte pieces per thread, operand and chunk
+    constexpr int PD = 4;                    // operands are read from LDS PD key / dim tiles ahead of their MFMAs
     // Two chunks in LDS, filled by direct global -> LDS loads (lane l of a wave lands 16 l bytes
     // after the wave's base).  Which piece lands where is chosen so that operand reads are free of
-    // bank conflicts (measured): a K piece (key, p) sits at piece p ^ f(key) of its key's row; the two
+    // bank conflicts: a K piece (key, p) sits at piece p ^ f(key) of its key's row; the two
     // halves (8 keys each) of a V row change places in every second group of 8 dims.
     __shared__ __attribute__((aligned(16))) uint16_t k_s[2][CH * HD];
-    __shared__ __attribute__((aligned(16))) uint16_t v_s[2][KT * SLAB];
+    __shared__ __attribute__((aligned(16))) uint16_t v_s[2][NPG * SLAB];
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int li = lane & 15, lq = lane >> 4;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int li = lane & 31, lh = lane >> 5;
     const int g = blockIdx.x;
-    const int qtile = gridDim.y - 1 - blockIdx.y;  // the longest blocks (last rows) start first
+    // The longest blocks (last rows) start first; where all blocks are resident at once (two per CU), the second
+    // half goes shortest first, so that a CU's two blocks are a long and a short one.
+    const int first = (256 + gridDim.x - 1) / gridDim.x, ny = gridDim.y;
+    const int qtile = ny <= 2 * first && (int)blockIdx.y >= first ? (int)blockIdx.y - first : ny - 1 - (int)blockIdx.y;
     const int Hq = a.n_heads, Hkv = a.kv.n_kv_heads, G = Hq / Hkv;
-    const int nq_total = a.M * G, q0 = qtile * (64 * QT);
+    const int nq_total = a.M * G, q0 = qtile * (32 * W);
     const int n_total = a.pos0 + a.M;
-    const int q_last = (q0 + 64 * QT < nq_total ? q0 + 64 * QT : nq_total) - 1;
+    const int q_last = (q0 + 32 * W < nq_total ? q0 + 32 * W : nq_total) - 1;
     const int n_chunks = (a.pos0 + q_last / G) / CH + 1;  // chunks with a key the block's last row sees
-    const int wq0 = q0 + wave * QT * 16;                   // the wave's queries: wq0 .. wq1
-    const int wq1 = (wq0 + QT * 16 - 1 < nq_total - 1) ? wq0 + QT * 16 - 1 : nq_total - 1;
+    const int wq0 = q0 + wave * 32;                        // the wave's queries: wq0 .. wq1
+    const int wq1 = (wq0 + 31 < nq_total - 1) ? wq0 + 31 : nq_total - 1;
     const bool wave_live = wq0 < nq_total;
     const int wpos_min = a.pos0 + wq0 / G, wpos_max = a.pos0 + wq1 / G;
-    const float c2 = 1.4426950408889634f / sqrtf((float)HD);  // scores in units of log 2
     const size_t page_elems = (size_t)Hkv * SLAB;
-    const uint16_t* const kbase = reinterpret_cast<const uint16_t*>(a.kv.pool) + (size_t)(a.layer * 2 + 0) * a.kv.n_pages * page_elems;
-    const uint16_t* const vbase = reinterpret_cast<const uint16_t*>(a.kv.pool) + (size_t)(a.layer * 2 + 1) * a.kv.n_pages * page_elems;
+    const uint16_t* const kbase = reinterpret_cast<const uint16_t*>(a.kv.pool) + (size_t)(a.layer * 2 + 0) * a.kv.n_pages * page_elems + (size_t)g * SLAB;
+    const uint16_t* const vbase = reinterpret_cast<const uint16_t*>(a.kv.pool) + (size_t)(a.layer * 2 + 1) * a.kv.n_pages * page_elems + (size_t)g * SLAB;
 
-    // ---- this wave's rotated queries as hi + lo B operands: lane (li, lq) has query li, dims 32 ks + 8 lq ..
-    bf16x8 qh[QT][KSQ], ql[QT][KSQ];
-    int qpos[QT], qrow[QT], qhead[QT];
-#pragma unroll
-    for (int qt = 0; qt < QT; ++qt) {
-        const int qq = wq0 + qt * 16 + li;
-        const bool valid = qq < nq_total;
-        const int r = valid ? qq / G : 0, gi = valid ? qq - r * G : 0;
-        qrow[qt] = valid ? r : -1;
-        qhead[qt] = g * G + gi;
-        qpos[qt] = valid ? a.pos0 + r : 0x7fffffff;  // (a query past the end: zeros, nothing masked, never stored)
-        const float* qp = a.q + (size_t)r * a.qkv_rows + (size_t)qhead[qt] * HD;
-        const float* cp = a.rope_cos + (size_t)(a.pos0 + r) * HALF;
-        const float* sp = a.rope_sin + (size_t)(a.pos0 + r) * HALF;
-#pragma unroll
-        for (int ks = 0; ks < KSQ; ++ks) {
-            const int d0 = ks * 32 + lq * 8;
-            const bool lower = d0 < HALF;
-            const int j0 = lower ? d0 : d0 - HALF;
-            uint16_t h[8], l[8];
-#pragma unroll
-            for (int e4 = 0; e4 < 8; e4 += 4) {
-                const float4 x = *reinterpret_cast<const float4*>(qp + j0 + e4);
-                const float4 y = *reinterpret_cast<const float4*>(qp + j0 + HALF + e4);
-                const float4 c = *reinterpret_cast<const float4*>(cp + j0 + e4);
-                const float4 sn = *reinterpret_cast<const float4*>(sp + j0 + e4);
-                const float xs4[4] = {x.x, x.y, x.z, x.w}, ys4[4] = {y.x, y.y, y.z, y.w};
-                const float cs4[4] = {c.x, c.y, c.z, c.w}, sn4[4] = {sn.x, sn.y, sn.z, sn.w};
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    float u = lower ? xs4[e] * cs4[e] - ys4[e] * sn4[e] : ys4[e] * cs4[e] + xs4[e] * sn4[e];
-                    u = valid ? u * c2 : 0.f;  // scores come out in units of log 2
-                    h[e4 + e] = f2bf(u);
-                    l[e4 + e] = f2bf(u - bf2f(h[e4 + e]));
-                }
-            }
-            const uint4 hv = make_uint4(h[0] | ((uint32_t)h[1] << 16), h[2] | ((uint32_t)h[3] << 16), h[4] | ((uint32_t)h[5] << 16), h[6] | ((uint32_t)h[7] << 16));
-            const uint4 lv = make_uint4(l[0] | ((uint32_t)l[1] << 16), l[2] | ((uint32_t)l[3] << 16), l[4] | ((uint32_t)l[5] << 16), l[6] | ((uint32_t)l[7] << 16));
-            qh[qt][ks] = __builtin_bit_cast(bf16x8, hv);
-            ql[qt][ks] = __builtin_bit_cast(bf16x8, lv);
-        }
-    }
-
-    f32x4 o[QT][DTN];  // O^T: register r of lane (li, lq) is dim 16 dt + 4 lq + r of query li
-    float m_run[QT], l_run[QT];  // running maximum (log-2 units); this lane's part of the running sum
-#pragma unroll
-    for (int qt = 0; qt < QT; ++qt) {
-        m_run[qt] = -__builtin_inff();
-        l_run[qt] = 0.f;
-#pragma unroll
-        for (int dt = 0; dt < DTN; ++dt) o[qt][dt] = f32x4{0.f, 0.f, 0.f, 0.f};
-    }
-
-    // ---- staging of a chunk: thread -> 16-byte pieces of the chunk's 4 pages (K and V slabs of head g)
-    int pg[NL];  // physical pages of the chunk issued next (-1: no key there); read one chunk ahead of the issue
+    // ---- staging of a chunk: thread -> 16-byte pieces of the chunk's pages (K and V slabs of head g).  A wave's 64
+    // pieces lie in one page, so the page is a scalar; lane i < NPG of `pg` holds the i-th page of the chunk
+    // issued next (-1: no key there), read one chunk ahead of the issue.
+    int pg;
     auto lookup = [&](int chunk) {
-#pragma unroll
-        for (int i = 0; i < NL; ++i) {
-            const int page = chunk * KT + (i * 256 + tid) / (SB_KV_BLOCK * PPK);
-            pg[i] = (page * SB_KV_BLOCK < n_total) ? a.kv.table[page] : -1;
-        }
+        const int page = chunk * NPG + (lane & (NPG - 1));
+        pg = (page * SB_KV_BLOCK < n_total) ? a.kv.table[page] : -1;
     };
     auto issue = [&](int buf) {
 #pragma unroll
         for (int i = 0; i < NL; ++i) {
-            const int slot = i * 256 + tid;             // the piece's place in LDS
-            const int key = slot / PPK, pp = slot - key * PPK;
+            const int slot0 = i * NT + wave * 64, slot = slot0 + lane;   // the piece's place in LDS
+            const int page = __builtin_amdgcn_readlane(pg, slot0 / (SB_KV_BLOCK * PPK));
+            const int key = slot / PPK, pp = slot % PPK;
             const int piece = pp ^ (PPK == 16 ? (key & 15) : ((key >> 1) & 7));
-            uint16_t* kw = &k_s[buf][(i * 256 + wave * 64) * 8];  // the wave's 64 pieces
-            uint16_t* vw = &v_s[buf][(i * 256 + wave * 64) * 8];
-            if (pg[i] >= 0) {
-                const size_t base = (size_t)pg[i] * page_elems + (size_t)g * SLAB;
-                __builtin_amdgcn_global_load_lds(kbase + base + (key % SB_KV_BLOCK) * HD + piece * 8, kw, 16, 0, 0);
-                __builtin_amdgcn_global_load_lds(vbase + base + ((slot ^ ((slot >> 4) & 1)) * 8) % SLAB, vw, 16, 0, 0);
+            uint16_t* kw = &k_s[buf][slot0 * 8];   // the wave's 64 pieces
+            uint16_t* vw = &v_s[buf][slot0 * 8];
+            if (page >= 0) {
+                const size_t base = (size_t)page * page_elems;
+                __builtin_amdgcn_global_load_lds(kbase + base + (uint32_t)((key % SB_KV_BLOCK) * HD + piece * 8), kw, 16, 0, 0);
+                __builtin_amdgcn_global_load_lds(vbase + base + (uint32_t)(((slot ^ ((slot >> 4) & 1)) * 8) % SLAB), vw, 16, 0, 0);
             } else {  // past the last key: zeros
                 *reinterpret_cast<u32x4*>(kw + lane * 8) = u32x4{0u, 0u, 0u, 0u};
                 *reinterpret_cast<u32x4*>(vw + lane * 8) = u32x4{0u, 0u, 0u, 0u};
             }
         }
     };
-    const int kswz = PPK == 16 ? li : ((li >> 1) & 7);  // f(key) of this lane's key in a score operand
-    const int vq = (((lq >> 1) ^ (li >> 3)) & 1) * 8 + (lq & 1) * 4;  // this lane's 4 keys within a V row in LDS
-
     lookup(0);
     issue(0);
     lookup(1);
+
+    const AttnQuery qi = attn_query(a, g, wq0 + li, nq_total);
+    bf16x8 qh[KS], ql[KS];
+    attn_load_query<HD>(a, qi, lh, qh, ql);
+
+    f32x16 o[DT];  // O^T: register r of lane (li, lh) is dim 32 dt + 8 (r / 4) + 4 lh + r % 4 of query li
+    float m_run = -__builtin_inff(), l_run = 0.f;  // reference point of the exponentials (log-2 units); this lane's part of the sum
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) o[dt][r] = 0.f;
+
+    // row li of a key tile is key (bits 2 and 3 of li swapped)
+    const int krow = (li & 19) | ((li & 4) << 1) | ((li & 8) >> 1);
+    const int kswz = PPK == 16 ? (krow & 15) : ((krow >> 1) & 7);   // f(key) of this lane's key
+
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
     for (int chunk = 0; chunk < n_chunks; ++chunk) {
@@ -803,7 +884,7 @@ __global__ __launch_bounds__(256, 2) void prefill_attn_kernel(AttnArgs a) {
             // nothing: those scores are masked.)  Once per block at most.
 #pragma unroll
             for (int i = 0; i < NL; ++i) {
-                const int slot = i * 256 + tid;
+                const int slot = i * NT + tid;
                 const int vk = key0 + (slot / (SB_KV_BLOCK * PPK)) * SB_KV_BLOCK + ((slot ^ (slot >> 4)) & 1) * 8;  // keys vk .. vk+7 of one dim
                 if (vk < n_total && vk + 8 > n_total) {
                     u32x4 vv = *reinterpret_cast<u32x4*>(&v_s[buf][slot * 8]);
@@ -818,102 +899,262 @@ __global__ __launch_bounds__(256, 2) void prefill_attn_kernel(AttnArgs a) {
             __syncthreads();
         }
         if (wave_live && key0 <= wpos_max) {
-            // ---- S^T = K Q^T for the 4 key tiles
-            f32x4 st[KT][QT];
+            // ---- S^T = K Q^T for the key tiles
+            f32x16 st[KT];
 #pragma unroll
-            for (int kt = 0; kt < KT; ++kt) {
+            for (int kt = 0; kt < KT; ++kt)
 #pragma unroll
-                for (int qt = 0; qt < QT; ++qt) st[kt][qt] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int ks = 0; ks < KSQ; ++ks) {
-                    const bf16x8 kop = *reinterpret_cast<const bf16x8*>(&k_s[buf][((kt * 16 + li) * PPK + ((ks * 4 + lq) ^ kswz)) * 8]);
-#pragma unroll
-                    for (int qt = 0; qt < QT; ++qt) {
-                        st[kt][qt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kop, qh[qt][ks], st[kt][qt], 0, 0, 0);
-                        st[kt][qt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kop, ql[qt][ks], st[kt][qt], 0, 0, 0);
-                    }
-                }
-            }
-            // ---- running soft-max of each query (register r of tile kt: key key0 + 16 kt + 4 lq + r)
-            bf16x8 ph[QT][KT / 2], pl[QT][KT / 2];
-            auto soft = [&](auto masked) {
-#pragma unroll
-                for (int qt = 0; qt < QT; ++qt) {
-                    float mx = -__builtin_inff();
-#pragma unroll
-                    for (int kt = 0; kt < KT; ++kt)
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) {
-                            if (decltype(masked)::value && key0 + kt * 16 + 4 * lq + r > qpos[qt]) st[kt][qt][r] = -__builtin_inff();
-                            mx = fmaxf(mx, st[kt][qt][r]);
-                        }
-                    mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
-                    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-                    const float m_new = fmaxf(m_run[qt], mx);  // finite from the first chunk on: key 0 is visible to all
-                    const float alpha = __builtin_amdgcn_exp2f(m_run[qt] - m_new);
-                    m_run[qt] = m_new;
-                    float sum = 0.f;
-                    uint32_t hw[KT][2], lw[KT][2];
-#pragma unroll
-                    for (int kt = 0; kt < KT; ++kt)
-#pragma unroll
-                        for (int r = 0; r < 4; r += 2) {
-                            const float p0 = __builtin_amdgcn_exp2f(st[kt][qt][r] - m_new);
-                            const float p1 = __builtin_amdgcn_exp2f(st[kt][qt][r + 1] - m_new);
-                            sum += p0 + p1;
-                            const uint32_t hp = pack_bf16(p0, p1);
-                            hw[kt][r >> 1] = hp;
-                            lw[kt][r >> 1] = pack_bf16(p0 - __uint_as_float(hp << 16), p1 - __uint_as_float(hp & 0xffff0000u));
-                        }
-                    l_run[qt] = l_run[qt] * alpha + sum;
-#pragma unroll
-                    for (int s2 = 0; s2 < KT / 2; ++s2) {
-                        ph[qt][s2] = __builtin_bit_cast(bf16x8, make_uint4(hw[2 * s2][0], hw[2 * s2][1], hw[2 * s2 + 1][0], hw[2 * s2 + 1][1]));
-                        pl[qt][s2] = __builtin_bit_cast(bf16x8, make_uint4(lw[2 * s2][0], lw[2 * s2][1], lw[2 * s2 + 1][0], lw[2 * s2 + 1][1]));
-                    }
-                    if (__builtin_amdgcn_ballot_w64(alpha != 1.0f) != 0) {  // (no query of the tile has a new maximum: nothing to rescale)
-#pragma unroll
-                        for (int dt = 0; dt < DTN; ++dt)
-#pragma unroll
-                            for (int r = 0; r < 4; ++r) o[qt][dt][r] *= alpha;
-                    }
-                }
+                for (int r = 0; r < 16; ++r) st[kt][r] = 0.f;
+            bf16x8 op[PD];
+            auto read_k = [&](int n) {   // step n / KT of key tile n % KT
+                op[n % PD] = *reinterpret_cast<const bf16x8*>(&k_s[buf][(((n % KT) * 32 + krow) * PPK + (((n / KT) * 2 + lh) ^ kswz)) * 8]);
             };
-            if (key0 + CH - 1 > wpos_min) soft(std::true_type{});
-            else soft(std::false_type{});
-            // ---- O^T += V^T P^T: k step s2 = keys (tile 2 s2: 4 lq ..+3, tile 2 s2 + 1: 4 lq ..+3) per lane group
 #pragma unroll
-            for (int s2 = 0; s2 < KT / 2; ++s2)
+            for (int n = 0; n < PD; ++n) read_k(n);
 #pragma unroll
-                for (int dt = 0; dt < DTN; ++dt) {
-                    const uint2 v0 = *reinterpret_cast<const uint2*>(&v_s[buf][(2 * s2) * SLAB + (dt * 16 + li) * SB_KV_BLOCK + vq]);
-                    const uint2 v1 = *reinterpret_cast<const uint2*>(&v_s[buf][(2 * s2 + 1) * SLAB + (dt * 16 + li) * SB_KV_BLOCK + vq]);
-                    const bf16x8 vop = __builtin_bit_cast(bf16x8, make_uint4(v0.x, v0.y, v1.x, v1.y));
+            for (int n = 0; n < KT * KS; n += KT) {
 #pragma unroll
-                    for (int qt = 0; qt < QT; ++qt) {
-                        o[qt][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vop, ph[qt][s2], o[qt][dt], 0, 0, 0);
-                        o[qt][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vop, pl[qt][s2], o[qt][dt], 0, 0, 0);
-                    }
-                }
+                for (int kt = 0; kt < KT; ++kt) st[kt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op[(n + kt) % PD], qh[n / KT], st[kt], 0, 0, 0);
+#pragma unroll
+                for (int kt = 0; kt < KT; ++kt) st[kt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op[(n + kt) % PD], ql[n / KT], st[kt], 0, 0, 0);
+#pragma unroll
+                for (int kt = 0; kt < KT; ++kt)
+                    if (n + kt + PD < KT * KS) read_k(n + kt + PD);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            // ---- running soft-max of the query (register r of tile kt: key key0 + 32 kt + 16 (r / 8) + 8 lh + r % 8)
+            if (key0 + CH - 1 > wpos_min) {
+                const int vis = qi.pos - key0 - 8 * lh;   // last visible key, from this lane's first one
+#pragma unroll
+                for (int kt = 0; kt < KT; ++kt)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r)
+                        if (kt * 32 + (r >> 3) * 16 + (r & 7) > vis) st[kt][r] = -__builtin_inff();
+            }
+            auto read_v = [&](int n) {   // page n / DT, dims 32 (n % DT) + li, keys 8 lh ..
+                const int slot = ((n % DT) * 32 + li) * 2 + lh;
+                op[n % PD] = *reinterpret_cast<const bf16x8*>(&v_s[buf][(n / DT) * SLAB + (slot ^ ((slot >> 4) & 1)) * 8]);
+            };
+#pragma unroll
+            for (int n = 0; n < PD; ++n) read_v(n);
+            bf16x8 ph[KT * 2], pl[KT * 2];
+            attn_softmax<KT, DT>(st, o, m_run, l_run, ph, pl);
+            // ---- O^T += V^T P^T: k step s = page s of the chunk
+#pragma unroll
+            for (int n = 0; n < KT * 2 * DT; n += 2) {
+#pragma unroll
+                for (int x = 0; x < 2; ++x) o[(n + x) % DT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op[(n + x) % PD], ph[n / DT], o[(n + x) % DT], 0, 0, 0);
+#pragma unroll
+                for (int x = 0; x < 2; ++x) o[(n + x) % DT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op[(n + x) % PD], pl[n / DT], o[(n + x) % DT], 0, 0, 0);
+#pragma unroll
+                for (int x = 0; x < 2; ++x)
+                    if (n + x + PD < KT * 2 * DT) read_v(n + x + PD);
+                __builtin_amdgcn_sched_barrier(0);
+            }
         }
         __builtin_amdgcn_s_waitcnt(0);  // this wave's pieces of the next chunk have landed
         __syncthreads();                // ... and everybody's; every wave is done with this chunk
     }
-    // ---- normalise; a lane has 4 neighbouring dims per tile of its query
+    // ---- normalise; a lane has 4 neighbouring dims in 4 neighbouring registers
+    const float inv_l = 1.0f / half_add(l_run);
+    if (!qi.valid) return;
 #pragma unroll
-    for (int qt = 0; qt < QT; ++qt) {
-        float lt = l_run[qt];
-        lt += __shfl_xor(lt, 16, 64);
-        lt += __shfl_xor(lt, 32, 64);
-        if (qrow[qt] < 0) continue;
-        const float inv_l = 1.0f / lt;
+    for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
-        for (int dt = 0; dt < DTN; ++dt) {
-            const int col = qhead[qt] * HD + dt * 16 + 4 * lq;
-            const float4 val = make_float4(o[qt][dt][0] * inv_l, o[qt][dt][1] * inv_l, o[qt][dt][2] * inv_l, o[qt][dt][3] * inv_l);
-            if (a.out) *reinterpret_cast<float4*>(a.out + (size_t)qrow[qt] * Hq * HD + col) = val;
-            else split_store4(a.out_split, Hq * HD, a.split_rows, qrow[qt], col, val);
+        for (int r = 0; r < 16; r += 4) {
+            const int col = qi.head * HD + dt * 32 + 2 * r + 4 * lh;
+            const float4 val = make_float4(o[dt][r] * inv_l, o[dt][r + 1] * inv_l, o[dt][r + 2] * inv_l, o[dt][r + 3] * inv_l);
+            if (a.out) *reinterpret_cast<float4*>(a.out + (size_t)qi.row * Hq * HD + col) = val;
+            else split_store4(a.out_split, Hq * HD, a.split_rows, qi.row, col, val);
         }
+}
+
+// The same for launches that the form above would leave short of blocks: a block owns 32 queries, its W waves
+// take the 32-key tiles in turn (tile t to wave t mod W) with a running soft-max each, and the waves'
+// results are added in wave order through LDS at the end.  Operands come straight from the cache into
+// registers, a tile ahead: the next tile's keys are requested when this tile's scores are done, its values
+// when this tile's products are.  grid (n_kv_heads, ceil(M G / 32)).  What bounds it: the chain page
+// table -> keys -> scores -> products of a wave's few tiles.  32 heads x 128: 512 rows 15.5 us, 64 rows 6.5 us;
+// as blocks of 64 queries that walk all keys 23.7 and 8.4 us.
+template <int HD, int W>
+__global__ __launch_bounds__(64 * W, W == 4 ? 2 : 1) void prefill_attn_split_kernel(AttnArgs a) {
+    constexpr int KS = HD / 16, DT = HD / 32, SLAB = SB_KV_BLOCK * HD, NS = DT * 4;
+    __shared__ __attribute__((aligned(16))) float o_s[W][NS][64][4];
+    __shared__ float m_s[W][32], l_s[W][32];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int li = lane & 31, lh = lane >> 5;
+    const int g = blockIdx.x, qtile = gridDim.y - 1 - blockIdx.y;   // (the longest blocks start first)
+    const int Hq = a.n_heads, Hkv = a.kv.n_kv_heads, G = Hq / Hkv;
+    const int nq_total = a.M * G, q0 = qtile * 32, n_total = a.pos0 + a.M;
+    const int q_last = (q0 + 32 < nq_total ? q0 + 32 : nq_total) - 1;
+    const int n_tiles = (a.pos0 + q_last / G) / 32 + 1;   // tiles with a key the block's last row sees
+    const int pos_min = a.pos0 + q0 / G;
+    const size_t page_elems = (size_t)Hkv * SLAB;
+    const uint16_t* const kbase = reinterpret_cast<const uint16_t*>(a.kv.pool) + (size_t)(a.layer * 2 + 0) * a.kv.n_pages * page_elems + (size_t)g * SLAB;
+    const uint16_t* const vbase = reinterpret_cast<const uint16_t*>(a.kv.pool) + (size_t)(a.layer * 2 + 1) * a.kv.n_pages * page_elems + (size_t)g * SLAB;
+    const int krow = (li & 19) | ((li & 4) << 1) | ((li & 8) >> 1);   // row li of a tile is key krow of it
+    const uint32_t koff = (uint32_t)((krow & 15) * HD + lh * 8), voff = (uint32_t)(li * SB_KV_BLOCK + lh * 8);
+    uint4 kr[KS], vr[2][DT];
+    // the two pages of the tile whose operands are requested next; where the second holds no key, the first twice (its
+    // scores are masked, its values zeroed).  (Scalars: an array here would be put into LDS.)
+    int pg0 = 0, pg1 = 0;
+    auto lookup = [&](int t) {
+        pg0 = a.kv.table[t * 2];
+        pg1 = (t * 2 + 1) * SB_KV_BLOCK < n_total ? a.kv.table[t * 2 + 1] : pg0;
+    };
+    auto load_k = [&]() {
+        const uint16_t* p = kbase + (size_t)((li & 16) ? pg1 : pg0) * page_elems + koff;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) kr[ks] = *reinterpret_cast<const uint4*>(p + ks * 16);
+    };
+    auto load_v = [&](int p0, int p1) {
+#pragma unroll
+        for (int x = 0; x < 2; ++x) {
+            const uint16_t* p = vbase + (size_t)(x ? p1 : p0) * page_elems + voff;
+#pragma unroll
+            for (int dt = 0; dt < DT; ++dt) vr[x][dt] = *reinterpret_cast<const uint4*>(p + dt * 32 * SB_KV_BLOCK);
+        }
+    };
+    int t = wave;
+    const bool any = t < n_tiles;
+    if (any) {
+        lookup(t);
+        load_k();
+        load_v(pg0, pg1);
+        if (t + W < n_tiles) lookup(t + W);
+    }
+    // ---- the block's rotated queries, hi + lo in LDS once for all waves (a wave that rotated them by itself would
+    // spend longer on that than on a tile), then as B operands in registers
+    const AttnQuery qi = attn_query(a, g, q0 + li, nq_total);
+    bf16x8 qh[KS], ql[KS];
+    {
+        constexpr int QS = HD + 8, HALF = HD / 2, TPQ = 2 * W < HALF / 4 ? 2 * W : HALF / 4;   // row stride; threads per query
+        uint16_t* const q_hi = reinterpret_cast<uint16_t*>(&o_s[0][0][0][0]);
+        uint16_t* const q_lo = q_hi + 32 * QS;
+        static_assert(2 * 32 * QS * 2 <= (int)sizeof(o_s), "the queries fit where the results go later");
+        const int r = tid / TPQ;
+        const AttnQuery qr = attn_query(a, g, q0 + r, nq_total);
+        const float* qp = a.q + (size_t)qr.row * a.qkv_rows + (size_t)qr.head * HD;
+        const float* cp = a.rope_cos + (size_t)(a.pos0 + qr.row) * HALF;
+        const float* sp = a.rope_sin + (size_t)(a.pos0 + qr.row) * HALF;
+        const float c2 = 1.4426950408889634f / sqrtf((float)HD);   // scores in units of log 2
+#pragma unroll
+        for (int i = 0; i < HALF / (4 * TPQ); ++i) {
+            if (r >= 32) break;
+            const int j = (i * TPQ + tid % TPQ) * 4;
+            const float4 x = *reinterpret_cast<const float4*>(qp + j), y = *reinterpret_cast<const float4*>(qp + j + HALF);
+            const float4 c = *reinterpret_cast<const float4*>(cp + j), sn = *reinterpret_cast<const float4*>(sp + j);
+            const float xs4[4] = {x.x, x.y, x.z, x.w}, ys4[4] = {y.x, y.y, y.z, y.w};
+            const float cs4[4] = {c.x, c.y, c.z, c.w}, sn4[4] = {sn.x, sn.y, sn.z, sn.w};
+            float u[2][4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                u[0][e] = qr.valid ? (xs4[e] * cs4[e] - ys4[e] * sn4[e]) * c2 : 0.f;
+                u[1][e] = qr.valid ? (ys4[e] * cs4[e] + xs4[e] * sn4[e]) * c2 : 0.f;
+            }
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                uint32_t h[2], l[2];
+#pragma unroll
+                for (int e = 0; e < 2; ++e) {
+                    h[e] = pack_bf16(u[k][2 * e], u[k][2 * e + 1]);
+                    l[e] = pack_bf16(u[k][2 * e] - __uint_as_float(h[e] << 16), u[k][2 * e + 1] - __uint_as_float(h[e] & 0xffff0000u));
+                }
+                *reinterpret_cast<uint2*>(q_hi + r * QS + j + k * HALF) = make_uint2(h[0], h[1]);
+                *reinterpret_cast<uint2*>(q_lo + r * QS + j + k * HALF) = make_uint2(l[0], l[1]);
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            qh[ks] = *reinterpret_cast<const bf16x8*>(q_hi + li * QS + ks * 16 + lh * 8);
+            ql[ks] = *reinterpret_cast<const bf16x8*>(q_lo + li * QS + ks * 16 + lh * 8);
+        }
+    }
+    f32x16 o[DT];
+    float m_run = -__builtin_inff(), l_run = 0.f;
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) o[dt][r] = 0.f;
+    for (; t < n_tiles; t += W) {
+        const int key0 = t * 32;
+        f32x16 st[1];
+#pragma unroll
+        for (int r = 0; r < 16; ++r) st[0][r] = 0.f;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            st[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kr[ks]), qh[ks], st[0], 0, 0, 0);
+            st[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kr[ks]), ql[ks], st[0], 0, 0, 0);
+        }
+        const bool more = t + W < n_tiles;
+        const int vp0 = pg0, vp1 = pg1;
+        if (more) {
+            load_k();
+            if (t + 2 * W < n_tiles) lookup(t + 2 * W);
+        }
+        if (key0 + 31 > pos_min) {
+            const int vis = qi.pos - key0 - 8 * lh;   // last visible key, from this lane's first one
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+                if ((r >> 3) * 16 + (r & 7) > vis) st[0][r] = -__builtin_inff();
+        }
+        if (key0 + 32 > n_total) {   // slots past the last key: 0 x (stale bits that read as NaN) is not 0
+#pragma unroll
+            for (int x = 0; x < 2; ++x) {
+                const int live = n_total - key0 - 16 * x - 8 * lh;   // keys of this lane's 8 that exist
+#pragma unroll
+                for (int dt = 0; dt < DT; ++dt) {
+                    uint32_t w[4] = {vr[x][dt].x, vr[x][dt].y, vr[x][dt].z, vr[x][dt].w};
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) w[e] = 2 * e + 1 < live ? w[e] : (2 * e < live ? w[e] & 0xffffu : 0u);
+                    vr[x][dt] = make_uint4(w[0], w[1], w[2], w[3]);
+                }
+            }
+        }
+        bf16x8 ph[2], pl[2];
+        attn_softmax<1, DT>(st, o, m_run, l_run, ph, pl);
+#pragma unroll
+        for (int x = 0; x < 2; ++x)
+#pragma unroll
+            for (int dt = 0; dt < DT; ++dt) {
+                o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, vr[x][dt]), ph[x], o[dt], 0, 0, 0);
+                o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, vr[x][dt]), pl[x], o[dt], 0, 0, 0);
+            }
+        if (more) load_v(vp0, vp1);
+    }
+    // ---- the waves' results, brought to one reference point and added in wave order
+    l_run = half_add(l_run);
+    if (lh == 0) { m_s[wave][li] = m_run; l_s[wave][li] = l_run; }
+    __syncthreads();
+    float mx = m_s[0][li];   // finite: wave 0 has key 0
+#pragma unroll
+    for (int w = 1; w < W; ++w) mx = fmaxf(mx, m_s[w][li]);
+    float l = 0.f;
+#pragma unroll
+    for (int w = 0; w < W; ++w) l += l_s[w][li] * __builtin_amdgcn_exp2f(m_s[w][li] - mx);
+    if (any) {
+        const float f = __builtin_amdgcn_exp2f(m_run - mx);
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+            for (int r = 0; r < 16; r += 4)
+                *reinterpret_cast<f32x4*>(o_s[wave][dt * 4 + r / 4][lane]) = f32x4{o[dt][r] * f, o[dt][r + 1] * f, o[dt][r + 2] * f, o[dt][r + 3] * f};
+    }
+    __syncthreads();
+    if (!qi.valid) return;
+    const float inv_l = 1.0f / l;
+    const int nw = n_tiles < W ? n_tiles : W;   // waves that had a tile
+    for (int s = wave; s < NS; s += W) {        // (a lane finishes its own query: slot s holds dims 32 (s / 4) + 8 (s % 4) + 4 lh ..)
+        f32x4 v = *reinterpret_cast<const f32x4*>(o_s[0][s][lane]);
+        for (int w = 1; w < nw; ++w) {
+            const f32x4 u = *reinterpret_cast<const f32x4*>(o_s[w][s][lane]);
+            v[0] += u[0]; v[1] += u[1]; v[2] += u[2]; v[3] += u[3];
+        }
+        const int col = qi.head * HD + (s >> 2) * 32 + (s & 3) * 8 + 4 * lh;
+        const float4 val = make_float4(v[0] * inv_l, v[1] * inv_l, v[2] * inv_l, v[3] * inv_l);
+        if (a.out) *reinterpret_cast<float4*>(a.out + (size_t)qi.row * Hq * HD + col) = val;
+        else split_store4(a.out_split, Hq * HD, a.split_rows, qi.row, col, val);
     }
 }
 
@@ -925,17 +1166,23 @@ hipError_t launch_prefill_attention(const AttnArgs& a, hipStream_t st) {
         (!a.out && (!a.out_split || a.split_rows < a.M)) || !a.rope_cos || !a.rope_sin)
         return hipErrorInvalidValue;
     const int G = a.n_heads / a.kv.n_kv_heads, nq = a.M * G;
-    // 32 queries per wave halve the LDS reads per product; 16 fill the chip at smaller sizes
-    const bool wide = (int64_t)a.kv.n_kv_heads * ((nq + 127) / 128) >= 512;
-    dim3 agrid((a.pos0 + a.M - 1) / SB_KV_BLOCK - a.pos0 / SB_KV_BLOCK + 1, a.kv.n_kv_heads), grid(a.kv.n_kv_heads, wide ? (nq + 127) / 128 : (nq + 63) / 64);
+    // Four waves of 32 queries share a staged chunk; a launch that this leaves with hardly a block per CU takes the
+    // key tiles apart instead, eight ways while that still fits the chip at once.  Measured, apart / shared: 256
+    // blocks of 128 queries 37 / 44 us, 384 65 / 64, 400 57 / 55, 512 107 / 86.
+    const int64_t tiles = (int64_t)a.kv.n_kv_heads * ((nq + 31) / 32);
+    const bool wide = (int64_t)a.kv.n_kv_heads * ((nq + 127) / 128) >= 320, eight = tiles <= 256;
+    const dim3 agrid((a.pos0 + a.M - 1) / SB_KV_BLOCK - a.pos0 / SB_KV_BLOCK + 1, a.kv.n_kv_heads);
+    const dim3 grid(a.kv.n_kv_heads, wide ? (nq + 127) / 128 : (nq + 31) / 32);
     if (hd == 128) {
         prefill_kv_append_kernel<128><<<agrid, 256, 0, st>>>(a);
-        if (wide) prefill_attn_kernel<128, 2><<<grid, 256, 0, st>>>(a);
-        else prefill_attn_kernel<128, 1><<<grid, 256, 0, st>>>(a);
+        if (wide) prefill_attn_kernel<128, 4><<<grid, 256, 0, st>>>(a);
+        else if (eight) prefill_attn_split_kernel<128, 8><<<grid, 512, 0, st>>>(a);
+        else prefill_attn_split_kernel<128, 4><<<grid, 256, 0, st>>>(a);
     } else {
         prefill_kv_append_kernel<64><<<agrid, 256, 0, st>>>(a);
-        if (wide) prefill_attn_kernel<64, 2><<<grid, 256, 0, st>>>(a);
-        else prefill_attn_kernel<64, 1><<<grid, 256, 0, st>>>(a);
+        if (wide) prefill_attn_kernel<64, 4><<<grid, 256, 0, st>>>(a);
+        else if (eight) prefill_attn_split_kernel<64, 8><<<grid, 512, 0, st>>>(a);
+        else prefill_attn_split_kernel<64, 4><<<grid, 256, 0, st>>>(a);
     }
     return hipGetLastError();
 }

@@ -406,6 +406,39 @@ def test_prompt_attention_wide_form(T, hd, n_ctx, M):
             assert np.max(np.abs(out[r, h * hd:(h + 1) * hd] - ref)) <= 2e-5, (h, r)
 
 
+# launches between the two above: key tiles taken apart by the four waves of a block (257 blocks of 32 queries up to
+# 319 of 128), with a prefix that ends inside a tile, fewer tiles than waves, a grouped-query shape whose
+# blocks straddle rows; then the smallest launch of the wide form
+@pytest.mark.parametrize("Hq,Hkv,hd,n_ctx,M", [(33, 33, 128, 0, 256), (40, 40, 64, 41, 213), (24, 8, 128, 70, 345), (32, 32, 64, 7, 1025),
+                                               (32, 32, 128, 0, 1153)])
+def test_prompt_attention_split_form(T, Hq, Hkv, hd, n_ctx, M):
+    import paper_2604_12247_amd as sb
+    base, G = 1e4, Hq // Hkv
+    g = np.random.default_rng(1700 + hd + M)
+    n_tot = n_ctx + M
+    n_pages = (n_tot + 15) // 16 + 2
+    qkv = (g.standard_normal((n_tot, (Hq + 2 * Hkv) * hd)) * 1.2).astype(np.float32)
+    pool = T.empty(2 * n_pages * Hkv * 16 * hd * 2, dtype=T.uint8, device="cuda")
+    pool.fill_(0xFF)
+    table = _dev(T, g.permutation(n_pages).astype(np.int32))
+    c, s = sb.rope_table(hd, base, n_pages * 16)
+    cd, sd = _dev(T, c), _dev(T, s)
+    if n_ctx:
+        sb.op_prompt_attention(_dev(T, qkv[:n_ctx]), Hq, Hkv, hd, pool, table, 0, cd, sd, 0)
+    out = sb.op_prompt_attention(_dev(T, qkv[n_ctx:]), Hq, Hkv, hd, pool, table, 0, cd, sd, n_ctx).cpu().numpy()
+    raw = pool.view(T.int16).cpu().numpy().view(np.uint16).reshape(2, n_pages, Hkv, 16 * hd)
+    tbl = table.cpu().numpy()
+    for kvh in (0, Hkv - 1):
+        K = si.bf16_to_f32(np.stack([raw[0, tbl[t // 16], kvh].reshape(16, hd)[t % 16] for t in range(n_tot)]))
+        V = si.bf16_to_f32(np.stack([raw[1, tbl[t // 16], kvh].reshape(hd, 16)[:, t % 16] for t in range(n_tot)]))
+        for r in sorted({0, 1, 10, 11, 31, 32, 127, 128, M // 2, M - 2, M - 1}):
+            p_ = n_ctx + r
+            for h in (kvh * G, kvh * G + G - 1):
+                q = orc.rope_apply(qkv[p_, h * hd:(h + 1) * hd], p_, base)
+                ref = orc.attention_head(q, K[:p_ + 1], V[:p_ + 1])
+                assert np.max(np.abs(out[r, h * hd:(h + 1) * hd] - ref)) <= 2e-5, (h, r)
+
+
 def test_attention_row_result_does_not_depend_on_m(T):
     """The same position gives the same bits alone and inside a pass of 6 rows."""
     args = (8, 8, 128, True)
