@@ -51,6 +51,12 @@ template <> struct KvVec<float> {
     }
 };
 
+// A finished value of row r, as the merge stage leaves it.
+__device__ __forceinline__ void attn_finish(const AttnArgs& a, int r, int col, int ld, float v) {
+    if (a.out) a.out[(size_t)r * ld + col] = v;
+    if (a.out_split) split_store_rows(a.out_split, ld, a.split_rows, r, col, v);
+}
+
 template <typename KVT, int HD>
 __global__ __launch_bounds__(256) void attn_kernel(AttnArgs a) {
     constexpr int CH = (HD * sizeof(KVT) <= 256) ? 128 : 64;  // keys per chunk
@@ -236,6 +242,11 @@ __global__ __launch_bounds__(256) void attn_kernel(AttnArgs a) {
                 for (int e = 0; e < EPV; ++e) o[e] += __shfl_xor(o[e], off, 64);
             const int qq = q0 + qi, r = qq / G, gi = qq - r * G;
             if (lane < DGW && key0 <= a.pos0 + r) {  // (a chunk with no visible key leaves no partial)
+                if (a.direct) {
+#pragma unroll
+                    for (int e = 0; e < EPV; ++e) attn_finish(a, r, (g * G + gi) * HD + vd0 + e, Hq * HD, o[e] / s_l[qi]);
+                    continue;
+                }
                 float* p = a.partials + ((size_t)(r * Hq + g * G + gi) * a.max_chunks + chunk) * (HD + 2);
 #pragma unroll
                 for (int e = 0; e < EPV; ++e) p[2 + vd0 + e] = o[e];
@@ -522,6 +533,11 @@ struct AttnItem {
                 if (qi >= nq) continue;
                 const int qq = q0 + qi, rr = qq / G, gi = qq - rr * G;
                 if (key0 > a.pos0 + rr) continue;  // (a chunk with no visible key leaves no partial)
+                if (a.direct) {
+    #pragma unroll
+                    for (int dt = 0; dt < DT; ++dt) attn_finish(a, rr, (g * G + gi) * HD + (wave * DT + dt) * 16 + li, Hq * HD, o[dt][r] / s_l[qi]);
+                    continue;
+                }
                 float* p = a.partials + ((size_t)(rr * Hq + g * G + gi) * a.max_chunks + chunk) * (HD + 2);
     #pragma unroll
                 for (int dt = 0; dt < DT; ++dt) p[2 + (wave * DT + dt) * 16 + li] = o[dt][r];
@@ -633,10 +649,7 @@ __device__ __forceinline__ void attn_merge_body(const AttnArgs& a, const int hq,
         float Ls = 0.f, Os = 0.f;
 #pragma unroll
         for (int gi = 0; gi < NG; ++gi) { Ls += gl[gi]; Os += go[gi][tid]; }
-        const float v = Os / Ls;
-        const size_t col = (size_t)hq * HD + tid;
-        if (a.out) a.out[(size_t)r * Hq * HD + col] = v;
-        if (a.out_split) split_store_rows(a.out_split, Hq * HD, a.split_rows, r, (int)col, v);
+        attn_finish(a, r, hq * HD + tid, Hq * HD, Os / Ls);
     }
 }
 
@@ -681,15 +694,18 @@ hipError_t launch_attention(const AttnArgs& a, hipStream_t st) {
     if (!attn_shape(a, &n_chunks, &n_qg, &qpb)) return hipErrorInvalidValue;
     AttnArgs b = a;
     b.qg_per_block = qpb;
+    // With a single chunk the merge would multiply by exp(0) and add zeros: the first stage divides and
+    // stores by itself (the same bits), a launch less.
+    b.direct = n_chunks == 1;
     dim3 grid(a.kv.n_kv_heads, n_chunks, (n_qg + qpb - 1) / qpb);
     dim3 grid1(a.kv.n_kv_heads, n_chunks, n_qg);
     dim3 mgrid(a.n_heads, a.M);
     if (a.kv.kv_dtype == SB_BF16) {
-        if (hd == 128) { attn_mfma_kernel<128><<<grid, 256, 0, st>>>(b); attn_merge_kernel<128, 128><<<mgrid, 256, 0, st>>>(a); }
-        else { attn_mfma_kernel<64><<<grid, 256, 0, st>>>(b); attn_merge_kernel<64, 128><<<mgrid, 256, 0, st>>>(a); }
+        if (hd == 128) { attn_mfma_kernel<128><<<grid, 256, 0, st>>>(b); if (!b.direct) attn_merge_kernel<128, 128><<<mgrid, 256, 0, st>>>(a); }
+        else { attn_mfma_kernel<64><<<grid, 256, 0, st>>>(b); if (!b.direct) attn_merge_kernel<64, 128><<<mgrid, 256, 0, st>>>(a); }
     } else {
-        if (hd == 128) { attn_kernel<float, 128><<<grid1, 256, 0, st>>>(a); attn_merge_kernel<128, 64><<<mgrid, 256, 0, st>>>(a); }
-        else { attn_kernel<float, 64><<<grid1, 256, 0, st>>>(a); attn_merge_kernel<64, 128><<<mgrid, 256, 0, st>>>(a); }
+        if (hd == 128) { attn_kernel<float, 128><<<grid1, 256, 0, st>>>(b); if (!b.direct) attn_merge_kernel<128, 64><<<mgrid, 256, 0, st>>>(a); }
+        else { attn_kernel<float, 64><<<grid1, 256, 0, st>>>(b); if (!b.direct) attn_merge_kernel<64, 128><<<mgrid, 256, 0, st>>>(a); }
     }
     return hipGetLastError();
 }
@@ -720,14 +736,15 @@ hipError_t launch_attention_batch(const AttnArgs* seqs, int n, hipStream_t st) {
         if (n_chunks > max_chunks) max_chunks = n_chunks;
         if (seqs[i].M > max_m) max_m = seqs[i].M;
     }
+    for (int i = 0; i < n; ++i) ab.seq[i].direct = max_chunks == 1;
     dim3 grid(seqs[0].kv.n_kv_heads, max_chunks, n * ab.zdim);
     dim3 mgrid(seqs[0].n_heads, max_m, n);
     if (seqs[0].kv.head_dim == 128) {
         attn_mfma_batch_kernel<128><<<grid, 256, 0, st>>>(ab);
-        attn_merge_batch_kernel<128, 128><<<mgrid, 256, 0, st>>>(ab);
+        if (max_chunks > 1) attn_merge_batch_kernel<128, 128><<<mgrid, 256, 0, st>>>(ab);
     } else {
         attn_mfma_batch_kernel<64><<<grid, 256, 0, st>>>(ab);
-        attn_merge_batch_kernel<64, 128><<<mgrid, 256, 0, st>>>(ab);
+        if (max_chunks > 1) attn_merge_batch_kernel<64, 128><<<mgrid, 256, 0, st>>>(ab);
     }
     return hipGetLastError();
 }

@@ -48,7 +48,10 @@ __device__ __forceinline__ void head_partial(const HeadArgs& h, float (*zs)[SB_M
 // owns 4 weight rows; lanes stride the K dimension in 16-byte pieces (128-bit
 // loads), partial sums are combined with a fixed shuffle tree.  x is staged in
 // LDS in chunks.  The order in which a row's products are added is a function of
-// K alone.
+// K alone.  Short rows (K <= SB_VALU_NORM_K: one 16-byte piece per thread) are normalised
+// while they are staged where the caller asks for it: a small model is bound by its number of
+// launches (4.2 us each in a chain of them), and the sum of squares costs a block two barriers.  Longer rows
+// would be read twice by every block.  Same order of additions as rmsnorm_kernel.
 
 template <typename WT, int M, int EPI>
 __global__ __launch_bounds__(256) void gemv_valu_kernel(GemvArgs a) {
@@ -89,11 +92,30 @@ __global__ __launch_bounds__(256) void gemv_valu_kernel(GemvArgs a) {
     for (int k0 = 0; k0 < K; k0 += KC) {
         const int kc = (K - k0 < KC) ? (K - k0) : KC;
         __syncthreads();
-        for (int i = tid * 4; i < M * KC; i += 1024) {
-            int m = i / KC, kk = i - m * KC;
-            if (kk < kc)
-                *reinterpret_cast<float4*>(&xs[m][kk]) =
-                    *reinterpret_cast<const float4*>(a.x + (size_t)m * K + k0 + kk);
+        if (a.norm_gain) {   // (one chunk)
+            const bool on = tid * 4 < K;
+            float4 v[M];
+#pragma unroll
+            for (int m = 0; m < M; ++m) v[m] = on ? *reinterpret_cast<const float4*>(a.x + (size_t)m * K + tid * 4) : make_float4(0.f, 0.f, 0.f, 0.f);
+            const float4 g = on ? *reinterpret_cast<const float4*>(a.norm_gain + tid * 4) : make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+            for (int m = 0; m < M; ++m) {
+                const float ss = wave_sum((v[m].x * v[m].x + v[m].y * v[m].y) + (v[m].z * v[m].z + v[m].w * v[m].w));
+                if (lane == 0) zs[wave][m] = ss;
+            }
+            __syncthreads();
+#pragma unroll
+            for (int m = 0; m < M; ++m) {
+                const float inv = 1.0f / sqrtf((((zs[0][m] + zs[1][m]) + zs[2][m]) + zs[3][m]) / (float)K + a.eps);
+                if (on) *reinterpret_cast<float4*>(&xs[m][tid * 4]) = make_float4(v[m].x * inv * g.x, v[m].y * inv * g.y, v[m].z * inv * g.z, v[m].w * inv * g.w);
+            }
+        } else {
+            for (int i = tid * 4; i < M * KC; i += 1024) {
+                int m = i / KC, kk = i - m * KC;
+                if (kk < kc)
+                    *reinterpret_cast<float4*>(&xs[m][kk]) =
+                        *reinterpret_cast<const float4*>(a.x + (size_t)m * K + k0 + kk);
+            }
         }
         __syncthreads();
 #pragma unroll 2
@@ -181,7 +203,7 @@ static hipError_t launch_gemv_valu_t(const GemvArgs& a, hipStream_t st) {
     }
 }
 hipError_t launch_gemv_valu(const GemvArgs& a, hipStream_t st) {
-    if (a.K % 8 != 0 || a.N < 1) return hipErrorInvalidValue;
+    if (a.K % 8 != 0 || a.N < 1 || (a.norm_gain && a.K > SB_VALU_NORM_K)) return hipErrorInvalidValue;
     return a.w_dtype == SB_BF16 ? launch_gemv_valu_t<uint16_t>(a, st) : launch_gemv_valu_t<float>(a, st);
 }
 

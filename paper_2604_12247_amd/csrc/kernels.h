@@ -30,6 +30,9 @@ struct RowToks { int32_t tok[SB_MAX_W]; };  // >= 0: host-known id; -1: read slo
 // RMSNorm outputs produced together with an embedding row (first layer's input).
 struct EmbedNorm { const float* gain; uint16_t* nx; float* ssq_out; int32_t ssq_ld; };
 
+// Longest rows that a vector-ALU projection normalises by itself (a launch less; see gemv_valu_kernel).
+#define SB_VALU_NORM_K 1024
+
 enum Epilogue { EPI_STORE = 0, EPI_RESID = 1, EPI_SWIGLU = 2, EPI_HEAD = 3 };
 enum HeadPost { POST_NONE = 0, POST_EXIT = 1, POST_ACCEPT = 2 };
 
@@ -71,6 +74,7 @@ struct GemvArgs {
     int32_t N;         // outputs per row of x (EPI_SWIGLU: d_ffn, W has 2N rows)
     int32_t K;
     const float* x;    // [M][K] float (VALU path)
+    const float* norm_gain;  // VALU path, K <= SB_VALU_NORM_K: x holds hidden rows, the kernel takes RMSNorm(x) * norm_gain (eps below)
     const uint16_t* xs;  // MFMA path: split bf16 operand, [16][K]: rows 0-7 high parts, 8-15 low parts
     float* y;          // [M][ldy]: STORE writes, RESID adds, SWIGLU writes silu(g)*u (float)
     uint16_t* ys;      // MFMA pipeline: optional split-bf16 copy of the output [16][ldy]
@@ -147,6 +151,7 @@ struct AttnArgs {
     uint16_t* out_split; // optional bf16 hi/lo copy: rows 0.. high parts, rows split_rows.. low parts
     int32_t split_rows;  // 8 for decode passes, SB_PREFILL_ROWS for prompt passes
     int32_t qg_per_block;  // set by launch_attention
+    int32_t direct;        // set by launch_attention: every row sees one chunk only, the first stage finishes it
 };
 int attn_chunk_keys(int32_t head_dim, int32_t kv_dtype);
 hipError_t launch_attention(const AttnArgs& a, hipStream_t st);

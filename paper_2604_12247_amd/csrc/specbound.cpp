@@ -283,13 +283,15 @@ int run_layer(sb_session* s, int l, int slot0, int M, const float* head_gain, in
     uint16_t* us = wsp<uint16_t>(s, s->L.us);
     int rc;
 
-    if (!mf) {
+    const bool own_norm = !mf && d <= SB_VALU_NORM_K;   // the vector-ALU projections normalise short rows themselves
+    if (!mf && !own_norm) {
         ProfScope ps(s, SB_K_RMSNORM, (int64_t)M * d * 8, st);
         HIP_TRY(launch_rmsnorm(H, m->attn_norm[l], xn, nullptr, d, M, d, c.rms_eps, st));
     }
     GemvArgs g{};
     g.w_dtype = c.weight_dtype; g.M = M; g.eps = c.rms_eps; g.ssq_ld = s->L.ssq_ld;
     g.W = m->w_qkv[l]; g.N = qkv_rows; g.K = d; g.x = xn; g.xs = xs_attn; g.y = qkv; g.ldy = qkv_rows; g.epi = EPI_STORE;
+    if (own_norm) { g.x = H; g.norm_gain = m->attn_norm[l]; }
     if (mf) { g.ssq_in = ssq_attn; g.ssq_nb = l == 0 ? 1 : d / 16; }  // layer 0 reads what the embedding left
     if ((rc = gemv(s, g, SB_K_QKV, st))) return rc;
 
@@ -304,21 +306,22 @@ int run_layer(sb_session* s, int l, int slot0, int M, const float* head_gain, in
         HIP_TRY(launch_attention(a, st));
     }
 
-    g.ssq_in = nullptr;
+    g.ssq_in = nullptr; g.norm_gain = nullptr;
     g.W = m->w_o[l]; g.N = d; g.K = hq; g.x = att; g.xs = atts; g.y = H; g.ldy = d; g.epi = EPI_RESID;
     if (mf) { g.gainA = m->ffn_norm[l]; g.nxA = xs_ffn; g.ssq_out = ssq_ffn; }
     if ((rc = gemv(s, g, SB_K_WO, st))) return rc;
     g.gainA = nullptr; g.nxA = nullptr; g.ssq_out = nullptr;
 
-    if (!mf) {
+    if (!mf && !own_norm) {
         ProfScope ps(s, SB_K_RMSNORM, (int64_t)M * d * 8, st);
         HIP_TRY(launch_rmsnorm(H, m->ffn_norm[l], xn, nullptr, d, M, d, c.rms_eps, st));
     }
     g.W = m->w_gate_up[l]; g.N = f; g.K = d; g.x = xn; g.xs = xs_ffn; g.y = mf ? nullptr : u; g.ys = mf ? us : nullptr;
     g.ldy = f; g.epi = EPI_SWIGLU;
     if (mf) { g.ssq_in = ssq_ffn; g.ssq_nb = d / 16; }
+    if (own_norm) { g.x = H; g.norm_gain = m->ffn_norm[l]; }
     if ((rc = gemv(s, g, SB_K_GATEUP, st))) return rc;
-    g.ssq_in = nullptr;
+    g.ssq_in = nullptr; g.norm_gain = nullptr;
 
     g.W = m->w_down[l]; g.N = d; g.K = f; g.x = u; g.xs = us; g.y = H; g.ys = nullptr; g.ldy = d; g.epi = EPI_RESID;
     if (mf) {
@@ -350,7 +353,8 @@ int run_head(sb_session* s, const void* W, const float* gain, int slot0, int M, 
     const bool mf = m->proj == SB_PROJ_MFMA;
     float* xn = wsp<float>(s, s->L.xn);
     const float* rows = wsp<float>(s, s->L.H) + (size_t)slot0 * c.d_model;
-    if (!mf) {
+    const bool own_norm = !mf && c.d_model <= SB_VALU_NORM_K;
+    if (!mf && !own_norm) {
         ProfScope ps(s, SB_K_RMSNORM, (int64_t)M * c.d_model * 8, st);
         HIP_TRY(launch_rmsnorm(rows, gain, xn, nullptr, c.d_model, M, c.d_model, c.rms_eps, st));
     }
@@ -359,6 +363,7 @@ int run_head(sb_session* s, const void* W, const float* gain, int slot0, int M, 
     GemvArgs g{};
     g.W = W; g.w_dtype = c.weight_dtype; g.N = c.vocab; g.K = c.d_model; g.x = xn; g.M = M;
     g.xs = wsp<uint16_t>(s, exit_buf == 1 ? s->L.xs_exit2 : s->L.xs_exit) + (size_t)slot0 * c.d_model;
+    if (own_norm) { g.x = rows; g.norm_gain = gain; g.eps = c.rms_eps; }
     if (mf && !prenormed) {  // (prenormed: xs already holds the normalised rows)
         g.ssq_in = exit_buf >= 0 ? wsp<float>(s, s->L.ssq_exit) + ((size_t)exit_buf * SB_MAX_W + slot0) * s->L.ssq_ld
                                  : wsp<float>(s, s->L.ssq_attn) + (size_t)slot0 * s->L.ssq_ld;
