@@ -130,14 +130,6 @@ __global__ __launch_bounds__(256) void attn_kernel(AttnArgs a) {
         if (key < a.pos0) vreg[i] = *reinterpret_cast<const uint4*>(vbase + vaddr[i]);
     }
 
-    // ---- rotated queries -> LDS
-#pragma unroll
-    for (int it = 0; it < QIT; ++it) {
-        const int i = tid + it * 256;
-        const int qi = i / HALF, j = i - qi * HALF;
-        qs[qi * HD + j] = qx[it] * qc[it] - qy[it] * qsn[it];
-        qs[qi * HD + j + HALF] = qy[it] * qc[it] + qx[it] * qsn[it];
-    }
     // ---- keys and values of the new rows: built from qkv, appended by query group 0
     if (kkey >= a.pos0 && kkey < n_total) {
         const int r = kkey - a.pos0;
@@ -169,6 +161,14 @@ __global__ __launch_bounds__(256) void attn_kernel(AttnArgs a) {
             vreg[i] = KvVec<KVT>::pack(f);
             if (qg == 0) *reinterpret_cast<uint4*>(vbase + vaddr[i]) = vreg[i];
         }
+    }
+    // ---- rotated queries -> LDS
+#pragma unroll
+    for (int it = 0; it < QIT; ++it) {
+        const int i = tid + it * 256;
+        const int qi = i / HALF, j = i - qi * HALF;
+        qs[qi * HD + j] = qx[it] * qc[it] - qy[it] * qsn[it];
+        qs[qi * HD + j + HALF] = qy[it] * qc[it] + qx[it] * qsn[it];
     }
     __syncthreads();
 
@@ -235,11 +235,9 @@ __global__ __launch_bounds__(256) void attn_kernel(AttnArgs a) {
 #pragma unroll
                 for (int e = 0; e < EPV; ++e) o[e] = fmaf(p, vf[i][e], o[e]);
             }
-            // sum over the key slots: fixed shuffle tree inside the wave
+            // sum over the key slots: fixed tree inside the wave
 #pragma unroll
-            for (int off = DGW; off < 64; off <<= 1)
-#pragma unroll
-                for (int e = 0; e < EPV; ++e) o[e] += __shfl_xor(o[e], off, 64);
+            for (int e = 0; e < EPV; ++e) o[e] = lanes_sum<32, DGW>(o[e]);
             const int qq = q0 + qi, r = qq / G, gi = qq - r * G;
             if (lane < DGW && key0 <= a.pos0 + r) {  // (a chunk with no visible key leaves no partial)
                 if (a.direct) {

@@ -29,15 +29,63 @@ __device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
 __device__ __forceinline__ float ldf(const float* p) { return *p; }
 __device__ __forceinline__ float ldf(const uint16_t* p) { return bf2f(*p); }
 
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
+// {v, the value of the lane whose number differs in bit O}: the exchange of a reduction tree, on the vector ALU
+// (data-parallel moves inside a row of 16 lanes, row and half-wave swaps across) instead of a round trip
+// through the LDS crossbar per step.  For O >= 16 both lanes of a pair get the two values in the same order,
+// so what is made of them has to be symmetric.  All lanes of the wave are active.
+template <int O>
+__device__ __forceinline__ void lane_pair(uint32_t v, uint32_t& x, uint32_t& y) {
+    static_assert(O == 1 || O == 2 || O == 4 || O == 8 || O == 16 || O == 32, "one bit of the lane number");
+    if constexpr (O >= 16) {
+        if constexpr (O == 32) {
+            const auto s = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+            x = s[0]; y = s[1];
+        } else {
+            const auto s = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+            x = s[0]; y = s[1];
+        }
+    } else {
+        x = v;
+        if constexpr (O == 1) y = __builtin_amdgcn_update_dpp(0u, v, 0xB1, 0xf, 0xf, true);        // quad_perm [1,0,3,2]
+        else if constexpr (O == 2) y = __builtin_amdgcn_update_dpp(0u, v, 0x4E, 0xf, 0xf, true);   // quad_perm [2,3,0,1]
+        else if constexpr (O == 8) y = __builtin_amdgcn_update_dpp(0u, v, 0x128, 0xf, 0xf, true);  // row_ror 8
+        else y = __builtin_amdgcn_update_dpp(0u, (uint32_t)__builtin_amdgcn_update_dpp(0u, v, 0x1B, 0xf, 0xf, true), 0x141, 0xf, 0xf, true);  // quads reversed, then row_half_mirror
+    }
 }
-__device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-    return v;
+template <int O>
+__device__ __forceinline__ void lane_pair(float v, float& x, float& y) {
+    uint32_t a, b;
+    lane_pair<O>(__float_as_uint(v), a, b);
+    x = __uint_as_float(a); y = __uint_as_float(b);
+}
+// sum / maximum over the lanes whose numbers agree in all bits but HI .. LO, in that order of steps
+template <int HI, int LO = 1>
+__device__ __forceinline__ float lanes_sum(float v) {
+    float x, y;
+    lane_pair<HI>(v, x, y);
+    if constexpr (HI > LO) return lanes_sum<HI / 2, LO>(x + y);
+    else return x + y;
+}
+template <int HI, int LO = 1>
+__device__ __forceinline__ float lanes_max(float v) {
+    float x, y;
+    lane_pair<HI>(v, x, y);
+    if constexpr (HI > LO) return lanes_max<HI / 2, LO>(fmaxf(x, y));
+    else return fmaxf(x, y);
+}
+__device__ __forceinline__ float wave_sum(float v) { return lanes_sum<32>(v); }
+__device__ __forceinline__ float wave_max(float v) { return lanes_max<32>(v); }
+// maximum with the index that goes with it (ties: the lower index)
+template <int HI>
+__device__ __forceinline__ void lanes_argmax(float& v, int& i) {
+    float x, y;
+    uint32_t a, b;
+    lane_pair<HI>(v, x, y);
+    lane_pair<HI>((uint32_t)i, a, b);
+    const bool second = y > x || (y == x && (int)b < (int)a);
+    v = second ? y : x;
+    i = second ? (int)b : (int)a;
+    if constexpr (HI > 1) lanes_argmax<HI / 2>(v, i);
 }
 
 // value v of row m, column i -> the two bf16 parts used by the MFMA path:

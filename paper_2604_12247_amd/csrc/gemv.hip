@@ -26,15 +26,8 @@ __device__ __forceinline__ void head_partial(const HeadArgs& h, float (*zs)[SB_M
     if (h.logits && live && row_on) h.logits[(size_t)m * N + n] = z;
     float mx = z;
     int idx = live ? n : 0x7fffffff;
-#pragma unroll
-    for (int o = ROWS / 2; o > 0; o >>= 1) {
-        const float ov = __shfl_xor(mx, o, 64);
-        const int oi = __shfl_xor(idx, o, 64);
-        if (ov > mx || (ov == mx && oi < idx)) { mx = ov; idx = oi; }
-    }
-    float sum = live ? expf((z - mx) / h.T) : 0.f;
-#pragma unroll
-    for (int o = ROWS / 2; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
+    lanes_argmax<ROWS / 2>(mx, idx);
+    const float sum = lanes_sum<ROWS / 2>(live ? expf((z - mx) / h.T) : 0.f);
     if (i == 0 && row_on) {
         float* p = h.partials + ((size_t)m * nb + blockIdx.x) * 4;
         p[0] = mx;
@@ -91,6 +84,12 @@ __global__ __launch_bounds__(256) void gemv_valu_kernel(GemvArgs a) {
 
     for (int k0 = 0; k0 < K; k0 += KC) {
         const int kc = (K - k0 < KC) ? (K - k0) : KC;
+        // the chunk's first weights are requested before its rows are staged: a short matrix is one such round trip
+        float w0[R][8];
+        const bool live0 = lane * 8 < kc;
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+            if (live0) load8(wrow[r] + k0 + lane * 8, w0[r]);
         __syncthreads();
         if (a.norm_gain) {   // (one chunk)
             const bool on = tid * 4 < K;
@@ -118,11 +117,7 @@ __global__ __launch_bounds__(256) void gemv_valu_kernel(GemvArgs a) {
             }
         }
         __syncthreads();
-#pragma unroll 2
-        for (int kk = lane * 8; kk < kc; kk += 512) {
-            float w[R][8];
-#pragma unroll
-            for (int r = 0; r < R; ++r) load8(wrow[r] + k0 + kk, w[r]);
+        auto madd = [&](const float (&w)[R][8], int kk) {
 #pragma unroll
             for (int m = 0; m < M; ++m) {
                 float4 xa = *reinterpret_cast<const float4*>(&xs[m][kk]);
@@ -137,6 +132,14 @@ __global__ __launch_bounds__(256) void gemv_valu_kernel(GemvArgs a) {
                     acc[r][m] = s;
                 }
             }
+        };
+        if (live0) madd(w0, lane * 8);
+#pragma unroll 2
+        for (int kk = lane * 8 + 512; kk < kc; kk += 512) {
+            float w[R][8];
+#pragma unroll
+            for (int r = 0; r < R; ++r) load8(wrow[r] + k0 + kk, w[r]);
+            madd(w, kk);
         }
     }
 #pragma unroll

@@ -237,12 +237,7 @@ __device__ __forceinline__ void head_merge_body(const HeadArgs& h, const int M, 
                 if (v[u].x > mx || (v[u].x == mx && i < idx)) { mx = v[u].x; idx = i; }
             }
         }
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) {
-            float ov = __shfl_xor(mx, o, 64);
-            int oi = __shfl_xor(idx, o, 64);
-            if (ov > mx || (ov == mx && oi < idx)) { mx = ov; idx = oi; }
-        }
+        lanes_argmax<32>(mx, idx);
         if (lane == 0) { r_max[m][half] = mx; r_idx[m][half] = idx; }
     }
     __syncthreads();

@@ -592,16 +592,6 @@ hipError_t launch_prefill_split(const float* x, uint16_t* xs, int32_t plane_rows
 
 // ---------------------------------------------------------------- prompt attention
 typedef float f32x16 __attribute__((ext_vector_type(16)));
-// maximum / sum over a lane and its counterpart in the other half of the wave
-__device__ __forceinline__ float half_max(float v) {
-    const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    return fmaxf(__uint_as_float(s[0]), __uint_as_float(s[1]));
-}
-__device__ __forceinline__ float half_add(float v) {
-    const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    return __uint_as_float(s[0]) + __uint_as_float(s[1]);
-}
-
 // The prompt's attention for a bf16 cache: first the keys and values of all rows of the
 // super-pass go into the cache (rotary embedding on the keys, both rounded to bf16; V
 // transposed per page, as everywhere), then one launch computes every row's attention with
@@ -741,7 +731,7 @@ __device__ __forceinline__ void attn_softmax(const f32x16 (&st)[KT], f32x16 (&o)
     for (int kt = 0; kt < KT; ++kt)
 #pragma unroll
         for (int r = 0; r < 16; ++r) mx = fmaxf(mx, st[kt][r]);
-    mx = half_max(mx);
+    mx = lanes_max<32, 32>(mx);
     const float m_new = mx > m_run + 8.0f ? mx : m_run;
     if (__builtin_amdgcn_ballot_w64(m_new != m_run) != 0) {
         const float alpha = m_new == m_run ? 1.0f : __builtin_amdgcn_exp2f(m_run - m_new);
@@ -956,7 +946,7 @@ __global__ __launch_bounds__(64 * W, 2) void prefill_attn_kernel(AttnArgs a) {
         __syncthreads();                // ... and everybody's; every wave is done with this chunk
     }
     // ---- normalise; a lane has 4 neighbouring dims in 4 neighbouring registers
-    const float inv_l = 1.0f / half_add(l_run);
+    const float inv_l = 1.0f / lanes_sum<32, 32>(l_run);
     if (!qi.valid) return;
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt)
@@ -1124,7 +1114,7 @@ __global__ __launch_bounds__(64 * W, W == 4 ? 2 : 1) void prefill_attn_split_ker
         if (more) load_v(vp0, vp1);
     }
     // ---- the waves' results, brought to one reference point and added in wave order
-    l_run = half_add(l_run);
+    l_run = lanes_sum<32, 32>(l_run);
     if (lh == 0) { m_s[wave][li] = m_run; l_s[wave][li] = l_run; }
     __syncthreads();
     float mx = m_s[0][li];   // finite: wave 0 has key 0
