@@ -26,6 +26,12 @@ typedef float f32x2v __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2v{a, b}, bf16x2v));
 }
+// the high and the low bf16 parts of two floats (given as bits), packed; the values split_store leaves
+__device__ __forceinline__ void split_pair(uint32_t f0, uint32_t f1, uint32_t& h, uint32_t& l) {
+    const float a = __uint_as_float(f0), b = __uint_as_float(f1);
+    h = pack_bf16(a, b);
+    l = pack_bf16(a - __uint_as_float(h << 16), b - __uint_as_float(h & 0xffff0000u));
+}
 __device__ __forceinline__ float ldf(const float* p) { return *p; }
 __device__ __forceinline__ float ldf(const uint16_t* p) { return bf2f(*p); }
 

@@ -253,7 +253,11 @@ hipError_t launch_repack(const void* W, void* P, int32_t N, int32_t K, hipStream
     return hipGetLastError();
 }
 
-template <int RT, int EPI, int WPB, bool PACKED>
+// RAW: the rows come as floats and every block makes the two bf16 parts of what it multiplies by itself: the same
+// bytes through L2 and the same registers (the lanes of a row's high and low column load four of its eight floats each
+// and exchange parts), some 80 vector instructions per k block, and no launch before this one.
+// [6144 x 4096], one row: 13.6 -> 10.6 us with the launch it saves, [27648 x 5120], six rows: 49.4 -> 48.5.
+template <int RT, int EPI, int WPB, bool PACKED, bool RAW>
 __global__ __launch_bounds__(64 * WPB) void gemv_mfma_kernel(GemvArgs a) {
     constexpr int NT = 64 * WPB;
     static_assert(NT >= RT * 128, "the tails take one element per thread");
@@ -287,6 +291,7 @@ __global__ __launch_bounds__(64 * WPB) void gemv_mfma_kernel(GemvArgs a) {
     const uint32_t rows = a.row_mask ? a.row_mask : ((1u << M) - 1u);
     const bool bact = (rows >> (li & 7)) & 1u;
     const uint16_t* bp = a.xs + (size_t)li * K;
+    const float* xp = a.x + (size_t)(li & 7) * K + (li >> 3) * 4;   // (RAW)
 
     f32x4 acc[RT];
 #pragma unroll
@@ -310,13 +315,24 @@ __global__ __launch_bounds__(64 * WPB) void gemv_mfma_kernel(GemvArgs a) {
                 wr[t][u] = PACKED ? ld_weights_packed(wp[t] + (size_t)kc * 2048 + u * 512)
                                   : *reinterpret_cast<const uint4*>(wp[t] + off + SB_KOFF(lq, u));
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
-            br[u] = bact ? *reinterpret_cast<const uint4*>(bp + off + SB_KOFF(lq, u)) : make_uint4(0, 0, 0, 0);
+        for (int u = 0; u < 4; ++u) {
+            if (RAW) br[u] = bact ? *reinterpret_cast<const uint4*>(xp + off + SB_KOFF(lq, u)) : make_uint4(0, 0, 0, 0);
+            else br[u] = bact ? *reinterpret_cast<const uint4*>(bp + off + SB_KOFF(lq, u)) : make_uint4(0, 0, 0, 0);
+        }
     };
     auto mma_block = [&](const uint4 (&wr)[RT][4], const uint4 (&br)[4]) {
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             bf16x8 bv = __builtin_bit_cast(bf16x8, br[u]);
+            if (RAW) {   // columns 0-7: high parts, floats 0-3 here, 4-7 in the lane 8 further; columns 8-15: low parts
+                uint32_t h0, h1, l0, l1, r0, r1, t;
+                split_pair(br[u].x, br[u].y, h0, l0);
+                split_pair(br[u].z, br[u].w, h1, l1);
+                const bool low = li >= 8;
+                lane_pair<8>(low ? h0 : l0, t, r0);
+                lane_pair<8>(low ? h1 : l1, t, r1);
+                bv = __builtin_bit_cast(bf16x8, make_uint4(low ? r0 : h0, low ? r1 : h1, low ? l0 : r0, low ? l1 : r1));
+            }
 #pragma unroll
             for (int t = 0; t < RT; ++t)
                 acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wr[t][u]), bv, acc[t],
@@ -434,20 +450,22 @@ static int mfma_row_tiles(int32_t N) { return N >= 15000 ? 2 : 1; }  // (measure
 static int mfma_waves(int32_t N) { return N <= 4096 ? 8 : 4; }  // (measured: [6144 x 4096] is 9-12 % faster with four waves and the deeper ring, [5120 x K] the same with either)
 int head_blocks_mfma(int32_t N) { return (N + 16 * mfma_row_tiles(N) - 1) / (16 * mfma_row_tiles(N)); }
 
-template <int EPI, bool PACKED>
+template <int EPI, bool PACKED, bool RAW = false>
 static void launch_gemv_mfma_e(const GemvArgs& a, hipStream_t st) {
+    if constexpr (!RAW && EPI != EPI_RESID)
+        if (!a.xs) return launch_gemv_mfma_e<EPI, PACKED, true>(a, st);
     if constexpr (EPI == EPI_SWIGLU) {
-        gemv_mfma_kernel<2, EPI, 4, PACKED><<<a.N / 16, 256, 0, st>>>(a);
+        gemv_mfma_kernel<2, EPI, 4, PACKED, RAW><<<a.N / 16, 256, 0, st>>>(a);
     } else {
         const int rt = mfma_row_tiles(a.N), wpb = mfma_waves(a.N);
-        if (rt == 2) gemv_mfma_kernel<2, EPI, 4, PACKED><<<(a.N + 31) / 32, 256, 0, st>>>(a);
-        else if (wpb == 8) gemv_mfma_kernel<1, EPI, 8, PACKED><<<a.N / 16, 512, 0, st>>>(a);
-        else gemv_mfma_kernel<1, EPI, 4, PACKED><<<a.N / 16, 256, 0, st>>>(a);
+        if (rt == 2) gemv_mfma_kernel<2, EPI, 4, PACKED, RAW><<<(a.N + 31) / 32, 256, 0, st>>>(a);
+        else if (wpb == 8) gemv_mfma_kernel<1, EPI, 8, PACKED, RAW><<<a.N / 16, 512, 0, st>>>(a);
+        else gemv_mfma_kernel<1, EPI, 4, PACKED, RAW><<<a.N / 16, 256, 0, st>>>(a);
     }
 }
 
 hipError_t launch_gemv_mfma(const GemvArgs& a, hipStream_t st) {
-    if (a.w_dtype != SB_BF16 || a.K % 128 != 0 || a.N % 16 != 0 || a.M < 1 || a.M > 8 || !a.xs)
+    if (a.w_dtype != SB_BF16 || a.K % 128 != 0 || a.N % 16 != 0 || a.M < 1 || a.M > 8 || (!a.xs && (!a.x || a.epi == EPI_RESID)))
         return hipErrorInvalidValue;
     switch (a.epi) {
         case EPI_STORE: a.packed ? launch_gemv_mfma_e<EPI_STORE, true>(a, st) : launch_gemv_mfma_e<EPI_STORE, false>(a, st); break;
@@ -466,12 +484,10 @@ hipError_t launch_gemv_mfma(const GemvArgs& a, hipStream_t st) {
 
 // ---------------------------------------------------------------- head evaluation without a workspace
 // For callers that cannot allocate device memory (code under graph capture, tight serving
-// loops): the head partials and the split-bf16 operand of a single head evaluation live in a
-// file-scope device array instead of a caller's scratch buffer.  Each GPU holds its own copy
+// loops): the head partials of a single head evaluation live in a file-scope device array instead of a caller's scratch buffer.  Each GPU holds its own copy
 // of the array at its own address, looked up once per device; every call on a GPU shares it,
 // so calls that overlap on one GPU race.  Nothing in it has to start at zero: every element a
-// launch reads was written by that launch sequence (partials of all blocks of rows < M, the
-// operand rows of rows < M).
+// launch reads was written by that launch sequence (partials of all blocks of rows < M).
 static __device__ __align__(256) unsigned char scratch[SB_STATIC_SCRATCH_BYTES];
 
 namespace {

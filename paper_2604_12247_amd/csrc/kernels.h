@@ -73,9 +73,9 @@ struct GemvArgs {
     int32_t w_dtype;   // SB_FP32 / SB_BF16
     int32_t N;         // outputs per row of x (EPI_SWIGLU: d_ffn, W has 2N rows)
     int32_t K;
-    const float* x;    // [M][K] float (VALU path)
+    const float* x;    // [M][K] float (VALU path; MFMA path where xs is nullptr: the kernel splits the rows itself)
     const float* norm_gain;  // VALU path, K <= SB_VALU_NORM_K: x holds hidden rows, the kernel takes RMSNorm(x) * norm_gain (eps below)
-    const uint16_t* xs;  // MFMA path: split bf16 operand, [16][K]: rows 0-7 high parts, 8-15 low parts
+    const uint16_t* xs;  // MFMA path, or nullptr: split bf16 operand, [16][K]: rows 0-7 high parts, 8-15 low parts
     float* y;          // [M][ldy]: STORE writes, RESID adds, SWIGLU writes silu(g)*u (float)
     uint16_t* ys;      // MFMA pipeline: optional split-bf16 copy of the output [16][ldy]
     int32_t ldy;
@@ -230,7 +230,7 @@ hipError_t launch_prefill_split(const float* x, uint16_t* xs, int32_t plane_rows
 
 // Device memory that belongs to the library itself (a file-scope device array, one copy per
 // GPU): *out receives its address on the current device.  No allocation takes place.
-#define SB_STATIC_SCRATCH_BYTES (256 + SB_MAX_W * (SB_STATIC_MAX_N / 16) * 16 + 16 * SB_STATIC_MAX_K * 2)
+#define SB_STATIC_SCRATCH_BYTES (256 + SB_MAX_W * (SB_STATIC_MAX_N / 16) * 16)
 hipError_t static_scratch(void** out);
 
 hipError_t launch_copy(void* dst, const void* src, size_t nbytes, hipStream_t st);

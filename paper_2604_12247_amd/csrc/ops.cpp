@@ -30,6 +30,15 @@ static int op_check(const void* W, int32_t w_dtype, int32_t N, int32_t K, const 
     return SB_OK;
 }
 
+// The MFMA kernel splits float rows itself while other blocks already store results: where the caller's output
+// lies over its input, the rows are split into the scratch area first.
+static hipError_t op_rows(GemvArgs& g, const float* out, size_t n_out, uint16_t* xs, hipStream_t st) {
+    const uintptr_t x0 = (uintptr_t)g.x, x1 = x0 + (size_t)g.M * g.K * 4, o0 = (uintptr_t)out, o1 = o0 + n_out * 4;
+    if (!out || o1 <= x0 || x1 <= o0) return hipSuccess;
+    g.xs = xs;
+    return launch_split(g.x, xs, g.M, g.K, st);
+}
+
 int32_t sb_op_gemv(const void* W, int32_t w_dtype, int32_t N, int32_t K, const float* x, float* y, int32_t M,
                    int32_t kernel, void* scratch, void* stream) {
     int rc = op_check(W, w_dtype, N, K, x, M, kernel);
@@ -40,8 +49,7 @@ int32_t sb_op_gemv(const void* W, int32_t w_dtype, int32_t N, int32_t K, const f
     g.packed = kernel == SB_PROJ_MFMA_PACKED;
     if (kernel != SB_PROJ_VALU) {
         if (!scratch || ((uintptr_t)scratch & 15)) return fail(SB_EINVAL, "op_gemv: MFMA path needs aligned scratch");
-        g.xs = (uint16_t*)scratch;
-        HIP_TRY(launch_split(x, (uint16_t*)scratch, M, K, (hipStream_t)stream));
+        HIP_TRY(op_rows(g, g.y, (size_t)M * N, (uint16_t*)scratch, (hipStream_t)stream));
         HIP_TRY(launch_gemv_mfma(g, (hipStream_t)stream));
     } else {
         HIP_TRY(launch_gemv_valu(g, (hipStream_t)stream));
@@ -60,8 +68,7 @@ int32_t sb_op_gate_up(const void* W, int32_t w_dtype, int32_t N, int32_t K, cons
     g.packed = kernel == SB_PROJ_MFMA_PACKED;
     if (kernel != SB_PROJ_VALU) {
         if (!scratch || ((uintptr_t)scratch & 15)) return fail(SB_EINVAL, "op_gate_up: MFMA path needs aligned scratch");
-        g.xs = (uint16_t*)scratch;
-        HIP_TRY(launch_split(x, (uint16_t*)scratch, M, K, (hipStream_t)stream));
+        HIP_TRY(op_rows(g, g.y, (size_t)M * N, (uint16_t*)scratch, (hipStream_t)stream));
         HIP_TRY(launch_gemv_mfma(g, (hipStream_t)stream));
     } else {
         HIP_TRY(launch_gemv_valu(g, (hipStream_t)stream));
@@ -121,8 +128,7 @@ int32_t sb_op_head(const void* W, int32_t w_dtype, int32_t N, int32_t K, const f
     g.head.logits = logits; g.head.argmax_out = argmax_out; g.head.conf_out = conf_out; g.head.post = POST_NONE;
     g.packed = kernel == SB_PROJ_MFMA_PACKED;
     if (kernel != SB_PROJ_VALU) {
-        g.xs = (uint16_t*)(sc + 256 + align_up((size_t)SB_MAX_W * nb * 16, 256));
-        HIP_TRY(launch_split(x, const_cast<uint16_t*>(g.xs), M, K, (hipStream_t)stream));
+        HIP_TRY(op_rows(g, logits, (size_t)M * N, (uint16_t*)(sc + 256 + align_up((size_t)SB_MAX_W * nb * 16, 256)), (hipStream_t)stream));
         HIP_TRY(launch_gemv_mfma(g, (hipStream_t)stream));
     } else {
         HIP_TRY(launch_gemv_valu(g, (hipStream_t)stream));
@@ -151,8 +157,6 @@ int32_t sb_op_head_static(const void* W, int32_t w_dtype, int32_t N, int32_t K, 
     g.head.logits = nullptr; g.head.argmax_out = argmax_out; g.head.conf_out = conf_out; g.head.post = POST_NONE;
     g.packed = kernel == SB_PROJ_MFMA_PACKED;
     if (kernel != SB_PROJ_VALU) {
-        g.xs = (uint16_t*)(sc + 256 + align_up((size_t)SB_MAX_W * nb * 16, 256));
-        HIP_TRY(launch_split(x, const_cast<uint16_t*>(g.xs), M, K, (hipStream_t)stream));
         HIP_TRY(launch_gemv_mfma(g, (hipStream_t)stream));
     } else {
         HIP_TRY(launch_gemv_valu(g, (hipStream_t)stream));

@@ -406,6 +406,22 @@ def test_prompt_attention_wide_form(T, hd, n_ctx, M):
             assert np.max(np.abs(out[r, h * hd:(h + 1) * hd] - ref)) <= 2e-5, (h, r)
 
 
+@pytest.mark.parametrize("M", [1, 8])
+def test_gemv_output_over_its_input(T, M):
+    """y may be the memory of x (N == K): the same bits as with an output of its own."""
+    import paper_2604_12247_amd as sb
+    g = np.random.default_rng(31 + M)
+    W = _dev(T, si.round_to_bf16((g.standard_normal((4096, 4096)) * 0.02).astype(np.float32)).view(np.int16))
+    x = _dev(T, g.standard_normal((M, 4096)).astype(np.float32))
+    P = sb.op_repack(W)
+    ref = sb.op_gemv(P, x, sb.PROJ_MFMA_PACKED)
+    scratch = T.empty(sb.lib().sb_op_gemv_scratch_bytes(M, 4096), dtype=T.uint8, device="cuda")
+    rc = sb.lib().sb_op_gemv(P.data_ptr(), sb.BF16, 4096, 4096, x.data_ptr(), x.data_ptr(), M, sb.PROJ_MFMA_PACKED,
+                             scratch.data_ptr(), T.cuda.current_stream().cuda_stream)
+    assert rc == 0
+    assert T.equal(x, ref)
+
+
 # launches between the two above: key tiles taken apart by the four waves of a block (257 blocks of 32 queries up to
 # 319 of 128), with a prefix that ends inside a tile, fewer tiles than waves, a grouped-query shape whose
 # blocks straddle rows; then the smallest launch of the wide form
