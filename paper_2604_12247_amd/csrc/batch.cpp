@@ -273,27 +273,33 @@ int batch_round(sb_batch* bt, const std::vector<int>& act, const sb_params* cons
         sb_session* s = bt->seq[b];
         const sb_params* p = P[b];
         const int M = s->n_slots;
-        if (p->sample_temperature > 0.f) {
+        HeadArgs& h = hb.h[n_merge];
+        h.T = 1.0f; h.partials = wsp<float>(hs, hs->L.head_part); h.round = s->d_round; h.row0 = b * wc;
+        if (p->sample_temperature > 0.f) {   // (the acceptance kernels start from the arg max)
             if (p->n_sample_u < 2 * (int64_t)(s->c + M))
                 return fail(SB_EINVAL, "batch_decode: sample_u of sequence %d has %lld entries, this round needs %lld", b,
                             (long long)p->n_sample_u, 2 * (long long)(s->c + M));
-            SampleArgs sa{};
-            sa.logits = logits + (size_t)(b * wc) * c.vocab; sa.wts = wsp<float>(hs, hs->L.sample_w) + (size_t)(b * wc) * (c.vocab > 32 * 1024 ? c.vocab - 32 * 1024 : 0);
-            sa.V = c.vocab; sa.M = M; sa.n_drafts = s->n_drafts;
-            sa.temp = p->sample_temperature; sa.top_p = p->top_p; sa.round = s->d_round;
-            for (int i = 0; i < M; ++i) {
-                sa.ua[i] = p->sample_u[2 * (int64_t)(s->c + i)];
-                sa.ur[i] = p->sample_u[2 * (int64_t)(s->c + i) + 1];
-            }
-            HIP_TRY(launch_sample_accept(sa, st));
+            h.post = POST_NONE; h.argmax_out = s->d_round->g;
         } else {
-            HeadArgs& h = hb.h[n_merge];
-            h.T = 1.0f; h.partials = wsp<float>(hs, hs->L.head_part); h.post = POST_ACCEPT; h.round = s->d_round;
-            h.n_drafts = s->n_drafts; h.row0 = b * wc;
-            hb.M[n_merge++] = M;
+            h.post = POST_ACCEPT; h.n_drafts = s->n_drafts;
         }
+        hb.M[n_merge++] = M;
     }
-    if (n_merge) HIP_TRY(launch_head_merge_batch(hb, n_merge, nb_head, st));
+    HIP_TRY(launch_head_merge_batch(hb, n_merge, nb_head, st));
+    for (int b : act) {
+        sb_session* s = bt->seq[b];
+        const sb_params* p = P[b];
+        if (!(p->sample_temperature > 0.f)) continue;
+        SampleArgs sa{};
+        sa.logits = logits + (size_t)(b * wc) * c.vocab; sa.scratch = wsp<char>(hs, hs->L.sample_w); sa.row0 = b * wc;
+        sa.V = c.vocab; sa.M = s->n_slots; sa.n_drafts = s->n_drafts;
+        sa.temp = p->sample_temperature; sa.top_p = p->top_p; sa.round = s->d_round;
+        for (int i = 0; i < sa.M; ++i) {
+            sa.ua[i] = p->sample_u[2 * (int64_t)(s->c + i)];
+            sa.ur[i] = p->sample_u[2 * (int64_t)(s->c + i) + 1];
+        }
+        HIP_TRY(launch_sample_accept(sa, st));
+    }
     if ((rc = batch_readback(bt, act))) return rc;
     for (int b : act) {
         sb_session* s = bt->seq[b];

@@ -101,12 +101,15 @@ struct GemvArgs {
 // Sampling-mode acceptance over the final-head logits of the M verified rows (device, [M][V]).
 struct SampleArgs {
     const float* logits;
-    float* wts;   // scratch [M][V - 32768] for the soft-max weights of a vocabulary's tokens from 32768 on (unused below that)
+    void* scratch;   // sample_scratch_bytes(V) bytes for SB_MAX_W rows, 8-byte aligned; this launch uses rows row0 .. row0 + M - 1 of it
+    int32_t row0;
     int32_t V, M, n_drafts;
     float temp, top_p;
     float ua[SB_MAX_W], ur[SB_MAX_W];  // per row: uniform of the acceptance test, uniform of the draw
-    DevRound* round;                   // reads drafts[], writes g[], gconf[] (= P(draft)), n_matched, n_emit
+    DevRound* round;                   // reads drafts[] and g[] (the rows' arg max, from the head's merge), writes g[], gconf[] (= P(draft)), n_matched, n_emit
 };
+struct SampleEdge { unsigned long long need, above1, above2; uint32_t bin1, bin2; float cut, keep; };   // (in the scratch, per row)
+size_t sample_scratch_bytes(int32_t V);
 hipError_t launch_sample_accept(const SampleArgs& a, hipStream_t st);
 
 // Second stage of a head evaluation (launched by launch_gemv_* unless head.skip_merge is set).

@@ -342,159 +342,258 @@ hipError_t launch_head_merge_batch(const HeadMergeBatch& hb, int32_t n, int32_t 
 // -- softmax(z / temp), cut to its nucleus of mass top_p and renormalised -- the row's draft x is
 // accepted with probability P(x); at the first rejection the token is drawn from P without x;
 // when every draft is accepted and one more row exists its token is drawn from P.  Each emitted
-// token is then distributed exactly as the full model's own sample.  One block, rows in order;
-// all sums are taken in a fixed order.  Works on unnormalised weights e_j = exp((z_j - max)/temp).
-struct BlockRed {
-    float* red;  // [16] shared
-    __device__ __forceinline__ float sum(float v) {
-        v = wave_sum(v);
-        __syncthreads();
-        if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
-        __syncthreads();
-        float t = 0.f;
-#pragma unroll
-        for (int w = 0; w < 16; ++w) t += red[w];
-        return t;
-    }
-    __device__ __forceinline__ float max(float v) {
-        v = wave_max(v);
-        __syncthreads();
-        if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
-        __syncthreads();
-        float t = red[0];
-#pragma unroll
-        for (int w = 1; w < 16; ++w) t = fmaxf(t, red[w]);
-        return t;
-    }
-};
+// token is then distributed exactly as the full model's own sample.  Works on unnormalised weights
+// e_j = exp((z_j - max)/temp).
+//
+// The nucleus' edge -- the largest weight value `cut` such that the weights >= cut hold a share top_p of the
+// sum (so equal weights at its edge stay together) -- is found by three histograms of the weights' mass over
+// ten bits of their bit pattern each (monotone in the value of a positive float).  Mass is counted in units of
+// 2^-40 of the largest weight, in 64-bit integers: exact in any order, finer than a float sum of as many
+// terms.  All rows and all of the vocabulary go through each stage side by side; whether a row is reached at
+// all is decided in the last one.  What bounds it: the launches (six of 4 to 6 us).  One block that searched the
+// edge by bisection, row after row, took 345 us a row at V = 128256 and 100 us at 32000.
+constexpr int SMP_T = 1024, SMP_PER = 4, SMP_TOK = SMP_T * SMP_PER;   // threads, tokens per thread, tokens per block
+constexpr int SMP_BINS = 1024;
+constexpr float SMP_UNIT = 1099511627776.0f;   // 2^40
 
-// A thread's share (tokens tid, tid + 1024, ... of the V in w) of the sum of the weights >= t, added to f
-// in index order; sixteen loads are in flight at a time.
-__device__ __forceinline__ float add_at_least(const float* w, int V, float t, float f) {
-    int j = threadIdx.x;
-    for (; j + 15 * 1024 < V; j += 16 * 1024) {
-        float e[16];
-#pragma unroll
-        for (int i = 0; i < 16; ++i) e[i] = w[j + 1024 * i];
-#pragma unroll
-        for (int i = 0; i < 16; ++i)
-            if (e[i] >= t) f += e[i];
-    }
-    for (; j < V; j += 1024) { const float e = w[j]; if (e >= t) f += e; }
-    return f;
+int sample_blocks(int32_t V) { return (V + SMP_TOK - 1) / SMP_TOK; }
+// Scratch of SB_MAX_W rows: weights, histograms, what is known of the edge, per block the mass without the draft and the last token.
+struct SampleRow { float* w; unsigned long long* hist; SampleEdge* edge; float* bsum; int* blast; };
+size_t sample_scratch_bytes(int32_t V) {
+    return (size_t)SB_MAX_W * (3 * SMP_BINS * 8 + sizeof(SampleEdge) + (size_t)V * 4 + (size_t)sample_blocks(V) * 8);
+}
+__host__ __device__ __forceinline__ SampleRow sample_row(void* scratch, int V, int nb, int row) {
+    SampleRow r;
+    char* p = (char*)scratch;
+    r.hist = (unsigned long long*)p + (size_t)row * 3 * SMP_BINS;
+    p += (size_t)SB_MAX_W * 3 * SMP_BINS * 8;
+    r.edge = (SampleEdge*)p + row;
+    p += SB_MAX_W * sizeof(SampleEdge);
+    r.w = (float*)p + (size_t)row * V;
+    p += (size_t)SB_MAX_W * V * 4;
+    r.bsum = (float*)p + (size_t)row * nb;
+    p += (size_t)SB_MAX_W * nb * 4;
+    r.blast = (int*)p + (size_t)row * nb;
+    return r;
 }
 
-// Thread tid owns the weights of tokens tid, tid + 1024, ...: the first 32 of them stay in registers
-// through the passes of the nucleus search, the rest (vocabularies above 32768) in a.wts, where a
-// thread re-reads only what it wrote itself.
-__global__ __launch_bounds__(1024) void sample_accept_kernel(SampleArgs a) {
-    constexpr int NR = 32, VR = NR * 1024;
-    __shared__ float red[16];
-    __shared__ float seg[1024];
+// Largest bin whose mass, with that of all bins above and `above`, reaches `need`: {bin, mass above it}.
+// 1024 threads, one bin each; every thread gets the result.
+__device__ __forceinline__ void find_bin(const unsigned long long* hist, unsigned long long above, unsigned long long need, int& bin, unsigned long long& mass_above) {
+    __shared__ unsigned long long wsum[16];
+    __shared__ unsigned long long s_above;
+    __shared__ int s_bin;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int b = SMP_BINS - 1 - tid;   // from the top
+    unsigned long long own = hist[b], v = own;
+    for (int o = 1; o < 64; o <<= 1) {
+        const unsigned long long u = __shfl_up(v, o, 64);
+        if (lane >= o) v += u;
+    }
+    if (lane == 63) wsum[wave] = v;
+    if (tid == 0) { s_bin = 0; s_above = above; }
+    __syncthreads();
+    unsigned long long base = above;
+    for (int w = 0; w < wave; ++w) base += wsum[w];
+    const unsigned long long upto = base + v, before = upto - own;   // mass of the bins >= b; > b
+    if (upto >= need && before < need) { s_bin = b; s_above = before; }
+    __syncthreads();
+    bin = s_bin;
+    mass_above = s_above;
+    __syncthreads();
+}
+
+// grid (blocks of the vocabulary, rows).  Level 0 makes the weights, counts all of them by their bits 29..20 and is
+// told by the head's arg max where the maximum is; level 1 and 2 first finish the level before (every block for
+// itself, block 0 leaves it for the next launch), then count the weights that agree with it so far.
+template <int LEVEL>
+__global__ __launch_bounds__(SMP_T) void sample_hist_kernel(SampleArgs a) {
+    __shared__ unsigned long long h[SMP_BINS];
+    const int tid = threadIdx.x, row = blockIdx.y, V = a.V;
+    const SampleRow r = sample_row(a.scratch, V, gridDim.x, a.row0 + row);
+    h[tid] = 0;
+    uint32_t prefix = 0;
+    if (LEVEL > 0) {
+        unsigned long long above = 0, need;
+        if (LEVEL == 1) {
+            unsigned long long total;
+            int bin;
+            __shared__ unsigned long long tsum[16];
+            unsigned long long v = r.hist[tid];
+            for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+            if ((tid & 63) == 0) tsum[tid >> 6] = v;
+            __syncthreads();
+            total = 0;
+            for (int w = 0; w < 16; ++w) total += tsum[w];
+            need = (unsigned long long)((double)a.top_p * (double)total);
+            if (need < 1) need = 1;   // (the largest weight alone)
+            find_bin(r.hist, 0, need, bin, above);
+            prefix = (uint32_t)bin;
+        } else {
+            int bin;
+            need = r.edge[0].need;
+            find_bin(r.hist + SMP_BINS, r.edge[0].above1, need, bin, above);
+            prefix = (r.edge[0].bin1 << 10) | (uint32_t)bin;
+        }
+        if (blockIdx.x == 0 && tid == 0) {
+            if (LEVEL == 1) { r.edge[0].need = need; r.edge[0].above1 = above; r.edge[0].bin1 = prefix; }
+            else { r.edge[0].above2 = above; r.edge[0].bin2 = prefix; }
+        }
+    }
+    __syncthreads();
+    const float* z = a.logits + (size_t)row * V;
+    const float mx = LEVEL == 0 ? z[a.round->g[row]] : 0.f;
+    for (int i = 0; i < SMP_PER; ++i) {
+        const int j = blockIdx.x * SMP_TOK + i * SMP_T + tid;
+        if (j >= V) break;
+        float e;
+        if (LEVEL == 0) {
+            e = expf((z[j] - mx) / a.temp);
+            r.w[j] = e;
+        } else {
+            e = r.w[j];
+        }
+        const uint32_t bits = __float_as_uint(e);
+        if (!(e > 0.f) || (LEVEL > 0 && (bits >> (30 - 10 * LEVEL)) != prefix)) continue;
+        const uint32_t bin = LEVEL == 0 ? bits >> 20 : (bits >> (20 - 10 * LEVEL)) & (SMP_BINS - 1);
+        atomicAdd(&h[bin < SMP_BINS ? bin : SMP_BINS - 1], (unsigned long long)(e * SMP_UNIT + 0.5f));
+    }
+    __syncthreads();
+    if (h[tid]) atomicAdd(&r.hist[LEVEL * SMP_BINS + tid], h[tid]);
+}
+
+// grid (blocks of the vocabulary, rows): the edge, the mass it keeps, and per block what is left to draw from.
+__global__ __launch_bounds__(SMP_T) void sample_mass_kernel(SampleArgs a) {
+    __shared__ float ws[16];
+    __shared__ int wl[16];
+    const int tid = threadIdx.x, row = blockIdx.y, V = a.V;
+    const SampleRow r = sample_row(a.scratch, V, gridDim.x, a.row0 + row);
+    float cut = 0.f;
+    unsigned long long kept = 0;
+    if (a.top_p < 1.0f) {
+        int bin;
+        unsigned long long above;
+        find_bin(r.hist + 2 * SMP_BINS, r.edge[0].above2, r.edge[0].need, bin, above);
+        cut = __uint_as_float((r.edge[0].bin2 << 10) | (uint32_t)bin);
+        kept = above + r.hist[2 * SMP_BINS + bin];
+    } else {   // everything is kept
+        unsigned long long v = r.hist[tid];
+        __shared__ unsigned long long tsum[16];
+        for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+        if ((tid & 63) == 0) tsum[tid >> 6] = v;
+        __syncthreads();
+        for (int w = 0; w < 16; ++w) kept += tsum[w];
+    }
+    if (blockIdx.x == 0 && tid == 0) {
+        r.edge[0].cut = cut;
+        r.edge[0].keep = (float)((double)kept * (1.0 / (double)SMP_UNIT));
+    }
+    const int x = row < a.n_drafts ? a.round->drafts[row] : -1;
+    const int j0 = blockIdx.x * SMP_TOK + tid * SMP_PER;
+    float s = 0.f;
+    int last = -1;
+#pragma unroll
+    for (int i = 0; i < SMP_PER; ++i) {
+        const int j = j0 + i;
+        const float e = j < V ? r.w[j] : 0.f;
+        if (j < V && e >= cut && j != x) { s += e; last = j; }
+    }
+    s = wave_sum(s);
+    for (int o = 32; o > 0; o >>= 1) { const int v = __shfl_xor(last, o, 64); last = v > last ? v : last; }
+    if ((tid & 63) == 0) { ws[tid >> 6] = s; wl[tid >> 6] = last; }
+    __syncthreads();
+    if (tid == 0) {
+        float t = 0.f;
+        int l = -1;
+        for (int w = 0; w < 16; ++w) { t += ws[w]; l = wl[w] > l ? wl[w] : l; }
+        r.bsum[blockIdx.x] = t;
+        r.blast[blockIdx.x] = l;
+    }
+}
+
+// One block: the rows in order, until one is not accepted.
+__global__ __launch_bounds__(SMP_T) void sample_accept_kernel(SampleArgs a, int nb) {
+    __shared__ float wtot[16], s_bs[SMP_T], s_cut[SB_MAX_W], s_keep[SB_MAX_W], s_ex[SB_MAX_W];
+    __shared__ int s_bl[SMP_T], s_x[SB_MAX_W];
     __shared__ float s_base;
-    __shared__ int s_seg, s_tok;
-    BlockRed br{red};
-    const int tid = threadIdx.x, V = a.V;
-    const int Vw = V > VR ? V - VR : 0;   // weights kept in a.wts
+    __shared__ int s_blk, s_tok;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, V = a.V;
     DevRound* R = a.round;
+    if (tid < a.M) {   // every row's edge, draft and weight of the draft
+        const SampleRow r = sample_row(a.scratch, V, nb, a.row0 + tid);
+        const int x = tid < a.n_drafts ? R->drafts[tid] : -1;
+        const float cut = r.edge[0].cut, e = x >= 0 && x < V ? r.w[x] : 0.f;
+        s_cut[tid] = cut;
+        s_keep[tid] = r.edge[0].keep;
+        s_x[tid] = x;
+        s_ex[tid] = e < cut ? 0.f : e;
+    }
+    __syncthreads();
     int m = 0;       // accepted drafts so far (uniform)
     int drawn = -1;  // row at which a token was drawn
     for (int row = 0; row < a.M; ++row) {
-        const float* z = a.logits + (size_t)row * V;
-        float* w = a.wts + (size_t)row * Vw;
-        float mx = -SB_INF;
-        for (int j = tid; j < V; j += 1024) mx = fmaxf(mx, z[j]);
-        mx = br.max(mx);
-        float sm = 0.f;
-        float ev[NR];   // weight of token tid + 1024 i
-#pragma unroll
-        for (int i = 0; i < NR; ++i) {
-            const int j = tid + 1024 * i;
-            ev[i] = j < V ? expf((z[j] - mx) / a.temp) : 0.f;
-            if (j < V) sm += ev[i];
-        }
-        for (int j = tid; j < Vw; j += 1024) { const float e = expf((z[VR + j] - mx) / a.temp); w[j] = e; sm += e; }
-        const float S = br.sum(sm);
-        auto mass_at_least = [&](float t) {   // sum of the weights >= t, in a fixed order
-            float f = 0.f;
-#pragma unroll
-            for (int i = 0; i < NR; ++i)
-                if (tid + 1024 * i < V && ev[i] >= t) f += ev[i];
-            if (Vw > 0) f = add_at_least(w, Vw, t, f);
-            return br.sum(f);
-        };
-        // nucleus: the largest weight value `cut` such that the weights >= cut hold a share top_p
-        // of S (so equal weights at its edge stay together); found by bisection on the bit
-        // pattern of a positive float, which is monotone in its value
-        float cut = 0.f, keep = S;
-        if (a.top_p < 1.0f) {
-            const float need = a.top_p * S;
-            uint32_t lo = 0u, hi = __float_as_uint(1.0f) + 1u;  // the largest weight is exp(0) = 1
-            while (hi - lo > 1u) {
-                const uint32_t mid = lo + (hi - lo) / 2u;
-                if (mass_at_least(__uint_as_float(mid)) >= need) lo = mid; else hi = mid;
-            }
-            cut = __uint_as_float(lo);
-            keep = mass_at_least(cut);
-        }
-        const bool has_draft = row < a.n_drafts;
-        const int x = has_draft ? R->drafts[row] : -1;
-        float ex = 0.f;
-        if (x >= 0 && x < V) {
-            ex = expf((z[x] - mx) / a.temp);
-            if (ex < cut) ex = 0.f;
-        }
+        const SampleRow r = sample_row(a.scratch, V, nb, a.row0 + row);
+        const float cut = s_cut[row], keep = s_keep[row], ex = s_ex[row];
+        const int x = s_x[row];
         if (tid == 0) R->gconf[row] = ex / keep;   // P(x): the row's acceptance probability
-        if (has_draft && a.ua[row] * keep < ex) {  // accepted
+        if (row < a.n_drafts && a.ua[row] * keep < ex) {  // accepted
             if (tid == 0) R->g[row] = x;
             ++m;
             continue;
         }
-        // draw from P without x: inverse CDF over the tokens in index order
-        const float total = keep - ex, target = a.ur[row] * total;
-        const int per = (V + 1023) / 1024, j0 = tid * per, j1 = (j0 + per < V) ? j0 + per : V;
-        float ssum = 0.f;
-        int last_mass = -1;
-        for (int j = j0; j < j1; ++j) {
-            const float e = expf((z[j] - mx) / a.temp);
-            if (e >= cut && j != x) { ssum += e; last_mass = j; }
-        }
-        seg[tid] = ssum;
-        __syncthreads();
-        if (tid == 0) {
-            float c = 0.f;
-            int chosen = -1;
-            for (int t = 0; t < 1024; ++t) {
-                if (c + seg[t] > target) { chosen = t; break; }
-                c += seg[t];
-            }
-            s_seg = chosen;
-            s_base = c;
-            s_tok = -1;
-        }
-        __syncthreads();
-        const int chosen = s_seg;
-        if (chosen >= 0) {
-            if (tid == chosen) {
+        // draw from P without x: inverse CDF over the tokens in index order, first the block, then the token
+        const float target = a.ur[row] * (keep - ex);
+        if (tid == 0) { s_blk = -1; s_base = 0.f; s_tok = -1; }
+        for (int t0 = 0; t0 < nb; t0 += SMP_T) {
+            __syncthreads();
+            if (s_blk >= 0) break;
+            s_bs[tid] = t0 + tid < nb ? r.bsum[t0 + tid] : 0.f;
+            s_bl[tid] = t0 + tid < nb ? r.blast[t0 + tid] : -1;
+            __syncthreads();
+            if (tid == 0) {
+                const int n = nb - t0 < SMP_T ? nb - t0 : SMP_T;
                 float c = s_base;
-                int tok = last_mass;
-                for (int j = j0; j < j1; ++j) {
-                    const float e = expf((z[j] - mx) / a.temp);
-                    if (e >= cut && j != x) {
-                        c += e;
-                        if (c > target) { tok = j; break; }
-                    }
+                int last = s_tok;   // (rounding at the upper end: the last token that has mass)
+                for (int t = 0; t < n; ++t) {
+                    if (c + s_bs[t] > target) { s_blk = t0 + t; break; }
+                    c += s_bs[t];
+                    last = s_bl[t] >= 0 ? s_bl[t] : last;
                 }
-                s_tok = tok;
+                s_base = c;
+                s_tok = s_blk >= 0 ? 0x7fffffff : last;
             }
-            __syncthreads();
-        } else {  // rounding at the upper end: the last token that has mass
-            int lm = last_mass;
+        }
+        __syncthreads();
+        const int blk = s_blk;
+        if (blk >= 0) {
+            const int j0 = blk * SMP_TOK + tid * SMP_PER;
+            float e[SMP_PER], s = 0.f;
 #pragma unroll
-            for (int o = 32; o > 0; o >>= 1) { int v = __shfl_xor(lm, o, 64); lm = v > lm ? v : lm; }
-            const float best = br.max((float)lm);   // token ids are exact in a float up to 2^24
-            if (tid == 0) s_tok = (int)best;
+            for (int i = 0; i < SMP_PER; ++i) {
+                const int j = j0 + i;
+                e[i] = j < V ? r.w[j] : 0.f;
+                if (!(j < V && e[i] >= cut && j != x)) e[i] = 0.f;
+                s += e[i];
+            }
+            float v = s;   // inclusive scan over the block's threads
+            for (int o = 1; o < 64; o <<= 1) {
+                const float u = __shfl_up(v, o, 64);
+                if (lane >= o) v += u;
+            }
+            if (lane == 63) wtot[wave] = v;
             __syncthreads();
+            float c = s_base;
+            for (int w = 0; w < wave; ++w) c += wtot[w];
+            c += v - s;
+            int tok = 0x7fffffff;
+#pragma unroll
+            for (int i = 0; i < SMP_PER; ++i) {
+                c += e[i];
+                if (tok == 0x7fffffff && e[i] > 0.f && c > target) tok = j0 + i;
+            }
+            if (tok != 0x7fffffff) atomicMin(&s_tok, tok);
+            __syncthreads();
+            if (tid == 0 && s_tok == 0x7fffffff) s_tok = r.blast[blk];
         }
         if (tid == 0) R->g[row] = s_tok;
         drawn = row;
@@ -508,10 +607,21 @@ __global__ __launch_bounds__(1024) void sample_accept_kernel(SampleArgs a) {
 }
 
 hipError_t launch_sample_accept(const SampleArgs& a, hipStream_t st) {
-    if (!a.logits || !a.round || a.V < 1 || a.V > (1 << 24) || a.M < 1 || a.M > SB_MAX_W || !(a.temp > 0.f) || !(a.top_p > 0.f))
+    if (!a.logits || !a.round || !a.scratch || ((uintptr_t)a.scratch & 7) || a.V < 1 || a.V > (1 << 24) || a.M < 1 || a.row0 < 0 ||
+        a.row0 + a.M > SB_MAX_W || !(a.temp > 0.f) || !(a.top_p > 0.f))
         return hipErrorInvalidValue;
-    if (a.V > 32 * 1024 && !a.wts) return hipErrorInvalidValue;
-    sample_accept_kernel<<<1, 1024, 0, st>>>(a);
+    const int nb = sample_blocks(a.V);
+    const dim3 grid(nb, a.M);
+    const SampleRow r = sample_row(a.scratch, a.V, nb, a.row0);
+    hipError_t e = launch_fill_u32((uint32_t*)r.hist, (size_t)a.M * 3 * SMP_BINS * 2, 0u, st);
+    if (e != hipSuccess) return e;
+    sample_hist_kernel<0><<<grid, SMP_T, 0, st>>>(a);
+    if (a.top_p < 1.0f) {
+        sample_hist_kernel<1><<<grid, SMP_T, 0, st>>>(a);
+        sample_hist_kernel<2><<<grid, SMP_T, 0, st>>>(a);
+    }
+    sample_mass_kernel<<<grid, SMP_T, 0, st>>>(a);
+    sample_accept_kernel<<<1, SMP_T, 0, st>>>(a, nb);
     return hipGetLastError();
 }
 

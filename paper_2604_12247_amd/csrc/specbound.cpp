@@ -106,8 +106,7 @@ WsLayout ws_layout(const sb_config* c) {
     L.head_part = take((size_t)SB_MAX_W * L.head_blocks * 16);
     L.logits_exit = take((size_t)(c->n_exit_heads > 0 ? c->n_exit_heads : 1) * V * 4);
     L.logits_final = take((size_t)SB_MAX_W * V * 4);
-    // the sampling-mode acceptance kernel keeps the soft-max weights of a large vocabulary here
-    L.sample_w = take(V > 32 * 1024 ? (size_t)SB_MAX_W * (V - 32 * 1024) * 4 : 0);
+    L.sample_w = take(sample_scratch_bytes(c->vocab));   // sampling-mode acceptance
     L.round = take(sizeof(DevRound));
     L.table = take((size_t)L.n_pages * 4);
     L.prefill_gemm = resolve_proj(c) == SB_PROJ_MFMA_PACKED;
@@ -710,12 +709,12 @@ int verify_impl(sb_session* s, const sb_params* p, sb_verify_result* out) {
     HeadArgs h{};
     h.T = 1.0f; h.post = sampling ? POST_NONE : POST_ACCEPT; h.n_drafts = s->n_drafts;
     h.logits = (s->debug || sampling) ? wsp<float>(s, s->L.logits_final) : nullptr;
-    if (sampling) { h.argmax_out = s->d_round->g; h.conf_out = s->d_round->gconf; }   // (overwritten by the acceptance kernel)
+    if (sampling) { h.argmax_out = s->d_round->g; h.conf_out = s->d_round->gconf; }   // (the acceptance kernels start from the arg max, then overwrite both)
     if ((rc = join_head(s))) return rc;
     if ((rc = run_head(s, m->lm_head, m->final_norm, 0, M, h, m->stream))) return rc;
     if (sampling) {
         SampleArgs sa{};
-        sa.logits = wsp<float>(s, s->L.logits_final); sa.wts = wsp<float>(s, s->L.sample_w); sa.V = c.vocab; sa.M = M; sa.n_drafts = s->n_drafts;
+        sa.logits = wsp<float>(s, s->L.logits_final); sa.scratch = wsp<char>(s, s->L.sample_w); sa.V = c.vocab; sa.M = M; sa.n_drafts = s->n_drafts;
         sa.temp = p->sample_temperature; sa.top_p = p->top_p; sa.round = s->d_round;
         for (int i = 0; i < M; ++i) {
             sa.ua[i] = p->sample_u[2 * (int64_t)(s->c + i)];

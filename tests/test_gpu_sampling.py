@@ -108,6 +108,12 @@ def test_sampling_decisions_follow_the_rule_on_the_librarys_own_logits(sb, varia
     assert flagged <= 1 and accepted > 0 and drawn > 0, (flagged, accepted, drawn)
 
 
+# whole blocks of 4096 tokens exactly, one token tile more; a nucleus of the likeliest token alone, one that leaves out the last few
+@pytest.mark.parametrize("variant,vocab,temp,top_p", [("bf16", 8192, 1.0, 0.999), ("fp32", 4096, 0.7, 0.02), ("bf16", 8208, 1.0, 0.97)])
+def test_sampling_decisions_at_block_edges(sb, variant, vocab, temp, top_p):
+    test_sampling_decisions_follow_the_rule_on_the_librarys_own_logits(sb, variant, vocab, temp, top_p)
+
+
 @pytest.mark.parametrize("variant", ["fp32", "bf16"])
 @pytest.mark.parametrize("temp,top_p", [(1.0, 1.0), (0.3, 1.0), (1.0, 0.9)])
 def test_sampling_rounds_match_the_oracle(sb, variant, temp, top_p):
