@@ -209,57 +209,73 @@ hipError_t launch_read(const void* src, size_t nbytes, float* sink, hipStream_t 
 // Second stage of a head evaluation: one block merges the per-block partials
 // (max, arg max, sum of exp((z - max)/T)) of every row in a fixed order -- so the
 // result does not depend on block scheduling -- and carries out the exit test
-// (Eq. 2) or the acceptance rule.  Rows are merged side by side, 128 threads each (a
-// row's order of additions does not depend on how many rows there are).  When a draft
+// (Eq. 2) or the acceptance rule.  Every row is merged by all 1024 threads (so a row's order of additions
+// does not depend on how many rows there are), two rows at a time, each partial read once: what bounds it is
+// one trip to memory that blocks on other XCDs wrote (4008 partials, V = 128256: 13.3 -> 8.3 us a row
+// against 128 threads a row that went over them twice).  When a draft
 // exits, the block also embeds the drafted token as the next row (the next draft step
 // then starts at its first layer).  It is a kernel of its own: publishing the
 // partials inside the projection kernel would need a device-wide fence per
 // block, which on this chip writes back and invalidates a whole L2.
 __device__ __forceinline__ void head_merge_body(const HeadArgs& h, const int M, const int nb) {
-    __shared__ float r_max[SB_MAX_W][2], r_sum[SB_MAX_W][2];
-    __shared__ int r_idx[SB_MAX_W][2];
+    constexpr int NW = 16, U = 4, RC = 2;   // waves; loads in flight per row and lane; rows a wave takes at a time
+    __shared__ float r_max[SB_MAX_W][NW], r_sum[SB_MAX_W][NW];
+    __shared__ int r_idx[SB_MAX_W][NW];
     __shared__ int s_am[SB_MAX_W];
     __shared__ float s_cf[SB_MAX_W];
     __shared__ int s_embed_tok;
     __shared__ float e_red[4];
-    const int tid = threadIdx.x, lane = tid & 63, m = tid >> 7, t = tid & 127, half = (tid >> 6) & 1;
-    const float4* p = reinterpret_cast<const float4*>(h.partials) + (size_t)(h.row0 + (m < M ? m : 0)) * nb;
-    float mx = -SB_INF;
-    int idx = 0x7fffffff;
-    if (m < M) {
-        for (int b0 = t; b0 < nb; b0 += 512) {  // four independent loads per round
-            float4 v[4];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const float4* p = reinterpret_cast<const float4*>(h.partials) + (size_t)h.row0 * nb;
+    for (int r0 = 0; r0 < M; r0 += RC) {
+        float mx[RC], sum[RC];
+        int idx[RC];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) v[u] = (b0 + 128 * u < nb) ? p[b0 + 128 * u] : make_float4(-SB_INF, __int_as_float(0x7fffffff), 0.f, 0.f);
+        for (int r = 0; r < RC; ++r) { mx[r] = -SB_INF; sum[r] = 0.f; idx[r] = 0x7fffffff; }
+        for (int b0 = 0; b0 < nb; b0 += 1024 * U) {
+            float4 v[RC][U];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int i = __float_as_int(v[u].y);
-                if (v[u].x > mx || (v[u].x == mx && i < idx)) { mx = v[u].x; idx = i; }
+            for (int r = 0; r < RC; ++r)
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int b = b0 + 1024 * u + tid;
+                    v[r][u] = (b < nb && r0 + r < M) ? p[(size_t)(r0 + r) * nb + b] : make_float4(-SB_INF, __int_as_float(0x7fffffff), 0.f, 0.f);
+                }
+#pragma unroll
+            for (int r = 0; r < RC; ++r) {
+                const float old = mx[r];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int i = __float_as_int(v[r][u].y);
+                    if (v[r][u].x > mx[r] || (v[r][u].x == mx[r] && i < idx[r])) { mx[r] = v[r][u].x; idx[r] = i; }
+                }
+                if (mx[r] > -SB_INF) {
+                    sum[r] *= expf((old - mx[r]) / h.T);
+#pragma unroll
+                    for (int u = 0; u < U; ++u) sum[r] += v[r][u].z * expf((v[r][u].x - mx[r]) / h.T);
+                }
             }
         }
-        lanes_argmax<32>(mx, idx);
-        if (lane == 0) { r_max[m][half] = mx; r_idx[m][half] = idx; }
-    }
-    __syncthreads();
-    float gmax = 0.f;
-    if (m < M) {
-        gmax = r_max[m][0];
-        int gi = r_idx[m][0];
-        if (r_max[m][1] > gmax || (r_max[m][1] == gmax && r_idx[m][1] < gi)) { gmax = r_max[m][1]; gi = r_idx[m][1]; }
-        if (t == 0) s_am[m] = gi == 0x7fffffff ? 0 : gi;
-        float sum = 0.f;
-        for (int b0 = t; b0 < nb; b0 += 512) {
-            float4 v[4];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) v[u] = (b0 + 128 * u < nb) ? p[b0 + 128 * u] : make_float4(-SB_INF, 0.f, 0.f, 0.f);
-#pragma unroll
-            for (int u = 0; u < 4; ++u) sum += v[u].z * expf((v[u].x - gmax) / h.T);
+        for (int r = 0; r < RC; ++r) {
+            if (r0 + r >= M) break;
+            const float own = mx[r];
+            lanes_argmax<32>(mx[r], idx[r]);
+            const float w = wave_sum(own > -SB_INF ? sum[r] * expf((own - mx[r]) / h.T) : 0.f);
+            if (lane == 0) { r_max[r0 + r][wave] = mx[r]; r_idx[r0 + r][wave] = idx[r]; r_sum[r0 + r][wave] = w; }
         }
-        sum = wave_sum(sum);
-        if (lane == 0) r_sum[m][half] = sum;
     }
     __syncthreads();
-    if (tid < M) s_cf[tid] = 1.0f / (r_sum[tid][0] + r_sum[tid][1]);
+    if (tid < SB_MAX_W * NW) {   // sixteen lanes a row
+        const int m = tid / NW, w = tid % NW;
+        const bool on = m < M;
+        const float own = on ? r_max[m][w] : 0.f;
+        float mx = own;
+        int idx = on ? r_idx[m][w] : 0;
+        lanes_argmax<NW / 2>(mx, idx);
+        const float sum = lanes_sum<NW / 2>(on && own > -SB_INF ? r_sum[m][w] * expf((own - mx) / h.T) : 0.f);
+        if (on && w == 0) { s_am[m] = idx == 0x7fffffff ? 0 : idx; s_cf[m] = 1.0f / sum; }
+    }
     if (tid == 0) s_embed_tok = -1;
     __syncthreads();
     if (tid == 0) {
