@@ -147,7 +147,6 @@ __global__ __launch_bounds__(256) void attn_kernel(AttnArgs a) {
                 f[e] = lo ? (x * c - y * sn) : (y * c + x * sn);
             }
             kreg[i] = KvVec<KVT>::pack(f);
-            if (qg == 0) *reinterpret_cast<uint4*>(kbase + kaddr + i * EPV) = kreg[i];
         }
     }
 #pragma unroll
@@ -159,7 +158,17 @@ __global__ __launch_bounds__(256) void attn_kernel(AttnArgs a) {
 #pragma unroll
             for (int e = 0; e < EPV; ++e) f[e] = vp[e];
             vreg[i] = KvVec<KVT>::pack(f);
-            if (qg == 0) *reinterpret_cast<uint4*>(vbase + vaddr[i]) = vreg[i];
+        }
+    }
+    // (stored after the last of these loads: a store between them, which might alias, would make each a round trip of its own)
+    if (qg == 0) {
+        if (kkey >= a.pos0 && kkey < n_total)
+#pragma unroll
+            for (int i = 0; i < NKV; ++i) *reinterpret_cast<uint4*>(kbase + kaddr + i * EPV) = kreg[i];
+#pragma unroll
+        for (int i = 0; i < KPT; ++i) {
+            const int key = key0 + vks + KS * i;
+            if (key >= a.pos0 && key < n_total) *reinterpret_cast<uint4*>(vbase + vaddr[i]) = vreg[i];
         }
     }
     // ---- rotated queries -> LDS
@@ -400,20 +409,18 @@ struct AttnItem {
                 if (key >= a.pos0 && key < n_total) {
                     const float* kp = a.q + (size_t)(key - a.pos0) * a.qkv_rows + (size_t)(Hq + g) * HD;
     #pragma unroll
-                    for (int ks = 0; ks < KSQ; ++ks) {
-                        const int d0 = ks * 32 + lq * 8;
-                        const bool lo = d0 < HALF;
-                        const int dj = lo ? d0 : d0 - HALF;
-                        float f[8];
+                    for (int ks = 0; ks < KSQ / 2; ++ks) {   // steps ks and ks + KSQ / 2: the two ends of the rotation's pairs
+                        float lo[8], hi[8];
     #pragma unroll
                         for (int e = 0; e < 8; ++e) {
-                            const int j = dj + e;
-                            float c = a.rope_cos[(size_t)key * HALF + j], sn = a.rope_sin[(size_t)key * HALF + j];
-                            float x = kp[j], y = kp[j + HALF];
-                            f[e] = lo ? (x * c - y * sn) : (y * c + x * sn);
+                            const int j = ks * 32 + lq * 8 + e;
+                            const float c = a.rope_cos[(size_t)key * HALF + j], sn = a.rope_sin[(size_t)key * HALF + j];
+                            const float x = kp[j], y = kp[j + HALF];
+                            lo[e] = x * c - y * sn;
+                            hi[e] = y * c + x * sn;
                         }
-                        kreg[t][ks] = KvVec<uint16_t>::pack(f);
-                        if (zb == 0) *reinterpret_cast<uint4*>(kbase + kaddr[t] + ks * 32) = kreg[t][ks];
+                        kreg[t][ks] = KvVec<uint16_t>::pack(lo);
+                        kreg[t][ks + KSQ / 2] = KvVec<uint16_t>::pack(hi);
                     }
                 }
             }
@@ -435,8 +442,25 @@ struct AttnItem {
                             }
                         }
                         vreg[dt][ks] = make_uint4(w[0], w[1], w[2], w[3]);
-                        if (zb == 0) *reinterpret_cast<uint4*>(vbase + vaddr[ks] + dt * 16 * SB_KV_BLOCK) = vreg[dt][ks];
                     }
+                }
+            }
+            // stored after the last of these loads: a store between them, which might alias, would make each a round
+            // trip of its own (the block with the new rows is what a short context waits for)
+            if (zb == 0) {
+    #pragma unroll
+                for (int t = 0; t < 2; ++t) {
+                    const int key = key0 + wave * 32 + t * 16 + li;
+                    if (key >= a.pos0 && key < n_total)
+    #pragma unroll
+                        for (int ks = 0; ks < KSQ; ++ks) *reinterpret_cast<uint4*>(kbase + kaddr[t] + ks * 32) = kreg[t][ks];
+                }
+    #pragma unroll
+                for (int ks = 0; ks < KSV; ++ks) {
+                    const int kf = key0 + ks * 32 + lq * 8;
+                    if (kf + 8 > a.pos0 && kf < n_total)
+    #pragma unroll
+                        for (int dt = 0; dt < DT; ++dt) *reinterpret_cast<uint4*>(vbase + vaddr[ks] + dt * 16 * SB_KV_BLOCK) = vreg[dt][ks];
                 }
             }
         }

@@ -85,11 +85,13 @@ __global__ __launch_bounds__(256) void gemv_valu_kernel(GemvArgs a) {
     for (int k0 = 0; k0 < K; k0 += KC) {
         const int kc = (K - k0 < KC) ? (K - k0) : KC;
         // the chunk's first weights are requested before its rows are staged: a short matrix is one such round trip
-        float w0[R][8];
-        const bool live0 = lane * 8 < kc;
+        float w0[R][8], w1[R][8];
+        const bool live0 = lane * 8 < kc, live1 = lane * 8 + 512 < kc;
 #pragma unroll
-        for (int r = 0; r < R; ++r)
+        for (int r = 0; r < R; ++r) {
             if (live0) load8(wrow[r] + k0 + lane * 8, w0[r]);
+            if (live1) load8(wrow[r] + k0 + lane * 8 + 512, w1[r]);
+        }
         __syncthreads();
         if (a.norm_gain) {   // (one chunk)
             const bool on = tid * 4 < K;
@@ -109,12 +111,22 @@ __global__ __launch_bounds__(256) void gemv_valu_kernel(GemvArgs a) {
                 if (on) *reinterpret_cast<float4*>(&xs[m][tid * 4]) = make_float4(v[m].x * inv * g.x, v[m].y * inv * g.y, v[m].z * inv * g.z, v[m].w * inv * g.w);
             }
         } else {
-            for (int i = tid * 4; i < M * KC; i += 1024) {
-                int m = i / KC, kk = i - m * KC;
-                if (kk < kc)
-                    *reinterpret_cast<float4*>(&xs[m][kk]) =
-                        *reinterpret_cast<const float4*>(a.x + (size_t)m * K + k0 + kk);
-            }
+            // all loads before the first store (a loop of load and store would be one round trip after the other)
+            float4 v[M][KC / 1024];
+#pragma unroll
+            for (int m = 0; m < M; ++m)
+#pragma unroll
+                for (int i = 0; i < KC / 1024; ++i) {
+                    const int kk = i * 1024 + tid * 4;
+                    v[m][i] = kk < kc ? *reinterpret_cast<const float4*>(a.x + (size_t)m * K + k0 + kk) : make_float4(0.f, 0.f, 0.f, 0.f);
+                }
+#pragma unroll
+            for (int m = 0; m < M; ++m)
+#pragma unroll
+                for (int i = 0; i < KC / 1024; ++i) {
+                    const int kk = i * 1024 + tid * 4;
+                    if (kk < kc) *reinterpret_cast<float4*>(&xs[m][kk]) = v[m][i];
+                }
         }
         __syncthreads();
         auto madd = [&](const float (&w)[R][8], int kk) {
@@ -134,8 +146,9 @@ __global__ __launch_bounds__(256) void gemv_valu_kernel(GemvArgs a) {
             }
         };
         if (live0) madd(w0, lane * 8);
+        if (live1) madd(w1, lane * 8 + 512);
 #pragma unroll 2
-        for (int kk = lane * 8 + 512; kk < kc; kk += 512) {
+        for (int kk = lane * 8 + 1024; kk < kc; kk += 512) {
             float w[R][8];
 #pragma unroll
             for (int r = 0; r < R; ++r) load8(wrow[r] + k0 + kk, w[r]);

@@ -232,7 +232,7 @@ __device__ __forceinline__ void head_merge_body(const HeadArgs& h, const int M, 
         int idx[RC];
 #pragma unroll
         for (int r = 0; r < RC; ++r) { mx[r] = -SB_INF; sum[r] = 0.f; idx[r] = 0x7fffffff; }
-        for (int b0 = 0; b0 < nb; b0 += 1024 * U) {
+        for (int b0 = 0; b0 + wave * 64 < nb; b0 += 1024 * U) {   // (waves past the partials have nothing to do)
             float4 v[RC][U];
 #pragma unroll
             for (int r = 0; r < RC; ++r)
@@ -243,6 +243,7 @@ __device__ __forceinline__ void head_merge_body(const HeadArgs& h, const int M, 
                 }
 #pragma unroll
             for (int r = 0; r < RC; ++r) {
+                if (r0 + r >= M) break;
                 const float old = mx[r];
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
@@ -259,9 +260,12 @@ __device__ __forceinline__ void head_merge_body(const HeadArgs& h, const int M, 
 #pragma unroll
         for (int r = 0; r < RC; ++r) {
             if (r0 + r >= M) break;
-            const float own = mx[r];
-            lanes_argmax<32>(mx[r], idx[r]);
-            const float w = wave_sum(own > -SB_INF ? sum[r] * expf((own - mx[r]) / h.T) : 0.f);
+            float w = 0.f;
+            if (wave * 64 < nb) {
+                const float own = mx[r];
+                lanes_argmax<32>(mx[r], idx[r]);
+                w = wave_sum(own > -SB_INF ? sum[r] * expf((own - mx[r]) / h.T) : 0.f);
+            }
             if (lane == 0) { r_max[r0 + r][wave] = mx[r]; r_idx[r0 + r][wave] = idx[r]; r_sum[r0 + r][wave] = w; }
         }
     }
