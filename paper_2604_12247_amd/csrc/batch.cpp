@@ -125,6 +125,8 @@ int batch_round(sb_batch* bt, const std::vector<int>& act, const sb_params* cons
             if (drafting[b]) step.push_back(b);
         if (step.empty()) break;
         std::vector<int> forced(B, -1), over(B, -1);
+        EmbedBatch eb{};
+        int n_embed = 0;
         for (int b : step) {
             sb_session* s = bt->seq[b];
             const sb_params* p = P[b];
@@ -140,19 +142,20 @@ int batch_round(sb_batch* bt, const std::vector<int>& act, const sb_params* cons
             if (over[b] < -1) over[b] = -1;
             const int idx = s->n_slots, slot = b * wc + idx;
             if (!(idx > 0 && s->next_embedded)) {
-                RowToks t;
-                for (int r = 0; r < SB_MAX_W; ++r) t.tok[r] = 0;
-                t.tok[0] = idx == 0 ? s->pending : s->draft_host[idx - 1];
-                EmbedNorm en{m->attn_norm[0], wsp<uint16_t>(hs, hs->L.xs_attn) + (size_t)slot * d,
-                             wsp<float>(hs, hs->L.ssq_attn) + (size_t)slot * hs->L.ssq_ld, hs->L.ssq_ld};
-                HIP_TRY(launch_embed(m->embed, c.weight_dtype, c.vocab, d, wsp<float>(hs, hs->L.H) + (size_t)slot * d, 1, t,
-                                     s->d_round->slot_tok + idx, &s->d_round->exit_flag, en, st));
+                EmbedRow& r = eb.row[n_embed++];
+                r.tok = idx == 0 ? s->pending : s->draft_host[idx - 1];
+                r.slot_tok = s->d_round->slot_tok + idx;
+                r.exit_flag_to_clear = &s->d_round->exit_flag;
+                r.H = wsp<float>(hs, hs->L.H) + (size_t)slot * d;
+                r.en = EmbedNorm{m->attn_norm[0], wsp<uint16_t>(hs, hs->L.xs_attn) + (size_t)slot * d,
+                                 wsp<float>(hs, hs->L.ssq_attn) + (size_t)slot * hs->L.ssq_ld, hs->L.ssq_ld};
             }
             s->next_embedded = false;
             s->draft_counter++; s->st.draft_steps++; s->n_slots++;
             s->reached[idx] = 0; s->exit_layer[idx] = 0; s->draft_host[idx] = -1;
             inflight[b] = 1;
         }
+        if (n_embed) HIP_TRY(launch_embed_batch(m->embed, c.weight_dtype, c.vocab, d, eb, n_embed, st));
         std::vector<int> exit_at(B, 0), heads_run(B, 0);
         for (int l = 1; l <= d_max_all; ++l) {
             uint32_t mask = 0, newest = 0;

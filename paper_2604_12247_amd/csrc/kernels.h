@@ -126,6 +126,10 @@ int head_blocks_mfma(int32_t N);
 hipError_t launch_embed(const void* E, int32_t w_dtype, int32_t vocab, int32_t d, float* H, int32_t M,
                         RowToks toks, const int32_t* slot_tok, int32_t* exit_flag_to_clear, EmbedNorm en,
                         hipStream_t st);
+// One row each of several sequences (batch > 1), wherever they lie, in one launch.
+struct EmbedRow { int32_t tok; const int32_t* slot_tok; int32_t* exit_flag_to_clear; float* H; EmbedNorm en; };
+struct EmbedBatch { EmbedRow row[SB_MAX_W]; };
+hipError_t launch_embed_batch(const void* E, int32_t w_dtype, int32_t vocab, int32_t d, const EmbedBatch& eb, int32_t n, hipStream_t st);
 hipError_t launch_rmsnorm(const float* x, const float* gain, float* out, uint16_t* out_split, int32_t ld_split,
                           int32_t M, int32_t d, float eps, hipStream_t st);
 hipError_t launch_gemv_valu(const GemvArgs& a, hipStream_t st);

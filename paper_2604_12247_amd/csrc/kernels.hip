@@ -93,6 +93,22 @@ hipError_t launch_embed(const void* E, int32_t w_dtype, int32_t vocab, int32_t d
     return hipGetLastError();
 }
 
+// The same for one row each of n sequences.
+template <typename WT>
+__global__ __launch_bounds__(256) void embed_batch_kernel(const WT* __restrict__ E, int vocab, int d, EmbedBatch eb) {
+    __shared__ float red[4];
+    const EmbedRow r = eb.row[blockIdx.x];
+    const int tok = r.tok < 0 ? *r.slot_tok : r.tok;
+    if (r.exit_flag_to_clear && threadIdx.x == 0) *r.exit_flag_to_clear = 0;
+    embed_row<WT>(E, vocab, d, r.H, tok, 0, r.en, red);
+}
+hipError_t launch_embed_batch(const void* E, int32_t w_dtype, int32_t vocab, int32_t d, const EmbedBatch& eb, int32_t n, hipStream_t st) {
+    if (n < 1 || n > SB_MAX_W) return hipErrorInvalidValue;
+    if (w_dtype == SB_BF16) embed_batch_kernel<uint16_t><<<n, 256, 0, st>>>((const uint16_t*)E, vocab, d, eb);
+    else embed_batch_kernel<float><<<n, 256, 0, st>>>((const float*)E, vocab, d, eb);
+    return hipGetLastError();
+}
+
 // ---------------------------------------------------------------- RMSNorm
 // out = x / sqrt(mean(x^2) + eps) * gain, one block per row.
 __global__ __launch_bounds__(256) void rmsnorm_kernel(const float* __restrict__ x, const float* __restrict__ gain,
