@@ -139,6 +139,19 @@ __device__ __forceinline__ void load8(const float* p, float (&w)[8]) {
     w[4] = b.x; w[5] = b.y; w[6] = b.z; w[7] = b.w;
 }
 
+// eight values of a hidden row and, where nx is given, the bf16 parts of gain * value (16-byte stores; the places
+// are multiples of 8 elements)
+__device__ __forceinline__ void store8_split(const float (&v)[8], const float (&gain)[8], float* h, uint16_t* nx, size_t hi, size_t lo) {
+    *reinterpret_cast<float4*>(h) = make_float4(v[0], v[1], v[2], v[3]);
+    *reinterpret_cast<float4*>(h + 4) = make_float4(v[4], v[5], v[6], v[7]);
+    if (!nx) return;
+    uint32_t a[4], b[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) split_pair(__float_as_uint(v[2 * k] * gain[2 * k]), __float_as_uint(v[2 * k + 1] * gain[2 * k + 1]), a[k], b[k]);
+    *reinterpret_cast<uint4*>(nx + hi) = make_uint4(a[0], a[1], a[2], a[3]);
+    *reinterpret_cast<uint4*>(nx + lo) = make_uint4(b[0], b[1], b[2], b[3]);
+}
+
 __device__ __forceinline__ float silu_mul(float g, float u) { return g / (1.0f + expf(-g)) * u; }
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));

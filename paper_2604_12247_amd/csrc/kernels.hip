@@ -49,12 +49,9 @@ __device__ __forceinline__ void embed_row(const WT* __restrict__ E, int vocab, i
         for (int j = 0; j < VMAX; ++j) {
             const int gi = tid + j * 256;
             if (gi < ngrp) {
+                store8_split(v[j], gn[j], H + (size_t)r * d + gi * 8, en.nx, (size_t)r * d + gi * 8, (size_t)(8 + r) * d + gi * 8);
 #pragma unroll
-                for (int k = 0; k < 8; ++k) {
-                    H[(size_t)r * d + gi * 8 + k] = v[j][k];
-                    ss += v[j][k] * v[j][k];
-                    if (en.nx) split_store(en.nx, d, r, gi * 8 + k, v[j][k] * gn[j][k]);
-                }
+                for (int k = 0; k < 8; ++k) ss += v[j][k] * v[j][k];
             }
         }
         for (int i = VMAX * 2048 + tid; i < d; i += 256) {  // d > 8192
