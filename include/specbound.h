@@ -363,7 +363,7 @@ int32_t sb_op_rmsnorm(const float *x, const float *gain, float *out, int32_t M, 
 /* y[m][n] = sum_k W[n][k] x[m][k]; W [N][K] in w_dtype, x [M][K], y [M][N] float.
  * kernel: SB_PROJ_VALU, SB_PROJ_MFMA or SB_PROJ_MFMA_PACKED (bf16 only; K % 128 == 0,
  * N % 16 == 0; PACKED: W is the output of sb_op_repack).
- * scratch: device, sb_op_gemv_scratch_bytes(M, K) bytes (MFMA operand staging). */
+ * scratch: device, sb_op_gemv_scratch_bytes(M, K) bytes (MFMA path: used where y lies over x). */
 int32_t sb_op_gemv(const void *W, int32_t w_dtype, int32_t N, int32_t K, const float *x, float *y,
                    int32_t M, int32_t kernel, void *scratch, void *stream);
 size_t sb_op_gemv_scratch_bytes(int32_t M, int32_t K);
@@ -389,7 +389,7 @@ size_t sb_op_head_scratch_bytes(int32_t M, int32_t N, int32_t K);
 /* sb_op_head for callers that cannot allocate device memory or carry a workspace (code under
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc): the same kernels
  * and the same results as sb_op_head with logits == NULL, with the scratch area in a static
- * device array of the library (1.3 MB, held by every GPU the library runs on until the
+ * device array of the library (1.0 MB, held by every GPU the library runs on until the
  * process ends) instead of a caller's buffer.  The call allocates nothing.  Limits:
  * N <= SB_STATIC_MAX_N and K <= SB_STATIC_MAX_K, else SB_ECAPACITY; otherwise arguments and
  * errors as sb_op_head.  All calls on one GPU share the array (its contents are whatever the

@@ -595,10 +595,10 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 // The prompt's attention for a bf16 cache: first the keys and values of all rows of the
 // super-pass go into the cache (rotary embedding on the keys, both rounded to bf16; V
 // transposed per page, as everywhere), then one launch computes every row's attention with
-// the running-softmax scheme: a block owns 64 queries of one kv head (rows x the heads of
-// its group, 128 in the wide form), walks the 64-key chunks up to its last row's position and
-// keeps the running maximum, the sum and the weighted values of each query in registers -- no
-// per-chunk partials, no merge pass.  Both products run on the matrix cores with hi + lo pairs
+// the running-softmax scheme: a wave owns 32 queries of one kv head (rows x the heads of
+// its group), walks the keys up to its last row's position and keeps a reference point of the
+// exponentials, their sum and the weighted values of each query in registers -- no
+// partials in memory, no merge pass.  Both products run on the matrix cores with hi + lo pairs
 // for the fp32 side (queries, probabilities) like the decode kernel; a query's result depends
 // only on its own column of the accumulators, not on the other queries of the block.
 //
