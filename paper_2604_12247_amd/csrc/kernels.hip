@@ -222,77 +222,81 @@ hipError_t launch_read(const void* src, size_t nbytes, float* sink, hipStream_t 
 // Second stage of a head evaluation: one block merges the per-block partials
 // (max, arg max, sum of exp((z - max)/T)) of every row in a fixed order -- so the
 // result does not depend on block scheduling -- and carries out the exit test
-// (Eq. 2) or the acceptance rule.  Every row is merged by all 1024 threads (so a row's order of additions
-// does not depend on how many rows there are), two rows at a time, each partial read once: what bounds it is
-// one trip to memory that blocks on other XCDs wrote (4008 partials, V = 128256: 13.3 -> 8.3 us a row
-// against 128 threads a row that went over them twice).  When a draft
+// (Eq. 2) or the acceptance rule.  When a draft
 // exits, the block also embeds the drafted token as the next row (the next draft step
 // then starts at its first layer).  It is a kernel of its own: publishing the
 // partials inside the projection kernel would need a device-wide fence per
 // block, which on this chip writes back and invalidates a whole L2.
-__device__ __forceinline__ void head_merge_body(const HeadArgs& h, const int M, const int nb) {
-    constexpr int NW = 16, U = 4, RC = 2;   // waves; loads in flight per row and lane; rows a wave takes at a time
+constexpr int MERGE_T = 1024;   // threads
+
+// TPR threads a row, MERGE_T / TPR rows side by side; a thread holds U partials in registers from the
+// search for the maximum to the sum, those past TPR * U are read again.  Every partial's sum is scaled once, from its own
+// maximum to the row's, whatever either is: a NaN in a partial reaches the confidence, and so does a row without a
+// finite logit.  A row's order of additions depends on nb alone.
+template <int TPR, int U>
+__device__ __forceinline__ void merge_rows(const HeadArgs& h, const int M, const int nb, int* s_am, float* s_cf) {
+    constexpr int NW = TPR / 64, SIDE = MERGE_T / TPR;   // waves per row, rows side by side
     __shared__ float r_max[SB_MAX_W][NW], r_sum[SB_MAX_W][NW];
     __shared__ int r_idx[SB_MAX_W][NW];
+    const int tid = threadIdx.x, lane = tid & 63, t = tid % TPR, w = t >> 6, side = tid / TPR;
+    for (int r0 = 0; r0 < M; r0 += SIDE) {
+        const int row = r0 + side;
+        const bool on = row < M;   // (whole waves)
+        const float4* p = reinterpret_cast<const float4*>(h.partials) + (size_t)(h.row0 + row) * nb;
+        float4 v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = (on && t + TPR * u < nb) ? p[t + TPR * u] : make_float4(-SB_INF, __int_as_float(0x7fffffff), 0.f, 0.f);
+        float mx = -SB_INF;
+        int idx = 0x7fffffff;
+        auto take = [&](float z, int i) {
+            if (z > mx || (z == mx && i < idx)) { mx = z; idx = i; }
+        };
+        if (on) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) take(v[u].x, __float_as_int(v[u].y));
+#pragma unroll 4
+            for (int b = t + TPR * U; b < nb; b += TPR) take(p[b].x, __float_as_int(p[b].y));
+            lanes_argmax<32>(mx, idx);
+            if (lane == 0) { r_max[row][w] = mx; r_idx[row][w] = idx; }
+        }
+        __syncthreads();
+        if (on) {
+            mx = r_max[row][0];
+            idx = r_idx[row][0];
+#pragma unroll
+            for (int i = 1; i < NW; ++i) take(r_max[row][i], r_idx[row][i]);
+            if (t == 0) s_am[row] = idx == 0x7fffffff ? 0 : idx;
+            float sum = 0.f;
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (t + TPR * u < nb) sum += v[u].z * expf((v[u].x - mx) / h.T);
+#pragma unroll 4
+            for (int b = t + TPR * U; b < nb; b += TPR) sum += p[b].z * expf((p[b].x - mx) / h.T);
+            sum = wave_sum(sum);
+            if (lane == 0) r_sum[row][w] = sum;
+        }
+    }
+    __syncthreads();
+    if (tid < M) {
+        float sum = r_sum[tid][0];
+#pragma unroll
+        for (int i = 1; i < NW; ++i) sum += r_sum[tid][i];
+        s_cf[tid] = 1.0f / sum;
+    }
+}
+
+__device__ __forceinline__ void head_merge_body(const HeadArgs& h, const int M, const int nb) {
     __shared__ int s_am[SB_MAX_W];
     __shared__ float s_cf[SB_MAX_W];
     __shared__ int s_embed_tok;
     __shared__ float e_red[4];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const float4* p = reinterpret_cast<const float4*>(h.partials) + (size_t)h.row0 * nb;
-    for (int r0 = 0; r0 < M; r0 += RC) {
-        float mx[RC], sum[RC];
-        int idx[RC];
-#pragma unroll
-        for (int r = 0; r < RC; ++r) { mx[r] = -SB_INF; sum[r] = 0.f; idx[r] = 0x7fffffff; }
-        for (int b0 = 0; b0 + wave * 64 < nb; b0 += 1024 * U) {   // (waves past the partials have nothing to do)
-            float4 v[RC][U];
-#pragma unroll
-            for (int r = 0; r < RC; ++r)
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    const int b = b0 + 1024 * u + tid;
-                    v[r][u] = (b < nb && r0 + r < M) ? p[(size_t)(r0 + r) * nb + b] : make_float4(-SB_INF, __int_as_float(0x7fffffff), 0.f, 0.f);
-                }
-#pragma unroll
-            for (int r = 0; r < RC; ++r) {
-                if (r0 + r >= M) break;
-                const float old = mx[r];
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    const int i = __float_as_int(v[r][u].y);
-                    if (v[r][u].x > mx[r] || (v[r][u].x == mx[r] && i < idx[r])) { mx[r] = v[r][u].x; idx[r] = i; }
-                }
-                if (mx[r] > -SB_INF) {
-                    sum[r] *= expf((old - mx[r]) / h.T);
-#pragma unroll
-                    for (int u = 0; u < U; ++u) sum[r] += v[r][u].z * expf((v[r][u].x - mx[r]) / h.T);
-                }
-            }
-        }
-#pragma unroll
-        for (int r = 0; r < RC; ++r) {
-            if (r0 + r >= M) break;
-            float w = 0.f;
-            if (wave * 64 < nb) {
-                const float own = mx[r];
-                lanes_argmax<32>(mx[r], idx[r]);
-                w = wave_sum(own > -SB_INF ? sum[r] * expf((own - mx[r]) / h.T) : 0.f);
-            }
-            if (lane == 0) { r_max[r0 + r][wave] = mx[r]; r_idx[r0 + r][wave] = idx[r]; r_sum[r0 + r][wave] = w; }
-        }
-    }
-    __syncthreads();
-    if (tid < SB_MAX_W * NW) {   // sixteen lanes a row
-        const int m = tid / NW, w = tid % NW;
-        const bool on = m < M;
-        const float own = on ? r_max[m][w] : 0.f;
-        float mx = own;
-        int idx = on ? r_idx[m][w] : 0;
-        lanes_argmax<NW / 2>(mx, idx);
-        const float sum = lanes_sum<NW / 2>(on && own > -SB_INF ? r_sum[m][w] * expf((own - mx) / h.T) : 0.f);
-        if (on && w == 0) { s_am[m] = idx == 0x7fffffff ? 0 : idx; s_cf[m] = 1.0f / sum; }
-    }
+    const int tid = threadIdx.x;
+    // What bounds it is one trip to memory that blocks on other XCDs wrote, then what one CU pulls.  Eight rows side by
+    // side where a row's partials fit into 128 threads' registers, four where they need 256 (larger vocabularies).  All
+    // 1024 threads on two rows at a time, head calls of 1 and 8 rows: [32000 x 4096] 44.7 and 59.3 us against 44.1 and
+    // 46.8, [128256 x 1024] 47.3 and 65.4 against 47.8 and 61.0.
+    if (nb <= 1024) merge_rows<128, 8>(h, M, nb, s_am, s_cf);
+    else merge_rows<256, 16>(h, M, nb, s_am, s_cf);
     if (tid == 0) s_embed_tok = -1;
     __syncthreads();
     if (tid == 0) {
@@ -347,24 +351,24 @@ __device__ __forceinline__ void head_merge_body(const HeadArgs& h, const int M, 
     }
 }
 
-__global__ __launch_bounds__(1024) void head_merge_kernel(HeadArgs h, int M, int nb) { head_merge_body(h, M, nb); }
+__global__ __launch_bounds__(MERGE_T) void head_merge_kernel(HeadArgs h, int M, int nb) { head_merge_body(h, M, nb); }
 
 // The merges of several sequences after one shared head sweep (batch > 1): block b is the
 // single-sequence merge on sequence b's arguments.
-__global__ __launch_bounds__(1024) void head_merge_batch_kernel(HeadMergeBatch hb, int nb) {
+__global__ __launch_bounds__(MERGE_T) void head_merge_batch_kernel(HeadMergeBatch hb, int nb) {
     const HeadArgs h = hb.h[blockIdx.x];
     head_merge_body(h, hb.M[blockIdx.x], nb);
 }
 
 hipError_t launch_head_merge(const HeadArgs& h, int32_t M, int32_t nb, hipStream_t st) {
-    head_merge_kernel<<<1, 1024, 0, st>>>(h, M, nb);
+    head_merge_kernel<<<1, MERGE_T, 0, st>>>(h, M, nb);
     return hipGetLastError();
 }
 
 hipError_t launch_head_merge_batch(const HeadMergeBatch& hb, int32_t n, int32_t nb, hipStream_t st) {
     if (n < 1 || n > SB_MAX_W) return hipErrorInvalidValue;
     if (n == 1) return launch_head_merge(hb.h[0], hb.M[0], nb, st);
-    head_merge_batch_kernel<<<n, 1024, 0, st>>>(hb, nb);
+    head_merge_batch_kernel<<<n, MERGE_T, 0, st>>>(hb, nb);
     return hipGetLastError();
 }
 

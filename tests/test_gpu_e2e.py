@@ -460,6 +460,28 @@ def test_prompt_pass_heights(sb, deep, n_prompt):
         assert np.max(np.abs(vg - vo)) <= 2.0 ** -7 * max(1.0, np.max(np.abs(vo))), pos
 
 
+@pytest.mark.parametrize("name", ["c1-fp32", "bf16-mfma-packed"])
+@pytest.mark.parametrize("threshold", [0.5, 2.0])
+def test_a_head_without_a_confidence_never_exits(sb, name, threshold):
+    """An exit head whose logits are not numbers decides nothing: no exit, and the round's token is the full model's."""
+    kw, proj = _variants(sb)[name]
+    shape = si.tiny_shape(n_layers=4, n_exit_heads=2, **kw)
+    w = si.make_weights(shape, 77, gain_jitter=0.1)
+    prompt = si.make_prompt(shape.vocab, 12, 5)
+    greedy, _ = gpu_model(shape, w, 64, proj).session().generate(prompt, 4, gpu_params(0, 1, T=[]))
+    for l in range(2):
+        w[f"exit_norm.{l}"] = np.full_like(w[f"exit_norm.{l}"], np.nan)
+    s = gpu_model(shape, w, 64, proj).session()
+    out = [s.prefill(prompt)]
+    p = gpu_params(2, 3, threshold=threshold)
+    while len(out) < 4:
+        d = s.draft_step(p)
+        assert d["status"] == sb.DEPTH_BOUND and d["exit_layer"] == 0 and np.isnan(d["confidence"]), d
+        v = s.verify(p)
+        out += v["tokens"][:v["n_emit"]]
+    assert out == greedy.tolist()
+
+
 @pytest.mark.parametrize("tau", [0.3, 0.7])
 def test_easy_token_fixture_accepts_computed_drafts_like_the_oracle(sb, tau):
     """The structured fixture (aliased, peaked heads; deep layers fading out): computed exits

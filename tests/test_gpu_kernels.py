@@ -210,6 +210,56 @@ def test_head_ties_take_lowest_index(T):
             assert int(am.cpu()[0]) == min(rows)
 
 
+# block partials of a row: one thread's registers or several rounds of them, 128 threads a row up to 1024 partials and the
+# whole block above (VALU: 16 weight rows a partial; MFMA from 15000 rows: 32), and more than the block holds in registers
+@pytest.mark.parametrize("kernel,N", [("valu", 16), ("valu", 2064), ("valu", 16384), ("valu", 16400), ("mfma_packed", 32768),
+                                      ("mfma_packed", 32784), ("valu", 65536), ("valu", 70000)])
+def test_head_merge_edges(T, kernel, N):
+    """Confidence of every row against 64 bits from the same logits, the same bits whatever rows are beside it."""
+    import paper_2604_12247_amd as sb
+    k = {"valu": sb.PROJ_VALU, "mfma_packed": sb.PROJ_MFMA_PACKED}[kernel]
+    g = np.random.default_rng(N)
+    W = _rand_w(g, N, 128, True, std=0.2)
+    x = g.standard_normal((8, 128)).astype(np.float32)
+    Wd = sb.op_repack(_dev(T, W)) if kernel == "mfma_packed" else _dev(T, W)
+    am, cf, z = (t.cpu().numpy() for t in sb.op_head(Wd, _dev(T, x), 1.3, k, want_logits=True))
+    z64 = z.astype(np.float64)
+    ref = 1.0 / np.exp((z64 - z64.max(1, keepdims=True)) / 1.3).sum(1)
+    assert np.array_equal(am, z.argmax(1))
+    # a term: exp of an argument up to 16 rounded once by 2^-24 of it (1e-6) and two products; the sums add less
+    assert np.max(np.abs(cf - ref) / ref) <= 4e-6
+    for M in (1, 2, 3, 5):
+        amM, cfM, _ = (None if t is None else t.cpu().numpy() for t in sb.op_head(Wd, _dev(T, x[:M]), 1.3, k))
+        assert np.array_equal(amM, am[:M]) and np.array_equal(cfM, cf[:M]), M
+
+
+@pytest.mark.parametrize("kernel,N", [("valu", 2064), ("mfma_packed", 32000), ("valu", 16400), ("valu", 70000)])
+def test_head_confidence_of_non_finite_logits_is_nan(T, kernel, N):
+    """A logit that is not a number, or a row of which no logit is finite, leaves no confidence."""
+    import paper_2604_12247_amd as sb
+    k = {"valu": sb.PROJ_VALU, "mfma_packed": sb.PROJ_MFMA_PACKED}[kernel]
+    g = np.random.default_rng(N + 1)
+    W = _rand_w(g, N, 128, True)
+    x = np.abs(g.standard_normal((3, 128))).astype(np.float32) + 0.1
+
+    def conf(W, x):
+        Wd = sb.op_repack(_dev(T, W)) if kernel == "mfma_packed" else _dev(T, W)
+        return sb.op_head(Wd, _dev(T, x), 1.0, k)[1].cpu().numpy()
+
+    good = conf(W, x)
+    assert np.all(np.isfinite(good))
+    xn = x.copy()
+    xn[1] = np.nan   # every logit of row 1
+    c = conf(W, xn)
+    assert np.isnan(c[1]) and c[0] == good[0] and c[2] == good[2]
+    for n in (0, N // 2 + 5, N - 1):   # one logit of every row: the first, the last, one inside a block
+        Wn = W.copy()
+        Wn[n] = 0x7fc0
+        assert np.all(np.isnan(conf(Wn, x))), n
+    W[:] = 0xff80    # -inf: no finite logit (the bf16 pairs of the matrix cores make NaN of it, the same here)
+    assert np.all(np.isnan(conf(W, x)))
+
+
 def _attention_case(T, Hq, Hkv, hd, kv_bf16, n_ctx, M, base, shuffle, seed, oracle=True):
     """Append n_ctx + M rows in passes, then compare the last pass's output rows."""
     import paper_2604_12247_amd as sb
