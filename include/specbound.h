@@ -427,7 +427,8 @@ int32_t sb_rope_table_host(int32_t head_dim, float base, int32_t n_pos, float *c
  * library's own, read it back with sb_debug_kv); table [n_pages] maps logical
  * to physical pages; rope_cos/sin: device tables with at least pos0+M
  * rows.  Each row attends to keys 0..its own position (scale 1/sqrt(head_dim));
- * out [M][n_heads head_dim] float.  scratch: sb_op_attention_scratch_bytes(). */
+ * out [M][n_heads head_dim] float, which may lie over qkv.  scratch:
+ * sb_op_attention_scratch_bytes(). */
 int32_t sb_op_attention(const float *qkv, int32_t n_heads, int32_t n_kv_heads, int32_t head_dim, int32_t kv_dtype,
                         void *pool, const int32_t *table, int32_t n_pages, int32_t layer, const float *rope_cos,
                         const float *rope_sin, int32_t pos0, int32_t M, float *out, void *scratch, void *stream);

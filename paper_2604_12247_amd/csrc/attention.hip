@@ -717,8 +717,8 @@ hipError_t launch_attention(const AttnArgs& a, hipStream_t st) {
     AttnArgs b = a;
     b.qg_per_block = qpb;
     // With a single chunk the merge would multiply by exp(0) and add zeros: the first stage divides and
-    // stores by itself (the same bits), a launch less.
-    b.direct = n_chunks == 1;
+    // stores by itself (the same bits), a launch less.  An output over the input has to wait for the end of the first stage.
+    b.direct = n_chunks == 1 && !attn_out_over_input(a);
     dim3 grid(a.kv.n_kv_heads, n_chunks, (n_qg + qpb - 1) / qpb);
     dim3 grid1(a.kv.n_kv_heads, n_chunks, n_qg);
     dim3 mgrid(a.n_heads, a.M);
@@ -758,7 +758,7 @@ hipError_t launch_attention_batch(const AttnArgs* seqs, int n, hipStream_t st) {
         if (n_chunks > max_chunks) max_chunks = n_chunks;
         if (seqs[i].M > max_m) max_m = seqs[i].M;
     }
-    for (int i = 0; i < n; ++i) ab.seq[i].direct = max_chunks == 1;
+    for (int i = 0; i < n; ++i) ab.seq[i].direct = max_chunks == 1;   // (the sessions' own buffers: no output over an input)
     dim3 grid(seqs[0].kv.n_kv_heads, max_chunks, n * ab.zdim);
     dim3 mgrid(seqs[0].n_heads, max_m, n);
     if (seqs[0].kv.head_dim == 128) {

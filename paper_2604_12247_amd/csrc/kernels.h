@@ -25,6 +25,12 @@ struct DevRound {
     int32_t n_matched, n_emit;
 };
 
+// Two ranges of memory share a byte (b may be nullptr).
+inline bool overlaps(const void* a, size_t a_bytes, const void* b, size_t b_bytes) {
+    const uintptr_t a0 = (uintptr_t)a, b0 = (uintptr_t)b;
+    return b && a0 < b0 + b_bytes && b0 < a0 + a_bytes;
+}
+
 struct RowToks { int32_t tok[SB_MAX_W]; };  // >= 0: host-known id; -1: read slot_tok on the device
 
 // RMSNorm outputs produced together with an embedding row (first layer's input).
@@ -158,10 +164,14 @@ struct AttnArgs {
     uint16_t* out_split; // optional bf16 hi/lo copy: rows 0.. high parts, rows split_rows.. low parts
     int32_t split_rows;  // 8 for decode passes, SB_PREFILL_ROWS for prompt passes
     int32_t qg_per_block;  // set by launch_attention
-    int32_t direct;        // set by launch_attention: every row sees one chunk only, the first stage finishes it
+    int32_t direct;        // set by launch_attention: the first stage finishes every row (they see one chunk only)
 };
 int attn_chunk_keys(int32_t head_dim, int32_t kv_dtype);
 hipError_t launch_attention(const AttnArgs& a, hipStream_t st);
+// `out` lies over the rows' projections, which blocks of other heads may still be reading when one stores its result.
+inline bool attn_out_over_input(const AttnArgs& a) {
+    return overlaps(a.q, (size_t)a.M * a.qkv_rows * 4, a.out, (size_t)a.M * a.n_heads * a.kv.head_dim * 4);
+}
 // The passes of up to SB_MAX_W sequences (each on its own cache, at most SB_MAX_W rows) in one
 // pair of launches; every value equals the one launch_attention computes for that sequence.
 struct AttnBatchArgs {

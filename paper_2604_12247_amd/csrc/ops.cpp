@@ -33,8 +33,7 @@ static int op_check(const void* W, int32_t w_dtype, int32_t N, int32_t K, const 
 // The MFMA kernel splits float rows itself while other blocks already store results: where the caller's output
 // lies over its input, the rows are split into the scratch area first.
 static hipError_t op_rows(GemvArgs& g, const float* out, size_t n_out, uint16_t* xs, hipStream_t st) {
-    const uintptr_t x0 = (uintptr_t)g.x, x1 = x0 + (size_t)g.M * g.K * 4, o0 = (uintptr_t)out, o1 = o0 + n_out * 4;
-    if (!out || o1 <= x0 || x1 <= o0) return hipSuccess;
+    if (!overlaps(g.x, (size_t)g.M * g.K * 4, out, n_out * 4)) return hipSuccess;
     g.xs = xs;
     return launch_split(g.x, xs, g.M, g.K, st);
 }

@@ -505,6 +505,37 @@ def test_prompt_attention_split_form(T, Hq, Hkv, hd, n_ctx, M):
                 assert np.max(np.abs(out[r, h * hd:(h + 1) * hd] - ref)) <= 2e-5, (h, r)
 
 
+# one chunk (finished by the first stage, unless the output lies over the input), two chunks; grouped queries, whose output
+# rows lie on other heads' keys; both caches
+@pytest.mark.parametrize("Hq,Hkv,hd,bf16", [(32, 8, 128, True), (8, 8, 64, True), (32, 1, 128, True), (4, 4, 64, False), (16, 4, 128, False)])
+@pytest.mark.parametrize("pos0", [0, 20, 56, 121])
+def test_attention_output_over_its_input(T, Hq, Hkv, hd, bf16, pos0):
+    """out may be the memory of qkv, from its start or from inside it: the same bits and the same cache as with an output of its own."""
+    import paper_2604_12247_amd as sb
+    kvd, M, n_pages = sb.BF16 if bf16 else sb.FP32, 7, 9
+    g = np.random.default_rng(41 + Hq + pos0)
+    c, s = sb.rope_table(hd, 1e4, n_pages * 16)
+    cd, sd = _dev(T, c), _dev(T, s)
+    table = _dev(T, g.permutation(n_pages).astype(np.int32))
+    n = 2 * n_pages * Hkv * 16 * hd
+    pool0 = _dev(T, g.standard_normal(n).astype(np.float32))
+    pool0 = pool0.to(T.bfloat16) if bf16 else pool0
+    qkv0 = _dev(T, g.standard_normal((M, (Hq + 2 * Hkv) * hd)).astype(np.float32))
+    pool_ref = pool0.clone()
+    ref = sb.op_attention(qkv0, Hq, Hkv, hd, kvd, pool_ref, table, 0, cd, sd, pos0)
+    scratch = T.empty(sb.lib().sb_op_attention_scratch_bytes(Hq, hd, kvd, n_pages), dtype=T.uint8, device="cuda")
+    for at in (0, hd, 2 * Hkv * hd):   # (the last: the end of out is the end of the first rows' keys and values)
+        pool = pool0.clone()
+        buf = T.empty(M * (Hq + 2 * Hkv) * hd + at, dtype=T.float32, device="cuda")
+        qkv = buf[:qkv0.numel()].view_as(qkv0)
+        qkv.copy_(qkv0)
+        out = buf[at:at + M * Hq * hd].view(M, Hq * hd)
+        rc = sb.lib().sb_op_attention(qkv.data_ptr(), Hq, Hkv, hd, kvd, pool.data_ptr(), table.data_ptr(), n_pages, 0, cd.data_ptr(),
+                                      sd.data_ptr(), pos0, M, out.data_ptr(), scratch.data_ptr(), T.cuda.current_stream().cuda_stream)
+        assert rc == 0
+        assert T.equal(out, ref) and T.equal(pool.view(T.uint8), pool_ref.view(T.uint8)), at
+
+
 def test_attention_row_result_does_not_depend_on_m(T):
     """The same position gives the same bits alone and inside a pass of 6 rows."""
     args = (8, 8, 128, True)
