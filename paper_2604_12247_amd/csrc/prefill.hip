@@ -600,7 +600,8 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 // exponentials, their sum and the weighted values of each query in registers -- no
 // partials in memory, no merge pass.  Both products run on the matrix cores with hi + lo pairs
 // for the fp32 side (queries, probabilities) like the decode kernel; a query's result depends
-// only on its own column of the accumulators, not on the other queries of the block.
+// only on its own column of the accumulators, not on the other queries of the block (three forms of the kernel, chosen in
+// launch_prefill_attention from the heads and the number of passes).
 //
 // grid (pages touched, n_kv_heads), 256 threads: a block writes one head's part of one page --
 // K as 16-byte pieces (8 dims of a key), V transposed as 16-byte pieces (8 keys of a dim);
@@ -1148,6 +1149,20 @@ __global__ __launch_bounds__(64 * W, W == 4 ? 2 : 1) void prefill_attn_split_ker
     }
 }
 
+// Four waves of 32 queries share a staged chunk; a launch that this leaves with hardly a block per CU takes the
+// key tiles apart instead.  The forms add a query's keys up in different orders, so the choice is made from the heads and
+// the number of 128-row passes alone, as the projections' plans are: a row's result does not depend on the rows beside it
+// within a launch of as many passes.  Measured with the append launch, apart / shared: 256 blocks of 128 queries 51 / 57 us,
+// 320 70 / 72 (99 / 101 behind 700 keys), 384 85 / 82 (124 / 114).  Apart eight / four ways, up to 64 such blocks: head_dim 64
+// 53 / 68 us (64 rows behind 8000), 19 / 22 (behind 2048), 12.2 / 12.4 (128 rows behind 300), but 22.8 / 20.9 for 128
+// blocks; head_dim 128, where the LDS of eight leaves one block per CU, 37.3 / 36.8 (64 rows behind 2048), 18.5 / 17.9
+// (256 rows): four throughout.
+enum AttnForm { ATTN_SHARED, ATTN_APART8, ATTN_APART4 };
+static AttnForm attn_form(int32_t n_heads, int32_t head_dim, int32_t M) {
+    const int64_t blocks = (int64_t)n_heads * ((M + PM - 1) / PM);   // blocks of 128 queries in full passes
+    return blocks >= 320 ? ATTN_SHARED : head_dim == 64 && blocks <= 64 ? ATTN_APART8 : ATTN_APART4;
+}
+
 // M rows at positions pos0.. (bf16 cache): append their K/V, then attention of all rows,
 // output as floats (out) or as bf16 planes (out_split / split_rows as in launch_attention).
 hipError_t launch_prefill_attention(const AttnArgs& a, hipStream_t st) {
@@ -1156,22 +1171,18 @@ hipError_t launch_prefill_attention(const AttnArgs& a, hipStream_t st) {
         (!a.out && (!a.out_split || a.split_rows < a.M)) || !a.rope_cos || !a.rope_sin)
         return hipErrorInvalidValue;
     const int G = a.n_heads / a.kv.n_kv_heads, nq = a.M * G;
-    // Four waves of 32 queries share a staged chunk; a launch that this leaves with hardly a block per CU takes the
-    // key tiles apart instead, eight ways while that still fits the chip at once.  Measured, apart / shared: 256
-    // blocks of 128 queries 37 / 44 us, 384 65 / 64, 400 57 / 55, 512 107 / 86.
-    const int64_t tiles = (int64_t)a.kv.n_kv_heads * ((nq + 31) / 32);
-    const bool wide = (int64_t)a.kv.n_kv_heads * ((nq + 127) / 128) >= 320, eight = tiles <= 256;
+    const AttnForm form = attn_form(a.n_heads, hd, a.M);
+    const bool wide = form == ATTN_SHARED;
     const dim3 agrid((a.pos0 + a.M - 1) / SB_KV_BLOCK - a.pos0 / SB_KV_BLOCK + 1, a.kv.n_kv_heads);
     const dim3 grid(a.kv.n_kv_heads, wide ? (nq + 127) / 128 : (nq + 31) / 32);
     if (hd == 128) {
         prefill_kv_append_kernel<128><<<agrid, 256, 0, st>>>(a);
         if (wide) prefill_attn_kernel<128, 4><<<grid, 256, 0, st>>>(a);
-        else if (eight) prefill_attn_split_kernel<128, 8><<<grid, 512, 0, st>>>(a);
         else prefill_attn_split_kernel<128, 4><<<grid, 256, 0, st>>>(a);
     } else {
         prefill_kv_append_kernel<64><<<agrid, 256, 0, st>>>(a);
         if (wide) prefill_attn_kernel<64, 4><<<grid, 256, 0, st>>>(a);
-        else if (eight) prefill_attn_split_kernel<64, 8><<<grid, 512, 0, st>>>(a);
+        else if (form == ATTN_APART8) prefill_attn_split_kernel<64, 8><<<grid, 512, 0, st>>>(a);
         else prefill_attn_split_kernel<64, 4><<<grid, 256, 0, st>>>(a);
     }
     return hipGetLastError();

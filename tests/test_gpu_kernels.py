@@ -536,6 +536,23 @@ def test_attention_output_over_its_input(T, Hq, Hkv, hd, bf16, pos0):
         assert T.equal(out, ref) and T.equal(pool.view(T.uint8), pool_ref.view(T.uint8)), at
 
 
+# two launches of as many 128-row passes whose rows call for different numbers of blocks, at each form
+@pytest.mark.parametrize("Hq,Hkv,hd,pos0,M,M2", [(40, 40, 64, 0, 190, 200), (16, 16, 64, 33, 390, 512), (32, 8, 128, 5, 1200, 1280),
+                                                 (40, 40, 128, 0, 897, 1000)])
+def test_prompt_attention_row_result_does_not_depend_on_the_rows_after_it(T, Hq, Hkv, hd, pos0, M, M2):
+    import paper_2604_12247_amd as sb
+    g = np.random.default_rng(59 + M)
+    n_pages = (pos0 + M2 + 15) // 16
+    c, s = sb.rope_table(hd, 1e4, n_pages * 16)
+    cd, sd = _dev(T, c), _dev(T, s)
+    table = _dev(T, g.permutation(n_pages).astype(np.int32))
+    pool = _dev(T, g.standard_normal(2 * n_pages * Hkv * 16 * hd).astype(np.float32)).to(T.bfloat16)
+    qkv = _dev(T, g.standard_normal((M2, (Hq + 2 * Hkv) * hd)).astype(np.float32))
+    long = sb.op_prompt_attention(qkv, Hq, Hkv, hd, pool.clone(), table, 0, cd, sd, pos0)
+    short = sb.op_prompt_attention(qkv[:M].contiguous(), Hq, Hkv, hd, pool.clone(), table, 0, cd, sd, pos0)
+    assert T.equal(short, long[:M])
+
+
 def test_attention_row_result_does_not_depend_on_m(T):
     """The same position gives the same bits alone and inside a pass of 6 rows."""
     args = (8, 8, 128, True)
