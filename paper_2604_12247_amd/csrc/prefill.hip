@@ -1171,7 +1171,9 @@ hipError_t launch_prefill_attention(const AttnArgs& a, hipStream_t st) {
         (!a.out && (!a.out_split || a.split_rows < a.M)) || !a.rope_cos || !a.rope_sin)
         return hipErrorInvalidValue;
     const int G = a.n_heads / a.kv.n_kv_heads, nq = a.M * G;
-    const AttnForm form = attn_form(a.n_heads, hd, a.M);
+    // An output over the input: a block reads its queries before any wave of it stores a result, so the form with the
+    // larger blocks takes what those blocks keep apart (one row, or one kv head with up to 128 queries).
+    const AttnForm form = attn_out_over_input(a) ? ATTN_SHARED : attn_form(a.n_heads, hd, a.M);
     const bool wide = form == ATTN_SHARED;
     const dim3 agrid((a.pos0 + a.M - 1) / SB_KV_BLOCK - a.pos0 / SB_KV_BLOCK + 1, a.kv.n_kv_heads);
     const dim3 grid(a.kv.n_kv_heads, wide ? (nq + 127) / 128 : (nq + 31) / 32);

@@ -553,6 +553,26 @@ def test_prompt_attention_row_result_does_not_depend_on_the_rows_after_it(T, Hq,
     assert T.equal(short, long[:M])
 
 
+# one row, or one kv head whose rows fit one block of 64 queries: blocks of 32 would read queries that another has overwritten
+@pytest.mark.parametrize("Hq,Hkv,hd,pos0,M", [(8, 8, 128, 70, 1), (64, 1, 128, 3, 1), (16, 1, 128, 40, 4), (32, 1, 64, 0, 2)])
+def test_prompt_attention_output_over_its_input(T, Hq, Hkv, hd, pos0, M):
+    import paper_2604_12247_amd as sb
+    g = np.random.default_rng(61 + Hq + M)
+    n_pages = (pos0 + M + 15) // 16
+    c, s = sb.rope_table(hd, 1e4, n_pages * 16)
+    cd, sd = _dev(T, c), _dev(T, s)
+    table = _dev(T, g.permutation(n_pages).astype(np.int32))
+    pool = _dev(T, g.standard_normal(2 * n_pages * Hkv * 16 * hd).astype(np.float32)).to(T.bfloat16)
+    qkv = _dev(T, g.standard_normal((M, (Hq + 2 * Hkv) * hd)).astype(np.float32))
+    ref = sb.op_prompt_attention(qkv, Hq, Hkv, hd, pool.clone(), table, 0, cd, sd, pos0)
+    out = qkv.view(-1)[:M * Hq * hd].view(M, Hq * hd)
+    rc = sb.lib().sb_op_prompt_attention(qkv.data_ptr(), Hq, Hkv, hd, pool.data_ptr(), table.data_ptr(), n_pages, 0, cd.data_ptr(),
+                                         sd.data_ptr(), pos0, M, out.data_ptr(), T.cuda.current_stream().cuda_stream)
+    assert rc == 0
+    # another order of additions over <= 71 keys: fp32 sums and 16-bit pairs (2e-5 as everywhere)
+    assert float((out - ref).abs().max()) <= 2e-5
+
+
 def test_attention_row_result_does_not_depend_on_m(T):
     """The same position gives the same bits alone and inside a pass of 6 rows."""
     args = (8, 8, 128, True)
