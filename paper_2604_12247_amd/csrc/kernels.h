@@ -182,6 +182,9 @@ hipError_t launch_attention_batch(const AttnArgs* seqs, int n, hipStream_t st);
 // The prompt's attention for a bf16 cache: K/V append for all M rows, then every row's attention
 // with a running softmax per query (no partials; `partials` is not used); M is not limited.
 hipError_t launch_prefill_attention(const AttnArgs& a, hipStream_t st);
+// Queries (rows x heads of a kv head's group) that a block of it takes together: it reads the keys and values up to its
+// last row once for them.
+int prefill_attention_block_queries(int32_t n_heads, int32_t head_dim, int32_t M);
 
 // ---- prompt passes: SB_PREFILL_ROWS rows each, against tile-packed bf16 weights ----
 // Up to SB_PREFILL_PASSES passes of one layer go into one launch (a "super-pass"), so

@@ -1162,6 +1162,9 @@ static AttnForm attn_form(int32_t n_heads, int32_t head_dim, int32_t M) {
     const int64_t blocks = (int64_t)n_heads * ((M + PM - 1) / PM);   // blocks of 128 queries in full passes
     return blocks >= 320 ? ATTN_SHARED : head_dim == 64 && blocks <= 64 ? ATTN_APART8 : ATTN_APART4;
 }
+int prefill_attention_block_queries(int32_t n_heads, int32_t head_dim, int32_t M) {
+    return attn_form(n_heads, head_dim, M) == ATTN_SHARED ? 128 : 32;
+}
 
 // M rows at positions pos0.. (bf16 cache): append their K/V, then attention of all rows,
 // output as floats (out) or as bf16 planes (out_split / split_rows as in launch_attention).

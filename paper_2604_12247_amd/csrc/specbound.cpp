@@ -455,11 +455,12 @@ int prefill_gemm_impl(sb_session* s, const int32_t* prompt, int32_t n, int32_t* 
                 a.qkv_rows = qkv_rows; a.n_heads = c.n_heads;
                 a.kv = s->kv; a.layer = l; a.pos0 = s->c; a.M = R;
                 a.out = nullptr; a.out_split = atts; a.split_rows = RS;
-                // a block of 64 queries reads the keys and values up to its last row once
-                const int G = c.n_heads / c.n_kv_heads, rows_per_block = 64 / G > 0 ? 64 / G : 1;
-                for (int q0 = 0; q0 < R; q0 += rows_per_block)
-                    kv_read += (int64_t)(s->c + (q0 + rows_per_block < R ? q0 + rows_per_block : R)) * 2 * c.n_kv_heads *
-                               c.head_dim * 2;
+                // a block reads the keys and values up to its last row once
+                const int G = c.n_heads / c.n_kv_heads, bq = prefill_attention_block_queries(c.n_heads, c.head_dim, R);
+                for (int64_t q0 = 0; q0 < (int64_t)R * G; q0 += bq) {
+                    const int64_t last = (q0 + bq < (int64_t)R * G ? q0 + bq : (int64_t)R * G) - 1;
+                    kv_read += (s->c + last / G + 1) * 2 * c.n_kv_heads * c.head_dim * 2;
+                }
                 ProfScope ps(s, SB_K_ATTN, kv_read, st);
                 HIP_TRY(launch_prefill_attention(a, st));
             } else

@@ -482,6 +482,18 @@ def test_a_head_without_a_confidence_never_exits(sb, name, threshold):
     assert out == greedy.tolist()
 
 
+# blocks of 32 queries, and of 128 from 320 blocks on (32 heads x 10 passes); grouped queries share a block's reads
+@pytest.mark.parametrize("kw,n_prompt,block", [(dict(), 100, 32), (dict(n_kv_heads=2), 75, 32), (dict(n_heads=32, n_kv_heads=32), 1200, 128)])
+def test_prompt_statistics_count_what_attention_reads(sb, kw, n_prompt, block):
+    B = si.configs.BF16
+    shape = si.tiny_shape(n_layers=2, n_exit_heads=1, **dict(dict(weight_dtype=B, kv_dtype=B, d_ffn=768), **kw))
+    s = gpu_model(shape, si.make_weights(shape, 3), 1216).session()
+    s.prefill(si.make_prompt(shape.vocab, n_prompt, 9))
+    G = shape.n_heads // shape.n_kv_heads
+    keys = sum((min(q + block, n_prompt * G) - 1) // G + 1 for q in range(0, n_prompt * G, block))
+    assert s.stats()["kv_bytes"] == shape.n_layers * keys * 2 * shape.n_kv_heads * shape.head_dim * 2
+
+
 @pytest.mark.parametrize("tau", [0.3, 0.7])
 def test_easy_token_fixture_accepts_computed_drafts_like_the_oracle(sb, tau):
     """The structured fixture (aliased, peaked heads; deep layers fading out): computed exits
