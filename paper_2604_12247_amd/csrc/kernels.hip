@@ -291,12 +291,13 @@ __device__ __forceinline__ void head_merge_body(const HeadArgs& h, const int M, 
     __shared__ int s_embed_tok;
     __shared__ float e_red[4];
     const int tid = threadIdx.x;
-    // What bounds it is one trip to memory that blocks on other XCDs wrote, then what one CU pulls.  Eight rows side by
-    // side where a row's partials fit into 128 threads' registers, four where they need 256 (larger vocabularies).  All
+    // What bounds it is one trip to memory that blocks on other XCDs wrote, then what one CU pulls.  As many rows side by
+    // side as leave a row's partials in registers: eight with 128 threads each, four with 256, two with 512.  All
     // 1024 threads on two rows at a time, head calls of 1 and 8 rows: [32000 x 4096] 44.7 and 59.3 us against 44.1 and
     // 46.8, [128256 x 1024] 47.3 and 65.4 against 47.8 and 61.0.
     if (nb <= 1024) merge_rows<128, 8>(h, M, nb, s_am, s_cf);
-    else merge_rows<256, 16>(h, M, nb, s_am, s_cf);
+    else if (nb <= 4096) merge_rows<256, 16>(h, M, nb, s_am, s_cf);
+    else merge_rows<512, 16>(h, M, nb, s_am, s_cf);
     if (tid == 0) s_embed_tok = -1;
     __syncthreads();
     if (tid == 0) {

@@ -210,10 +210,10 @@ def test_head_ties_take_lowest_index(T):
             assert int(am.cpu()[0]) == min(rows)
 
 
-# block partials of a row: one thread's registers or several rounds of them, 128 threads a row up to 1024 partials and the
-# whole block above (VALU: 16 weight rows a partial; MFMA from 15000 rows: 32), and more than the block holds in registers
+# block partials of a row (VALU: 16 weight rows each; MFMA from 15000 rows: 32): 128 threads a row up to 1024 of them, 256 up to
+# 4096, 512 above, and from 8193 on more than these hold in registers
 @pytest.mark.parametrize("kernel,N", [("valu", 16), ("valu", 2064), ("valu", 16384), ("valu", 16400), ("mfma_packed", 32768),
-                                      ("mfma_packed", 32784), ("valu", 65536), ("valu", 70000)])
+                                      ("mfma_packed", 32784), ("valu", 65536), ("valu", 65552), ("valu", 131072), ("valu", 140000)])
 def test_head_merge_edges(T, kernel, N):
     """Confidence of every row against 64 bits from the same logits, the same bits whatever rows are beside it."""
     import paper_2604_12247_amd as sb
@@ -233,7 +233,7 @@ def test_head_merge_edges(T, kernel, N):
         assert np.array_equal(amM, am[:M]) and np.array_equal(cfM, cf[:M]), M
 
 
-@pytest.mark.parametrize("kernel,N", [("valu", 2064), ("mfma_packed", 32000), ("valu", 16400), ("valu", 70000)])
+@pytest.mark.parametrize("kernel,N", [("valu", 2064), ("mfma_packed", 32000), ("valu", 16400), ("valu", 70000), ("valu", 140000)])
 def test_head_confidence_of_non_finite_logits_is_nan(T, kernel, N):
     """A logit that is not a number, or a row of which no logit is finite, leaves no confidence."""
     import paper_2604_12247_amd as sb
