@@ -139,6 +139,27 @@ __device__ __forceinline__ void load8(const float* p, float (&w)[8]) {
     w[4] = b.x; w[5] = b.y; w[6] = b.z; w[7] = b.w;
 }
 
+// eight weights as loaded, to be made floats where they are used
+template <typename WT>
+struct Piece8 {
+    uint4 v[sizeof(WT) / 2];
+    __device__ __forceinline__ void load(const WT* p) {
+#pragma unroll
+        for (int i = 0; i < (int)sizeof(WT) / 2; ++i) v[i] = reinterpret_cast<const uint4*>(p)[i];
+    }
+    __device__ __forceinline__ void unpack(float (&w)[8]) const {
+        const uint32_t u[4] = {v[0].x, v[0].y, v[0].z, v[0].w};
+        if constexpr (sizeof(WT) == 2) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) { w[2 * i] = __uint_as_float(u[i] << 16); w[2 * i + 1] = __uint_as_float(u[i] & 0xffff0000u); }
+        } else {
+            const uint32_t h[4] = {v[1].x, v[1].y, v[1].z, v[1].w};
+#pragma unroll
+            for (int i = 0; i < 4; ++i) { w[i] = __uint_as_float(u[i]); w[4 + i] = __uint_as_float(h[i]); }
+        }
+    }
+};
+
 // eight values of a hidden row and, where nx is given, the bf16 parts of gain * value (16-byte stores; the places
 // are multiples of 8 elements)
 __device__ __forceinline__ void store8_split(const float (&v)[8], const float (&gain)[8], float* h, uint16_t* nx, size_t hi, size_t lo) {

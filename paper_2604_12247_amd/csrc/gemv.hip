@@ -41,15 +41,17 @@ __device__ __forceinline__ void head_partial(const HeadArgs& h, float (*zs)[SB_M
 // owns 4 weight rows; lanes stride the K dimension in 16-byte pieces (128-bit
 // loads), partial sums are combined with a fixed shuffle tree.  x is staged in
 // LDS in chunks.  The order in which a row's products are added is a function of
-// K alone.  Short rows (K <= SB_VALU_NORM_K: one 16-byte piece per thread) are normalised
-// while they are staged where the caller asks for it: a small model is bound by its number of
-// launches (4.2 us each in a chain of them), and the sum of squares costs a block two barriers.  Longer rows
-// would be read twice by every block.  Same order of additions as rmsnorm_kernel.
-
-template <typename WT, int M, int EPI>
+// K alone.
+//
+// SHORT (K <= SB_VALU_NORM_K, one 16-byte piece of a row per thread): the whole matrix is one round trip, so the weights are
+// requested before the rows are staged, and the rows are normalised while they are staged where the caller asks for it: a
+// small model is bound by its number of launches (4.2 us each in a chain of them), and the sum of squares costs
+// a block two barriers (same order of additions as rmsnorm_kernel).  Longer rows would be read twice by every
+// block, and registers that hold weights through the staging are waves the stream misses.
+template <typename WT, int M, int EPI, bool SHORT>
 __global__ __launch_bounds__(256) void gemv_valu_kernel(GemvArgs a) {
     constexpr int R = 4;
-    constexpr int KC = (M <= 4) ? 2048 : 1024;
+    constexpr int KC = SHORT ? SB_VALU_NORM_K : (M <= 4) ? 2048 : 1024;
     constexpr int OUT_PER_BLOCK = (EPI == EPI_SWIGLU) ? 8 : 16;
     __shared__ __attribute__((aligned(16))) float xs[M][KC];
     __shared__ float zs[16][SB_MAX_W];
@@ -82,77 +84,87 @@ __global__ __launch_bounds__(256) void gemv_valu_kernel(GemvArgs a) {
 #pragma unroll
         for (int m = 0; m < M; ++m) acc[r][m] = 0.f;
 
-    for (int k0 = 0; k0 < K; k0 += KC) {
-        const int kc = (K - k0 < KC) ? (K - k0) : KC;
-        // the chunk's first weights are requested before its rows are staged: a short matrix is one such round trip
-        float w0[R][8], w1[R][8];
-        const bool live0 = lane * 8 < kc, live1 = lane * 8 + 512 < kc;
+    auto madd = [&](const float (&w)[R][8], int kk) {
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-            if (live0) load8(wrow[r] + k0 + lane * 8, w0[r]);
-            if (live1) load8(wrow[r] + k0 + lane * 8 + 512, w1[r]);
+        for (int m = 0; m < M; ++m) {
+            float4 xa = *reinterpret_cast<const float4*>(&xs[m][kk]);
+            float4 xb = *reinterpret_cast<const float4*>(&xs[m][kk + 4]);
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                float s = acc[r][m];
+                s = fmaf(w[r][0], xa.x, s); s = fmaf(w[r][1], xa.y, s);
+                s = fmaf(w[r][2], xa.z, s); s = fmaf(w[r][3], xa.w, s);
+                s = fmaf(w[r][4], xb.x, s); s = fmaf(w[r][5], xb.y, s);
+                s = fmaf(w[r][6], xb.z, s); s = fmaf(w[r][7], xb.w, s);
+                acc[r][m] = s;
+            }
         }
-        __syncthreads();
-        if (a.norm_gain) {   // (one chunk)
-            const bool on = tid * 4 < K;
-            float4 v[M];
+    };
+    for (int k0 = 0; k0 < K; k0 += KC) {   // (SHORT: one chunk)
+        const int kc = (K - k0 < KC) ? (K - k0) : KC;
+        Piece8<WT> w0[R], w1[R];   // (SHORT)
+        const bool live0 = lane * 8 < kc, live1 = lane * 8 + 512 < kc;
+        // rows: all loads before the first store (a loop of load and store would be one round trip after the other)
+        float4 v[M][KC / 1024];
 #pragma unroll
-            for (int m = 0; m < M; ++m) v[m] = on ? *reinterpret_cast<const float4*>(a.x + (size_t)m * K + tid * 4) : make_float4(0.f, 0.f, 0.f, 0.f);
-            const float4 g = on ? *reinterpret_cast<const float4*>(a.norm_gain + tid * 4) : make_float4(0.f, 0.f, 0.f, 0.f);
+        for (int m = 0; m < M; ++m)
+#pragma unroll
+            for (int i = 0; i < KC / 1024; ++i) {
+                const int kk = i * 1024 + tid * 4;
+                v[m][i] = kk < kc ? *reinterpret_cast<const float4*>(a.x + (size_t)m * K + k0 + kk) : make_float4(0.f, 0.f, 0.f, 0.f);
+            }
+        if (SHORT) {
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                if (live0) w0[r].load(wrow[r] + lane * 8);
+                if (live1) w1[r].load(wrow[r] + lane * 8 + 512);
+            }
+        }
+        if (SHORT && a.norm_gain) {
+            const float4 g = tid * 4 < K ? *reinterpret_cast<const float4*>(a.norm_gain + tid * 4) : make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
             for (int m = 0; m < M; ++m) {
-                const float ss = wave_sum((v[m].x * v[m].x + v[m].y * v[m].y) + (v[m].z * v[m].z + v[m].w * v[m].w));
+                const float4 q = v[m][0];
+                const float ss = wave_sum((q.x * q.x + q.y * q.y) + (q.z * q.z + q.w * q.w));
                 if (lane == 0) zs[wave][m] = ss;
             }
             __syncthreads();
 #pragma unroll
             for (int m = 0; m < M; ++m) {
                 const float inv = 1.0f / sqrtf((((zs[0][m] + zs[1][m]) + zs[2][m]) + zs[3][m]) / (float)K + a.eps);
-                if (on) *reinterpret_cast<float4*>(&xs[m][tid * 4]) = make_float4(v[m].x * inv * g.x, v[m].y * inv * g.y, v[m].z * inv * g.z, v[m].w * inv * g.w);
+                const float4 q = v[m][0];
+                v[m][0] = make_float4(q.x * inv * g.x, q.y * inv * g.y, q.z * inv * g.z, q.w * inv * g.w);
+            }
+        }
+        if (!SHORT) __syncthreads();   // (the last chunk's rows have been read)
+#pragma unroll
+        for (int m = 0; m < M; ++m)
+#pragma unroll
+            for (int i = 0; i < KC / 1024; ++i) {
+                const int kk = i * 1024 + tid * 4;
+                if (kk < kc) *reinterpret_cast<float4*>(&xs[m][kk]) = v[m][i];
+            }
+        __syncthreads();
+        if (SHORT) {
+            float w[R][8];
+            if (live0) {
+#pragma unroll
+                for (int r = 0; r < R; ++r) w0[r].unpack(w[r]);
+                madd(w, lane * 8);
+            }
+            if (live1) {
+#pragma unroll
+                for (int r = 0; r < R; ++r) w1[r].unpack(w[r]);
+                madd(w, lane * 8 + 512);
             }
         } else {
-            // all loads before the first store (a loop of load and store would be one round trip after the other)
-            float4 v[M][KC / 1024];
-#pragma unroll
-            for (int m = 0; m < M; ++m)
-#pragma unroll
-                for (int i = 0; i < KC / 1024; ++i) {
-                    const int kk = i * 1024 + tid * 4;
-                    v[m][i] = kk < kc ? *reinterpret_cast<const float4*>(a.x + (size_t)m * K + k0 + kk) : make_float4(0.f, 0.f, 0.f, 0.f);
-                }
-#pragma unroll
-            for (int m = 0; m < M; ++m)
-#pragma unroll
-                for (int i = 0; i < KC / 1024; ++i) {
-                    const int kk = i * 1024 + tid * 4;
-                    if (kk < kc) *reinterpret_cast<float4*>(&xs[m][kk]) = v[m][i];
-                }
-        }
-        __syncthreads();
-        auto madd = [&](const float (&w)[R][8], int kk) {
-#pragma unroll
-            for (int m = 0; m < M; ++m) {
-                float4 xa = *reinterpret_cast<const float4*>(&xs[m][kk]);
-                float4 xb = *reinterpret_cast<const float4*>(&xs[m][kk + 4]);
-#pragma unroll
-                for (int r = 0; r < R; ++r) {
-                    float s = acc[r][m];
-                    s = fmaf(w[r][0], xa.x, s); s = fmaf(w[r][1], xa.y, s);
-                    s = fmaf(w[r][2], xa.z, s); s = fmaf(w[r][3], xa.w, s);
-                    s = fmaf(w[r][4], xb.x, s); s = fmaf(w[r][5], xb.y, s);
-                    s = fmaf(w[r][6], xb.z, s); s = fmaf(w[r][7], xb.w, s);
-                    acc[r][m] = s;
-                }
-            }
-        };
-        if (live0) madd(w0, lane * 8);
-        if (live1) madd(w1, lane * 8 + 512);
 #pragma unroll 2
-        for (int kk = lane * 8 + 1024; kk < kc; kk += 512) {
-            float w[R][8];
+            for (int kk = lane * 8; kk < kc; kk += 512) {
+                float w[R][8];
 #pragma unroll
-            for (int r = 0; r < R; ++r) load8(wrow[r] + k0 + kk, w[r]);
-            madd(w, kk);
+                for (int r = 0; r < R; ++r) load8(wrow[r] + k0 + kk, w[r]);
+                madd(w, kk);
+            }
         }
     }
 #pragma unroll
@@ -189,14 +201,14 @@ __global__ __launch_bounds__(256) void gemv_valu_kernel(GemvArgs a) {
 
 int head_blocks_valu(int32_t N) { return (N + 15) / 16; }
 
-template <typename WT, int M>
+template <typename WT, int M, bool SHORT>
 static hipError_t launch_gemv_valu_m(const GemvArgs& a, hipStream_t st) {
     switch (a.epi) {
-        case EPI_STORE: gemv_valu_kernel<WT, M, EPI_STORE><<<(a.N + 15) / 16, 256, 0, st>>>(a); break;
-        case EPI_RESID: gemv_valu_kernel<WT, M, EPI_RESID><<<(a.N + 15) / 16, 256, 0, st>>>(a); break;
-        case EPI_SWIGLU: gemv_valu_kernel<WT, M, EPI_SWIGLU><<<(a.N + 7) / 8, 256, 0, st>>>(a); break;
+        case EPI_STORE: gemv_valu_kernel<WT, M, EPI_STORE, SHORT><<<(a.N + 15) / 16, 256, 0, st>>>(a); break;
+        case EPI_RESID: gemv_valu_kernel<WT, M, EPI_RESID, SHORT><<<(a.N + 15) / 16, 256, 0, st>>>(a); break;
+        case EPI_SWIGLU: gemv_valu_kernel<WT, M, EPI_SWIGLU, SHORT><<<(a.N + 7) / 8, 256, 0, st>>>(a); break;
         case EPI_HEAD: {
-            gemv_valu_kernel<WT, M, EPI_HEAD><<<(a.N + 15) / 16, 256, 0, st>>>(a);
+            gemv_valu_kernel<WT, M, EPI_HEAD, SHORT><<<(a.N + 15) / 16, 256, 0, st>>>(a);
             hipError_t e = hipGetLastError();
             return e != hipSuccess ? e : launch_head_merge(a.head, M, (a.N + 15) / 16, st);
         }
@@ -207,14 +219,14 @@ static hipError_t launch_gemv_valu_m(const GemvArgs& a, hipStream_t st) {
 template <typename WT>
 static hipError_t launch_gemv_valu_t(const GemvArgs& a, hipStream_t st) {
     switch (a.M) {
-        case 1: return launch_gemv_valu_m<WT, 1>(a, st);
-        case 2: return launch_gemv_valu_m<WT, 2>(a, st);
-        case 3: return launch_gemv_valu_m<WT, 3>(a, st);
-        case 4: return launch_gemv_valu_m<WT, 4>(a, st);
-        case 5: return launch_gemv_valu_m<WT, 5>(a, st);
-        case 6: return launch_gemv_valu_m<WT, 6>(a, st);
-        case 7: return launch_gemv_valu_m<WT, 7>(a, st);
-        case 8: return launch_gemv_valu_m<WT, 8>(a, st);
+        case 1: return a.K <= SB_VALU_NORM_K ? launch_gemv_valu_m<WT, 1, true>(a, st) : launch_gemv_valu_m<WT, 1, false>(a, st);
+        case 2: return a.K <= SB_VALU_NORM_K ? launch_gemv_valu_m<WT, 2, true>(a, st) : launch_gemv_valu_m<WT, 2, false>(a, st);
+        case 3: return a.K <= SB_VALU_NORM_K ? launch_gemv_valu_m<WT, 3, true>(a, st) : launch_gemv_valu_m<WT, 3, false>(a, st);
+        case 4: return a.K <= SB_VALU_NORM_K ? launch_gemv_valu_m<WT, 4, true>(a, st) : launch_gemv_valu_m<WT, 4, false>(a, st);
+        case 5: return a.K <= SB_VALU_NORM_K ? launch_gemv_valu_m<WT, 5, true>(a, st) : launch_gemv_valu_m<WT, 5, false>(a, st);
+        case 6: return a.K <= SB_VALU_NORM_K ? launch_gemv_valu_m<WT, 6, true>(a, st) : launch_gemv_valu_m<WT, 6, false>(a, st);
+        case 7: return a.K <= SB_VALU_NORM_K ? launch_gemv_valu_m<WT, 7, true>(a, st) : launch_gemv_valu_m<WT, 7, false>(a, st);
+        case 8: return a.K <= SB_VALU_NORM_K ? launch_gemv_valu_m<WT, 8, true>(a, st) : launch_gemv_valu_m<WT, 8, false>(a, st);
         default: return hipErrorInvalidValue;
     }
 }
