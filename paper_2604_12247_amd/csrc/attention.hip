@@ -57,8 +57,10 @@ __device__ __forceinline__ void attn_finish(const AttnArgs& a, int r, int col, i
     if (a.out_split) split_store_rows(a.out_split, ld, a.split_rows, r, col, v);
 }
 
-template <typename KVT, int HD>
-__global__ __launch_bounds__(256) void attn_kernel(AttnArgs a) {
+// WAVES: blocks a CU holds at once (one wave of each per SIMD).  All of the new rows' loads in flight take 160 registers, three blocks; in
+// 128, with some 30 values spilled where a chunk holds new rows, four fit.  launch_attention says when which.
+template <typename KVT, int HD, int WAVES>
+__global__ __launch_bounds__(256, WAVES) void attn_kernel(AttnArgs a) {
     constexpr int CH = (HD * sizeof(KVT) <= 256) ? 128 : 64;  // keys per chunk
     constexpr int EPV = KvVec<KVT>::EPV;                      // elements per 16 bytes
     constexpr int QG = 16;                                    // queries per block
@@ -726,8 +728,20 @@ hipError_t launch_attention(const AttnArgs& a, hipStream_t st) {
         if (hd == 128) { attn_mfma_kernel<128><<<grid, 256, 0, st>>>(b); if (!b.direct) attn_merge_kernel<128, 128><<<mgrid, 256, 0, st>>>(a); }
         else { attn_mfma_kernel<64><<<grid, 256, 0, st>>>(b); if (!b.direct) attn_merge_kernel<64, 128><<<mgrid, 256, 0, st>>>(a); }
     } else {
-        if (hd == 128) { attn_kernel<float, 128><<<grid1, 256, 0, st>>>(b); if (!b.direct) attn_merge_kernel<128, 64><<<mgrid, 256, 0, st>>>(a); }
-        else { attn_kernel<float, 64><<<grid1, 256, 0, st>>>(b); if (!b.direct) attn_merge_kernel<64, 128><<<mgrid, 256, 0, st>>>(a); }
+        // Four blocks per CU where that saves a round of blocks over the chip, else three, whose blocks are faster.  32 heads,
+        // one row, three / four: 768 blocks 20.8 / 21.0 us (1500 keys, head_dim 128), 864 27.2 / 23.8, 1504 34.7 / 36.9 (6000 keys,
+        // head_dim 64), 4512 89.5 / 85.6 (9000 keys, head_dim 128).
+        const int64_t blocks = (int64_t)grid1.x * grid1.y * grid1.z;
+        const bool four = (blocks + 4 * 256 - 1) / (4 * 256) < (blocks + 3 * 256 - 1) / (3 * 256);
+        if (hd == 128) {
+            if (four) attn_kernel<float, 128, 4><<<grid1, 256, 0, st>>>(b);
+            else attn_kernel<float, 128, 3><<<grid1, 256, 0, st>>>(b);
+            if (!b.direct) attn_merge_kernel<128, 64><<<mgrid, 256, 0, st>>>(a);
+        } else {
+            if (four) attn_kernel<float, 64, 4><<<grid1, 256, 0, st>>>(b);
+            else attn_kernel<float, 64, 3><<<grid1, 256, 0, st>>>(b);
+            if (!b.direct) attn_merge_kernel<64, 128><<<mgrid, 256, 0, st>>>(a);
+        }
     }
     return hipGetLastError();
 }

@@ -573,6 +573,16 @@ def test_prompt_attention_output_over_its_input(T, Hq, Hkv, hd, pos0, M):
     assert float((out - ref).abs().max()) <= 2e-5
 
 
+# an fp32 cache: up to 768 blocks three to a CU, up to 1024 four, then three again (a row alone and beside others may be on
+# either side of a line)
+@pytest.mark.parametrize("hd,pos0", [(64, 3070), (64, 4095), (128, 1535), (128, 2047)])
+def test_attention_fp32_cache_block_counts(T, hd, pos0):
+    _, out6 = _attention_case(T, 32, 32, hd, False, pos0, 6, 1e4, True, seed=83 + pos0, oracle=False)
+    for r in (0, 5):
+        _, out1 = _attention_case(T, 32, 32, hd, False, pos0 + r, 1, 1e4, True, seed=83 + pos0, oracle=r == 5 and pos0 in (3070, 1535))
+        assert np.array_equal(out1[0], out6[r]), r
+
+
 def test_attention_row_result_does_not_depend_on_m(T):
     """The same position gives the same bits alone and inside a pass of 6 rows."""
     args = (8, 8, 128, True)
