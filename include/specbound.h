@@ -391,7 +391,8 @@ size_t sb_op_head_scratch_bytes(int32_t M, int32_t N, int32_t K);
  * and the same results as sb_op_head with logits == NULL, with the scratch area in a static
  * device array of the library (1.0 MB, held by every GPU the library runs on until the
  * process ends) instead of a caller's buffer.  The call allocates nothing.  Limits:
- * N <= SB_STATIC_MAX_N and K <= SB_STATIC_MAX_K, else SB_ECAPACITY; otherwise arguments and
+ * N <= SB_STATIC_MAX_N and K <= SB_STATIC_MAX_K, else SB_ECAPACITY (the array holds nothing that
+ * depends on K; the bound on it is kept as part of the interface); otherwise arguments and
  * errors as sb_op_head.  All calls on one GPU share the array (its contents are whatever the
  * last call left; nothing in it needs clearing), so calls that overlap on one GPU -- on
  * different streams or from different threads -- race: serialise them. */

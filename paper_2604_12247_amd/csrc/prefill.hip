@@ -254,7 +254,7 @@ __global__ __launch_bounds__(64 * WPB) void prefill_gemm_kernel(GemmArgs a, int 
     constexpr int STAGE = stage_bytes(CT), UB = D / 4;   // UB: k blocks per turn of the ring
     // staging units requested at the start of a k block; the rest half way
     constexpr int H0 = CT > 4 ? (CT + 1) / 2 : CT, H1 = CT > H0 ? CT - H0 : 1;
-    static_assert(D % 4 == 0 && D >= 4, "the ring turns over in whole k blocks");
+    static_assert(D == 4 || D == 8, "the ring turns over in whole k blocks");
     static_assert(!SWI || RT % 2 == 0, "gate and up tiles in one wave");
     extern __shared__ __attribute__((aligned(16))) unsigned char bt[];  // [2][STAGE], then PM floats: the rows' RMSNorm scales (fused tails)
     const int tid = threadIdx.x, lane = tid & 63;
@@ -365,12 +365,8 @@ __global__ __launch_bounds__(64 * WPB) void prefill_gemm_kernel(GemmArgs a, int 
     for (; it + UB <= c.it1; it += UB) {
         k_block(std::integral_constant<int, 0>{}, it);
         if constexpr (UB > 1) k_block(std::integral_constant<int, 1>{}, it + 1);
-        if constexpr (UB > 2) k_block(std::integral_constant<int, 2>{}, it + 2);
-        if constexpr (UB > 3) k_block(std::integral_constant<int, 3>{}, it + 3);
     }
     if constexpr (UB > 1) if (it < c.it1) k_block(std::integral_constant<int, 0>{}, it);
-    if constexpr (UB > 2) if (it + 1 < c.it1) k_block(std::integral_constant<int, 1>{}, it + 1);
-    if constexpr (UB > 3) if (it + 2 < c.it1) k_block(std::integral_constant<int, 2>{}, it + 2);
 }
 
 template <int RT, int CT, int D, int PD, bool STREAM, bool SWI>
@@ -763,7 +759,7 @@ __device__ __forceinline__ void attn_softmax(const f32x16 (&st)[KT], f32x16 (&o)
     l_run += sum0 + sum1;
 }
 
-// grid (n_kv_heads, ceil(M G / (32 W))), 64 W threads.  A wave owns 32 queries and is independent of the
+// grid (n_kv_heads, ceil(M G / 128)), 256 threads.  A wave owns 32 queries and is independent of the
 // other waves but for the K/V chunk (64 keys) the block stages in LDS.  Scores are computed transposed,
 // S^T = K Q^T in 32 x 32 tiles, so a lane holds, for ONE query (its column), 16 keys of every key tile: the
 // running maximum, sum and rescaling are per-lane scalars, completed across the two halves of the wave
@@ -777,9 +773,9 @@ __device__ __forceinline__ void attn_softmax(const f32x16 (&st)[KT], f32x16 (&o)
 // were waited for one by one, with 480 vector instructions per chunk and spills.
 constexpr int ATTN_CH = 64;   // keys per chunk
 
-template <int HD, int W>
-__global__ __launch_bounds__(64 * W, 2) void prefill_attn_kernel(AttnArgs a) {
-    constexpr int CH = ATTN_CH, NT = 64 * W;
+template <int HD>
+__global__ __launch_bounds__(256, 2) void prefill_attn_kernel(AttnArgs a) {
+    constexpr int CH = ATTN_CH, NT = 256, BQ = 128;   // keys of a chunk, threads, queries of a block
     constexpr int KT = CH / 32;              // key tiles of a chunk
     constexpr int KS = HD / 16;              // k steps (16 dims) of the score product
     constexpr int DT = HD / 32;              // 32-dim tiles of the output
@@ -803,9 +799,9 @@ __global__ __launch_bounds__(64 * W, 2) void prefill_attn_kernel(AttnArgs a) {
     const int first = (256 + gridDim.x - 1) / gridDim.x, ny = gridDim.y;
     const int qtile = ny <= 2 * first && (int)blockIdx.y >= first ? (int)blockIdx.y - first : ny - 1 - (int)blockIdx.y;
     const int Hq = a.n_heads, Hkv = a.kv.n_kv_heads, G = Hq / Hkv;
-    const int nq_total = a.M * G, q0 = qtile * (32 * W);
+    const int nq_total = a.M * G, q0 = qtile * BQ;
     const int n_total = a.pos0 + a.M;
-    const int q_last = (q0 + 32 * W < nq_total ? q0 + 32 * W : nq_total) - 1;
+    const int q_last = (q0 + BQ < nq_total ? q0 + BQ : nq_total) - 1;
     const int n_chunks = (a.pos0 + q_last / G) / CH + 1;  // chunks with a key the block's last row sees
     const int wq0 = q0 + wave * 32;                        // the wave's queries: wq0 .. wq1
     const int wq1 = (wq0 + 31 < nq_total - 1) ? wq0 + 31 : nq_total - 1;
@@ -1182,11 +1178,11 @@ hipError_t launch_prefill_attention(const AttnArgs& a, hipStream_t st) {
     const dim3 grid(a.kv.n_kv_heads, wide ? (nq + 127) / 128 : (nq + 31) / 32);
     if (hd == 128) {
         prefill_kv_append_kernel<128><<<agrid, 256, 0, st>>>(a);
-        if (wide) prefill_attn_kernel<128, 4><<<grid, 256, 0, st>>>(a);
+        if (wide) prefill_attn_kernel<128><<<grid, 256, 0, st>>>(a);
         else prefill_attn_split_kernel<128, 4><<<grid, 256, 0, st>>>(a);
     } else {
         prefill_kv_append_kernel<64><<<agrid, 256, 0, st>>>(a);
-        if (wide) prefill_attn_kernel<64, 4><<<grid, 256, 0, st>>>(a);
+        if (wide) prefill_attn_kernel<64><<<grid, 256, 0, st>>>(a);
         else if (form == ATTN_APART8) prefill_attn_split_kernel<64, 8><<<grid, 512, 0, st>>>(a);
         else prefill_attn_split_kernel<64, 4><<<grid, 256, 0, st>>>(a);
     }
