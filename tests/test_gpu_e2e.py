@@ -460,6 +460,27 @@ def test_prompt_pass_heights(sb, deep, n_prompt):
         assert np.max(np.abs(vg - vo)) <= 2.0 ** -7 * max(1.0, np.max(np.abs(vo))), pos
 
 
+@pytest.mark.parametrize("n_prompt", [45, 129, 180, 208, 256, 300])
+@pytest.mark.parametrize("deep", [False, True])
+def test_prompt_pass_heights_fp32_cache(sb, deep, n_prompt):
+    """The same through a cache that does not round: every product's low activation part shows (2^-9 of a value without it)."""
+    kw = dict(d_model=1024, n_heads=8, n_kv_heads=8, head_dim=128, d_ffn=2048) if deep else {}
+    shape = si.tiny_shape(n_layers=2, n_exit_heads=1, **dict(_variants(sb)["bf16-mfma-packed"][0], kv_dtype=si.configs.FP32, **kw))
+    w = si.make_weights(shape, 68, gain_jitter=0.1)
+    om, gm = Oracle(shape, w, 320), gpu_model(shape, w, 320)
+    prompt = si.make_prompt(shape.vocab, n_prompt, 74)
+    osn, gsn = om.session(), gm.session()
+    osn.prefill(prompt)
+    gsn.prefill(prompt)
+    worst = 0.0
+    for pos in range(n_prompt):
+        (ko, vo), (kg, vg) = osn.kv_read(1, pos), gsn.debug_kv(1, pos)
+        worst = max(worst, np.max(np.abs(kg - ko)) / np.max(np.abs(ko)), np.max(np.abs(vg - vo)) / np.max(np.abs(vo)))
+    # five products in a row (Q K V, W_o, gate / up, W_down, the next K V), each within 3e-5 of its largest value
+    # (test_prompt_pass_gemm_heights) and between norms that keep the scale
+    assert worst <= 1.5e-4, worst
+
+
 @pytest.mark.parametrize("name", ["c1-fp32", "bf16-mfma-packed"])
 @pytest.mark.parametrize("threshold", [0.5, 2.0])
 def test_a_head_without_a_confidence_never_exits(sb, name, threshold):

@@ -472,6 +472,36 @@ def test_gemv_output_over_its_input(T, M):
     assert T.equal(x, ref)
 
 
+@pytest.mark.parametrize("kernel", ["mfma", "mfma_packed"])
+@pytest.mark.parametrize("entry", ["gemv", "gate_up", "head"])
+@pytest.mark.parametrize("at", [0, 128, -128])   # the output begins with the input, inside it, before it
+def test_projection_outputs_over_their_input(T, kernel, entry, at):
+    """The outputs of every projection entry point (a head's logits among them) may lie over x: the same bits."""
+    import paper_2604_12247_amd as sb
+    L, n, M = sb.lib(), 1024, 5
+    k = {"mfma": sb.PROJ_MFMA, "mfma_packed": sb.PROJ_MFMA_PACKED}[kernel]
+    g = np.random.default_rng(37)
+    W = _dev(T, _rand_w(g, 2 * n if entry == "gate_up" else n, n, True))
+    W = sb.op_repack(W) if kernel == "mfma_packed" else W
+    x0 = _dev(T, g.standard_normal((M, n)).astype(np.float32))
+    buf = T.empty(M * n + 256, dtype=T.float32, device="cuda")
+    x, y = buf[128:128 + M * n].view(M, n), buf[128 + at:128 + at + M * n].view(M, n)
+    x.copy_(x0)
+    st = T.cuda.current_stream().cuda_stream
+    scratch = T.empty(max(L.sb_op_gemv_scratch_bytes(M, n), L.sb_op_head_scratch_bytes(M, n, n)), dtype=T.uint8, device="cuda")
+    if entry == "head":
+        am, cf, ref = sb.op_head(W, x0, 1.1, k, want_logits=True)
+        am2, cf2 = T.empty_like(am), T.empty_like(cf)
+        rc = L.sb_op_head(W.data_ptr(), sb.BF16, n, n, x.data_ptr(), M, 1.1, k, am2.data_ptr(), cf2.data_ptr(), y.data_ptr(), scratch.data_ptr(), st)
+        assert rc == 0 and T.equal(am, am2) and T.equal(cf, cf2)
+    else:
+        ref = (sb.op_gemv if entry == "gemv" else sb.op_gate_up)(W, x0, k)
+        call = L.sb_op_gemv if entry == "gemv" else L.sb_op_gate_up
+        rc = call(W.data_ptr(), sb.BF16, n, n, x.data_ptr(), y.data_ptr(), M, k, scratch.data_ptr(), st)
+        assert rc == 0
+    assert T.equal(y, ref)
+
+
 # launches between the two above: key tiles taken apart by the four waves of a block (257 blocks of 32 queries up to
 # 319 of 128), with a prefix that ends inside a tile, fewer tiles than waves, a grouped-query shape whose
 # blocks straddle rows; then the smallest launch of the wide form

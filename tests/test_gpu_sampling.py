@@ -49,8 +49,8 @@ def _near_boundary(P, u_acc, u_draw, x, tok_gpu, tol=1e-4):
 
 
 @pytest.mark.parametrize("variant,vocab", [("fp32", 1024), ("bf16", 1024), ("bf16", 4112), ("bf16", 32000),
-                                            # above 32768 the kernel keeps the remaining weights in memory: a tail of 16 tokens
-                                            # (most threads own none of it), one full group of sixteen loads plus a ragged rest
+                                            # blocks of 4096 tokens: part of one, one and a tail of 16, the last nearly full, eight and
+                                            # a tail, twelve and a ragged rest, 31 and a third
                                             ("bf16", 32784), ("bf16", 32768 + 17 * 1024 + 16), ("bf16", 128256)])
 @pytest.mark.parametrize("temp,top_p", [(1.0, 1.0), (0.3, 1.0), (1.0, 0.9), (0.7, 0.5)])
 def test_sampling_decisions_follow_the_rule_on_the_librarys_own_logits(sb, variant, vocab, temp, top_p):
