@@ -203,7 +203,7 @@ struct GemmArgs {
     int32_t pass_rows;   // set by launch_prefill_gemm: rows per pass, the M rows in n_pass equal parts of whole 16-row tiles
     float* part;
     int32_t S;           // partial-sum slots per row block, from gemm_splits()
-    // Tail done by the GEMM itself for the row blocks (256 weight rows) whose whole k range one thread
+    // Tail done by the GEMM itself for the row blocks (GemmPlan::block_rows) whose whole k range one thread
     // block owns; the epilogue, which must be given the same `fused`, then only finishes the row blocks
     // that were cut along k.  0: none.  1 + EPI_STORE: y = scale * product.  1 + EPI_SWIGLU (rows = 2 N:
     // N gate rows, then N up rows; a thread block takes matching gate and up tiles together):

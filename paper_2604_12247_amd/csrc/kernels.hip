@@ -388,7 +388,7 @@ hipError_t launch_head_merge_batch(const HeadMergeBatch& hb, int32_t n, int32_t 
 // ten bits of their bit pattern each (monotone in the value of a positive float).  Mass is counted in units of
 // 2^-40 of the largest weight, in 64-bit integers: exact in any order, finer than a float sum of as many
 // terms.  All rows and all of the vocabulary go through each stage side by side; whether a row is reached at
-// all is decided in the last one.  What bounds it: the launches (six of 4 to 6 us).  One block that searched the
+// all is decided in the last one.  What bounds it: the launches (six of 4.5 to 9 us).  One block that searched the
 // edge by bisection, row after row, took 345 us a row at V = 128256 and 100 us at 32000.
 constexpr int SMP_T = 1024, SMP_PER = 4, SMP_TOK = SMP_T * SMP_PER;   // threads, tokens per thread, tokens per block
 constexpr int SMP_BINS = 1024;
