@@ -149,7 +149,6 @@ int32_t sb_op_head_static(const void* W, int32_t w_dtype, int32_t N, int32_t K, 
     hipError_t e = static_scratch(&base);   // address of the library's own device array on this GPU
     if (e != hipSuccess) return fail(SB_EDEVICE, "op_head_static: static scratch area: %s", hipGetErrorString(e));
     char* sc = (char*)base;
-    const int nb = head_blocks_valu(N);
     GemvArgs g{};
     g.W = W; g.w_dtype = w_dtype; g.N = N; g.K = K; g.x = x; g.M = M; g.epi = EPI_HEAD;
     g.head.T = T; g.head.partials = (float*)(sc + 256);
