@@ -47,7 +47,8 @@ __device__ __forceinline__ void head_partial(const HeadArgs& h, float (*zs)[SB_M
 // requested before the rows are staged, and the rows are normalised while they are staged where the caller asks for it: a
 // small model is bound by its number of launches (4.2 us each in a chain of them), and the sum of squares costs
 // a block two barriers (same order of additions as rmsnorm_kernel).  Longer rows would be read twice by every
-// block, and registers that hold weights through the staging are waves the stream misses.
+// block, and registers that hold weights through the staging are waves the stream misses: [11008 x 4096] bf16, 8 rows, 52.7 us
+// with the weights first and 24.6 without ([1024 x 1024] fp32, one row, 3.4 us with them first, 4.0 in a loop of load and store).
 template <typename WT, int M, int EPI, bool SHORT>
 __global__ __launch_bounds__(256) void gemv_valu_kernel(GemvArgs a) {
     constexpr int R = 4;
