@@ -49,17 +49,17 @@ __device__ __forceinline__ void head_partial(const HeadArgs& h, float (*zs)[SB_M
 // a block two barriers (same order of additions as rmsnorm_kernel).  Longer rows would be read twice by every
 // block, and registers that hold weights through the staging are waves the stream misses: [11008 x 4096] bf16, 8 rows, 52.7 us
 // with the weights first and 24.6 without ([1024 x 1024] fp32, one row, 3.4 us with them first, 4.0 in a loop of load and store).
-template <typename WT, int M, int EPI, bool SHORT>
+template <typename WT, int M, int EPI, bool SHORT, int R>
 __global__ __launch_bounds__(256) void gemv_valu_kernel(GemvArgs a) {
-    constexpr int R = 4;
+    static_assert(EPI != EPI_HEAD || R == 4, "a head's partial is taken over 16 logits");
     constexpr int KC = SHORT ? SB_VALU_NORM_K : (M <= 4) ? 2048 : 1024;
-    constexpr int OUT_PER_BLOCK = (EPI == EPI_SWIGLU) ? 8 : 16;
+    constexpr int RO = (EPI == EPI_SWIGLU) ? R / 2 : R;   // outputs per wave
     __shared__ __attribute__((aligned(16))) float xs[M][KC];
     __shared__ float zs[16][SB_MAX_W];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const WT* __restrict__ W = reinterpret_cast<const WT*>(a.W);
     const int N = a.N, K = a.K;
-    const int n0 = blockIdx.x * OUT_PER_BLOCK;
+    const int n0 = blockIdx.x * 4 * RO;
     const int total_rows = (EPI == EPI_SWIGLU) ? 2 * N : N;
 
     int outn[R];
@@ -68,10 +68,10 @@ __global__ __launch_bounds__(256) void gemv_valu_kernel(GemvArgs a) {
     for (int r = 0; r < R; ++r) {
         int n, row;
         if (EPI == EPI_SWIGLU) {
-            n = n0 + wave * 2 + (r & 1);
-            row = (r < 2) ? n : N + n;
+            n = n0 + wave * RO + r % RO;
+            row = (r < RO) ? n : N + n;
         } else {
-            n = n0 + wave * 4 + r;
+            n = n0 + wave * R + r;
             row = n;
         }
         outn[r] = n;
@@ -101,6 +101,9 @@ __global__ __launch_bounds__(256) void gemv_valu_kernel(GemvArgs a) {
             }
         }
     };
+    // (the residual's element is requested with the first weights, not after the last)
+    float pre_y = 0.f;
+    if (EPI == EPI_RESID && lane < R * M && n0 + wave * R + lane / M < N) pre_y = a.y[(size_t)(lane % M) * a.ldy + n0 + wave * R + lane / M];
     for (int k0 = 0; k0 < K; k0 += KC) {   // (SHORT: one chunk)
         const int kc = (K - k0 < KC) ? (K - k0) : KC;
         Piece8<WT> w0[R], w1[R];   // (SHORT)
@@ -180,15 +183,15 @@ __global__ __launch_bounds__(256) void gemv_valu_kernel(GemvArgs a) {
             for (int m = 0; m < M; ++m)
                 if (lane == r * M + m && outn[r] < N) {
                     float* yp = a.y + (size_t)m * a.ldy + outn[r];
-                    *yp = (EPI == EPI_RESID) ? (*yp + acc[r][m]) : acc[r][m];
+                    *yp = (EPI == EPI_RESID) ? (pre_y + acc[r][m]) : acc[r][m];
                 }
     } else if (EPI == EPI_SWIGLU) {
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int j = 0; j < RO; ++j)
 #pragma unroll
             for (int m = 0; m < M; ++m)
                 if (lane == j * M + m && outn[j] < N)
-                    a.y[(size_t)m * a.ldy + outn[j]] = silu_mul(acc[j][m], acc[2 + j][m]);
+                    a.y[(size_t)m * a.ldy + outn[j]] = silu_mul(acc[j][m], acc[RO + j][m]);
     } else {  // EPI_HEAD
 #pragma unroll
         for (int r = 0; r < R; ++r)
@@ -202,14 +205,30 @@ __global__ __launch_bounds__(256) void gemv_valu_kernel(GemvArgs a) {
 
 int head_blocks_valu(int32_t N) { return (N + 15) / 16; }
 
+// Weight rows per wave: one (gate / up: a pair), so that a small matrix has four (two) times the blocks, or four, so that a block's rows
+// are staged for four times the weights.  One while four would leave CUs without a block, and beyond that while a block
+// stages no more bytes than it reads of the weights.  Four / one, in us: fp32 [256 x 688], one row 3.7 / 2.5, four 6.2 / 3.5, eight
+// 9.6 / 4.0; bf16 [4000 x 4096], eight 17.4 / 16.9; fp32 [12288 x 1024], one 10.8 / 10.1, [16000 x 4096], one 51.4 / 46.2, four
+// 54.6 / 46.5; but bf16 [6144 x 4096], eight 19.7 / 24.7, [12288 x 4096], four 25.0 / 28.5.  A row's sums are the same either way.
 template <typename WT, int M, bool SHORT>
 static hipError_t launch_gemv_valu_m(const GemvArgs& a, hipStream_t st) {
+    const int n = a.epi == EPI_SWIGLU ? 2 * a.N : a.N;
+    const bool few = n < 16 * 256 || (M <= (int)sizeof(WT) && n < 16 * 1024);
     switch (a.epi) {
-        case EPI_STORE: gemv_valu_kernel<WT, M, EPI_STORE, SHORT><<<(a.N + 15) / 16, 256, 0, st>>>(a); break;
-        case EPI_RESID: gemv_valu_kernel<WT, M, EPI_RESID, SHORT><<<(a.N + 15) / 16, 256, 0, st>>>(a); break;
-        case EPI_SWIGLU: gemv_valu_kernel<WT, M, EPI_SWIGLU, SHORT><<<(a.N + 7) / 8, 256, 0, st>>>(a); break;
+        case EPI_STORE:
+            if (few) gemv_valu_kernel<WT, M, EPI_STORE, SHORT, 1><<<(a.N + 3) / 4, 256, 0, st>>>(a);
+            else gemv_valu_kernel<WT, M, EPI_STORE, SHORT, 4><<<(a.N + 15) / 16, 256, 0, st>>>(a);
+            break;
+        case EPI_RESID:
+            if (few) gemv_valu_kernel<WT, M, EPI_RESID, SHORT, 1><<<(a.N + 3) / 4, 256, 0, st>>>(a);
+            else gemv_valu_kernel<WT, M, EPI_RESID, SHORT, 4><<<(a.N + 15) / 16, 256, 0, st>>>(a);
+            break;
+        case EPI_SWIGLU:
+            if (few) gemv_valu_kernel<WT, M, EPI_SWIGLU, SHORT, 2><<<(a.N + 3) / 4, 256, 0, st>>>(a);
+            else gemv_valu_kernel<WT, M, EPI_SWIGLU, SHORT, 4><<<(a.N + 7) / 8, 256, 0, st>>>(a);
+            break;
         case EPI_HEAD: {
-            gemv_valu_kernel<WT, M, EPI_HEAD, SHORT><<<(a.N + 15) / 16, 256, 0, st>>>(a);
+            gemv_valu_kernel<WT, M, EPI_HEAD, SHORT, 4><<<(a.N + 15) / 16, 256, 0, st>>>(a);
             hipError_t e = hipGetLastError();
             return e != hipSuccess ? e : launch_head_merge(a.head, M, (a.N + 15) / 16, st);
         }

@@ -61,6 +61,26 @@ def test_gemv_valu(T, N, K, bf16, M):
     assert np.max(np.abs(y - ref)) <= 1e-5 * np.max(np.abs(ref)) + 1e-7
 
 
+# either side of the lines between one and four weight rows per wave (256 blocks of four; 1024 for as few rows as a weight has bytes)
+@pytest.mark.parametrize("N,K,bf16", [(4080, 264, False), (4096, 264, False), (4097, 1032, True), (16383, 136, False), (16400, 136, True)])
+@pytest.mark.parametrize("M", [1, 2, 3, 4, 5])
+def test_gemv_valu_rows_per_wave(T, N, K, bf16, M):
+    """The rows per wave change who adds a row's products, not how: the bits of a row equal those of eight rows together."""
+    import paper_2604_12247_amd as sb
+    g = np.random.default_rng(N + K)
+    W = _rand_w(g, N, K, bf16)
+    x = g.standard_normal((8, K)).astype(np.float32)
+    Wd = _dev(T, W)
+    y = sb.op_gemv(Wd, _dev(T, x[:M]), sb.PROJ_VALU).cpu().numpy()
+    ref = _oracle_rows(W, x[:M])
+    assert np.max(np.abs(y - ref)) <= 1e-5 * np.max(np.abs(ref)) + 1e-7
+    assert np.array_equal(y, sb.op_gemv(Wd, _dev(T, x), sb.PROJ_VALU).cpu().numpy()[:M])
+    if N % 2 == 0:   # the same lines for gate / up, which takes the rows in pairs
+        u = sb.op_gate_up(Wd, _dev(T, x[:M]), sb.PROJ_VALU).cpu().numpy()
+        assert np.max(np.abs(u - np.stack([orc.swiglu(r) for r in ref]))) <= 1e-4 * np.max(np.abs(ref))
+        assert np.array_equal(u, sb.op_gate_up(Wd, _dev(T, x), sb.PROJ_VALU).cpu().numpy()[:M])
+
+
 MFMA_CASES = [(16, 128), (64, 256), (4096, 4096), (12288, 4096), (4096, 11008), (32000, 4096), (48, 384),
               (15024, 256),      # two row tiles per block, an odd number of tiles: the last block owns one
               (4096, 14336),
@@ -611,6 +631,14 @@ def test_attention_fp32_cache_block_counts(T, hd, pos0):
     for r in (0, 5):
         _, out1 = _attention_case(T, 32, 32, hd, False, pos0 + r, 1, 1e4, True, seed=83 + pos0, oracle=r == 5 and pos0 in (3070, 1535))
         assert np.array_equal(out1[0], out6[r]), r
+
+
+@pytest.mark.parametrize("Hq,Hkv,hd,bf16", [(4, 4, 64, False), (2, 2, 128, False), (4, 2, 64, True), (4, 4, 128, True)])
+def test_new_rows_at_every_place_of_a_chunk(T, Hq, Hkv, hd, bf16):
+    """New rows on either side of half pages, pages, operand steps and chunks, from one to eight, as the chunk's first and last keys."""
+    for pos0, M in ((0, 8), (7, 1), (8, 8), (13, 6), (15, 2), (31, 3), (57, 8), (63, 1), (64, 8), (95, 4), (120, 8), (121, 8), (127, 1), (128, 1)):
+        worst, _ = _attention_case(T, Hq, Hkv, hd, bf16, pos0, M, 1e4, True, seed=pos0 * 9 + M)
+        assert worst <= 2e-5, (pos0, M, worst)
 
 
 def test_attention_row_result_does_not_depend_on_m(T):
