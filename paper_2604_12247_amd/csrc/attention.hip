@@ -5,6 +5,7 @@
 #include "device_utils.h"
 
 #include <math.h>
+#include <type_traits>
 
 namespace sb {
 
@@ -51,15 +52,65 @@ template <> struct KvVec<float> {
     }
 };
 
+// A value as the cache holds it.
+template <typename KVT>
+__device__ __forceinline__ KVT kv_round(float f) {
+    if constexpr (sizeof(KVT) == 2) return f2bf(f);
+    else return f;
+}
+
 // A finished value of row r, as the merge stage leaves it.
 __device__ __forceinline__ void attn_finish(const AttnArgs& a, int r, int col, int ld, float v) {
     if (a.out) a.out[(size_t)r * ld + col] = v;
     if (a.out_split) split_store_rows(a.out_split, ld, a.split_rows, r, col, v);
 }
 
-// WAVES: blocks a CU holds at once (one wave of each per SIMD).  All of the new rows' loads in flight take 160 registers, three blocks; in
-// 128, with some 30 values spilled where a chunk holds new rows, four fit.  launch_attention says when which.
-template <typename KVT, int HD, int WAVES>
+// (by value: `c ? a : b` on two arrays' elements is a choice of addresses, which would keep the arrays in memory)
+__device__ __forceinline__ uint4 pick(bool c, uint4 a, uint4 b) {
+    return make_uint4(c ? a.x : b.x, c ? a.y : b.y, c ? a.z : b.z, c ? a.w : b.w);
+}
+
+// The new rows' keys and values of kv head g (at most SB_MAX_W rows), an element of a pair or a value per thread: loaded with everything
+// else a block reads, rotated and rounded once, and left in LDS for the lanes whose keys they are.
+template <int HD>
+struct NewRows {
+    static constexpr int HALF = HD / 2, NP = HALF / 32, NV = HD / 32;
+    float x[NP], y[NP], c[NP], sn[NP], v[NV];
+    __device__ __forceinline__ void load(const AttnArgs& a, int g) {
+        const int r = threadIdx.x >> 5, j = threadIdx.x & 31;   // 32 threads per row
+        const float* kp = a.q + (size_t)(r < a.M ? r : 0) * a.qkv_rows + (size_t)(a.n_heads + g) * HD + j;
+        const float* vp = kp + (size_t)a.kv.n_kv_heads * HD;
+        const size_t rope = (size_t)(a.pos0 + (r < a.M ? r : 0)) * HALF + j;
+#pragma unroll
+        for (int i = 0; i < NP; ++i) {
+            x[i] = kp[i * 32]; y[i] = kp[i * 32 + HALF];
+            c[i] = a.rope_cos[rope + i * 32]; sn[i] = a.rope_sin[rope + i * 32];
+        }
+#pragma unroll
+        for (int i = 0; i < NV; ++i) v[i] = vp[i * 32];
+    }
+    template <typename KVT, int LDK>
+    __device__ __forceinline__ void store(const AttnArgs& a, KVT* k_s, KVT* v_s) const {
+        const int r = threadIdx.x >> 5, j = threadIdx.x & 31;
+        if (r >= a.M) return;
+#pragma unroll
+        for (int i = 0; i < NP; ++i) {
+            k_s[r * LDK + j + i * 32] = kv_round<KVT>(x[i] * c[i] - y[i] * sn[i]);
+            k_s[r * LDK + j + i * 32 + HALF] = kv_round<KVT>(y[i] * c[i] + x[i] * sn[i]);
+        }
+#pragma unroll
+        for (int i = 0; i < NV; ++i) v_s[r * HD + j + i * 32] = kv_round<KVT>(v[i]);
+    }
+};
+
+// WAVES: blocks a CU holds at once (one wave of each per SIMD).  MANY: passes of more than SB_MAX_W rows, whose chunks are full of new
+// rows: each thread prepares its own, which takes 160 registers, three blocks per CU (in 128, with some spilled, four fit;
+// launch_attention says when which).  Else the new rows go through LDS and four blocks fit.
+// What bounds a decode pass: few keys the chain of round trips (page table, operands, LDS), many the memory.  The page table through
+// the scalar cache and everything else in one go, instead of a table entry, a wait and a load for each of a thread's eight
+// value pieces: 4 heads x 64, 90 keys, one row 6.5 -> 5.2 us, four 9.0 -> 7.4; 32 heads, one row, 2000 keys x 128 24.8 -> 17.6,
+// 9000 x 128 85 -> 63, 9000 x 64 47.5 -> 33.6.
+template <typename KVT, int HD, int WAVES, bool MANY>
 __global__ __launch_bounds__(256, WAVES) void attn_kernel(AttnArgs a) {
     constexpr int CH = (HD * sizeof(KVT) <= 256) ? 128 : 64;  // keys per chunk
     constexpr int EPV = KvVec<KVT>::EPV;                      // elements per 16 bytes
@@ -73,14 +124,20 @@ __global__ __launch_bounds__(256, WAVES) void attn_kernel(AttnArgs a) {
     constexpr int DGW = HD / 4 / EPV;                         // 16-byte dim groups per wave
     constexpr int KS = 64 / DGW;                              // key slots (lanes per dim group)
     constexpr int KPT = CH / KS;                              // keys per value thread
+    // A score thread reads 128 bytes of its key, a piece per load, so a wave's lines have to stay in the L1 over all of its
+    // loads: at head_dim 128 the values are requested behind them (32 heads, 9000 keys: 85 us; together 94).
+    constexpr bool LATE_V = HD * sizeof(KVT) > 256;
     static_assert(DPT <= HALF && HALF % DPT == 0, "a score thread's dims lie in one rotary half");
     static_assert(DGW >= 1 && KS * KPT == CH, "value mapping");
     __shared__ __attribute__((aligned(16))) float qs[QG * HD];
     __shared__ __attribute__((aligned(16))) float sp[DSPLIT * QG * CH];  // partial scores, then probabilities
     __shared__ float s_m[QG], s_l[QG];
+    constexpr int NR = MANY ? 1 : SB_MAX_W;
+    __shared__ __attribute__((aligned(16))) KVT nk_s[NR * HD], nv_s[NR * HD];   // (!MANY) the new rows' keys and values
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int g = blockIdx.x, chunk = blockIdx.y, qg = blockIdx.z;
+    // (the chunk with the new rows, the longest to prepare, first)
+    const int g = blockIdx.x, chunk = gridDim.y - 1 - blockIdx.y, qg = blockIdx.z;
     const int Hq = a.n_heads, Hkv = a.kv.n_kv_heads, G = Hq / Hkv;
     const int nq_total = a.M * G, q0 = qg * QG;
     const int nq = (nq_total - q0 < QG) ? (nq_total - q0) : QG;
@@ -90,7 +147,30 @@ __global__ __launch_bounds__(256, WAVES) void attn_kernel(AttnArgs a) {
     KVT* const kbase = reinterpret_cast<KVT*>(a.kv.pool) + (size_t)(a.layer * 2 + 0) * a.kv.n_pages * page_elems;
     KVT* const vbase = reinterpret_cast<KVT*>(a.kv.pool) + (size_t)(a.layer * 2 + 1) * a.kv.n_pages * page_elems;
 
-    // ---- issue every global load first: q (+ its rotary factors), K, V
+    // ---- page-table entries of this thread's keys, all in flight at once; a key past the end takes the last page (what its slot
+    // holds is not used)
+    const bool has_new = key0 + CH > a.pos0;
+    // scores mapping: key kt, dims [kd0, kd0 + DPT)
+    const int kt = tid % CH, kd0 = (tid / CH) * DPT;
+    const int kkey = key0 + kt;
+    // values mapping: dims [vd0, vd0 + EPV), keys vks + KS * i
+    const int vd0 = wave * (HD / 4) + (lane % DGW) * EPV, vks = lane / DGW;
+    static_assert(SB_KV_BLOCK % KS == 0 && CH % 64 == 0, "a value load's keys lie in one page, a wave's score keys in four");
+    auto page_at = [&](int key) {   // (key: the same in all lanes, so through the scalar cache)
+        const int p = key / SB_KV_BLOCK, last = (n_total - 1) / SB_KV_BLOCK;
+        return a.kv.table[p < last ? p : last];
+    };
+    int vpage[KPT];
+#pragma unroll
+    for (int i = 0; i < KPT; ++i) vpage[i] = page_at(key0 + KS * i);
+    int kpage;   // of this lane's key, from the wave's four (a choice in registers, not of addresses)
+    {
+        const int k0 = __builtin_amdgcn_readfirstlane(key0 + (kt & ~63)), sel = lane / SB_KV_BLOCK;
+        const int p0 = page_at(k0), p1 = page_at(k0 + SB_KV_BLOCK), p2 = page_at(k0 + 2 * SB_KV_BLOCK), p3 = page_at(k0 + 3 * SB_KV_BLOCK);
+        const int lo = p0 + ((p1 - p0) & -(sel & 1)), hi = p2 + ((p3 - p2) & -(sel & 1));
+        kpage = lo + ((hi - lo) & -(sel >> 1));
+    }
+    // ---- the other loads: q (+ its rotary factors), the new rows, K, V
     constexpr int QIT = QG * HALF / 256;
     float qx[QIT], qy[QIT], qc[QIT], qsn[QIT];
 #pragma unroll
@@ -108,72 +188,21 @@ __global__ __launch_bounds__(256, WAVES) void attn_kernel(AttnArgs a) {
             qsn[it] = a.rope_sin[(size_t)(a.pos0 + r) * HALF + j];
         }
     }
-    // scores mapping: key kt, dims [kd0, kd0 + DPT)
-    const int kt = tid % CH, kd0 = (tid / CH) * DPT;
-    const int kkey = key0 + kt;
+    NewRows<HD> nr;
+    if (!MANY && has_new) nr.load(a, g);
     uint4 kreg[NKV];
-    size_t kaddr = 0;  // element offset of this thread's K slice inside the K pool of the layer
-    if (kkey < n_total) kaddr = (size_t)a.kv.table[kkey / SB_KV_BLOCK] * page_elems + ((size_t)g * SB_KV_BLOCK + (kkey % SB_KV_BLOCK)) * HD + kd0;
+    // element offset of this thread's K slice inside the K pool of the layer
+    const size_t kaddr = (size_t)kpage * page_elems + (uint32_t)((g * SB_KV_BLOCK + (kkey % SB_KV_BLOCK)) * HD + kd0);
 #pragma unroll
-    for (int i = 0; i < NKV; ++i) {
-        kreg[i] = make_uint4(0, 0, 0, 0);
-        if (kkey < a.pos0) kreg[i] = *reinterpret_cast<const uint4*>(kbase + kaddr + i * EPV);
-    }
-    // values mapping: dims [vd0, vd0 + EPV), keys vks + KS * i
-    const int vd0 = wave * (HD / 4) + (lane % DGW) * EPV, vks = lane / DGW;
+    for (int i = 0; i < NKV; ++i) kreg[i] = *reinterpret_cast<const uint4*>(kbase + kaddr + i * EPV);
     uint4 vreg[KPT];
-    size_t vaddr[KPT];
+    auto vaddr = [&](int i) { return (size_t)vpage[i] * page_elems + (uint32_t)((g * SB_KV_BLOCK + ((vks + KS * i) % SB_KV_BLOCK)) * HD + vd0); };
+    auto load_v = [&]() {
 #pragma unroll
-    for (int i = 0; i < KPT; ++i) {
-        const int key = key0 + vks + KS * i;
-        vreg[i] = make_uint4(0, 0, 0, 0);
-        vaddr[i] = 0;
-        if (key < n_total) vaddr[i] = (size_t)a.kv.table[key / SB_KV_BLOCK] * page_elems + ((size_t)g * SB_KV_BLOCK + (key % SB_KV_BLOCK)) * HD + vd0;
-        if (key < a.pos0) vreg[i] = *reinterpret_cast<const uint4*>(vbase + vaddr[i]);
-    }
-
-    // ---- keys and values of the new rows: built from qkv, appended by query group 0
-    if (kkey >= a.pos0 && kkey < n_total) {
-        const int r = kkey - a.pos0;
-        const float* kp = a.q + (size_t)r * a.qkv_rows + (size_t)(Hq + g) * HD;
-        const bool lo = kd0 < HALF;
-        const int dj = lo ? kd0 : kd0 - HALF;
-#pragma unroll
-        for (int i = 0; i < NKV; ++i) {
-            float f[EPV];
-#pragma unroll
-            for (int e = 0; e < EPV; ++e) {
-                const int j = dj + i * EPV + e;
-                float c = a.rope_cos[(size_t)kkey * HALF + j], sn = a.rope_sin[(size_t)kkey * HALF + j];
-                float x = kp[j], y = kp[j + HALF];
-                f[e] = lo ? (x * c - y * sn) : (y * c + x * sn);
-            }
-            kreg[i] = KvVec<KVT>::pack(f);
-        }
-    }
-#pragma unroll
-    for (int i = 0; i < KPT; ++i) {
-        const int key = key0 + vks + KS * i;
-        if (key >= a.pos0 && key < n_total) {
-            const float* vp = a.q + (size_t)(key - a.pos0) * a.qkv_rows + (size_t)(Hq + Hkv + g) * HD + vd0;
-            float f[EPV];
-#pragma unroll
-            for (int e = 0; e < EPV; ++e) f[e] = vp[e];
-            vreg[i] = KvVec<KVT>::pack(f);
-        }
-    }
-    // (stored after the last of these loads: a store between them, which might alias, would make each a round trip of its own)
-    if (qg == 0) {
-        if (kkey >= a.pos0 && kkey < n_total)
-#pragma unroll
-            for (int i = 0; i < NKV; ++i) *reinterpret_cast<uint4*>(kbase + kaddr + i * EPV) = kreg[i];
-#pragma unroll
-        for (int i = 0; i < KPT; ++i) {
-            const int key = key0 + vks + KS * i;
-            if (key >= a.pos0 && key < n_total) *reinterpret_cast<uint4*>(vbase + vaddr[i]) = vreg[i];
-        }
-    }
-    // ---- rotated queries -> LDS
+        for (int i = 0; i < KPT; ++i) vreg[i] = *reinterpret_cast<const uint4*>(vbase + vaddr(i));
+    };
+    if (!LATE_V) load_v();
+    // ---- rotated queries -> LDS, and the new rows' keys and values as they are stored
 #pragma unroll
     for (int it = 0; it < QIT; ++it) {
         const int i = tid + it * 256;
@@ -181,7 +210,83 @@ __global__ __launch_bounds__(256, WAVES) void attn_kernel(AttnArgs a) {
         qs[qi * HD + j] = qx[it] * qc[it] - qy[it] * qsn[it];
         qs[qi * HD + j + HALF] = qy[it] * qc[it] + qx[it] * qsn[it];
     }
+    if (!MANY && has_new) nr.template store<KVT, HD>(a, nk_s, nv_s);
     __syncthreads();
+    if (LATE_V) {
+        __builtin_amdgcn_sched_barrier(0);
+        load_v();
+    }
+    // ---- keys (and, below, values) of the new rows take the place of what the cache held, appended by query group 0
+    if (has_new) {
+        if (MANY) {
+            if (kkey >= a.pos0 && kkey < n_total) {
+                const int r = kkey - a.pos0;
+                const float* kp = a.q + (size_t)r * a.qkv_rows + (size_t)(Hq + g) * HD;
+                const bool lo = kd0 < HALF;
+                const int dj = lo ? kd0 : kd0 - HALF;
+#pragma unroll
+                for (int i = 0; i < NKV; ++i) {
+                    float f[EPV];
+#pragma unroll
+                    for (int e = 0; e < EPV; ++e) {
+                        const int j = dj + i * EPV + e;
+                        float c = a.rope_cos[(size_t)kkey * HALF + j], sn = a.rope_sin[(size_t)kkey * HALF + j];
+                        float x = kp[j], y = kp[j + HALF];
+                        f[e] = lo ? (x * c - y * sn) : (y * c + x * sn);
+                    }
+                    kreg[i] = KvVec<KVT>::pack(f);
+                }
+            }
+        } else {
+            const bool fresh = kkey >= a.pos0 && kkey < n_total;
+            const KVT* kp = &nk_s[(fresh ? kkey - a.pos0 : 0) * HD + kd0];
+#pragma unroll
+            for (int i = 0; i < NKV; ++i) {
+                const uint4 v = *reinterpret_cast<const uint4*>(kp + i * EPV);
+                kreg[i] = pick(fresh, v, kreg[i]);
+            }
+        }
+    }
+    auto append_values = [&]() {
+#pragma unroll
+        for (int i = 0; i < KPT; ++i) {
+            const int key = key0 + vks + KS * i;
+            if (key >= a.pos0 && key < n_total) *reinterpret_cast<uint4*>(vbase + vaddr(i)) = vreg[i];
+        }
+    };
+    // values of the new rows; zeros in slots past the last key (0 x stale bits that read as NaN is not 0)
+    auto new_values = [&]() {
+        if (!has_new) return;
+        if (MANY) {
+#pragma unroll
+            for (int i = 0; i < KPT; ++i) {
+                const int key = key0 + vks + KS * i;
+                if (key >= a.pos0 && key < n_total) {
+                    const float* vp = a.q + (size_t)(key - a.pos0) * a.qkv_rows + (size_t)(Hq + Hkv + g) * HD + vd0;
+                    float f[EPV];
+#pragma unroll
+                    for (int e = 0; e < EPV; ++e) f[e] = vp[e];
+                    vreg[i] = KvVec<KVT>::pack(f);
+                }
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < KPT; ++i) {
+                const int key = key0 + vks + KS * i;
+                const uint4 v = *reinterpret_cast<const uint4*>(&nv_s[(key >= a.pos0 && key < n_total ? key - a.pos0 : 0) * HD + vd0]);
+                vreg[i] = pick(key >= a.pos0, v, vreg[i]);
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < KPT; ++i) vreg[i] = pick(key0 + vks + KS * i >= n_total, make_uint4(0, 0, 0, 0), vreg[i]);
+    };
+    if (!LATE_V) new_values();
+    if (has_new && qg == 0) {
+        if (kkey >= a.pos0 && kkey < n_total)
+#pragma unroll
+            for (int i = 0; i < NKV; ++i) *reinterpret_cast<uint4*>(kbase + kaddr + i * EPV) = kreg[i];
+        if (!LATE_V) append_values();
+    }
 
     // ---- partial scores: this thread's DPT dims of key kt against every live query
     {
@@ -190,14 +295,18 @@ __global__ __launch_bounds__(256, WAVES) void attn_kernel(AttnArgs a) {
         for (int i = 0; i < NKV; ++i) KvVec<KVT>::unpack(kreg[i], kf[i]);
         for (int qi = 0; qi < nq; ++qi) {
             const float* qp = &qs[qi * HD + kd0];
+            float4 qv[DPT / 4];   // (all requested before the first is used: one wait, not one per piece)
+#pragma unroll
+            for (int i = 0; i < DPT / 4; ++i) qv[i] = *reinterpret_cast<const float4*>(qp + 4 * i);
+            __builtin_amdgcn_sched_barrier(0);
             float s = 0.f;
 #pragma unroll
             for (int i = 0; i < NKV; ++i)
 #pragma unroll
                 for (int e = 0; e < EPV; e += 4) {
-                    float4 qv = *reinterpret_cast<const float4*>(qp + i * EPV + e);
-                    s = fmaf(qv.x, kf[i][e], s); s = fmaf(qv.y, kf[i][e + 1], s);
-                    s = fmaf(qv.z, kf[i][e + 2], s); s = fmaf(qv.w, kf[i][e + 3], s);
+                    const float4 v = qv[(i * EPV + e) / 4];
+                    s = fmaf(v.x, kf[i][e], s); s = fmaf(v.y, kf[i][e + 1], s);
+                    s = fmaf(v.z, kf[i][e + 2], s); s = fmaf(v.w, kf[i][e + 3], s);
                 }
             sp[((tid / CH) * QG + qi) * CH + kt] = s;
         }
@@ -231,21 +340,25 @@ __global__ __launch_bounds__(256, WAVES) void attn_kernel(AttnArgs a) {
         if (lane == 0) { s_m[qi] = mx; s_l[qi] = l; }
     }
     __syncthreads();
+    if (LATE_V) {
+        new_values();
+        if (has_new && qg == 0) append_values();
+    }
     // ---- weighted values
     {
         float vf[KPT][EPV];
 #pragma unroll
         for (int i = 0; i < KPT; ++i) KvVec<KVT>::unpack(vreg[i], vf[i]);
         for (int qi = 0; qi < nq; ++qi) {
-            float o[EPV];
+            float p[KPT], o[EPV];
+#pragma unroll
+            for (int i = 0; i < KPT; ++i) p[i] = sp[qi * CH + vks + KS * i];
 #pragma unroll
             for (int e = 0; e < EPV; ++e) o[e] = 0.f;
 #pragma unroll
-            for (int i = 0; i < KPT; ++i) {
-                const float p = sp[qi * CH + vks + KS * i];
+            for (int i = 0; i < KPT; ++i)
 #pragma unroll
-                for (int e = 0; e < EPV; ++e) o[e] = fmaf(p, vf[i][e], o[e]);
-            }
+                for (int e = 0; e < EPV; ++e) o[e] = fmaf(p[i], vf[i][e], o[e]);
             // sum over the key slots: fixed tree inside the wave
 #pragma unroll
             for (int e = 0; e < EPV; ++e) o[e] = lanes_sum<32, DGW>(o[e]);
@@ -256,10 +369,10 @@ __global__ __launch_bounds__(256, WAVES) void attn_kernel(AttnArgs a) {
                     for (int e = 0; e < EPV; ++e) attn_finish(a, r, (g * G + gi) * HD + vd0 + e, Hq * HD, o[e] / s_l[qi]);
                     continue;
                 }
-                float* p = a.partials + ((size_t)(r * Hq + g * G + gi) * a.max_chunks + chunk) * (HD + 2);
+                float* dst = a.partials + ((size_t)(r * Hq + g * G + gi) * a.max_chunks + chunk) * (HD + 2);
 #pragma unroll
-                for (int e = 0; e < EPV; ++e) p[2 + vd0 + e] = o[e];
-                if (tid == 0) { p[0] = s_m[qi]; p[1] = s_l[qi]; }
+                for (int e = 0; e < EPV; ++e) dst[2 + vd0 + e] = o[e];
+                if (tid == 0) { dst[0] = s_m[qi]; dst[1] = s_l[qi]; }
             }
         }
     }
@@ -276,6 +389,11 @@ __global__ __launch_bounds__(256, WAVES) void attn_kernel(AttnArgs a) {
 //            and a wave's loads cover whole pages.  A wave owns HD/4 output dims.
 // Every output row of an MFMA depends on its own operand row only, so a query's
 // partial does not depend on which other queries share the block.
+// What bounds it: the chain page table -> operands -> scores -> soft-max -> values of a block, of which three per CU cover for each
+// other.  The chunk with the new rows is the longest: it is started first, and its new keys and values come with the other operands
+// and through LDS (a load and a wait for each element, as lanes picked them from the projections, cost 3 us at six rows).
+// 32 heads x 128, both kernels: six rows behind 100 / 700 / 4200 keys 8.6 / 13.6 / 27.3 -> 6.9 / 10.2 / 21.6 us, one row 6.0 / 9.3 / 22.2
+// -> 5.3 / 8.7 / 19.6; 8 kv heads, eight rows behind 8000 25.7 -> 22.4.
 // LDS of one block of the matrix-core attention kernels (one work item is computed at a time).
 template <int HD>
 struct AttnLds {
@@ -301,9 +419,10 @@ struct AttnItem {
     int g, chunk, zb;
     float qx[QIT], qy[QIT], qc[QIT], qsn[QIT];
     uint4 kreg[2][KSQ];
-    size_t kaddr[2];
+    int kpage[2];
     uint4 vreg[DT][KSV];
-    size_t vaddr[KSV];
+    int vpg[KSV];       // page of this lane's keys of a step
+    NewRows<HD> nr;
 
     __device__ __forceinline__ void load_q(const AttnArgs& a, int qg) {
         const int tid = threadIdx.x;
@@ -346,40 +465,40 @@ struct AttnItem {
         const bool has_new = key0 + CH > a.pos0;  // the chunk holds keys of the new rows
         (void)lane; (void)wave; (void)li; (void)lq; (void)n_qg; (void)qg_first; (void)qg_last; (void)n_total; (void)scale;
         (void)kbase; (void)vbase; (void)has_new; (void)page_elems; (void)nq_total;
-        // ---- every global load of the item: q (+ its rotary factors) of the first group, K, V
+        // ---- page-table entries of the chunk, all in flight at once, through the scalar cache; a page past the end is the
+        // last one (what its slots hold is masked or replaced)
+        const int last_page = (n_total - 1) / SB_KV_BLOCK;
+        int vpage[2 * KSV];
+    #pragma unroll
+        for (int i = 0; i < 2 * KSV; ++i) {
+            const int p = key0 / SB_KV_BLOCK + i;
+            vpage[i] = a.kv.table[p < last_page ? p : last_page];
+        }
+    #pragma unroll
+        for (int t = 0; t < 2; ++t) {   // (a tile is one page)
+            const int p = __builtin_amdgcn_readfirstlane(key0 / SB_KV_BLOCK + wave * 2 + t);
+            kpage[t] = a.kv.table[p < last_page ? p : last_page];
+        }
+        // ---- every other load of the item: q (+ its rotary factors) of the first group, the new rows, K, V
         load_q(a, qg_first);
+        if (has_new) nr.load(a, g);
         // K operands: tile t of this wave = keys key0 + wave*32 + t*16 + li (one page), dims ks*32 + lq*8 ..
     #pragma unroll
         for (int t = 0; t < 2; ++t) {
-            const int key = key0 + wave * 32 + t * 16 + li;
-            // a tile is one page: its table entry is wave-uniform, read through the scalar cache
-            const int kpage = __builtin_amdgcn_readfirstlane((key0 + wave * 32 + t * 16) / SB_KV_BLOCK);
-            kaddr[t] = 0;
-            if (kpage * SB_KV_BLOCK < n_total)
-                kaddr[t] = (size_t)a.kv.table[kpage] * page_elems + ((size_t)g * SB_KV_BLOCK + li) * HD + lq * 8;
+            const uint16_t* kp = kbase + (size_t)kpage[t] * page_elems + (uint32_t)((g * SB_KV_BLOCK + li) * HD + lq * 8);
     #pragma unroll
-            for (int ks = 0; ks < KSQ; ++ks) {
-                kreg[t][ks] = make_uint4(0, 0, 0, 0);
-                if (key < a.pos0) kreg[t][ks] = *reinterpret_cast<const uint4*>(kbase + kaddr[t] + ks * 32);
-            }
+            for (int ks = 0; ks < KSQ; ++ks) kreg[t][ks] = *reinterpret_cast<const uint4*>(kp + ks * 32);
         }
-        // V operands: dim (wave*DT + dt)*16 + li, keys key0 + ks*32 + lq*8 .. +8 (half a page row)
+        // V operands: dim (wave*DT + dt)*16 + li, keys key0 + ks*32 + lq*8 .. +8 (half a page row); the 32 keys of a step lie
+        // in two pages (lq 0-1, lq 2-3)
+        const uint32_t voff = (uint32_t)((g * HD + wave * DT * 16 + li) * SB_KV_BLOCK + (lq & 1) * 8);
     #pragma unroll
         for (int ks = 0; ks < KSV; ++ks) {
-            const int kf = key0 + ks * 32 + lq * 8;  // first key of this lane's 8
-            // the 32 keys of a step lie in two pages (lq 0-1, lq 2-3): two wave-uniform table entries
-            const int vpage = (key0 + ks * 32) / SB_KV_BLOCK;
-            const int pg0 = vpage * SB_KV_BLOCK < n_total ? a.kv.table[vpage] : 0;
-            const int pg1 = (vpage + 1) * SB_KV_BLOCK < n_total ? a.kv.table[vpage + 1] : 0;
-            vaddr[ks] = 0;
-            if (kf < n_total) vaddr[ks] = (size_t)(lq < 2 ? pg0 : pg1) * page_elems + ((size_t)g * HD + wave * DT * 16 + li) * SB_KV_BLOCK + (lq & 1) * 8;
+            vpg[ks] = vpage[2 * ks] + ((vpage[2 * ks + 1] - vpage[2 * ks]) & -(lq >> 1));   // (a choice in registers, not of addresses)
+            const uint16_t* vp = vbase + (size_t)vpg[ks] * page_elems + voff;
     #pragma unroll
-            for (int dt = 0; dt < DT; ++dt) {
-                vreg[dt][ks] = make_uint4(0, 0, 0, 0);
-                if (kf < a.pos0) vreg[dt][ks] = *reinterpret_cast<const uint4*>(vbase + vaddr[ks] + dt * 16 * SB_KV_BLOCK);
-            }
+            for (int dt = 0; dt < DT; ++dt) vreg[dt][ks] = *reinterpret_cast<const uint4*>(vp + dt * 16 * SB_KV_BLOCK);
         }
-
     }
 
     __device__ __forceinline__ void compute(const AttnArgs& a, AttnLds<HD>& lds) {
@@ -403,70 +522,17 @@ struct AttnItem {
         uint16_t* const q_hi = lds.q_hi; uint16_t* const q_lo = lds.q_lo;
         uint16_t* const p_hi = lds.p_hi; uint16_t* const p_lo = lds.p_lo;
         float* const s_s = lds.s_s; float* const s_m = lds.s_m; float* const s_l = lds.s_l;
-        // ---- keys and values of the new rows: built from qkv, appended by query group 0
-        if (has_new) {
-    #pragma unroll
-            for (int t = 0; t < 2; ++t) {
-                const int key = key0 + wave * 32 + t * 16 + li;
-                if (key >= a.pos0 && key < n_total) {
-                    const float* kp = a.q + (size_t)(key - a.pos0) * a.qkv_rows + (size_t)(Hq + g) * HD;
-    #pragma unroll
-                    for (int ks = 0; ks < KSQ / 2; ++ks) {   // steps ks and ks + KSQ / 2: the two ends of the rotation's pairs
-                        float lo[8], hi[8];
-    #pragma unroll
-                        for (int e = 0; e < 8; ++e) {
-                            const int j = ks * 32 + lq * 8 + e;
-                            const float c = a.rope_cos[(size_t)key * HALF + j], sn = a.rope_sin[(size_t)key * HALF + j];
-                            const float x = kp[j], y = kp[j + HALF];
-                            lo[e] = x * c - y * sn;
-                            hi[e] = y * c + x * sn;
-                        }
-                        kreg[t][ks] = KvVec<uint16_t>::pack(lo);
-                        kreg[t][ks + KSQ / 2] = KvVec<uint16_t>::pack(hi);
-                    }
-                }
-            }
-    #pragma unroll
-            for (int ks = 0; ks < KSV; ++ks) {
-                const int kf = key0 + ks * 32 + lq * 8;
-                if (kf + 8 > a.pos0 && kf < n_total) {  // some of the 8 keys are new
-    #pragma unroll
-                    for (int dt = 0; dt < DT; ++dt) {
-                        const int d = (wave * DT + dt) * 16 + li;
-                        uint32_t w[4] = {vreg[dt][ks].x, vreg[dt][ks].y, vreg[dt][ks].z, vreg[dt][ks].w};
-    #pragma unroll
-                        for (int e = 0; e < 8; ++e) {
-                            const int key = kf + e;
-                            if (key >= a.pos0) {  // new row, or past the end: zero
-                                uint32_t h = 0;
-                                if (key < n_total) h = f2bf(a.q[(size_t)(key - a.pos0) * a.qkv_rows + (size_t)(Hq + Hkv + g) * HD + d]);
-                                w[e >> 1] = (e & 1) ? ((w[e >> 1] & 0x0000ffffu) | (h << 16)) : ((w[e >> 1] & 0xffff0000u) | h);
-                            }
-                        }
-                        vreg[dt][ks] = make_uint4(w[0], w[1], w[2], w[3]);
-                    }
-                }
-            }
-            // stored after the last of these loads: a store between them, which might alias, would make each a round
-            // trip of its own (the block with the new rows is what a short context waits for)
-            if (zb == 0) {
-    #pragma unroll
-                for (int t = 0; t < 2; ++t) {
-                    const int key = key0 + wave * 32 + t * 16 + li;
-                    if (key >= a.pos0 && key < n_total)
-    #pragma unroll
-                        for (int ks = 0; ks < KSQ; ++ks) *reinterpret_cast<uint4*>(kbase + kaddr[t] + ks * 32) = kreg[t][ks];
-                }
-    #pragma unroll
-                for (int ks = 0; ks < KSV; ++ks) {
-                    const int kf = key0 + ks * 32 + lq * 8;
-                    if (kf + 8 > a.pos0 && kf < n_total)
-    #pragma unroll
-                        for (int dt = 0; dt < DT; ++dt) *reinterpret_cast<uint4*>(vbase + vaddr[ks] + dt * 16 * SB_KV_BLOCK) = vreg[dt][ks];
-                }
-            }
-        }
+        // (the new rows lie where the probabilities come later)
+        uint16_t* const nk_s = lds.p_hi; uint16_t* const nv_s = lds.p_lo;
+        static_assert(SB_MAX_W * QS <= QG * PS, "the new rows fit");
+        if (has_new) nr.template store<uint16_t, QS>(a, nk_s, nv_s);
         for (int qg = qg_first; qg < qg_last; ++qg) {
+        // (the thread's number anew for every group: the addresses that follow from it, some hundred instructions and
+        // as many registers, would otherwise be worked out ahead of the loop, which most launches go round once)
+        int tid = threadIdx.x;
+        asm volatile("" : "+v"(tid));
+        const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+        const int li = lane & 15, lq = lane >> 4;
         const int q0 = qg * QG;
         const int nq = (nq_total - q0 < QG) ? (nq_total - q0) : QG;
         // ---- rotated queries -> LDS as hi + lo
@@ -483,6 +549,56 @@ struct AttnItem {
         }
         if (qg + 1 < qg_last) load_q(a, qg + 1);  // (in flight during this group's products)
         __syncthreads();
+        // ---- keys and values of the new rows take the place of what the cache held, appended by query group 0; values of
+        // slots past the last key become zero (0 x stale bits that read as NaN is not 0; their scores are masked)
+        if (has_new && qg == qg_first) {
+    #pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                const int key = key0 + wave * 32 + t * 16 + li;
+                const bool fresh = key >= a.pos0 && key < n_total;
+                const uint16_t* kp = nk_s + (fresh ? key - a.pos0 : 0) * QS + lq * 8;
+    #pragma unroll
+                for (int ks = 0; ks < KSQ; ++ks) {
+                    const uint4 v = *reinterpret_cast<const uint4*>(kp + ks * 32);
+                    kreg[t][ks] = pick(fresh, v, kreg[t][ks]);
+                }
+            }
+    #pragma unroll
+            for (int ks = 0; ks < KSV; ++ks) {
+                const int kf = key0 + ks * 32 + lq * 8;
+                if (key0 + ks * 32 + 32 <= a.pos0) continue;   // (block-uniform: no new row in this step)
+    #pragma unroll
+                for (int dt = 0; dt < DT; ++dt) {
+                    const uint16_t* vp = nv_s + (wave * DT + dt) * 16 + li;
+                    uint32_t w[4] = {vreg[dt][ks].x, vreg[dt][ks].y, vreg[dt][ks].z, vreg[dt][ks].w};
+    #pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        const int r = kf + e - a.pos0;   // new row, if any
+                        const uint32_t v = vp[(r >= 0 && r < a.M ? r : 0) * HD];
+                        const uint32_t h = r < a.M ? v : 0u;
+                        const uint32_t x = (e & 1) ? ((w[e >> 1] & 0x0000ffffu) | (h << 16)) : ((w[e >> 1] & 0xffff0000u) | h);
+                        w[e >> 1] = r >= 0 ? x : w[e >> 1];
+                    }
+                    vreg[dt][ks] = make_uint4(w[0], w[1], w[2], w[3]);
+                }
+            }
+            if (zb == 0) {
+    #pragma unroll
+                for (int t = 0; t < 2; ++t) {
+                    const int key = key0 + wave * 32 + t * 16 + li;
+                    if (key >= a.pos0 && key < n_total)
+    #pragma unroll
+                        for (int ks = 0; ks < KSQ; ++ks) *reinterpret_cast<uint4*>(kbase + (size_t)kpage[t] * page_elems + (uint32_t)((g * SB_KV_BLOCK + li) * HD + lq * 8) + ks * 32) = kreg[t][ks];
+                }
+    #pragma unroll
+                for (int ks = 0; ks < KSV; ++ks) {
+                    const int kf = key0 + ks * 32 + lq * 8;
+                    if (kf + 8 > a.pos0 && kf < n_total)
+    #pragma unroll
+                        for (int dt = 0; dt < DT; ++dt) *reinterpret_cast<uint4*>(vbase + (size_t)vpg[ks] * page_elems + (uint32_t)((g * HD + (wave * DT + dt) * 16 + li) * SB_KV_BLOCK + (lq & 1) * 8)) = vreg[dt][ks];
+                }
+            }
+        }
 
         // ---- scores of this wave's 32 keys against the 16 query rows
         {
@@ -583,7 +699,7 @@ __device__ __forceinline__ void attn_mfma_body(const AttnArgs& a, const int g, c
 
 template <int HD>
 __global__ __launch_bounds__(256, 3) void attn_mfma_kernel(AttnArgs a) {
-    attn_mfma_body<HD>(a, blockIdx.x, blockIdx.y, blockIdx.z);
+    attn_mfma_body<HD>(a, blockIdx.x, gridDim.y - 1 - blockIdx.y, blockIdx.z);   // (the chunk with the new rows first)
 }
 
 // Several sequences' passes in one launch (batch > 1): grid.z = sequence x query-group slice, grid.y
@@ -597,7 +713,7 @@ __global__ __launch_bounds__(256, 3) void attn_mfma_batch_kernel(AttnBatchArgs a
     const int n_chunks = (a.pos0 + a.M + 127) / 128;
     const int n_qg = (a.M * (a.n_heads / a.kv.n_kv_heads) + 15) / 16;
     if ((int)blockIdx.y >= n_chunks || zb * a.qg_per_block >= n_qg) return;
-    attn_mfma_body<HD>(a, blockIdx.x, blockIdx.y, zb);
+    attn_mfma_body<HD>(a, blockIdx.x, n_chunks - 1 - blockIdx.y, zb);
 }
 
 // Second stage: one block per (row, query head) merges that row's chunk partials
@@ -725,21 +841,28 @@ hipError_t launch_attention(const AttnArgs& a, hipStream_t st) {
     dim3 grid1(a.kv.n_kv_heads, n_chunks, n_qg);
     dim3 mgrid(a.n_heads, a.M);
     if (a.kv.kv_dtype == SB_BF16) {
+        if (a.M > SB_MAX_W) return hipErrorInvalidValue;   // (more rows: launch_prefill_attention)
         if (hd == 128) { attn_mfma_kernel<128><<<grid, 256, 0, st>>>(b); if (!b.direct) attn_merge_kernel<128, 128><<<mgrid, 256, 0, st>>>(a); }
         else { attn_mfma_kernel<64><<<grid, 256, 0, st>>>(b); if (!b.direct) attn_merge_kernel<64, 128><<<mgrid, 256, 0, st>>>(a); }
     } else {
-        // Four blocks per CU where that saves a round of blocks over the chip, else three, whose blocks are faster.  32 heads,
-        // one row, three / four: 768 blocks 20.8 / 21.0 us (1500 keys, head_dim 128), 864 27.2 / 23.8, 1504 34.7 / 36.9 (6000 keys,
-        // head_dim 64), 4512 89.5 / 85.6 (9000 keys, head_dim 128).
+        // Passes of more than SB_MAX_W rows: four blocks per CU where that saves a round of blocks over the chip, else three, whose
+        // blocks are faster.  Decode passes: four always.
         const int64_t blocks = (int64_t)grid1.x * grid1.y * grid1.z;
         const bool four = (blocks + 4 * 256 - 1) / (4 * 256) < (blocks + 3 * 256 - 1) / (3 * 256);
+        const auto first = [&](auto hd_c) {
+            constexpr int HD = decltype(hd_c)::value;
+            if (a.M > SB_MAX_W) {
+                if (four) attn_kernel<float, HD, 4, true><<<grid1, 256, 0, st>>>(b);
+                else attn_kernel<float, HD, 3, true><<<grid1, 256, 0, st>>>(b);
+            } else {
+                attn_kernel<float, HD, 4, false><<<grid1, 256, 0, st>>>(b);
+            }
+        };
         if (hd == 128) {
-            if (four) attn_kernel<float, 128, 4><<<grid1, 256, 0, st>>>(b);
-            else attn_kernel<float, 128, 3><<<grid1, 256, 0, st>>>(b);
+            first(std::integral_constant<int, 128>{});
             if (!b.direct) attn_merge_kernel<128, 64><<<mgrid, 256, 0, st>>>(a);
         } else {
-            if (four) attn_kernel<float, 64, 4><<<grid1, 256, 0, st>>>(b);
-            else attn_kernel<float, 64, 3><<<grid1, 256, 0, st>>>(b);
+            first(std::integral_constant<int, 64>{});
             if (!b.direct) attn_merge_kernel<64, 128><<<mgrid, 256, 0, st>>>(a);
         }
     }
