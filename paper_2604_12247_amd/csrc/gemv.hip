@@ -302,7 +302,7 @@ hipError_t launch_repack(const void* W, void* P, int32_t N, int32_t K, hipStream
 // bytes through L2 and the same registers (the lanes of a row's high and low column load four of its eight floats each
 // and exchange parts), some 80 vector instructions per k block, and no launch before this one.
 // [6144 x 4096], one row: 13.6 -> 10.6 us with the launch it saves, [27648 x 5120], six rows: 49.4 -> 48.5.
-template <int RT, int EPI, int WPB, bool PACKED, bool RAW>
+template <int RT, int EPI, int WPB, int DEPTH, bool PACKED, bool RAW>
 __global__ __launch_bounds__(64 * WPB) void gemv_mfma_kernel(GemvArgs a) {
     constexpr int NT = 64 * WPB;
     static_assert(NT >= RT * 128, "the tails take one element per thread");
@@ -344,9 +344,6 @@ __global__ __launch_bounds__(64 * WPB) void gemv_mfma_kernel(GemvArgs a) {
 
     // Ring of DEPTH register buffers, DEPTH - 1 k blocks in flight per wave.  The
     // stage loop is fully unrolled, so every buffer index is a compile-time constant.
-    // chosen by measurement: three buffers, but two for the eight-wave blocks of the
-    // narrow projections (a deeper ring there only costs occupancy)
-    constexpr int DEPTH = (RT == 1 && WPB == 8) ? 2 : 3;
     uint4 wbuf[DEPTH][RT][4], bbuf[DEPTH][4];
     // k block index is clamped instead of tested: loads past the end re-read the last
     // block (unused), which keeps the steady-state loop free of bounds tests.
@@ -488,11 +485,31 @@ __global__ __launch_bounds__(64 * WPB) void gemv_mfma_kernel(GemvArgs a) {
     }
 }
 
-// Row tiles and waves per block: fixed by the operand shape alone (never by M).
-// Few output rows -> one tile per block and eight waves splitting K, so that
-// enough loads are in flight; many rows -> two tiles sharing one B operand.
-static int mfma_row_tiles(int32_t N) { return N >= 15000 ? 2 : 1; }  // (measured: [15360 x 5120] gains 13 % at six rows with two, [12288 x 4096] loses 5 %)
-static int mfma_waves(int32_t N) { return N <= 4096 ? 8 : 4; }  // (measured: [6144 x 4096] is 9-12 % faster with four waves and the deeper ring, [5120 x K] the same with either)
+// Row tiles and waves of a block.  The waves (the order in which a row's products are added) are fixed by the operand shape alone, never
+// by the rows; the tiles also by how many rows there are.  A CU takes in about 39 GB/s whatever it has in flight, against the 28
+// that are its share of the card's rate, so what counts first is that no CU has more tiles than the others (256 CUs):
+//   up to 256 tiles   a tile per block, eight waves splitting K, a ring of two (a deeper one only costs occupancy)
+//   up to 512         a CU with two tiles sets the time; as one block they read the rows once, not twice.  K > 4096: eight waves,
+//                     [5120 x 13824] at one / four / eight rows 29.8 / 33.7 / 40.8 -> 26.2 / 29.9 / 31.4 us, [5120 x 5120] 12.5 / 14.7 / 17.4
+//                     -> 10.5 / 12.5 / 13.3, [8192 x 5120] 14.8 / 17.1 / 20.5 -> 14.2 / 15.6 / 16.6.  K <= 4096: four waves, too short for
+//                     more, and two tiles from three rows on, [6144 x 4096] with one tile 11.5 / 11.6 / 13.9, two 11.6 / 11.0 / 11.7,
+//                     [8192 x 4096], one and four rows, 12.9 / 13.4 and 13.6 / 13.5
+//   up to 768         a tile per block of four waves, three blocks per CU ([12288 x 4096], four rows: 18.6, two tiles 23.8)
+//   more              two tiles (row-major weights and few rows: one, [13312 x 4096] 24.2 and 25.9); K > 4096: eight waves, [13824 x 13824]
+//                     64.9 / 69.7 / 85.2 -> 60.7 / 63.0 / 69.4, [15360 x 5120] 26.4 / 27.5 / 29.7 -> 25.7 / 26.2 / 28.2; [14336 x 4096], four
+//                     rows, one tile 22.8, two 21.0, with eight waves 23.6
+// Heads keep four waves and gate / up their pair of tiles: [32000 x 4096] 46.7, with eight waves 49.6; [2 * 11008 x 4096] 30.3 and 31.9.
+struct MfmaShape { int rt, wpb; };
+static MfmaShape mfma_shape(const GemvArgs& a) {
+    const int rows = a.row_mask ? __builtin_popcount(a.row_mask) : a.M;
+    const bool few = rows < 3, long_k = a.K > 4096;
+    if (a.N <= 4096) return {1, 8};
+    if (a.N <= 8192) return {long_k || !few ? 2 : 1, long_k ? 8 : 4};
+    if (a.N <= 12288) return {1, 4};
+    return {long_k || a.packed || !few ? 2 : 1, long_k ? 8 : 4};
+}
+static int mfma_row_tiles(int32_t N) { return N >= 15000 ? 2 : 1; }   // (heads)
+static int mfma_waves(int32_t N) { return N <= 4096 ? 8 : 4; }
 int head_blocks_mfma(int32_t N) { return (N + 16 * mfma_row_tiles(N) - 1) / (16 * mfma_row_tiles(N)); }
 
 template <int EPI, bool PACKED, bool RAW = false>
@@ -500,12 +517,17 @@ static void launch_gemv_mfma_e(const GemvArgs& a, hipStream_t st) {
     if constexpr (!RAW && EPI != EPI_RESID)
         if (!a.xs) return launch_gemv_mfma_e<EPI, PACKED, true>(a, st);
     if constexpr (EPI == EPI_SWIGLU) {
-        gemv_mfma_kernel<2, EPI, 4, PACKED, RAW><<<a.N / 16, 256, 0, st>>>(a);
+        gemv_mfma_kernel<2, EPI, 4, 3, PACKED, RAW><<<a.N / 16, 256, 0, st>>>(a);
     } else {
-        const int rt = mfma_row_tiles(a.N), wpb = mfma_waves(a.N);
-        if (rt == 2) gemv_mfma_kernel<2, EPI, 4, PACKED, RAW><<<(a.N + 31) / 32, 256, 0, st>>>(a);
-        else if (wpb == 8) gemv_mfma_kernel<1, EPI, 8, PACKED, RAW><<<a.N / 16, 512, 0, st>>>(a);
-        else gemv_mfma_kernel<1, EPI, 4, PACKED, RAW><<<a.N / 16, 256, 0, st>>>(a);
+        const MfmaShape sh = EPI == EPI_HEAD ? MfmaShape{mfma_row_tiles(a.N), mfma_waves(a.N)} : mfma_shape(a);
+        const int one = a.N / 16, two = (a.N + 31) / 32;
+        if (sh.rt == 1 && sh.wpb == 8) gemv_mfma_kernel<1, EPI, 8, 2, PACKED, RAW><<<one, 512, 0, st>>>(a);
+        else if (sh.rt == 1) gemv_mfma_kernel<1, EPI, 4, 3, PACKED, RAW><<<one, 256, 0, st>>>(a);
+        else if (sh.wpb == 4) gemv_mfma_kernel<2, EPI, 4, 3, PACKED, RAW><<<two, 256, 0, st>>>(a);
+        else if constexpr (EPI != EPI_HEAD) {
+            if (a.N <= 8192) gemv_mfma_kernel<2, EPI, 8, 3, PACKED, RAW><<<two, 512, 0, st>>>(a);
+            else gemv_mfma_kernel<2, EPI, 8, 2, PACKED, RAW><<<two, 512, 0, st>>>(a);
+        }
     }
 }
 

@@ -144,6 +144,25 @@ def test_prompt_pass_gemm_heights(T, N, K, M):
     assert float((y - ref).abs().max()) <= 3e-5 * float(ref.abs().max())
 
 
+# either side of the lines between the block shapes (4096, 8192 and 12288 output rows, K = 4096, two and three rows), an odd number of tiles
+@pytest.mark.parametrize("N,K", [(4112, 4096), (4112, 4224), (8176, 256), (8192, 4224), (8208, 4224), (12288, 384), (12304, 384), (12304, 4224)])
+@pytest.mark.parametrize("kernel", ["mfma", "mfma_packed"])
+def test_gemv_mfma_block_shapes(T, kernel, N, K):
+    import paper_2604_12247_amd as sb
+    k = {"mfma": sb.PROJ_MFMA, "mfma_packed": sb.PROJ_MFMA_PACKED}[kernel]
+    g = np.random.default_rng(N + K)
+    W = _rand_w(g, N, K, True)
+    x = g.standard_normal((8, K)).astype(np.float32)
+    Wd = _dev(T, W)
+    if kernel == "mfma_packed":
+        Wd = sb.op_repack(Wd)
+    y8 = sb.op_gemv(Wd, _dev(T, x), k).cpu().numpy()
+    ref = _oracle_rows(W, x)
+    assert np.max(np.abs(y8 - ref)) <= 3e-5 * np.max(np.abs(ref))     # 16-bit activation parts, as in test_gemv_mfma
+    for M in (1, 2, 3, 7):
+        assert np.array_equal(sb.op_gemv(Wd, _dev(T, x[:M]), k).cpu().numpy(), y8[:M]), M
+
+
 GATE_UP_SHAPES = [(64, 256, 3), (11008, 4096, 1), (11008, 4096, 6), (14336, 4096, 8)]
 GATE_UP_CASES = [(k, *c) for k in ("valu", "mfma", "mfma_packed") for c in GATE_UP_SHAPES] + [("valu", 1000, 512, 5)]
 
