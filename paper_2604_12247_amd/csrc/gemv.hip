@@ -197,7 +197,7 @@ __global__ __launch_bounds__(256) void gemv_valu_kernel(GemvArgs a) {
         for (int r = 0; r < R; ++r)
 #pragma unroll
             for (int m = 0; m < M; ++m)
-                if (lane == r * M + m) zs[wave * 4 + r][m] = acc[r][m];
+                if (lane == r * M + m) zs[wave * R + r][m] = acc[r][m];
         __syncthreads();
         head_partial<16>(a.head, zs, (1u << M) - 1u, n0, N, gridDim.x);
     }
@@ -305,7 +305,7 @@ hipError_t launch_repack(const void* W, void* P, int32_t N, int32_t K, hipStream
 template <int RT, int EPI, int WPB, int DEPTH, bool PACKED, bool RAW>
 __global__ __launch_bounds__(64 * WPB) void gemv_mfma_kernel(GemvArgs a) {
     constexpr int NT = 64 * WPB;
-    static_assert(NT >= RT * 128, "the tails take one element per thread");
+    static_assert(NT >= (EPI == EPI_SWIGLU ? RT / 2 : RT) * 128, "the tails take one element per thread");
     __shared__ __attribute__((aligned(16))) float red[WPB][RT][64][4];
     __shared__ float cs[RT][16][17];
     __shared__ float zs[16 * RT][SB_MAX_W];
@@ -315,12 +315,13 @@ __global__ __launch_bounds__(64 * WPB) void gemv_mfma_kernel(GemvArgs a) {
     const uint16_t* __restrict__ W = reinterpret_cast<const uint16_t*>(a.W);
     const int N = a.N, K = a.K, M = a.M;
     const int KB = K >> 7;  // k blocks of 128
-    const int n0 = blockIdx.x * ((EPI == EPI_SWIGLU) ? 16 : 16 * RT);
+    constexpr int OT = (EPI == EPI_SWIGLU) ? RT / 2 : RT;   // 16-output tiles of the block (gate / up: the gate tiles, then their up tiles)
+    const int n0 = blockIdx.x * 16 * OT;
 
     const uint16_t* wp[RT];
 #pragma unroll
     for (int t = 0; t < RT; ++t) {
-        int row0 = (EPI == EPI_SWIGLU) ? (t == 0 ? n0 : N + n0) : (n0 + t * 16);  // first row of the tile
+        int row0 = (EPI == EPI_SWIGLU) ? (t < OT ? n0 + t * 16 : N + n0 + (t - OT) * 16) : (n0 + t * 16);  // first row of the tile
         int total = (EPI == EPI_SWIGLU) ? 2 * N : N;
         if (PACKED) {
             if (row0 > total - 16) row0 = total - 16;
@@ -464,18 +465,18 @@ __global__ __launch_bounds__(64 * WPB) void gemv_mfma_kernel(GemvArgs a) {
             }
         }
     } else if (EPI == EPI_SWIGLU) {
-        if (tid < 128) {
-            int m = tid >> 4, i = tid & 15;
-            int n = n0 + i;
+        if (tid < OT * 128) {
+            int t = tid >> 7, m = (tid >> 4) & 7, i = tid & 15;
+            int n = n0 + t * 16 + i;
             if (((rows >> m) & 1u) && n < N) {
-                float g = (cs[0][i][m] + cs[0][i][m + 8]) * s_inv[m];
-                float u = (cs[1][i][m] + cs[1][i][m + 8]) * s_inv[m];
+                float g = (cs[t][i][m] + cs[t][i][m + 8]) * s_inv[m];
+                float u = (cs[OT + t][i][m] + cs[OT + t][i][m + 8]) * s_inv[m];
                 float v = silu_mul(g, u);
                 if (a.y) a.y[(size_t)m * a.ldy + n] = v;
                 if (a.ys) split_store(a.ys, a.ldy, m, n, v);
             }
         }
-    } else {  // EPI_HEAD
+    } else if constexpr (EPI == EPI_HEAD) {
         for (int e = tid; e < RT * 16 * 8; e += NT) {
             int t = e >> 7, m = (e >> 4) & 7, i = e & 15;
             zs[t * 16 + i][m] = (cs[t][i][m] + cs[t][i][m + 8]) * (((rows >> m) & 1u) ? s_inv[m] : 0.f);
@@ -500,9 +501,9 @@ __global__ __launch_bounds__(64 * WPB) void gemv_mfma_kernel(GemvArgs a) {
 //                     rows, one tile 22.8, two 21.0, with eight waves 23.6
 // Heads keep four waves and gate / up their pair of tiles: [32000 x 4096] 46.7, with eight waves 49.6; [2 * 11008 x 4096] 30.3 and 31.9.
 struct MfmaShape { int rt, wpb; };
+static int mfma_rows(const GemvArgs& a) { return a.row_mask ? __builtin_popcount(a.row_mask) : a.M; }
 static MfmaShape mfma_shape(const GemvArgs& a) {
-    const int rows = a.row_mask ? __builtin_popcount(a.row_mask) : a.M;
-    const bool few = rows < 3, long_k = a.K > 4096;
+    const bool few = mfma_rows(a) < 3, long_k = a.K > 4096;
     if (a.N <= 4096) return {1, 8};
     if (a.N <= 8192) return {long_k || !few ? 2 : 1, long_k ? 8 : 4};
     if (a.N <= 12288) return {1, 4};
@@ -517,7 +518,14 @@ static void launch_gemv_mfma_e(const GemvArgs& a, hipStream_t st) {
     if constexpr (!RAW && EPI != EPI_RESID)
         if (!a.xs) return launch_gemv_mfma_e<EPI, PACKED, true>(a, st);
     if constexpr (EPI == EPI_SWIGLU) {
-        gemv_mfma_kernel<2, EPI, 4, 3, PACKED, RAW><<<a.N / 16, 256, 0, st>>>(a);
+        const int pairs = a.N / 16;
+        // Four tiles (two pairs) read the rows half as often; two blocks of them fit on a CU, so up to 1024 pairs, and only where
+        // one pair per block would give a CU more than three and a block is long enough.  Two / four tiles: [2 * 13824 x 5120] at
+        // three / six / eight rows 49.5 / 50.9 / 52.8 and 47.6 / 48.6 / 49.5 us, one row 45.5 and 46.4, [2 * 16384 x 5120], eight rows
+        // 56.5 and 54.3, [2 * 13824 x 13824], six 130.8 and 118.9; [2 * 12304 x 5120], six 47.5 and 48.0, [2 * 14336 x 4096], three
+        // 38.9 and 39.5, [2 * 11008 x 4096], six 30.6 and 37.8; row-major [2 * 14336 x 4096], three 47.4 and 50.4.
+        if (a.packed && a.K > 4096 && mfma_rows(a) >= 3 && pairs > 816 && pairs <= 1024) gemv_mfma_kernel<4, EPI, 4, 2, PACKED, RAW><<<(pairs + 1) / 2, 256, 0, st>>>(a);
+        else gemv_mfma_kernel<2, EPI, 4, 3, PACKED, RAW><<<pairs, 256, 0, st>>>(a);
     } else {
         const MfmaShape sh = EPI == EPI_HEAD ? MfmaShape{mfma_row_tiles(a.N), mfma_waves(a.N)} : mfma_shape(a);
         const int one = a.N / 16, two = (a.N + 31) / 32;

@@ -186,6 +186,22 @@ def test_gate_up_swiglu(T, kernel, N, K, M):
         assert np.max(np.abs(u[m] - ref)) <= 1e-4 * scale, (m, np.max(np.abs(u[m] - ref)), scale)
 
 
+# one and two pairs of tiles per block: 816 pairs, 817 (the last block owns one), 1024 and 1025, K on either side of 4096
+@pytest.mark.parametrize("N,K", [(13056, 4224), (13072, 4224), (13072, 4096), (16384, 4224), (16400, 4224)])
+def test_gate_up_pairs_per_block(T, N, K):
+    import paper_2604_12247_amd as sb
+    g = np.random.default_rng(N + K)
+    W = _rand_w(g, 2 * N, K, True, std=0.03)
+    x = g.standard_normal((8, K)).astype(np.float32)
+    Wp = sb.op_repack(_dev(T, W))
+    u8 = sb.op_gate_up(Wp, _dev(T, x), sb.PROJ_MFMA_PACKED).cpu().numpy()
+    for m in (0, 7):
+        ref = orc.swiglu(orc.matvec(W, x[m].astype(np.float64)))
+        assert np.max(np.abs(u8[m] - ref)) <= 1e-4 * np.max(np.abs(ref)), m
+    for M in (1, 2, 3, 5):
+        assert np.array_equal(sb.op_gate_up(Wp, _dev(T, x[:M]), sb.PROJ_MFMA_PACKED).cpu().numpy(), u8[:M]), M
+
+
 @pytest.mark.parametrize("kernel", ["valu", "mfma", "mfma_packed"])
 def test_gemv_row_result_does_not_depend_on_m(T, kernel):
     """A row's output is bit-identical whether it is computed alone or with others."""
