@@ -437,9 +437,8 @@ hipError_t launch_prefill_gemm(const GemmArgs& a_, hipStream_t st) {
 // Partial sums that row block b received: thread blocks first..last of the plan.
 struct GemmSplitMap { int rows_per_block, KB, q, pass_rows; };
 __device__ __forceinline__ int splits_of(const GemmSplitMap& mp, int n) {
-    const int b = n / mp.rows_per_block;
-    const int first = (int)(((long)b * mp.KB) / mp.q), last = (int)(((long)(b + 1) * mp.KB - 1) / mp.q);
-    return last - first + 1;
+    const uint32_t b = (uint32_t)n / (uint32_t)mp.rows_per_block;   // (pairs are checked on the host to fit an int)
+    return (int)(((b + 1) * mp.KB - 1) / (uint32_t)mp.q - b * mp.KB / (uint32_t)mp.q) + 1;
 }
 
 // Partial sums of four neighbouring elements, added in slot order; eight loads in flight at a time.
@@ -463,6 +462,11 @@ __global__ __launch_bounds__(256) void prefill_epilogue_kernel(GemmEpiArgs a, Ge
     const int m = blockIdx.y * 4 + (threadIdx.x >> 6);  // row of the super-pass
     const int n = blockIdx.x * 256 + lane * 4;
     if (m >= a.M) return;
+    const bool fused = (EPI == EPI_SWIGLU || EPI == EPI_STORE) && a.fused;
+    const int sp = n < a.N ? splits_of(mp, n) : 0;
+    // (row blocks that the GEMM finished: a whole wave of them leaves before it reads anything; [28672 x 4096] at 1999 rows, where they are
+    // six in seven, took 46 us with every wave adding up its row's sums of squares first, now 29)
+    if (fused && __builtin_amdgcn_ballot_w64(sp > 1) == 0) return;
     float inv = 1.0f;
     if (a.ssq_in) {  // (added in index order; sixteen loads in flight at a time)
         float t = 0.f;
@@ -479,9 +483,8 @@ __global__ __launch_bounds__(256) void prefill_epilogue_kernel(GemmEpiArgs a, Ge
     const float* p = a.part + ((size_t)(m / mp.pass_rows) * a.S * mp.pass_rows + m % mp.pass_rows) * a.rows;
     float sq = 0.f;
     if (n < a.N) {
-        if (EPI == EPI_SWIGLU && a.fused) {
+        if (EPI == EPI_SWIGLU && fused) {
             // (a row block holds gate and up tiles side by side; one partial = finished by the GEMM)
-            const int sp = splits_of(mp, n);
             if (sp > 1) {
                 const float4 g = sum_splits4(p + n, plane, sp);
                 const float4 u = sum_splits4(p + a.N + n, plane, sp);
@@ -490,15 +493,15 @@ __global__ __launch_bounds__(256) void prefill_epilogue_kernel(GemmEpiArgs a, Ge
                 split_store4(a.ys, a.N, a.plane_rows, m, n, v);
             }
         } else if (EPI == EPI_SWIGLU) {
-            const float4 g = sum_splits4(p + n, plane, splits_of(mp, n));
+            const float4 g = sum_splits4(p + n, plane, sp);
             const float4 u = sum_splits4(p + a.N + n, plane, splits_of(mp, a.N + n));
             const float4 v = make_float4(silu_mul(g.x * inv, u.x * inv), silu_mul(g.y * inv, u.y * inv),
                                          silu_mul(g.z * inv, u.z * inv), silu_mul(g.w * inv, u.w * inv));
             split_store4(a.ys, a.N, a.plane_rows, m, n, v);
-        } else if (EPI == EPI_STORE && a.fused && splits_of(mp, n) == 1) {
+        } else if (EPI == EPI_STORE && fused && sp == 1) {
             // (finished by the GEMM)
         } else {
-            float4 v = sum_splits4(p + n, plane, splits_of(mp, n));
+            float4 v = sum_splits4(p + n, plane, sp);
             v.x *= inv; v.y *= inv; v.z *= inv; v.w *= inv;
             float4* yp = reinterpret_cast<float4*>(a.y + (size_t)m * a.ldy + n);
             if (EPI == EPI_RESID) {
