@@ -972,7 +972,8 @@ __global__ __launch_bounds__(256, 2) void prefill_attn_kernel(AttnArgs a) {
 // registers, a tile ahead: the next tile's keys are requested when this tile's scores are done, its values
 // when this tile's products are.  grid (n_kv_heads, ceil(M G / 32)).  What bounds it: the chain page
 // table -> keys -> scores -> products of a wave's few tiles.  32 heads x 128: 512 rows 15.5 us, 64 rows 6.5 us;
-// as blocks of 64 queries that walk all keys 23.7 and 8.4 us.
+// as blocks of 64 queries that walk all keys 23.7 and 8.4 us.  With the queries loaded without conditions, and the append launch:
+// 512 rows 26.2 -> 22.7 us, 64 rows 11.5 -> 9.1, 100 rows of 8 heads x 64 behind 2000 19.7 -> 17.7.
 template <int HD, int W>
 __global__ __launch_bounds__(64 * W, W == 4 ? 2 : 1) void prefill_attn_split_kernel(AttnArgs a) {
     constexpr int KS = HD / 16, DT = HD / 32, SLAB = SB_KV_BLOCK * HD, NS = DT * 4;
@@ -1035,30 +1036,40 @@ __global__ __launch_bounds__(64 * W, W == 4 ? 2 : 1) void prefill_attn_split_ker
         const float* cp = a.rope_cos + (size_t)(a.pos0 + qr.row) * HALF;
         const float* sp = a.rope_sin + (size_t)(a.pos0 + qr.row) * HALF;
         const float c2 = 1.4426950408889634f / sqrtf((float)HD);   // scores in units of log 2
+        // (all loads first, and a query past the end is one of the block's that is blanked afterwards: no load under a condition,
+        // which would be a wait each)
+        constexpr int NQ = HALF / (4 * TPQ);
+        const uint32_t keep = qr.valid ? 0xffffffffu : 0u;
+        float4 x[NQ], y[NQ], c[NQ], sn[NQ];
+        if (r < 32) {
 #pragma unroll
-        for (int i = 0; i < HALF / (4 * TPQ); ++i) {
-            if (r >= 32) break;
-            const int j = (i * TPQ + tid % TPQ) * 4;
-            const float4 x = *reinterpret_cast<const float4*>(qp + j), y = *reinterpret_cast<const float4*>(qp + j + HALF);
-            const float4 c = *reinterpret_cast<const float4*>(cp + j), sn = *reinterpret_cast<const float4*>(sp + j);
-            const float xs4[4] = {x.x, x.y, x.z, x.w}, ys4[4] = {y.x, y.y, y.z, y.w};
-            const float cs4[4] = {c.x, c.y, c.z, c.w}, sn4[4] = {sn.x, sn.y, sn.z, sn.w};
-            float u[2][4];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                u[0][e] = qr.valid ? (xs4[e] * cs4[e] - ys4[e] * sn4[e]) * c2 : 0.f;
-                u[1][e] = qr.valid ? (ys4[e] * cs4[e] + xs4[e] * sn4[e]) * c2 : 0.f;
+            for (int i = 0; i < NQ; ++i) {
+                const int j = (i * TPQ + tid % TPQ) * 4;
+                x[i] = *reinterpret_cast<const float4*>(qp + j); y[i] = *reinterpret_cast<const float4*>(qp + j + HALF);
+                c[i] = *reinterpret_cast<const float4*>(cp + j); sn[i] = *reinterpret_cast<const float4*>(sp + j);
             }
 #pragma unroll
-            for (int k = 0; k < 2; ++k) {
-                uint32_t h[2], l[2];
+            for (int i = 0; i < NQ; ++i) {
+                const int j = (i * TPQ + tid % TPQ) * 4;
+                const float xs4[4] = {x[i].x, x[i].y, x[i].z, x[i].w}, ys4[4] = {y[i].x, y[i].y, y[i].z, y[i].w};
+                const float cs4[4] = {c[i].x, c[i].y, c[i].z, c[i].w}, sn4[4] = {sn[i].x, sn[i].y, sn[i].z, sn[i].w};
+                float u[2][4];
 #pragma unroll
-                for (int e = 0; e < 2; ++e) {
-                    h[e] = pack_bf16(u[k][2 * e], u[k][2 * e + 1]);
-                    l[e] = pack_bf16(u[k][2 * e] - __uint_as_float(h[e] << 16), u[k][2 * e + 1] - __uint_as_float(h[e] & 0xffff0000u));
+                for (int e = 0; e < 4; ++e) {
+                    u[0][e] = (xs4[e] * cs4[e] - ys4[e] * sn4[e]) * c2;
+                    u[1][e] = (ys4[e] * cs4[e] + xs4[e] * sn4[e]) * c2;
                 }
-                *reinterpret_cast<uint2*>(q_hi + r * QS + j + k * HALF) = make_uint2(h[0], h[1]);
-                *reinterpret_cast<uint2*>(q_lo + r * QS + j + k * HALF) = make_uint2(l[0], l[1]);
+#pragma unroll
+                for (int k = 0; k < 2; ++k) {
+                    uint32_t h[2], l[2];
+#pragma unroll
+                    for (int e = 0; e < 2; ++e) {
+                        h[e] = pack_bf16(u[k][2 * e], u[k][2 * e + 1]);
+                        l[e] = pack_bf16(u[k][2 * e] - __uint_as_float(h[e] << 16), u[k][2 * e + 1] - __uint_as_float(h[e] & 0xffff0000u));
+                    }
+                    *reinterpret_cast<uint2*>(q_hi + r * QS + j + k * HALF) = make_uint2(h[0] & keep, h[1] & keep);
+                    *reinterpret_cast<uint2*>(q_lo + r * QS + j + k * HALF) = make_uint2(l[0] & keep, l[1] & keep);
+                }
             }
         }
         __syncthreads();
