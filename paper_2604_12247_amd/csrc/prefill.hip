@@ -251,12 +251,14 @@ __device__ __forceinline__ void gemm_flush(f32x4 (&acc)[RT][CT], const GemmArgs&
 // throughout, took 819 us there against 739; multiplying all 128 rows of a pass whatever it holds took 82 us on
 // [27648 x 5120] at 45 rows against 55 (5.1 TB/s) with only the live column tiles.  32 x 32 x 16 MFMAs, which the
 // MFMA-only loop prefers by 4 %, were 5 % slower here.
-template <int RT, int CT, int D, int PD, bool STREAM, bool SWI>
+template <int RT, int CT, int D, int PD, bool STREAM, bool SWI, bool WHOLE>
 __global__ __launch_bounds__(64 * WPB) void prefill_gemm_kernel(GemmArgs a, int q, int xa) {
     constexpr int STAGE = stage_bytes(CT), UB = D / 4;   // UB: k blocks per turn of the ring
     // staging units requested at the start of a k block; the rest half way
     constexpr int H0 = CT > 4 ? (CT + 1) / 2 : CT, H1 = CT > H0 ? CT - H0 : 1;
     static_assert(D == 4 || D == 8, "the ring turns over in whole k blocks");
+    static_assert(!WHOLE || D == 8, "one k block multiplied, the next requested");
+    constexpr int AHEAD = WHOLE ? 4 : D - 1;   // steps requested before the first is multiplied
     static_assert(!SWI || RT % 2 == 0, "gate and up tiles in one wave");
     extern __shared__ __attribute__((aligned(16))) unsigned char bt[];  // [2][STAGE], then PM floats: the rows' RMSNorm scales (fused tails)
     const int tid = threadIdx.x, lane = tid & 63;
@@ -298,7 +300,7 @@ __global__ __launch_bounds__(64 * WPB) void prefill_gemm_kernel(GemmArgs a, int 
         u32x4 br[CT];
         sg.template load<0, CT>(br, kb);
 #pragma unroll
-        for (int s = 0; s < D - 1; ++s) {
+        for (int s = 0; s < AHEAD; ++s) {
             gemm_load_a<RT, STREAM, SWI>(ar[s], w, s & 3, lane_off);
             if ((s & 3) == 3) w.next(c, a.Wp);
         }
@@ -339,8 +341,16 @@ __global__ __launch_bounds__(64 * WPB) void prefill_gemm_kernel(GemmArgs a, int 
                 sg.template store<0, H0>(dst, br0);
                 sg.template load<H0, CT>(br1, kbn);
             }
-            gemm_load_a<RT, STREAM, SWI>(ar[(P + u + D - 1) % D], w, (u + 3) & 3, lane_off);
-            if (u == 0) w.next(c, a.Wp);
+            if (WHOLE) {
+                if (u == 0) {
+#pragma unroll
+                    for (int s = 0; s < 4; ++s) gemm_load_a<RT, STREAM, SWI>(ar[(P + 4 + s) % D], w, s, lane_off);
+                    w.next(c, a.Wp);
+                }
+            } else {
+                gemm_load_a<RT, STREAM, SWI>(ar[(P + u + D - 1) % D], w, (u + 3) & 3, lane_off);
+                if (u == 0) w.next(c, a.Wp);
+            }
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int n = u * CT; n < (u + 1) * CT; ++n) {
@@ -371,28 +381,34 @@ __global__ __launch_bounds__(64 * WPB) void prefill_gemm_kernel(GemmArgs a, int 
     if constexpr (UB > 1) if (it < c.it1) k_block(std::integral_constant<int, 0>{}, it);
 }
 
-template <int RT, int CT, int D, int PD, bool STREAM, bool SWI>
+template <int RT, int CT, int D, int PD, bool STREAM, bool SWI, bool WHOLE>
 static hipError_t launch_gemm_t(const GemmArgs& a, int q, int xa, int grid, hipStream_t st) {
     constexpr int LDS = lds_bytes(CT);
     static bool attr_set = false;
     if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&prefill_gemm_kernel<RT, CT, D, PD, STREAM, SWI>),
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&prefill_gemm_kernel<RT, CT, D, PD, STREAM, SWI, WHOLE>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
         if (e != hipSuccess) return e;
         attr_set = true;
     }
-    prefill_gemm_kernel<RT, CT, D, PD, STREAM, SWI><<<grid, 64 * WPB, LDS, st>>>(a, q, xa);
+    prefill_gemm_kernel<RT, CT, D, PD, STREAM, SWI, WHOLE><<<grid, 64 * WPB, LDS, st>>>(a, q, xa);
     return hipGetLastError();
 }
 // D and PD by measurement (45 and 128 rows, 7B to 13B shapes): one tile per wave keeps seven steps in flight
 // ([4096 x 4096], 45 rows: 9.6 us), two or four tiles three; reading two operands ahead instead of one
 // takes [22016 x 4096] at 512 rows from 200 to 173 us with two tiles, with four tiles it only costs registers.
+// A single pass with two tiles and a range of 16 k blocks or more requests the weights a whole k block at a time, 4 KB of a tile in one
+// go ([27648 x 5120], q = 17, 45 and 128 rows with their epilogues: 67.0 -> 63.7 and 95.6 -> 92.5 us); shorter ranges pay more for
+// the longer start than they gain ([15360 x 5120], q = 10, 16 and 128 rows: 33.5 and 35.0, 58.7 and 60.0).
 template <int RT, int CT, bool STREAM>
 static hipError_t launch_gemm_ct(const GemmArgs& a, int q, int xa, int grid, hipStream_t st) {
     constexpr int D = RT == 1 ? 8 : 4, PD = RT == 4 ? 1 : 2;
+    if constexpr (RT == 2 && STREAM)
+        if (q >= 16) return a.fused == 1 + EPI_SWIGLU ? launch_gemm_t<RT, CT, 8, PD, STREAM, true, true>(a, q, xa, grid, st)
+                                                      : launch_gemm_t<RT, CT, 8, PD, STREAM, false, true>(a, q, xa, grid, st);
     if constexpr (RT > 1)
-        if (a.fused == 1 + EPI_SWIGLU) return launch_gemm_t<RT, CT, D, PD, STREAM, true>(a, q, xa, grid, st);
-    return launch_gemm_t<RT, CT, D, PD, STREAM, false>(a, q, xa, grid, st);
+        if (a.fused == 1 + EPI_SWIGLU) return launch_gemm_t<RT, CT, D, PD, STREAM, true, false>(a, q, xa, grid, st);
+    return launch_gemm_t<RT, CT, D, PD, STREAM, false, false>(a, q, xa, grid, st);
 }
 
 hipError_t launch_prefill_gemm(const GemmArgs& a_, hipStream_t st) {
