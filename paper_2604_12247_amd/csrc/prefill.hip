@@ -198,6 +198,9 @@ __device__ __forceinline__ void gemm_flush(f32x4 (&acc)[RT][CT], const GemmArgs&
                                            const float* s_inv, int lane) {
     const int first = (b * c.KB) / q;
     const bool whole = first == ((b + 1) * c.KB - 1) / q;
+    // (the lane's number anew: the addresses that follow from it, forty registers and some spilled, would otherwise be worked out
+    // ahead of the main loop and kept from its operands)
+    asm volatile("" : "+v"(lane));
     const int li = lane & 15, sub = 4 * (lane >> 4);
     if (SWI && whole) {
 #pragma unroll
@@ -396,13 +399,15 @@ static hipError_t launch_gemm_t(const GemmArgs& a, int q, int xa, int grid, hipS
 }
 // D and PD by measurement (45 and 128 rows, 7B to 13B shapes): one tile per wave keeps seven steps in flight
 // ([4096 x 4096], 45 rows: 9.6 us), two or four tiles three; reading two operands ahead instead of one
-// takes [22016 x 4096] at 512 rows from 200 to 173 us with two tiles, with four tiles it only costs registers.
+// takes [22016 x 4096] at 512 rows from 200 to 173 us with two tiles, four operands or seven steps no further.  Four tiles take two
+// operands as well (three: 4 % slower) since the flush's addresses stay out of the main loop's registers: 1999 rows of the 8B shape, four layers,
+// 6.28 -> 6.13 ms, of which 0.03 are the operands.
 // A single pass with two tiles and a range of 16 k blocks or more requests the weights a whole k block at a time, 4 KB of a tile in one
 // go ([27648 x 5120], q = 17, 45 and 128 rows with their epilogues: 67.0 -> 63.7 and 95.6 -> 92.5 us); shorter ranges pay more for
 // the longer start than they gain ([15360 x 5120], q = 10, 16 and 128 rows: 33.5 and 35.0, 58.7 and 60.0).
 template <int RT, int CT, bool STREAM>
 static hipError_t launch_gemm_ct(const GemmArgs& a, int q, int xa, int grid, hipStream_t st) {
-    constexpr int D = RT == 1 ? 8 : 4, PD = RT == 4 ? 1 : 2;
+    constexpr int D = RT == 1 ? 8 : 4, PD = 2;
     if constexpr (RT == 2 && STREAM)
         if (q >= 16) return a.fused == 1 + EPI_SWIGLU ? launch_gemm_t<RT, CT, 8, PD, STREAM, true, true>(a, q, xa, grid, st)
                                                       : launch_gemm_t<RT, CT, 8, PD, STREAM, false, true>(a, q, xa, grid, st);
