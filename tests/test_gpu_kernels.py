@@ -144,6 +144,21 @@ def test_prompt_pass_gemm_heights(T, N, K, M):
     assert float((y - ref).abs().max()) <= 3e-5 * float(ref.abs().max())
 
 
+# a single pass whose thread blocks own 15, 16 and 17 k blocks: from 16 on the weights are requested a whole k block at a time
+@pytest.mark.parametrize("N,K", [(20480, 6144), (20480, 6528), (20480, 6784)])
+@pytest.mark.parametrize("M", [9, 40, 128])
+def test_prompt_pass_gemm_long_ranges(T, N, K, M):
+    import paper_2604_12247_amd as sb
+    g = T.Generator(device="cuda")
+    g.manual_seed(N + K + M)
+    W = (T.randn(N, K, generator=g, device="cuda") * 0.02).to(T.bfloat16)
+    x = T.randn(M, K, generator=g, device="cuda")
+    scratch = T.empty(sb.lib().sb_op_gemm_scratch_bytes(N, K), dtype=T.uint8, device="cuda")
+    y = sb.op_gemm(sb.op_repack(W), x, scratch).double()
+    ref = x.double() @ W.double().t().contiguous()
+    assert float((y - ref).abs().max()) <= 3e-5 * float(ref.abs().max())   # 16-bit activation parts, as in test_prompt_pass_gemm
+
+
 # either side of the lines between the block shapes (4096, 8192 and 12288 output rows, K = 4096, two and three rows), an odd number of tiles
 @pytest.mark.parametrize("N,K", [(4112, 4096), (4112, 4224), (8176, 256), (8192, 4224), (8208, 4224), (12288, 384), (12304, 384), (12304, 4224)])
 @pytest.mark.parametrize("kernel", ["mfma", "mfma_packed"])
