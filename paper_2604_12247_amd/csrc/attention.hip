@@ -59,6 +59,11 @@ __device__ __forceinline__ KVT kv_round(float f) {
     else return f;
 }
 
+// A rotated pair, x cos - y sin and y cos + x sin, with the product that is rounded by itself spelled out: the compiler's choice
+// between the two follows the code around it, and a stored key's last bit would change with that.
+__device__ __forceinline__ float rope_lo(float x, float y, float c, float sn) { return fmaf(x, c, -(y * sn)); }
+__device__ __forceinline__ float rope_hi(float x, float y, float c, float sn) { return fmaf(x, sn, y * c); }
+
 // A finished value of row r, as the merge stage leaves it.
 __device__ __forceinline__ void attn_finish(const AttnArgs& a, int r, int col, int ld, float v) {
     if (a.out) a.out[(size_t)r * ld + col] = v;
@@ -95,8 +100,8 @@ struct NewRows {
         if (r >= a.M) return;
 #pragma unroll
         for (int i = 0; i < NP; ++i) {
-            k_s[r * LDK + j + i * 32] = kv_round<KVT>(x[i] * c[i] - y[i] * sn[i]);
-            k_s[r * LDK + j + i * 32 + HALF] = kv_round<KVT>(y[i] * c[i] + x[i] * sn[i]);
+            k_s[r * LDK + j + i * 32] = kv_round<KVT>(rope_lo(x[i], y[i], c[i], sn[i]));
+            k_s[r * LDK + j + i * 32 + HALF] = kv_round<KVT>(rope_hi(x[i], y[i], c[i], sn[i]));
         }
 #pragma unroll
         for (int i = 0; i < NV; ++i) v_s[r * HD + j + i * 32] = kv_round<KVT>(v[i]);
@@ -232,7 +237,7 @@ __global__ __launch_bounds__(256, WAVES) void attn_kernel(AttnArgs a) {
                         const int j = dj + i * EPV + e;
                         float c = a.rope_cos[(size_t)kkey * HALF + j], sn = a.rope_sin[(size_t)kkey * HALF + j];
                         float x = kp[j], y = kp[j + HALF];
-                        f[e] = lo ? (x * c - y * sn) : (y * c + x * sn);
+                        f[e] = lo ? rope_lo(x, y, c, sn) : rope_hi(x, y, c, sn);
                     }
                     kreg[i] = KvVec<KVT>::pack(f);
                 }

@@ -691,6 +691,39 @@ def test_new_rows_at_every_place_of_a_chunk(T, Hq, Hkv, hd, bf16):
         assert worst <= 2e-5, (pos0, M, worst)
 
 
+def _bf16_value(a):
+    return si.bf16_to_f32(si.round_to_bf16(a))
+
+
+def _rotated(k, c, s):
+    """Keys [M, heads, hd] rotated as a decode pass stores them: x cos - (y sin), x sin + (y cos), the product in brackets rounded by
+    itself and the rest once (64 mantissa bits hold the other product; the sum is rounded twice, which 3e4 values do not show)."""
+    h = k.shape[-1] // 2
+    x, y, c, s = k[..., :h], k[..., h:], c[:, None], s[:, None]
+    L = np.longdouble
+    return np.concatenate([(L(1) * x * c - (y * s)).astype(np.float32), (L(1) * x * s + (y * c)).astype(np.float32)], -1)
+
+
+@pytest.mark.parametrize("hd", [64, 128])
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("M", [1, 8])
+def test_new_keys_bits(T, hd, bf16, M):
+    """The last bit of an appended key is a property of its row and position, whatever form the kernel has."""
+    import paper_2604_12247_amd as sb
+    H, n_pages = 32, 64
+    g = np.random.default_rng(67 + hd)
+    c, s = sb.rope_table(hd, 1e4, n_pages * 16)
+    for pos0 in (0, 121, 1000):
+        pool = T.zeros(2 * n_pages * H * 16 * hd, dtype=T.bfloat16 if bf16 else T.float32, device="cuda")
+        table = g.permutation(n_pages).astype(np.int32)
+        qkv = g.standard_normal((M, 3 * H * hd)).astype(np.float32)
+        sb.op_attention(_dev(T, qkv), H, H, hd, sb.BF16 if bf16 else sb.FP32, pool, _dev(T, table), 0, _dev(T, c), _dev(T, s), pos0)
+        ref = _rotated(qkv[:, H * hd:2 * H * hd].reshape(M, H, hd), c[pos0:pos0 + M], s[pos0:pos0 + M])
+        K = pool.float().cpu().numpy().reshape(2, n_pages, H, 16, hd)[0]
+        K = np.stack([K[table[p // 16], :, p % 16] for p in range(pos0, pos0 + M)])
+        assert np.array_equal(K, _bf16_value(ref) if bf16 else ref), pos0
+
+
 def test_attention_row_result_does_not_depend_on_m(T):
     """The same position gives the same bits alone and inside a pass of 6 rows."""
     args = (8, 8, 128, True)
