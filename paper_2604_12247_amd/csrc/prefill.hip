@@ -1085,6 +1085,8 @@ __global__ __launch_bounds__(64 * W, W == 4 ? 2 : 1) void prefill_attn_split_ker
                     uint32_t h[2], l[2];
 #pragma unroll
                     for (int e = 0; e < 2; ++e) {
+                        // (the low part is the remainder of the value, not of the product that it was rounded from)
+#pragma clang fp contract(off)
                         h[e] = pack_bf16(u[k][2 * e], u[k][2 * e + 1]);
                         l[e] = pack_bf16(u[k][2 * e] - __uint_as_float(h[e] << 16), u[k][2 * e + 1] - __uint_as_float(h[e] & 0xffff0000u));
                     }

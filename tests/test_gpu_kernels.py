@@ -724,6 +724,44 @@ def test_new_keys_bits(T, hd, bf16, M):
         assert np.array_equal(K, _bf16_value(ref) if bf16 else ref), pos0
 
 
+# the three launches that take the key tiles apart
+@pytest.mark.parametrize("H,hd", [(4, 64), (80, 64), (4, 128)])
+def test_prompt_attention_query_parts(T, H, hd):
+    """A query's low part is what its rounded value leaves over its high part.  Without rotation (cos 1, sin 0) two keys weigh one
+    dim each by 1024, so that a last bit of a low part (2^-16 of a value near 1) is 2^-6 in the difference of the two scores."""
+    import paper_2604_12247_amd as sb
+    M, pos0, n_pages = 40, 2, 3
+    g = np.random.default_rng(71 + hd)
+    bf = _bf16_value
+    c2 = np.float32(np.float32(1.4426950408889634) / np.sqrt(np.float32(hd)))
+    x = g.uniform(5.5, 11, 400000).astype(np.float32)
+    u = x * c2
+    hi = bf(u)
+    lo = bf(u - hi)
+    at = np.flatnonzero(bf((np.longdouble(1) * x * c2 - hi).astype(np.float32)) != lo)   # where the unrounded product leaves another one
+    assert len(at) >= 100
+    a = at[np.arange(M * H) % len(at)].reshape(M, H)
+    z = np.argsort(u)
+    near = z[np.clip(np.searchsorted(u[z], u[a] + g.uniform(-1e-3, 1e-3, a.shape).astype(np.float32)), 0, len(z) - 1)]
+    q = np.zeros((M, H, hd), np.float32)
+    q[:, :, 0], q[:, :, 1] = x[a], x[near]
+    pool = np.zeros((2, n_pages, H, 16 * hd), np.float32)
+    pool[0].reshape(n_pages, H, 16, hd)[0, :, 0, 0] = 1024
+    pool[0].reshape(n_pages, H, 16, hd)[0, :, 1, 1] = 1024
+    pool[1].reshape(n_pages, H, hd, 16)[0, :, :, 0] = 1          # (values: transposed within a page; the other key's are 0)
+    qkv = np.concatenate([q.reshape(M, -1), np.zeros((M, 2 * H * hd), np.float32)], 1)
+    one, zero = np.ones((n_pages * 16, hd // 2), np.float32), np.zeros((n_pages * 16, hd // 2), np.float32)
+    out = sb.op_prompt_attention(_dev(T, qkv), H, H, hd, _dev(T, pool).to(T.bfloat16), _dev(T, np.arange(n_pages, dtype=np.int32)), 0,
+                                 _dev(T, one), _dev(T, zero), pos0).cpu().numpy().reshape(M, H, hd)
+
+    def parts(i):
+        return hi[i].astype(np.float64) + lo[i]
+
+    ref = 1 / (1 + 2.0 ** (1024 * (parts(near) - parts(a))))     # (the other keys' scores are 1024 to 2048 lower)
+    # scores near 2^11 as floats: 2^-13 of them, at most ln 2 / 4 of that in the result; probabilities as 16-bit pairs: 2^-17
+    assert np.max(np.abs(out - ref[:, :, None])) <= 2 * 2.0 ** -13
+
+
 def test_attention_row_result_does_not_depend_on_m(T):
     """The same position gives the same bits alone and inside a pass of 6 rows."""
     args = (8, 8, 128, True)
