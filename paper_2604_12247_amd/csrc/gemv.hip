@@ -486,29 +486,28 @@ __global__ __launch_bounds__(64 * WPB) void gemv_mfma_kernel(GemvArgs a) {
     }
 }
 
-// Row tiles and waves of a block.  The waves (the order in which a row's products are added) are fixed by the operand shape alone, never
-// by the rows; the tiles also by how many rows there are.  A CU takes in about 39 GB/s whatever it has in flight, against the 28
-// that are its share of the card's rate, so what counts first is that no CU has more tiles than the others (256 CUs):
+// Row tiles and waves of a block.  The waves (the order in which a row's products are added) are fixed by the number of output rows
+// alone: eight up to 4096, four above.  The tiles follow the rows too.  What counts first is that no CU has more tiles than the others
+// (256 CUs):
 //   up to 256 tiles   a tile per block, eight waves splitting K, a ring of two (a deeper one only costs occupancy)
-//   up to 512         a CU with two tiles sets the time; as one block they read the rows once, not twice.  K > 4096: eight waves,
-//                     [5120 x 13824] at one / four / eight rows 29.8 / 33.7 / 40.8 -> 26.2 / 29.9 / 31.4 us, [5120 x 5120] 12.5 / 14.7 / 17.4
-//                     -> 10.5 / 12.5 / 13.3, [8192 x 5120] 14.8 / 17.1 / 20.5 -> 14.2 / 15.6 / 16.6.  K <= 4096: four waves, too short for
-//                     more, and two tiles from three rows on, [6144 x 4096] with one tile 11.5 / 11.6 / 13.9, two 11.6 / 11.0 / 11.7,
-//                     [8192 x 4096], one and four rows, 12.9 / 13.4 and 13.6 / 13.5
-//   up to 768         a tile per block of four waves, three blocks per CU ([12288 x 4096], four rows: 18.6, two tiles 23.8)
-//   more              two tiles (row-major weights and few rows: one, [13312 x 4096] 24.2 and 25.9); K > 4096: eight waves, [13824 x 13824]
-//                     64.9 / 69.7 / 85.2 -> 60.7 / 63.0 / 69.4, [15360 x 5120] 26.4 / 27.5 / 29.7 -> 25.7 / 26.2 / 28.2; [14336 x 4096], four
-//                     rows, one tile 22.8, two 21.0, with eight waves 23.6
-// Heads keep four waves and gate / up their pair of tiles: [32000 x 4096] 46.7, with eight waves 49.6; [2 * 11008 x 4096] 30.3 and 31.9.
+//   up to 512         a CU with two tiles sets the time; as one block they read the rows once, not twice.  One / two tiles per block at
+//                     one, four and eight rows: [5120 x 5120] 12.5 / 14.3 / 17.5 and 12.4 / 12.8 / 14.1 us, [5120 x 13824] 29.8 / 34.2 / 42.1
+//                     and 28.2 / 30.6 / 35.1, [8192 x 8192] 22.8 / 22.6 / 26.2 and 23.8 / 22.7 / 22.9, [6656 x 5120] 13.3 / 16.2 / 17.9 and
+//                     13.8 / 14.9 / 15.1, [6144 x 4096] 11.5 / 11.6 / 13.9 and 11.6 / 11.0 / 11.7: two from three rows on, and for fewer
+//                     where the second tile is rare enough to leave CUs idle and K is long.  Eight waves on two tiles would take
+//                     10.5 / 11.6 / 13.3 on [5120 x 5120] and 26.2 / 29.8 / 35.4 on [5120 x 13824], in another order of additions
+//   up to 768         a tile per block, three blocks per CU ([12288 x 4096], four rows: 18.6, two tiles 23.8)
+//   more              two tiles (row-major weights, few rows and short K: one, [13312 x 4096] 24.2 and 25.9)
 struct MfmaShape { int rt, wpb; };
 static int mfma_rows(const GemvArgs& a) { return a.row_mask ? __builtin_popcount(a.row_mask) : a.M; }
 static MfmaShape mfma_shape(const GemvArgs& a) {
     const bool few = mfma_rows(a) < 3, long_k = a.K > 4096;
     if (a.N <= 4096) return {1, 8};
-    if (a.N <= 8192) return {long_k || !few ? 2 : 1, long_k ? 8 : 4};
+    if (a.N <= 8192) return {!few || (long_k && a.N <= 6144) ? 2 : 1, 4};
     if (a.N <= 12288) return {1, 4};
-    return {long_k || a.packed || !few ? 2 : 1, long_k ? 8 : 4};
+    return {long_k || a.packed || !few ? 2 : 1, 4};
 }
+// Heads, and gate / up with its pair of tiles, keep four waves: [32000 x 4096] 46.7 us, with eight 49.6; [2 * 11008 x 4096] 30.3 and 31.9.
 static int mfma_row_tiles(int32_t N) { return N >= 15000 ? 2 : 1; }   // (heads)
 static int mfma_waves(int32_t N) { return N <= 4096 ? 8 : 4; }
 int head_blocks_mfma(int32_t N) { return (N + 16 * mfma_row_tiles(N) - 1) / (16 * mfma_row_tiles(N)); }
@@ -531,11 +530,7 @@ static void launch_gemv_mfma_e(const GemvArgs& a, hipStream_t st) {
         const int one = a.N / 16, two = (a.N + 31) / 32;
         if (sh.rt == 1 && sh.wpb == 8) gemv_mfma_kernel<1, EPI, 8, 2, PACKED, RAW><<<one, 512, 0, st>>>(a);
         else if (sh.rt == 1) gemv_mfma_kernel<1, EPI, 4, 3, PACKED, RAW><<<one, 256, 0, st>>>(a);
-        else if (sh.wpb == 4) gemv_mfma_kernel<2, EPI, 4, 3, PACKED, RAW><<<two, 256, 0, st>>>(a);
-        else if constexpr (EPI != EPI_HEAD) {
-            if (a.N <= 8192) gemv_mfma_kernel<2, EPI, 8, 3, PACKED, RAW><<<two, 512, 0, st>>>(a);
-            else gemv_mfma_kernel<2, EPI, 8, 2, PACKED, RAW><<<two, 512, 0, st>>>(a);
-        }
+        else gemv_mfma_kernel<2, EPI, 4, 3, PACKED, RAW><<<two, 256, 0, st>>>(a);
     }
 }
 

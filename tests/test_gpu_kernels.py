@@ -159,8 +159,8 @@ def test_prompt_pass_gemm_long_ranges(T, N, K, M):
     assert float((y - ref).abs().max()) <= 3e-5 * float(ref.abs().max())   # 16-bit activation parts, as in test_prompt_pass_gemm
 
 
-# either side of the lines between the block shapes (4096, 8192 and 12288 output rows, K = 4096, two and three rows), an odd number of tiles
-@pytest.mark.parametrize("N,K", [(4112, 4096), (4112, 4224), (8176, 256), (8192, 4224), (8208, 4224), (12288, 384), (12304, 384), (12304, 4224)])
+# either side of the lines between the block shapes (4096, 6144, 8192 and 12288 output rows, K = 4096, two and three rows), an odd number of tiles
+@pytest.mark.parametrize("N,K", [(4112, 4096), (4112, 4224), (6144, 4224), (6160, 4224), (8176, 256), (8192, 4224), (8208, 4224), (12288, 384), (12304, 384), (12304, 4224)])
 @pytest.mark.parametrize("kernel", ["mfma", "mfma_packed"])
 def test_gemv_mfma_block_shapes(T, kernel, N, K):
     import paper_2604_12247_amd as sb
@@ -176,6 +176,23 @@ def test_gemv_mfma_block_shapes(T, kernel, N, K):
     assert np.max(np.abs(y8 - ref)) <= 3e-5 * np.max(np.abs(ref))     # 16-bit activation parts, as in test_gemv_mfma
     for M in (1, 2, 3, 7):
         assert np.array_equal(sb.op_gemv(Wd, _dev(T, x[:M]), k).cpu().numpy(), y8[:M]), M
+
+
+# k blocks 0, 4 and 12 hold 2^24, 1 and 1: a wave that owns all three loses both ones to its 2^24, one that does not own the first adds them up
+@pytest.mark.parametrize("kernel", ["mfma", "mfma_packed"])
+@pytest.mark.parametrize("N", [4096, 4112, 6144, 6160, 8192, 8208, 12288, 12304, 16384])
+@pytest.mark.parametrize("K", [2048, 4096, 4224])
+def test_gemv_mfma_order_of_additions(T, kernel, N, K):
+    """k blocks are dealt to eight waves up to 4096 output rows and to four above, whatever K, the rows and the form of the weights."""
+    import paper_2604_12247_amd as sb
+    W = T.zeros(N, K, dtype=T.bfloat16, device="cuda")
+    for kb, v in ((0, 2.0 ** 24), (4, 1), (12, 1)):
+        W[:, kb * 128] = v
+    if kernel == "mfma_packed":
+        W = sb.op_repack(W)
+    for M in (1, 3, 8):
+        y = sb.op_gemv(W, T.ones(M, K, device="cuda"), sb.PROJ_MFMA_PACKED if kernel == "mfma_packed" else sb.PROJ_MFMA)
+        assert bool((y == 2.0 ** 24 + (2 if N <= 4096 else 0)).all()), M
 
 
 GATE_UP_SHAPES = [(64, 256, 3), (11008, 4096, 1), (11008, 4096, 6), (14336, 4096, 8)]
