@@ -347,6 +347,19 @@ def test_head_confidence_of_non_finite_logits_is_nan(T, kernel, N):
     assert np.all(np.isnan(conf(W, x)))
 
 
+def _bf16_value(a):
+    return si.bf16_to_f32(si.round_to_bf16(a))
+
+
+def _rotated(k, c, s):
+    """Keys [M, heads, hd] rotated as a decode pass stores them: x cos - (y sin), x sin + (y cos), the product in brackets rounded by
+    itself and the rest once (64 mantissa bits hold the other product; the sum is rounded twice, which 3e4 values do not show)."""
+    h = k.shape[-1] // 2
+    x, y, c, s = k[..., :h], k[..., h:], c[:, None], s[:, None]
+    L = np.longdouble
+    return np.concatenate([(L(1) * x * c - (y * s)).astype(np.float32), (L(1) * x * s + (y * c)).astype(np.float32)], -1)
+
+
 def _attention_case(T, Hq, Hkv, hd, kv_bf16, n_ctx, M, base, shuffle, seed, oracle=True):
     """Append n_ctx + M rows in passes, then compare the last pass's output rows."""
     import paper_2604_12247_amd as sb
@@ -382,7 +395,12 @@ def _attention_case(T, Hq, Hkv, hd, kv_bf16, n_ctx, M, base, shuffle, seed, orac
     K = np.zeros((n_tot, Hkv, hd), np.float32); V = np.zeros_like(K)
     for t in range(n_tot):
         for h in range(Hkv):
-            K[t, h] = rnd(orc.rope_apply(qkv[t, (Hq + h) * hd:(Hq + h + 1) * hd], t, base))
+            K[t, h] = exact = orc.rope_apply(qkv[t, (Hq + h) * hd:(Hq + h + 1) * hd], t, base)
+            if kv_bf16:
+                # (as the cache holds it: where the float rotation and the double one lie on two sides of a rounding boundary, a unit of one
+                # key apart, 2^-8 of it, moves an output by up to 2^-8 of that key's share of its score; test_new_keys_bits pins the bits)
+                K[t, h] = _bf16_value(_rotated(qkv[t:t + 1, (Hq + h) * hd:(Hq + h + 1) * hd][:, None], c[t:t + 1], s[t:t + 1])[0, 0])
+                assert np.all(np.abs(K[t, h] - exact) <= 2.0 ** -8 * np.abs(exact) + 1e-6)
             V[t, h] = rnd(qkv[t, (Hq + Hkv + h) * hd:(Hq + Hkv + h + 1) * hd])
     G = Hq // Hkv
     worst = 0.0
@@ -706,19 +724,6 @@ def test_new_rows_at_every_place_of_a_chunk(T, Hq, Hkv, hd, bf16):
     for pos0, M in ((0, 8), (7, 1), (8, 8), (13, 6), (15, 2), (31, 3), (57, 8), (63, 1), (64, 8), (95, 4), (120, 8), (121, 8), (127, 1), (128, 1)):
         worst, _ = _attention_case(T, Hq, Hkv, hd, bf16, pos0, M, 1e4, True, seed=pos0 * 9 + M)
         assert worst <= 2e-5, (pos0, M, worst)
-
-
-def _bf16_value(a):
-    return si.bf16_to_f32(si.round_to_bf16(a))
-
-
-def _rotated(k, c, s):
-    """Keys [M, heads, hd] rotated as a decode pass stores them: x cos - (y sin), x sin + (y cos), the product in brackets rounded by
-    itself and the rest once (64 mantissa bits hold the other product; the sum is rounded twice, which 3e4 values do not show)."""
-    h = k.shape[-1] // 2
-    x, y, c, s = k[..., :h], k[..., h:], c[:, None], s[:, None]
-    L = np.longdouble
-    return np.concatenate([(L(1) * x * c - (y * s)).astype(np.float32), (L(1) * x * s + (y * c)).astype(np.float32)], -1)
 
 
 @pytest.mark.parametrize("hd", [64, 128])
