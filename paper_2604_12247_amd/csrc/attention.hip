@@ -555,7 +555,10 @@ struct AttnItem {
         if (qg + 1 < qg_last) load_q(a, qg + 1);  // (in flight during this group's products)
         __syncthreads();
         // ---- keys and values of the new rows take the place of what the cache held, appended by query group 0; values of
-        // slots past the last key become zero (0 x stale bits that read as NaN is not 0; their scores are masked)
+        // slots past the last key become zero (0 x stale bits that read as NaN is not 0; their scores are masked): in a step
+        // with new rows value by value, in a later one all at once (value by value there as well, a chunk of few keys was slower
+        // than with a load for every value: 32 heads over 8 x 128, one row behind 3 / 130 keys 6.8 / 8.6 us then, 7.3 / 9.0 value
+        // by value, 6.3 / 8.1 now)
         if (has_new && qg == qg_first) {
     #pragma unroll
             for (int t = 0; t < 2; ++t) {
@@ -571,7 +574,7 @@ struct AttnItem {
     #pragma unroll
             for (int ks = 0; ks < KSV; ++ks) {
                 const int kf = key0 + ks * 32 + lq * 8;
-                if (key0 + ks * 32 + 32 <= a.pos0) continue;   // (block-uniform: no new row in this step)
+                if (key0 + ks * 32 + 32 <= a.pos0 || key0 + ks * 32 >= n_total) continue;   // (block-uniform: no new row in this step)
     #pragma unroll
                 for (int dt = 0; dt < DT; ++dt) {
                     const uint16_t* vp = nv_s + (wave * DT + dt) * 16 + li;
@@ -587,6 +590,10 @@ struct AttnItem {
                     vreg[dt][ks] = make_uint4(w[0], w[1], w[2], w[3]);
                 }
             }
+    #pragma unroll
+            for (int ks = 1; ks < KSV; ++ks)   // (the first step holds a key)
+    #pragma unroll
+                for (int dt = 0; dt < DT; ++dt) vreg[dt][ks] = pick(key0 + ks * 32 >= n_total, make_uint4(0, 0, 0, 0), vreg[dt][ks]);
             if (zb == 0) {
     #pragma unroll
                 for (int t = 0; t < 2; ++t) {
