@@ -519,12 +519,16 @@ static void launch_gemv_mfma_e(const GemvArgs& a, hipStream_t st) {
     if constexpr (EPI == EPI_SWIGLU) {
         const int pairs = a.N / 16;
         // Four tiles (two pairs) read the rows half as often; two blocks of them fit on a CU, so up to 1024 pairs, and only where
-        // one pair per block would give a CU more than three and a block is long enough.  Two / four tiles: [2 * 13824 x 5120] at
-        // three / six / eight rows 49.5 / 50.9 / 52.8 and 47.6 / 48.6 / 49.5 us, one row 45.5 and 46.4, [2 * 16384 x 5120], eight rows
-        // 56.5 and 54.3, [2 * 13824 x 13824], six 130.8 and 118.9; [2 * 12304 x 5120], six 47.5 and 48.0, [2 * 14336 x 4096], three
-        // 38.9 and 39.5, [2 * 11008 x 4096], six 30.6 and 37.8; row-major [2 * 14336 x 4096], three 47.4 and 50.4.
-        if (a.packed && a.K > 4096 && mfma_rows(a) >= 3 && pairs > 816 && pairs <= 1024) gemv_mfma_kernel<4, EPI, 4, 2, PACKED, RAW><<<(pairs + 1) / 2, 256, 0, st>>>(a);
-        else gemv_mfma_kernel<2, EPI, 4, 3, PACKED, RAW><<<pairs, 256, 0, st>>>(a);
+        // one pair per block would give a CU more than three, with K long enough and three rows or more. Two / four tiles at K = 5120:
+        // 688 pairs, six rows 39.9 / 46.0 us; 769, three / six / eight rows 45.1 / 43.2, 46.9 / 44.6, 49.1 / 45.6; 816 47.5 / 45.5, 49.4 /
+        // 47.0, 51.6 / 48.2; 864 49.2 / 45.6, 50.6 / 46.5, 52.8 / 47.5, one row 45.5 and 46.4; 1024 52.8 / 52.3, 54.4 / 53.5, 56.5 / 52.8;
+        // 1040, six rows 61.0 / 65.5. K = 4096: 896 pairs, three rows 38.9 and 39.5, row-major weights 47.4 and 50.4.
+        if constexpr (PACKED)
+            if (a.K > 4096 && mfma_rows(a) >= 3 && pairs > 768 && pairs <= 1024) {
+                gemv_mfma_kernel<4, EPI, 4, 2, PACKED, RAW><<<(pairs + 1) / 2, 256, 0, st>>>(a);
+                return;
+            }
+        gemv_mfma_kernel<2, EPI, 4, 3, PACKED, RAW><<<pairs, 256, 0, st>>>(a);
     } else {
         const MfmaShape sh = EPI == EPI_HEAD ? MfmaShape{mfma_row_tiles(a.N), mfma_waves(a.N)} : mfma_shape(a);
         const int one = a.N / 16, two = (a.N + 31) / 32;

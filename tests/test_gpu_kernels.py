@@ -218,8 +218,8 @@ def test_gate_up_swiglu(T, kernel, N, K, M):
         assert np.max(np.abs(u[m] - ref)) <= 1e-4 * scale, (m, np.max(np.abs(u[m] - ref)), scale)
 
 
-# one and two pairs of tiles per block: 816 pairs, 817 (the last block owns one), 1024 and 1025, K on either side of 4096
-@pytest.mark.parametrize("N,K", [(13056, 4224), (13072, 4224), (13072, 4096), (16384, 4224), (16400, 4224)])
+# one and two pairs of tiles per block: 768 pairs, 769 (the last block owns one), 1024 and 1025, K on either side of 4096
+@pytest.mark.parametrize("N,K", [(12288, 4224), (12304, 4224), (12304, 4096), (16384, 4224), (16400, 4224)])
 def test_gate_up_pairs_per_block(T, N, K):
     import paper_2604_12247_amd as sb
     g = np.random.default_rng(N + K)
