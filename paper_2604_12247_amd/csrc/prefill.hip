@@ -402,14 +402,17 @@ static hipError_t launch_gemm_t(const GemmArgs& a, int q, int xa, int grid, hipS
 // takes [22016 x 4096] at 512 rows from 200 to 173 us with two tiles, four operands or seven steps no further.  Four tiles take two
 // operands as well (three: 4 % slower) since the flush's addresses stay out of the main loop's registers: 1999 rows of the 8B shape, four layers,
 // 6.28 -> 6.13 ms, of which 0.03 are the operands.
-// A single pass with two tiles and a range of 16 k blocks or more requests the weights a whole k block at a time, 4 KB of a tile in one
-// go ([27648 x 5120], q = 17, 45 and 128 rows with their epilogues: 67.0 -> 63.7 and 95.6 -> 92.5 us); shorter ranges pay more for
-// the longer start than they gain ([15360 x 5120], q = 10, 16 and 128 rows: 33.5 and 35.0, 58.7 and 60.0).
+// A single pass with two tiles and a range of an odd number of k blocks, nine or more, requests the weights a whole k block at a time,
+// 4 KB of a tile in one go: thread blocks start their ranges that many 4 KB pieces apart, and an odd distance keeps their
+// bursts off each other's channels. Three shapes for each q from 9 to 24 at 16, 45 and 112 rows, step by step / whole: odd q 0.98 to
+// 1.07x, 1.03 on the average ([27648 x 5120], q = 17, 45 rows 67.1 -> 63.6 us, [20480 x 6784] 66.0 -> 62.8, [24144 x 3584], q = 11, 1.06x), even
+// q 0.96 to 1.02x, 0.99 ([20480 x 8192], q = 20, 45 rows 76.1 and 78.5, [16384 x 8192], q = 16, 62.1 and 64.0). Below nine only gate / up takes two
+// tiles, and a range has hardly more than the start, which is longer this way.
 template <int RT, int CT, bool STREAM>
 static hipError_t launch_gemm_ct(const GemmArgs& a, int q, int xa, int grid, hipStream_t st) {
     constexpr int D = RT == 1 ? 8 : 4, PD = 2;
     if constexpr (RT == 2 && STREAM)
-        if (q >= 16) return a.fused == 1 + EPI_SWIGLU ? launch_gemm_t<RT, CT, 8, PD, STREAM, true, true>(a, q, xa, grid, st)
+        if (q >= 9 && q % 2) return a.fused == 1 + EPI_SWIGLU ? launch_gemm_t<RT, CT, 8, PD, STREAM, true, true>(a, q, xa, grid, st)
                                                       : launch_gemm_t<RT, CT, 8, PD, STREAM, false, true>(a, q, xa, grid, st);
     if constexpr (RT > 1)
         if (a.fused == 1 + EPI_SWIGLU) return launch_gemm_t<RT, CT, D, PD, STREAM, true, false>(a, q, xa, grid, st);

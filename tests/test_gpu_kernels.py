@@ -144,8 +144,8 @@ def test_prompt_pass_gemm_heights(T, N, K, M):
     assert float((y - ref).abs().max()) <= 3e-5 * float(ref.abs().max())
 
 
-# a single pass whose thread blocks own 15, 16 and 17 k blocks: from 16 on the weights are requested a whole k block at a time
-@pytest.mark.parametrize("N,K", [(20480, 6144), (20480, 6528), (20480, 6784)])
+# a single pass whose thread blocks own 9, 10, 15, 16 and 17 k blocks: odd numbers of weight blocks are requested whole
+@pytest.mark.parametrize("N,K", [(17088, 4096), (7184, 10368), (20480, 6144), (20480, 6528), (20480, 6784)])
 @pytest.mark.parametrize("M", [9, 40, 128])
 def test_prompt_pass_gemm_long_ranges(T, N, K, M):
     import paper_2604_12247_amd as sb
