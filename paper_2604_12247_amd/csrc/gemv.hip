@@ -490,22 +490,25 @@ __global__ __launch_bounds__(64 * WPB) void gemv_mfma_kernel(GemvArgs a) {
 // alone: eight up to 4096, four above.  The tiles follow the rows too.  What counts first is that no CU has more tiles than the others
 // (256 CUs):
 //   up to 256 tiles   a tile per block, eight waves splitting K, a ring of two (a deeper one only costs occupancy)
-//   up to 512         a CU with two tiles sets the time; as one block they read the rows once, not twice.  One / two tiles per block at
-//                     one, four and eight rows: [5120 x 5120] 12.5 / 14.3 / 17.5 and 12.4 / 12.8 / 14.1 us, [5120 x 13824] 29.8 / 34.2 / 42.1
-//                     and 28.2 / 30.6 / 35.1, [8192 x 8192] 22.8 / 22.6 / 26.2 and 23.8 / 22.7 / 22.9, [6656 x 5120] 13.3 / 16.2 / 17.9 and
-//                     13.8 / 14.9 / 15.1, [6144 x 4096] 11.5 / 11.6 / 13.9 and 11.6 / 11.0 / 11.7: two from three rows on, and for fewer
-//                     where the second tile is rare enough to leave CUs idle and K is long.  Eight waves on two tiles would take
-//                     10.5 / 11.6 / 13.3 on [5120 x 5120] and 26.2 / 29.8 / 35.4 on [5120 x 13824], in another order of additions
+//   up to 512         a CU with two tiles sets the time; as one block they read the rows once, not twice, which pays with several rows, fewer
+//                     of them where only some CUs have a second tile, and a K long enough for the start. One / two tiles per block at
+//                     three, four and eight rows: [5120 x 5120] 13.5 / 12.7, 14.3 / 12.8 and 17.5 / 14.1 us, [6144 x 4096] 1.02, 1.07 and 1.18x,
+//                     [5120 x 2048] 1.02, 1.04 and 1.15x, [5120 x 1024] 0.96, 0.98 and 1.03x; [8192 x 4096] 0.97, 1.00 and 1.13x, [8192 x 8192]
+//                     22.0 / 23.3, 22.6 / 22.7 and 26.2 / 22.9. One row: [5120 x 13824] 29.8 / 28.2, [5120 x 10240] 22.5 / 21.9, [4224 x 6144]
+//                     14.5 / 15.0, [8192 x 5120] 14.7 / 15.7, row-major [5120 x 5120] 16.9 / 18.1. (Row-major
+//                     [8192 x 8192], rows 16 KB apart, is slower at five rows, 29.7 / 34.8; 8192 x 4224, 5120 and 13824 gain.) Eight waves on two tiles would take 10.5 /
+//                     11.6 / 13.3 at one, four and eight rows of [5120 x 5120], 26.2 / 29.8 / 35.4 of [5120 x 13824], in another order of additions
 //   up to 768         a tile per block, three blocks per CU ([12288 x 4096], four rows: 18.6, two tiles 23.8)
 //   more              two tiles (row-major weights, few rows and short K: one, [13312 x 4096] 24.2 and 25.9)
 struct MfmaShape { int rt, wpb; };
 static int mfma_rows(const GemvArgs& a) { return a.row_mask ? __builtin_popcount(a.row_mask) : a.M; }
 static MfmaShape mfma_shape(const GemvArgs& a) {
-    const bool few = mfma_rows(a) < 3, long_k = a.K > 4096;
+    const int rows = mfma_rows(a);
     if (a.N <= 4096) return {1, 8};
-    if (a.N <= 8192) return {!few || (long_k && a.N <= 6144) ? 2 : 1, 4};
+    if (a.N <= 6144) return {(rows >= 3 && a.K >= 2048) || (a.packed && a.K > 8192) ? 2 : 1, 4};
+    if (a.N <= 8192) return {rows >= 5 && a.K >= 2048 ? 2 : 1, 4};
     if (a.N <= 12288) return {1, 4};
-    return {long_k || a.packed || !few ? 2 : 1, 4};
+    return {a.K > 4096 || a.packed || rows >= 3 ? 2 : 1, 4};
 }
 // Heads, and gate / up with its pair of tiles, keep four waves: [32000 x 4096] 46.7 us, with eight 49.6; [2 * 11008 x 4096] 30.3 and 31.9.
 static int mfma_row_tiles(int32_t N) { return N >= 15000 ? 2 : 1; }   // (heads)

@@ -159,8 +159,9 @@ def test_prompt_pass_gemm_long_ranges(T, N, K, M):
     assert float((y - ref).abs().max()) <= 3e-5 * float(ref.abs().max())   # 16-bit activation parts, as in test_prompt_pass_gemm
 
 
-# either side of the lines between the block shapes (4096, 6144, 8192 and 12288 output rows, K = 4096, two and three rows), an odd number of tiles
-@pytest.mark.parametrize("N,K", [(4112, 4096), (4112, 4224), (6144, 4224), (6160, 4224), (8176, 256), (8192, 4224), (8208, 4224), (12288, 384), (12304, 384), (12304, 4224)])
+# either side of the lines between the block shapes (4096, 6144, 8192 and 12288 output rows, K = 2048, 4096 and 8192, three and five rows)
+@pytest.mark.parametrize("N,K", [(4112, 4096), (4112, 1920), (4112, 8320), (6144, 2048), (6160, 2048), (8176, 256), (8192, 2048), (8208, 4224),
+                                 (12288, 384), (12304, 384), (12304, 4224)])
 @pytest.mark.parametrize("kernel", ["mfma", "mfma_packed"])
 def test_gemv_mfma_block_shapes(T, kernel, N, K):
     import paper_2604_12247_amd as sb
@@ -174,7 +175,7 @@ def test_gemv_mfma_block_shapes(T, kernel, N, K):
     y8 = sb.op_gemv(Wd, _dev(T, x), k).cpu().numpy()
     ref = _oracle_rows(W, x)
     assert np.max(np.abs(y8 - ref)) <= 3e-5 * np.max(np.abs(ref))     # 16-bit activation parts, as in test_gemv_mfma
-    for M in (1, 2, 3, 7):
+    for M in (1, 2, 3, 4, 5, 7):
         assert np.array_equal(sb.op_gemv(Wd, _dev(T, x[:M]), k).cpu().numpy(), y8[:M]), M
 
 
