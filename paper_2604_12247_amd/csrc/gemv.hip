@@ -207,13 +207,16 @@ int head_blocks_valu(int32_t N) { return (N + 15) / 16; }
 
 // Weight rows per wave: one (gate / up: a pair), so that a small matrix has four (two) times the blocks, or four, so that a block's rows
 // are staged for four times the weights.  One while four would leave CUs without a block, and beyond that while a block
-// stages no more bytes than it reads of the weights.  Four / one, in us: fp32 [256 x 688], one row 3.7 / 2.5, four 6.2 / 3.5, eight
-// 9.6 / 4.0; bf16 [4000 x 4096], eight 17.4 / 16.9; fp32 [12288 x 1024], one 10.8 / 10.1, [16000 x 4096], one 51.4 / 46.2, four
-// 54.6 / 46.5; but bf16 [6144 x 4096], eight 19.7 / 24.7, [12288 x 4096], four 25.0 / 28.5.  A row's sums are the same either way.
+// stages no more bytes than it reads of the weights, up to four blocks a CU where K is long enough for more blocks to pay and two
+// else (gate / up, whose waves keep a pair, gains at K = 256 as well: [2 * 8000 x 256] bf16, one row, 1.07x).
+// Four / one, in us: fp32 [256 x 688], one row 3.7 / 2.5, four 6.2 / 3.5, eight 9.6 / 4.0; bf16 [4000 x 4096], eight 17.4 / 16.9;
+// one row, bf16 [6144 x 4096] 12.7 / 11.7, [12288 x 4096] 21.4 / 20.4, [6144 x 256] 1.07x, fp32 [12288 x 1024] 10.8 / 10.1, [16000 x 4096]
+// 51.4 / 46.2, four 54.6 / 46.5; but bf16 [6144 x 4096], eight 19.7 / 24.7, [12288 x 4096], four 25.0 / 28.5, and one row of
+// [12288 x 256] bf16 4.0 / 4.3, fp32 5.0 / 5.3.  A row's sums are the same either way.
 template <typename WT, int M, bool SHORT>
 static hipError_t launch_gemv_valu_m(const GemvArgs& a, hipStream_t st) {
     const int n = a.epi == EPI_SWIGLU ? 2 * a.N : a.N;
-    const bool few = n < 16 * 256 || (M <= (int)sizeof(WT) && n < 16 * 1024);
+    const bool few = n < 16 * 256 || (M <= (int)sizeof(WT) && n < 16 * (a.K >= 1024 || a.epi == EPI_SWIGLU ? 1024 : 512));
     switch (a.epi) {
         case EPI_STORE:
             if (few) gemv_valu_kernel<WT, M, EPI_STORE, SHORT, 1><<<(a.N + 3) / 4, 256, 0, st>>>(a);

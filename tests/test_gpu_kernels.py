@@ -61,8 +61,10 @@ def test_gemv_valu(T, N, K, bf16, M):
     assert np.max(np.abs(y - ref)) <= 1e-5 * np.max(np.abs(ref)) + 1e-7
 
 
-# either side of the lines between one and four weight rows per wave (256 blocks of four; 1024 for as few rows as a weight has bytes)
-@pytest.mark.parametrize("N,K,bf16", [(4080, 264, False), (4096, 264, False), (4097, 1032, True), (16383, 136, False), (16400, 136, True)])
+# either side of the lines between one and four weight rows per wave (256 blocks of four; for as few rows as a weight has bytes 512, and 1024
+# with K >= 1024 or for gate / up)
+@pytest.mark.parametrize("N,K,bf16", [(4080, 264, False), (4096, 264, False), (4097, 1032, True), (8191, 136, False), (8208, 136, True),
+                                      (16383, 1032, False), (16400, 1032, True)])
 @pytest.mark.parametrize("M", [1, 2, 3, 4, 5])
 def test_gemv_valu_rows_per_wave(T, N, K, bf16, M):
     """The rows per wave change who adds a row's products, not how: the bits of a row equal those of eight rows together."""
