@@ -108,15 +108,16 @@ struct NewRows {
     }
 };
 
-// WAVES: blocks a CU holds at once (one wave of each per SIMD).  MANY: passes of more than SB_MAX_W rows, whose chunks are full of new
-// rows: each thread prepares its own, which takes 160 registers, three blocks per CU (in 128, with some spilled, four fit;
-// launch_attention says when which).  Else the new rows go through LDS and four blocks fit.
+// Four blocks per CU (one wave of each per SIMD).  MANY: passes of more than SB_MAX_W rows, whose chunks are full of new rows: each thread
+// prepares its own, in the 128 registers that four blocks leave it, with some spilled (in 160, three blocks per CU: prompts of up to 1000
+// rows through two layers of the 7B and 8B shapes the same, 1999 rows 6.1 and 6.4 ms where four take 5.8 and 6.1).  Else the
+// new rows go through LDS.
 // What bounds a decode pass: few keys the chain of round trips (page table, operands, LDS), many the memory.  The page table through
 // the scalar cache and everything else in one go, instead of a table entry, a wait and a load for each of a thread's eight
 // value pieces: 4 heads x 64, 90 keys, one row 6.5 -> 5.2 us, four 9.0 -> 7.4; 32 heads, one row, 2000 keys x 128 24.8 -> 17.6,
 // 9000 x 128 85 -> 63, 9000 x 64 47.5 -> 33.6.
-template <typename KVT, int HD, int WAVES, bool MANY>
-__global__ __launch_bounds__(256, WAVES) void attn_kernel(AttnArgs a) {
+template <typename KVT, int HD, bool MANY>
+__global__ __launch_bounds__(256, 4) void attn_kernel(AttnArgs a) {
     constexpr int CH = (HD * sizeof(KVT) <= 256) ? 128 : 64;  // keys per chunk
     constexpr int EPV = KvVec<KVT>::EPV;                      // elements per 16 bytes
     constexpr int QG = 16;                                    // queries per block
@@ -857,18 +858,10 @@ hipError_t launch_attention(const AttnArgs& a, hipStream_t st) {
         if (hd == 128) { attn_mfma_kernel<128><<<grid, 256, 0, st>>>(b); if (!b.direct) attn_merge_kernel<128, 128><<<mgrid, 256, 0, st>>>(a); }
         else { attn_mfma_kernel<64><<<grid, 256, 0, st>>>(b); if (!b.direct) attn_merge_kernel<64, 128><<<mgrid, 256, 0, st>>>(a); }
     } else {
-        // Passes of more than SB_MAX_W rows: four blocks per CU where that saves a round of blocks over the chip, else three, whose
-        // blocks are faster.  Decode passes: four always.
-        const int64_t blocks = (int64_t)grid1.x * grid1.y * grid1.z;
-        const bool four = (blocks + 4 * 256 - 1) / (4 * 256) < (blocks + 3 * 256 - 1) / (3 * 256);
         const auto first = [&](auto hd_c) {
             constexpr int HD = decltype(hd_c)::value;
-            if (a.M > SB_MAX_W) {
-                if (four) attn_kernel<float, HD, 4, true><<<grid1, 256, 0, st>>>(b);
-                else attn_kernel<float, HD, 3, true><<<grid1, 256, 0, st>>>(b);
-            } else {
-                attn_kernel<float, HD, 4, false><<<grid1, 256, 0, st>>>(b);
-            }
+            if (a.M > SB_MAX_W) attn_kernel<float, HD, true><<<grid1, 256, 0, st>>>(b);
+            else attn_kernel<float, HD, false><<<grid1, 256, 0, st>>>(b);
         };
         if (hd == 128) {
             first(std::integral_constant<int, 128>{});

@@ -711,8 +711,7 @@ def test_prompt_attention_output_over_its_input(T, Hq, Hkv, hd, pos0, M):
     assert float((out - ref).abs().max()) <= 2e-5
 
 
-# an fp32 cache: up to 768 blocks three to a CU, up to 1024 four, then three again (a row alone and beside others may be on
-# either side of a line)
+# an fp32 cache, launches of 768 and 800, 1024 and 1056 blocks, where four to a CU are 1024 (a row alone and beside others may be on either side)
 @pytest.mark.parametrize("hd,pos0", [(64, 3070), (64, 4095), (128, 1535), (128, 2047)])
 def test_attention_fp32_cache_block_counts(T, hd, pos0):
     _, out6 = _attention_case(T, 32, 32, hd, False, pos0, 6, 1e4, True, seed=83 + pos0, oracle=False)

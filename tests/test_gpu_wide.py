@@ -86,14 +86,14 @@ def _worst_kv(session, ref, layer):
     return worst
 
 
-# 512 rows in passes of 128: 256, 512, 768 (three blocks to a CU) and 1024 attention blocks (four), whatever the head's size
-@pytest.mark.parametrize("Hq,Hkv,hd", [(32, 8, 64), (16, 16, 128)])
-def test_prompt_through_fp32_cache_block_counts(T, Hq, Hkv, hd):
+# 512 rows in passes of 128: 256, 512, 768 and 1024 attention blocks (a chip full) of both head sizes; 1100 rows: up to 2048
+@pytest.mark.parametrize("Hq,Hkv,hd,n", [(32, 8, 64, 512), (16, 16, 128, 512), (16, 16, 128, 1100)])
+def test_prompt_through_fp32_cache_block_counts(T, Hq, Hkv, hd, n):
     shape = si.tiny_shape(n_layers=2, n_exit_heads=1, weight_dtype=B16, kv_dtype=F32, d_model=2048, n_heads=Hq, n_kv_heads=Hkv, head_dim=hd,
                           d_ffn=768)
     host, dev = _weights(T, shape, 5 + hd)
-    prompt = si.make_prompt(shape.vocab, 512, 7)
-    s = gpu_model(shape, host, 544).session()
+    prompt = si.make_prompt(shape.vocab, n, 7)
+    s = gpu_model(shape, host, 1120).session()
     s.prefill(prompt)
     # five products in a row, each within 3e-5 of its largest value, between norms that keep the scale
     assert _worst_kv(s, _double(T, shape, dev, prompt, 1), 1) <= 1.5e-4
