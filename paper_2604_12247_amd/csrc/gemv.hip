@@ -38,7 +38,7 @@ __device__ __forceinline__ void head_partial(const HeadArgs& h, float (*zs)[SB_M
 
 // ---------------------------------------------------------------- GEMV, vector ALU
 // y[m][n] = sum_k W[n][k] x[m][k] for M rows sharing one sweep over W.  One wave
-// owns 4 weight rows; lanes stride the K dimension in 16-byte pieces (128-bit
+// owns one, two or four weight rows (launch_gemv_valu_m); lanes stride the K dimension in 16-byte pieces (128-bit
 // loads), partial sums are combined with a fixed shuffle tree.  x is staged in
 // LDS in chunks.  The order in which a row's products are added is a function of
 // K alone.

@@ -245,7 +245,7 @@ __device__ __forceinline__ void gemm_flush(f32x4 (&acc)[RT][CT], const GemmArgs&
 
 // 512 threads; a wave multiplies its RT weight tiles (16 rows each, registers) with all CT column
 // tiles (16 of the pass's rows, bf16 high and low parts, LDS): a 16 RT x 16 CT tile of the result.
-//   weights      a ring of D register stages, 32 k each, requested D - 1 steps ahead
+//   weights      a ring of D register stages, 32 k each, requested D - 1 steps ahead (WHOLE: the four of a k block together, four to seven ahead)
 //   activations  a k block (128 k) ahead through registers into the other LDS stage; one barrier per k block
 //   operands     read from LDS PD column tiles before the MFMAs that take them
 // What bounds it: a long prompt the power the card gives the matrix cores (random operands: an MFMA-only loop
@@ -296,7 +296,7 @@ __global__ __launch_bounds__(64 * WPB) void prefill_gemm_kernel(GemmArgs a, int 
     uint4 ar[D][RT];
     GemmStage<CT> sg;
     sg.init(a, c, tid);
-    GemmWeights<RT, SWI> w;  // the pair whose step 3 is requested at the first step of a k block; then the pair after it
+    GemmWeights<RT, SWI> w;  // the pair whose last step (WHOLE: all steps) is requested at the first step of a k block; then the pair after it
     w.init(c, a.Wp, it0);
     int b = w.b, kb = w.kb;  // the pair being multiplied
     {
@@ -1060,7 +1060,7 @@ __global__ __launch_bounds__(64 * W, W == 4 ? 2 : 1) void prefill_attn_split_ker
         const float* cp = a.rope_cos + (size_t)(a.pos0 + qr.row) * HALF;
         const float* sp = a.rope_sin + (size_t)(a.pos0 + qr.row) * HALF;
         const float c2 = 1.4426950408889634f / sqrtf((float)HD);   // scores in units of log 2
-        // (all loads first, and a query past the end is one of the block's that is blanked afterwards: no load under a condition,
+        // (all loads first, and a query past the end reads row 0's first head and is blanked afterwards: no load under a condition,
         // which would be a wait each)
         constexpr int NQ = HALF / (4 * TPQ);
         const uint32_t keep = qr.valid ? 0xffffffffu : 0u;

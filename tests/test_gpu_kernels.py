@@ -86,7 +86,7 @@ def test_gemv_valu_rows_per_wave(T, N, K, bf16, M):
 MFMA_CASES = [(16, 128), (64, 256), (4096, 4096), (12288, 4096), (4096, 11008), (32000, 4096), (48, 384),
               (15024, 256),      # two row tiles per block, an odd number of tiles: the last block owns one
               (4096, 14336),
-              (6144, 4096), (5120, 5120), (5120, 13824)]   # between 4096 and 8192 output rows: one tile per block, four waves
+              (6144, 4096), (5120, 5120), (5120, 13824)]   # between 4096 and 8192 output rows: one or two tiles per block, by the rows, of four waves
 
 
 @pytest.mark.parametrize("N,K", MFMA_CASES)
