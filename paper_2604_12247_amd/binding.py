@@ -453,8 +453,12 @@ class Batch:
             pass
 
 
-def _stream_ptr(torch, device):
-    return C.c_void_p(torch.cuda.current_stream(device).cuda_stream)
+def _stream_ptr(torch, x):
+    """The handle of the current stream on x's GPU.  Taken as a number: a Stream object made and thrown away for it
+    cost 2.1 us of the 9.5 us that a single-kernel call kept the host."""
+    if not x.is_cuda:
+        raise ValueError(f"expected a tensor on a GPU, not on {x.device}")
+    return torch._C._cuda_getCurrentRawStream(x.get_device())
 
 
 def op_rmsnorm(x, gain, eps: float):
@@ -462,7 +466,7 @@ def op_rmsnorm(x, gain, eps: float):
     import torch
     out = torch.empty_like(x)
     check(lib().sb_op_rmsnorm(x.data_ptr(), gain.data_ptr(), out.data_ptr(), x.shape[0], x.shape[1], eps,
-                              _stream_ptr(torch, x.device)))
+                              _stream_ptr(torch, x)))
     return out
 
 
@@ -480,7 +484,7 @@ def op_repack(W):
     import torch
     N, K = W.shape
     P = torch.empty_like(W)
-    check(lib().sb_op_repack(W.data_ptr(), N, K, P.data_ptr(), _stream_ptr(torch, W.device)))
+    check(lib().sb_op_repack(W.data_ptr(), N, K, P.data_ptr(), _stream_ptr(torch, W)))
     return P
 
 
@@ -493,8 +497,17 @@ def op_gemm(Wp, x, scratch=None):
     if scratch is None:
         scratch = torch.empty(max(lib().sb_op_gemm_scratch_bytes(N, K), 256), dtype=torch.uint8, device=x.device)
     check(lib().sb_op_gemm(Wp.data_ptr(), N, K, x.data_ptr(), y.data_ptr(), M, scratch.data_ptr(),
-                           _stream_ptr(torch, x.device)))
+                           _stream_ptr(torch, x)))
     return y
+
+
+def _unused_scratch(torch, x, y):
+    """The scratch area of a decode projection of x into y.  The library writes to it only where y lies over x, which a
+    newly made y does not: y itself stands in for it (an allocation less).  Rows that are not dense get an area, as the
+    range that the library takes them to fill is not theirs alone."""
+    if x.is_contiguous():
+        return y
+    return torch.empty(max(lib().sb_op_gemv_scratch_bytes(x.shape[0], x.shape[1]), 256), dtype=torch.uint8, device=x.device)
 
 
 def op_gemv(W, x, kernel: int = PROJ_VALU):
@@ -504,10 +517,9 @@ def op_gemv(W, x, kernel: int = PROJ_VALU):
     N, K = W.shape
     M = x.shape[0]
     y = torch.empty((M, N), dtype=torch.float32, device=x.device)
-    nbytes = lib().sb_op_gemv_scratch_bytes(M, K)
-    scratch = torch.empty(max(nbytes, 256), dtype=torch.uint8, device=x.device)
+    scratch = _unused_scratch(torch, x, y)
     check(lib().sb_op_gemv(W.data_ptr(), _wdtype(W), N, K, x.data_ptr(), y.data_ptr(), M, kernel,
-                           scratch.data_ptr(), _stream_ptr(torch, x.device)))
+                           scratch.data_ptr(), _stream_ptr(torch, x)))
     return y
 
 
@@ -518,9 +530,9 @@ def op_gate_up(W, x, kernel: int = PROJ_VALU):
     N, K = W.shape[0] // 2, W.shape[1]
     M = x.shape[0]
     u = torch.empty((M, N), dtype=torch.float32, device=x.device)
-    scratch = torch.empty(max(lib().sb_op_gemv_scratch_bytes(M, K), 256), dtype=torch.uint8, device=x.device)
+    scratch = _unused_scratch(torch, x, u)
     check(lib().sb_op_gate_up(W.data_ptr(), _wdtype(W), N, K, x.data_ptr(), u.data_ptr(), M, kernel,
-                              scratch.data_ptr(), _stream_ptr(torch, x.device)))
+                              scratch.data_ptr(), _stream_ptr(torch, x)))
     return u
 
 
@@ -532,10 +544,11 @@ def op_head(W, x, T: float, kernel: int = PROJ_VALU, want_logits: bool = False):
     am = torch.empty(M, dtype=torch.int32, device=x.device)
     cf = torch.empty(M, dtype=torch.float32, device=x.device)
     logits = torch.empty((M, N), dtype=torch.float32, device=x.device) if want_logits else None
-    scratch = torch.zeros(lib().sb_op_head_scratch_bytes(M, N, K), dtype=torch.uint8, device=x.device)
+    # (nothing in it has to be cleared: a fill was a launch of 3.4 us before a head of 40)
+    scratch = torch.empty(lib().sb_op_head_scratch_bytes(M, N, K), dtype=torch.uint8, device=x.device)
     check(lib().sb_op_head(W.data_ptr(), _wdtype(W), N, K, x.data_ptr(), M, T, kernel, am.data_ptr(),
                            cf.data_ptr(), logits.data_ptr() if want_logits else None, scratch.data_ptr(),
-                           _stream_ptr(torch, x.device)))
+                           _stream_ptr(torch, x)))
     return am, cf, logits
 
 
@@ -545,7 +558,7 @@ def op_head_static(W, x, T: float, kernel: int, am, cf):
     import torch
     N, K = W.shape
     check(lib().sb_op_head_static(W.data_ptr(), _wdtype(W), N, K, x.data_ptr(), x.shape[0], T, kernel,
-                                  am.data_ptr(), cf.data_ptr(), _stream_ptr(torch, x.device)))
+                                  am.data_ptr(), cf.data_ptr(), _stream_ptr(torch, x)))
 
 
 def rope_table(head_dim: int, base: float, n_pos: int):
@@ -566,7 +579,7 @@ def op_attention(qkv, n_heads, n_kv_heads, head_dim, kv_dtype, pool, table, laye
                               dtype=torch.uint8, device=qkv.device)
     check(lib().sb_op_attention(qkv.data_ptr(), n_heads, n_kv_heads, head_dim, kv_dtype, pool.data_ptr(),
                                 table.data_ptr(), table.numel(), layer, rope_cos.data_ptr(), rope_sin.data_ptr(),
-                                pos0, M, out.data_ptr(), scratch.data_ptr(), _stream_ptr(torch, qkv.device)))
+                                pos0, M, out.data_ptr(), scratch.data_ptr(), _stream_ptr(torch, qkv)))
     return out
 
 
@@ -577,7 +590,7 @@ def op_prompt_attention(qkv, n_heads, n_kv_heads, head_dim, pool, table, layer, 
     out = torch.empty((M, n_heads * head_dim), dtype=torch.float32, device=qkv.device)
     check(lib().sb_op_prompt_attention(qkv.data_ptr(), n_heads, n_kv_heads, head_dim, pool.data_ptr(),
                                        table.data_ptr(), table.numel(), layer, rope_cos.data_ptr(),
-                                       rope_sin.data_ptr(), pos0, M, out.data_ptr(), _stream_ptr(torch, qkv.device)))
+                                       rope_sin.data_ptr(), pos0, M, out.data_ptr(), _stream_ptr(torch, qkv)))
     return out
 
 
@@ -586,10 +599,10 @@ def op_copy(dst, src):
     import torch
     n = src.numel() * src.element_size()
     assert dst.numel() * dst.element_size() == n
-    check(lib().sb_op_copy(dst.data_ptr(), src.data_ptr(), n, _stream_ptr(torch, src.device)))
+    check(lib().sb_op_copy(dst.data_ptr(), src.data_ptr(), n, _stream_ptr(torch, src)))
 
 
 def op_read(src, sink):
     import torch
     check(lib().sb_op_read(src.data_ptr(), src.numel() * src.element_size(), sink.data_ptr(),
-                           _stream_ptr(torch, src.device)))
+                           _stream_ptr(torch, src)))

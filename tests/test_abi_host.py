@@ -152,3 +152,12 @@ def test_new_config_fields_and_sizes_are_validated_on_the_host():
     assert L.sb_phase_timing(None, 1) == sb.EINVAL
     x = np.zeros(64, np.float32).ctypes.data
     assert L.sb_op_head_static(x, 0, 131072 + 16, 64, x, 1, 1.0, sb.PROJ_VALU, x, x, None) == sb.ECAPACITY
+
+
+def test_single_kernel_calls_refuse_host_tensors():
+    import torch
+    W, x = torch.zeros(16, 128), torch.zeros(1, 128)
+    for call in (lambda: sb.op_gemv(W, x), lambda: sb.op_gate_up(W, x), lambda: sb.op_head(W, x, 1.0),
+                 lambda: sb.op_rmsnorm(x, x[0], 1e-6), lambda: sb.op_copy(x, x.clone())):
+        with pytest.raises(ValueError):
+            call()
