@@ -12,6 +12,9 @@ namespace sb {
 // rows of one prompt pass (the decode passes have at most SB_MAX_W)
 #define SB_PREFILL_ROWS 128
 
+// columns of one partial sum of squares of a prompt row
+#define SB_PREFILL_SSQ 64
+
 // ---- device-resident record of the current round (read back once per sync) ----
 struct DevRound {
     int32_t slot_tok[SB_MAX_W + 1];  // input token of each row (row 0: pending token)
@@ -191,7 +194,7 @@ int prefill_attention_block_queries(int32_t n_heads, int32_t head_dim, int32_t M
 // that the passes' thread blocks meet on the same weights in the caches.  Activations
 // come as bf16 planes xs [2][plane_rows][K] (high parts, then low parts; row r of pass p
 // is row p * pass_rows + r); the product is left as k-split partial sums
-// part [n_pass][S][pass_rows][rows] for the epilogue that follows.
+// part [n_pass][S][rows / 16][pass_rows / 16][64 lanes][4] for the epilogue that follows (16 x 16 tiles as the matrix cores leave them).
 #define SB_PREFILL_PASSES 16
 struct GemmArgs {
     const void* Wp;      // packed weights [rows][K]
@@ -229,14 +232,14 @@ struct GemmEpiArgs {
     int32_t N, M, n_pass;  // output columns (rows, or rows / 2 for the gate/up pair), live rows, passes
     int32_t plane_rows;    // rows between the high and the low plane of nx / ys
     int32_t epi;           // EPI_STORE, EPI_RESID, EPI_SWIGLU
-    const float* ssq_in;   // [M][ssq_ld] partial sums of squares of the input rows
+    const float* ssq_in;   // [M][ssq_ld] partial sums of squares of the input rows (16-byte aligned, ssq_ld a multiple of 4)
     int32_t ssq_nb, ssq_ld, K;
     float eps;
     float* y;              // STORE: y = v; RESID: y += v        [M][ldy]
     int32_t ldy;
     const float* gain;     // RESID: nx = bf16 planes of gain * y (nullable)
     uint16_t* nx;
-    float* ssq_out;        // RESID: partial sums of squares of y per 256 columns
+    float* ssq_out;        // RESID: partial sums of squares of y per SB_PREFILL_SSQ columns
     uint16_t* ys;          // SWIGLU: bf16 planes of silu(gate) * up
     int32_t fused;         // the GEMM ran with this `fused` (row blocks with one partial are done)
 };

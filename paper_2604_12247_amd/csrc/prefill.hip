@@ -85,6 +85,24 @@ int gemm_splits(int32_t rows, int32_t K, int32_t n_pass, bool gate_up) { return 
 // Rows of a pass: the super-pass in n_pass equal parts, rounded up to whole column tiles.
 static int gemm_pass_rows(int32_t M, int32_t n_pass) { return ((M + n_pass - 1) / n_pass + 15) / 16 * 16; }
 
+// Of the n values at p (16-byte aligned, readable up to the next multiple of four) this thread's share, four at a time: thread i of LANES. U
+// loads in flight together (a loop of load and add would be a round trip for each, single values four times the requests).
+template <int LANES, int U>
+__device__ __forceinline__ float sum_share(const float* p, int i, int n) {
+    float t = 0.f;
+    for (int j0 = i * 4; j0 < n; j0 += LANES * 4 * U) {
+        float4 q[U];
+#pragma unroll
+        for (int k = 0; k < U; ++k) q[k] = *reinterpret_cast<const float4*>(p + (j0 + k * LANES * 4 < n ? j0 + k * LANES * 4 : 0));
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            const int j = j0 + k * LANES * 4;
+            t += ((j < n ? q[k].x : 0.f) + (j + 1 < n ? q[k].y : 0.f)) + ((j + 2 < n ? q[k].z : 0.f) + (j + 3 < n ? q[k].w : 0.f));
+        }
+    }
+    return t;
+}
+
 // ---- pieces of the GEMM kernel (all inlined; register arrays are passed by reference) ----
 struct GemmCtx {
     int KB, n_tiles, it1, wr;          // wr: the wave's row group
@@ -192,7 +210,9 @@ struct GemmStage {
 
 // Partial sum of row block b, or the finished tail where the row block's whole k range was this thread
 // block's; then zero for the next row block.  C layout: register r of lane l is weight row 4 (l / 16) + r
-// of the tile, activation row l % 16.
+// of the tile, activation row l % 16.  A partial sum is left as the registers hold it, 1 KB per weight tile and column tile, lane l's four
+// values at 16 l: as rows of the result, 64 bytes of each of 16 rows per store, the launches took 4 to 6 % longer
+// ([22016 x 4096] at 512 rows 154 us, now 144; without any partial sums 132).
 template <int RT, int CT, bool SWI>
 __device__ __forceinline__ void gemm_flush(f32x4 (&acc)[RT][CT], const GemmArgs& a, const GemmCtx& c, int b, int q,
                                            const float* s_inv, int lane) {
@@ -218,11 +238,8 @@ __device__ __forceinline__ void gemm_flush(f32x4 (&acc)[RT][CT], const GemmArgs&
                 }
             }
         }
-    } else {
-        const bool store = !SWI && a.fused && whole;
-        const int slot = c.cid - first;
-        float* const y = store ? a.y + (size_t)c.row0 * a.ldy : a.part + (size_t)(c.pass * a.S + slot) * a.pass_rows * a.rows;
-        const int ld = store ? a.ldy : a.rows;
+    } else if (!SWI && a.fused && whole) {
+        float* const y = a.y + (size_t)c.row0 * a.ldy;
 #pragma unroll
         for (int t = 0; t < RT; ++t) {
             const int tile = gemm_tile<RT, SWI>(c, b, t);
@@ -230,11 +247,20 @@ __device__ __forceinline__ void gemm_flush(f32x4 (&acc)[RT][CT], const GemmArgs&
             for (int ct = 0; ct < CT; ++ct) {
                 const int m = ct * 16 + li;
                 if (tile >= 0 && m < c.Mp) {
-                    const float f = store ? s_inv[m] : 1.0f;
+                    const float f = s_inv[m];
                     const f32x4 v = acc[t][ct];
-                    *reinterpret_cast<float4*>(y + (size_t)m * ld + tile * 16 + sub) = make_float4(v[0] * f, v[1] * f, v[2] * f, v[3] * f);
+                    *reinterpret_cast<float4*>(y + (size_t)m * a.ldy + tile * 16 + sub) = make_float4(v[0] * f, v[1] * f, v[2] * f, v[3] * f);
                 }
             }
+        }
+    } else {
+        float* const p = a.part + (size_t)(c.pass * a.S + c.cid - first) * a.pass_rows * a.rows + lane * 4;
+#pragma unroll
+        for (int t = 0; t < RT; ++t) {
+            const int tile = gemm_tile<RT, SWI>(c, b, t);
+            if (tile < 0) continue;
+#pragma unroll
+            for (int ct = 0; ct < CT; ++ct) *reinterpret_cast<f32x4*>(p + ((size_t)tile * CT + ct) * 256) = acc[t][ct];
         }
     }
 #pragma unroll
@@ -313,8 +339,7 @@ __global__ __launch_bounds__(64 * WPB) void prefill_gemm_kernel(GemmArgs a, int 
     if (a.fused) {  // 1 / rms of this pass's input rows, from the partial sums of squares their producer left
         const int m = tid >> 2, part = tid & 3;
         float t = 0.f;
-        if (a.ssq_in && m < c.Mp)
-            for (int i = part; i < a.ssq_nb; i += 4) t += a.ssq_in[(size_t)(c.row0 + m) * a.ssq_ld + i];
+        if (a.ssq_in) t = sum_share<4, 6>(a.ssq_in + (size_t)(c.row0 + (m < c.Mp ? m : 0)) * a.ssq_ld, part, a.ssq_nb);
         t += __shfl_xor(t, 1, 64);
         t += __shfl_xor(t, 2, 64);
         if (part == 0) s_inv[m] = a.ssq_in ? 1.0f / sqrtf(t / (float)a.K + a.eps) : 1.0f;
@@ -430,7 +455,7 @@ hipError_t launch_prefill_gemm(const GemmArgs& a_, hipStream_t st) {
     if (a.fused != 0 && a.fused != 1 + EPI_STORE && a.fused != 1 + EPI_SWIGLU) return hipErrorInvalidValue;
     if (a.fused == 1 + EPI_SWIGLU && (a.rows != 2 * a.N || a.N % 16 || !a.ys)) return hipErrorInvalidValue;
     if (a.fused == 1 + EPI_STORE && (a.rows != a.N || !a.y || a.ldy < a.N || a.ldy % 4)) return hipErrorInvalidValue;
-    if (a.fused && a.ssq_in && (a.ssq_nb < 1 || a.ssq_ld < a.ssq_nb)) return hipErrorInvalidValue;
+    if (a.fused && a.ssq_in && (a.ssq_nb < 1 || a.ssq_ld < a.ssq_nb || a.ssq_ld % 4 || ((uintptr_t)a.ssq_in & 15))) return hipErrorInvalidValue;
     // XCD array shape, by measurement at the 7B shapes: with few passes the weights dominate what the
     // L2s fetch (one L2 per range: 8 % faster than every L2 fetching everything at 4 passes); with many
     // passes the activations weigh as much and 2 x 4 is 2 % ahead of both 8 x 1 and 1 x 8
@@ -465,108 +490,164 @@ __device__ __forceinline__ int splits_of(const GemmSplitMap& mp, int n) {
     return (int)(((b + 1) * mp.KB - 1) / (uint32_t)mp.q - b * mp.KB / (uint32_t)mp.q) + 1;
 }
 
-// Partial sums of four neighbouring elements, added in slot order; eight loads in flight at a time.
-__device__ __forceinline__ float4 sum_splits4(const float* p, size_t plane, int n_splits) {
-    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int s0 = 0; s0 < n_splits; s0 += 8) {
-        float4 t[8];
+// This lane's four values of TN neighbouring weight tiles, one column tile (16 rows): the partial sums added in slot order, U
+// slots in flight at a time.  p: the first tile's piece in slot 0, tile_stride and plane in floats.
+template <int TN, int U>
+__device__ __forceinline__ void sum_splits(f32x4 (&v)[TN], const float* p, size_t tile_stride, size_t plane, int n_splits) {
 #pragma unroll
-        for (int i = 0; i < 8; ++i)
-            t[i] = s0 + i < n_splits ? *reinterpret_cast<const float4*>(p + (size_t)(s0 + i) * plane) : make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int t = 0; t < TN; ++t) v[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int s0 = 0; s0 < n_splits; s0 += U) {
+        f32x4 x[U][TN];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) { v.x += t[i].x; v.y += t[i].y; v.z += t[i].z; v.w += t[i].w; }
+        for (int i = 0; i < U; ++i)
+#pragma unroll
+            for (int t = 0; t < TN; ++t) {
+                x[i][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+                if (s0 + i < n_splits) x[i][t] = *reinterpret_cast<const f32x4*>(p + (size_t)(s0 + i) * plane + t * tile_stride);   // (uniform)
+            }
+#pragma unroll
+        for (int i = 0; i < U; ++i)
+#pragma unroll
+            for (int t = 0; t < TN; ++t) v[t] += x[i][t];
     }
-    return v;
 }
-// grid (ceil(N / 256), ceil(M / 4)), 256 threads: a wave takes one row and 256 columns, a
-// lane four neighbouring columns (all in one row block, hence with the same partial sums)
-template <int EPI>
+// grid (ceil(N / (64 TN)), column tiles of all passes), 256 threads: a block takes 16 rows and 64 TN columns.  The sums are read as the
+// GEMM left them, a 1 KB piece per load, a wave TN weight tiles, and turned in LDS: then 16 TN lanes have a row's neighbouring
+// columns, and what is loaded and stored is whole cache lines (1999 rows, N = 6144: launch and GEMM 179 -> 169 us, of which 24 -> 20 here, with
+// rows of float4 read from row-major partial sums before).  The sums of squares are left per 64 columns.
+template <int EPI, int TN>
 __global__ __launch_bounds__(256) void prefill_epilogue_kernel(GemmEpiArgs a, GemmSplitMap mp) {
-    const int lane = threadIdx.x & 63;
-    const int m = blockIdx.y * 4 + (threadIdx.x >> 6);  // row of the super-pass
-    const int n = blockIdx.x * 256 + lane * 4;
-    if (m >= a.M) return;
+    constexpr int COLS = 64 * TN, LD = COLS + 4, U = TN == 1 ? 8 : 2;   // (LDS rows four banks apart)
+    __shared__ __attribute__((aligned(16))) float turn[16 * LD];
+    __shared__ float s_inv[16];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int CT = mp.pass_rows / 16, pass = blockIdx.y / CT, ct = blockIdx.y - pass * CT;
+    const int m0 = pass * mp.pass_rows + ct * 16;   // first row, in the super-pass
+    const int rows = a.M - m0;                      // live rows from there (a pass before the last is full)
+    if (rows <= 0) return;
     const bool fused = (EPI == EPI_SWIGLU || EPI == EPI_STORE) && a.fused;
-    const int sp = n < a.N ? splits_of(mp, n) : 0;
-    // (row blocks that the GEMM finished: a whole wave of them leaves before it reads anything; [28672 x 4096] at 1999 rows, where they are
-    // six in seven, took 46 us with every wave adding up its row's sums of squares first, now 29)
-    if (fused && __builtin_amdgcn_ballot_w64(sp > 1) == 0) return;
-    float inv = 1.0f;
-    if (a.ssq_in) {  // (added in index order; sixteen loads in flight at a time)
-        float t = 0.f;
-        for (int b0 = 0; b0 < a.ssq_nb; b0 += 16) {
-            float q[16];
-#pragma unroll
-            for (int i = 0; i < 16; ++i) q[i] = b0 + i < a.ssq_nb ? a.ssq_in[(size_t)m * a.ssq_ld + b0 + i] : 0.f;
-#pragma unroll
-            for (int i = 0; i < 16; ++i) t += q[i];
-        }
-        inv = 1.0f / sqrtf(t / (float)a.K + a.eps);
+    const int nb0 = blockIdx.x * COLS, nt = nb0 + wave * TN * 16;   // the block's first column, this wave's (its tiles lie in one row block)
+    const bool skip = nt >= a.N || (fused && splits_of(mp, nt) == 1);   // (past the end, or finished by the GEMM)
+    // ([28672 x 4096] at 1999 rows, where the GEMM finishes six row blocks in seven, took 46 us with every wave adding up its rows' sums
+    // of squares first, 29 without)
+    if (fused && __syncthreads_and(skip)) return;
+    if (a.ssq_in) {   // scales of the rows
+        const int r = tid >> 4, i = tid & 15;
+        const float t = lanes_sum<8>(sum_share<16, 2>(a.ssq_in + (size_t)(m0 + (r < rows ? r : 0)) * a.ssq_ld, i, a.ssq_nb));
+        if (i == 0) s_inv[r] = 1.0f / sqrtf(t / (float)a.K + a.eps);
     }
-    const size_t plane = (size_t)mp.pass_rows * a.rows;
-    const float* p = a.part + ((size_t)(m / mp.pass_rows) * a.S * mp.pass_rows + m % mp.pass_rows) * a.rows;
-    float sq = 0.f;
-    if (n < a.N) {
-        if (EPI == EPI_SWIGLU && fused) {
-            // (a row block holds gate and up tiles side by side; one partial = finished by the GEMM)
-            if (sp > 1) {
-                const float4 g = sum_splits4(p + n, plane, sp);
-                const float4 u = sum_splits4(p + a.N + n, plane, sp);
-                const float4 v = make_float4(silu_mul(g.x * inv, u.x * inv), silu_mul(g.y * inv, u.y * inv),
-                                             silu_mul(g.z * inv, u.z * inv), silu_mul(g.w * inv, u.w * inv));
-                split_store4(a.ys, a.N, a.plane_rows, m, n, v);
-            }
-        } else if (EPI == EPI_SWIGLU) {
-            const float4 g = sum_splits4(p + n, plane, sp);
-            const float4 u = sum_splits4(p + a.N + n, plane, splits_of(mp, a.N + n));
-            const float4 v = make_float4(silu_mul(g.x * inv, u.x * inv), silu_mul(g.y * inv, u.y * inv),
-                                         silu_mul(g.z * inv, u.z * inv), silu_mul(g.w * inv, u.w * inv));
-            split_store4(a.ys, a.N, a.plane_rows, m, n, v);
-        } else if (EPI == EPI_STORE && fused && sp == 1) {
-            // (finished by the GEMM)
-        } else {
-            float4 v = sum_splits4(p + n, plane, sp);
-            v.x *= inv; v.y *= inv; v.z *= inv; v.w *= inv;
-            float4* yp = reinterpret_cast<float4*>(a.y + (size_t)m * a.ldy + n);
-            if (EPI == EPI_RESID) {
-                const float4 y0 = *yp;
-                v.x += y0.x; v.y += y0.y; v.z += y0.z; v.w += y0.w;
-                if (a.nx) {
-                    const float4 gn = *reinterpret_cast<const float4*>(a.gain + n);
-                    split_store4(a.nx, a.N, a.plane_rows, m, n, make_float4(v.x * gn.x, v.y * gn.y, v.z * gn.z, v.w * gn.w));
+    const int li = lane & 15, lq = lane >> 4;
+    f32x4 v[TN], u[TN];
+    if (!skip) {
+        const size_t plane = (size_t)mp.pass_rows * a.rows, tstride = (size_t)CT * 256;
+        const float* const p0 = a.part + (size_t)pass * a.S * plane + (size_t)lane * 4;
+        const int sp = splits_of(mp, nt);
+        const bool full = nt + TN * 16 <= a.N;
+        const auto sum = [&](f32x4 (&x)[TN], int c0, int splits) {
+            const float* p = p0 + ((size_t)(c0 / 16) * CT + ct) * 256;
+            // (the last wave of a row may have fewer tiles: the first again, not stored)
+            sum_splits<TN, U>(x, p, full ? tstride : 0, plane, splits);
+            if (TN > 1 && !full)
+#pragma unroll
+                for (int t = 1; t < TN; ++t)
+                    if (nt + t * 16 < a.N) {
+                        f32x4 one[1];
+                        sum_splits<1, 4>(one, p + t * tstride, 0, plane, splits);
+                        x[t] = one[0];
+                    }
+        };
+        sum(v, nt, sp);
+        if (EPI == EPI_SWIGLU) sum(u, a.N + nt, sp);   // (a row block holds gate and up tiles side by side)
+    }
+    if constexpr (TN == 1 && EPI != EPI_RESID) {   // (as the registers hold them: a short launch gains more by a barrier less)
+        if (a.ssq_in) __syncthreads();
+        if (skip || li >= rows) return;
+        const float inv = a.ssq_in ? s_inv[li] : 1.0f;
+        const int m = m0 + li, n = nt + lq * 4;
+        if (EPI == EPI_SWIGLU)
+            split_store4(a.ys, a.N, a.plane_rows, m, n, make_float4(silu_mul(v[0][0] * inv, u[0][0] * inv), silu_mul(v[0][1] * inv, u[0][1] * inv),
+                                                                    silu_mul(v[0][2] * inv, u[0][2] * inv), silu_mul(v[0][3] * inv, u[0][3] * inv)));
+        else
+            *reinterpret_cast<float4*>(a.y + (size_t)m * a.ldy + n) = make_float4(v[0][0] * inv, v[0][1] * inv, v[0][2] * inv, v[0][3] * inv);
+        return;
+    }
+    // this thread's four columns, the same for all of its TN rows; what the residual needs of them is on its way while the block turns its tiles
+    const int c4 = (tid % (16 * TN)) * 4, n = nb0 + c4, r0 = tid / (16 * TN);
+    const bool mine = n < a.N && !(fused && splits_of(mp, n) == 1);
+    float4 gn = make_float4(0.f, 0.f, 0.f, 0.f), y0[TN];
+    if (EPI == EPI_RESID && mine) {
+        if (a.nx) gn = *reinterpret_cast<const float4*>(a.gain + n);
+#pragma unroll
+        for (int k = 0; k < TN; ++k) {
+            const int r = r0 + k * (16 / TN);
+            y0[k] = *reinterpret_cast<const float4*>(a.y + (size_t)(m0 + (r < rows ? r : 0)) * a.ldy + n);
+        }
+    }
+    if (a.ssq_in) __syncthreads();
+    if (!skip) {
+        const float inv = a.ssq_in ? s_inv[li] : 1.0f;
+#pragma unroll
+        for (int t = 0; t < TN; ++t) {
+            f32x4 x;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) x[r] = EPI == EPI_SWIGLU ? silu_mul(v[t][r] * inv, u[t][r] * inv) : v[t][r] * inv;
+            *reinterpret_cast<f32x4*>(turn + li * LD + (wave * TN + t) * 16 + lq * 4) = x;
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < TN; ++k) {
+        const int r = r0 + k * (16 / TN), m = m0 + r;
+        float sq = 0.f;
+        if (mine && r < rows) {
+            float4 x = *reinterpret_cast<const float4*>(turn + r * LD + c4);
+            if (EPI == EPI_SWIGLU) {
+                split_store4(a.ys, a.N, a.plane_rows, m, n, x);
+            } else {
+                if (EPI == EPI_RESID) {
+                    x.x += y0[k].x; x.y += y0[k].y; x.z += y0[k].z; x.w += y0[k].w;
+                    if (a.nx) split_store4(a.nx, a.N, a.plane_rows, m, n, make_float4(x.x * gn.x, x.y * gn.y, x.z * gn.z, x.w * gn.w));
+                    sq = (x.x * x.x + x.y * x.y) + (x.z * x.z + x.w * x.w);
                 }
-                sq = (v.x * v.x + v.y * v.y) + (v.z * v.z + v.w * v.w);
+                *reinterpret_cast<float4*>(a.y + (size_t)m * a.ldy + n) = x;
             }
-            *yp = v;
+        }
+        if (EPI == EPI_RESID && a.ssq_out) {
+            sq = lanes_sum<8>(sq);
+            if ((lane & 15) == 0 && mine && r < rows) a.ssq_out[(size_t)m * a.ssq_ld + n / SB_PREFILL_SSQ] = sq;
         }
     }
-    if (EPI == EPI_RESID && a.ssq_out) {
-        sq = wave_sum(sq);
-        if (lane == 0) a.ssq_out[(size_t)m * a.ssq_ld + blockIdx.x] = sq;
-    }
+}
+template <int EPI, int TN>
+static void launch_epilogue_t(const GemmEpiArgs& a, const GemmSplitMap& mp, hipStream_t st) {
+    const dim3 grid((a.N + 64 * TN - 1) / (64 * TN), a.n_pass * (mp.pass_rows / 16));
+    prefill_epilogue_kernel<EPI, TN><<<grid, 256, 0, st>>>(a, mp);
 }
 
 hipError_t launch_prefill_epilogue(const GemmEpiArgs& a, hipStream_t st) {
     if (a.M < 1 || a.N < 1 || a.S < 1 || a.n_pass != (a.M + PM - 1) / PM || a.plane_rows < a.M) return hipErrorInvalidValue;
     if (a.epi == EPI_SWIGLU ? (!a.ys || a.rows != 2 * a.N) : (!a.y || a.rows != a.N)) return hipErrorInvalidValue;
-    if (a.ssq_out && (a.N + 255) / 256 > a.ssq_ld) return hipErrorInvalidValue;
-    if (a.N % 4 || a.ldy % 4) return hipErrorInvalidValue;
-    dim3 grid((a.N + 255) / 256, (a.M + 3) / 4);
+    if (a.ssq_out && (a.N + SB_PREFILL_SSQ - 1) / SB_PREFILL_SSQ > a.ssq_ld) return hipErrorInvalidValue;
+    if (a.N % 16 || a.ldy % 4) return hipErrorInvalidValue;
+    if (a.ssq_in && (a.ssq_nb < 1 || a.ssq_ld < a.ssq_nb || a.ssq_ld % 4 || ((uintptr_t)a.ssq_in & 15))) return hipErrorInvalidValue;
     const GemmPlan pl = gemm_plan(a.rows, a.K, a.n_pass, a.fused == 1 + EPI_SWIGLU);
     if (a.S != pl.smax) return hipErrorInvalidValue;
-    if (a.fused && a.fused != 1 + a.epi) return hipErrorInvalidValue;
-    const GemmSplitMap mp{a.epi == EPI_SWIGLU && a.fused ? pl.block_rows / 2 : pl.block_rows, a.K >> 7, pl.q,
+    if ((a.fused && a.fused != 1 + a.epi) || (a.epi == EPI_SWIGLU && !a.fused)) return hipErrorInvalidValue;
+    const GemmSplitMap mp{a.epi == EPI_SWIGLU ? pl.block_rows / 2 : pl.block_rows, a.K >> 7, pl.q,
                           gemm_pass_rows(a.M, a.n_pass)};
-    switch (a.epi) {
-        case EPI_STORE: prefill_epilogue_kernel<EPI_STORE><<<grid, 256, 0, st>>>(a, mp); break;
-        case EPI_RESID: prefill_epilogue_kernel<EPI_RESID><<<grid, 256, 0, st>>>(a, mp); break;
-        case EPI_SWIGLU: prefill_epilogue_kernel<EPI_SWIGLU><<<grid, 256, 0, st>>>(a, mp); break;
-        default: return hipErrorInvalidValue;
-    }
+    if (a.epi != EPI_STORE && a.epi != EPI_RESID && a.epi != EPI_SWIGLU) return hipErrorInvalidValue;
+    // A wave with four weight tiles stores whole rows of 1 KB; with one there are four times the blocks, which a launch of few
+    // needs and a residual, bound by what it reads, takes throughout. GEMM and epilogue, four / one, us: STORE [12288 x 4096] at 512 rows (1536 blocks) 100.4 / 104.5, 128 rows
+    // (384) 44.1 / 44.3, [15360 x 5120] at 45 rows (180) 38.1 / 36.9; SwiGLU [22016 x 4096] at 512 rows (1376) 163.5 / 164.7, [27648 x 5120] at 1000 rows 436 / 448, at 128
+    // rows (432) 90.0 / 89.5, 45 rows (162) 62.8 / 61.8; residual [4096 x 4096] at 512 rows 41.7 / 40.8, [5120 x 13824] at 45 rows 35.0 / 32.2, at 1999 rows the same.
+    const long wide_blocks = (long)((a.N + 255) / 256) * a.n_pass * (mp.pass_rows / 16);
+    if (a.epi == EPI_RESID) launch_epilogue_t<EPI_RESID, 1>(a, mp, st);
+    else if (a.epi == EPI_STORE) wide_blocks >= 512 ? launch_epilogue_t<EPI_STORE, 4>(a, mp, st) : launch_epilogue_t<EPI_STORE, 1>(a, mp, st);
+    else wide_blocks >= 512 ? launch_epilogue_t<EPI_SWIGLU, 4>(a, mp, st) : launch_epilogue_t<EPI_SWIGLU, 1>(a, mp, st);
     return hipGetLastError();
 }
 
-// grid (ceil(d / 2048), M), d % 8 == 0: a thread takes eight neighbouring columns, the 32 lanes of half a wave the 256
+// grid (ceil(d / 2048), M), d % 8 == 0: a thread takes eight neighbouring columns, eight lanes the 64
 // columns of one partial sum of squares (16-byte stores throughout: 1999 rows of 4096 took 37 us with two-byte ones)
 template <typename WT>
 __global__ __launch_bounds__(256) void prefill_embed_kernel(const WT* __restrict__ E, int vocab, int d,
@@ -586,15 +667,16 @@ __global__ __launch_bounds__(256) void prefill_embed_kernel(const WT* __restrict
         for (int k = 0; k < 8; ++k) sq += v[k] * v[k];
     }
     if (ssq_out) {
-        sq = lanes_sum<16>(sq);
-        if ((tid & 31) == 0 && n < d) ssq_out[(size_t)m * ssq_ld + n / 256] = sq;
+        static_assert(SB_PREFILL_SSQ == 64, "eight lanes of eight columns");
+        sq = lanes_sum<4>(sq);
+        if ((tid & 7) == 0 && n < d) ssq_out[(size_t)m * ssq_ld + n / SB_PREFILL_SSQ] = sq;
     }
 }
 
 hipError_t launch_prefill_embed(const void* E, int32_t w_dtype, int32_t vocab, int32_t d, const int32_t* tokens,
                                 int32_t M, float* H, const float* gain, uint16_t* nx, int32_t plane_rows,
                                 float* ssq_out, int32_t ssq_ld, hipStream_t st) {
-    if (M < 1 || plane_rows < M || d % 8 || (ssq_out && (d + 255) / 256 > ssq_ld)) return hipErrorInvalidValue;
+    if (M < 1 || plane_rows < M || d % 8 || (ssq_out && (d + SB_PREFILL_SSQ - 1) / SB_PREFILL_SSQ > ssq_ld)) return hipErrorInvalidValue;
     dim3 grid((d + 2047) / 2048, M);
     if (w_dtype == SB_BF16)
         prefill_embed_kernel<uint16_t><<<grid, 256, 0, st>>>((const uint16_t*)E, vocab, d, tokens, H, gain, nx, plane_rows,

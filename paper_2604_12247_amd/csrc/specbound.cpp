@@ -116,7 +116,7 @@ WsLayout ws_layout(const sb_config* c) {
         size_t RS = (size_t)(c->max_seq + PM - 1) / PM * PM;
         if (RS > PM * SB_PREFILL_PASSES) RS = PM * SB_PREFILL_PASSES;
         L.p_rows = (int)RS;
-        L.p_ssq_ld = (int)((d + 255) / 256);
+        L.p_ssq_ld = (int)((d + 4 * SB_PREFILL_SSQ - 1) / (4 * SB_PREFILL_SSQ) * 4);
         L.p_tok = take((size_t)c->max_seq * 4);
         L.p_H = take(RS * d * 4);
         L.p_xs = take(2 * RS * d * 2);
@@ -428,7 +428,7 @@ int prefill_gemm_impl(sb_session* s, const int32_t* prompt, int32_t n, int32_t* 
     hipStream_t st = m->stream;
     const int d = c.d_model, f = c.d_ffn, hq = c.n_heads * c.head_dim;
     const int qkv_rows = (c.n_heads + 2 * c.n_kv_heads) * c.head_dim;
-    const int nb_d = (d + 255) / 256, PM = SB_PREFILL_ROWS, RS = s->L.p_rows;
+    const int nb_d = (d + SB_PREFILL_SSQ - 1) / SB_PREFILL_SSQ, PM = SB_PREFILL_ROWS, RS = s->L.p_rows;
     int32_t* toks = wsp<int32_t>(s, s->L.p_tok);
     float* H = wsp<float>(s, s->L.p_H);
     uint16_t* xs = wsp<uint16_t>(s, s->L.p_xs);

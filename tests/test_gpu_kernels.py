@@ -146,6 +146,22 @@ def test_prompt_pass_gemm_heights(T, N, K, M):
     assert float((y - ref).abs().max()) <= 3e-5 * float(ref.abs().max())
 
 
+# the epilogue's two forms (512 blocks of 256 columns and 16 rows: N = 20480 at seven and six column tiles) with one to four weight
+# tiles in the last wave, rows that end inside a column tile, one and several partial sums
+@pytest.mark.parametrize("N", [20480, 20496, 20512, 20528, 48])
+@pytest.mark.parametrize("K", [128, 1280])
+@pytest.mark.parametrize("M", [90, 100, 33])
+def test_prompt_pass_gemm_last_columns(T, N, K, M):
+    import paper_2604_12247_amd as sb
+    g = T.Generator(device="cuda")
+    g.manual_seed(N + K + M)
+    W = (T.randn(N, K, generator=g, device="cuda") * 0.02).to(T.bfloat16)
+    x = T.randn(M, K, generator=g, device="cuda")
+    y = sb.op_gemm(sb.op_repack(W), x).double()
+    ref = x.double() @ W.double().t().contiguous()
+    assert float((y - ref).abs().max()) <= 3e-5 * float(ref.abs().max())   # 16-bit activation parts, as in test_prompt_pass_gemm
+
+
 # a single pass whose thread blocks own 9, 10, 15, 16 and 17 k blocks: odd numbers of weight blocks are requested whole
 @pytest.mark.parametrize("N,K", [(17088, 4096), (7184, 10368), (20480, 6144), (20480, 6528), (20480, 6784)])
 @pytest.mark.parametrize("M", [9, 40, 128])
