@@ -75,36 +75,110 @@ __device__ __forceinline__ uint4 pick(bool c, uint4 a, uint4 b) {
     return make_uint4(c ? a.x : b.x, c ? a.y : b.y, c ? a.z : b.z, c ? a.w : b.w);
 }
 
-// The new rows' keys and values of kv head g (at most SB_MAX_W rows), an element of a pair or a value per thread: loaded with everything
+// N neighbouring floats: one load where the operands are 16-byte aligned (VEC), else N.
+template <int N, bool VEC>
+__device__ __forceinline__ void load_near(const float* p, float (&v)[N]) {
+    typedef float vec_t __attribute__((ext_vector_type(N == 1 ? 2 : N)));
+    if constexpr (N > 1 && VEC) {
+        const vec_t t = *reinterpret_cast<const vec_t*>(p);
+#pragma unroll
+        for (int i = 0; i < N; ++i) v[i] = t[i];
+    } else {
+#pragma unroll
+        for (int i = 0; i < N; ++i) v[i] = p[i];
+    }
+}
+// N neighbouring values into LDS at a multiple of their size
+template <int N, typename T>
+__device__ __forceinline__ void store_near(T* p, const T (&v)[N]) {
+    if constexpr (N == 1) {
+        p[0] = v[0];
+    } else {
+        typedef T vec_t __attribute__((ext_vector_type(N)));
+        vec_t t;
+#pragma unroll
+        for (int i = 0; i < N; ++i) t[i] = v[i];
+        *reinterpret_cast<vec_t*>(p) = t;
+    }
+}
+
+// Row of a kv head's query qq (row-major over the head's group), qq / G.  VEC: by a multiplication with 2^32 / G rounded up, exact while
+// qq (G - 1) < 2^32, as attn_fast sees to; a division by a number that only the launch knows is some forty instructions, here in
+// front of the query loads.
+template <bool VEC>
+__device__ __forceinline__ int attn_row(const AttnArgs& a, int qq) {
+    if constexpr (VEC) return a.g_inv ? (int)__umulhi((uint32_t)qq, a.g_inv) : qq;   // (0: one query per row and kv head)
+    else return qq / (a.n_heads / a.kv.n_kv_heads);
+}
+
+// The queries of a block with their rotary factors, four pairs per thread.  VEC: four loads of 16 bytes each instead of sixteen.
+template <int HD, bool VEC>
+struct QueryRows {
+    static constexpr int HALF = HD / 2, TPQ = HALF / 4;   // threads per query
+    float x[4], y[4], c[4], sn[4];
+    bool live;
+    static __device__ __forceinline__ int query() { return threadIdx.x / TPQ; }
+    static __device__ __forceinline__ int dim() { return threadIdx.x % TPQ * 4; }
+    // queries q0 .. q0 + nq - 1 of kv head g; the others read the first one and count as zeros
+    __device__ __forceinline__ void load(const AttnArgs& a, int g, int q0, int nq) {
+        const int G = a.n_heads / a.kv.n_kv_heads, qi = query(), j = dim();
+        live = qi < nq;
+        const int qq = q0 + (live ? qi : 0), r = attn_row<VEC>(a, qq), gi = qq - r * G;
+        const float* qp = a.q + (size_t)r * a.qkv_rows + (size_t)(g * G + gi) * HD + j;
+        const size_t rope = (size_t)(a.pos0 + r) * HALF + j;
+        load_near<sizeof(x) / 4, VEC>(qp, x);
+        load_near<sizeof(y) / 4, VEC>(qp + HALF, y);
+        load_near<sizeof(c) / 4, VEC>(a.rope_cos + rope, c);
+        load_near<sizeof(sn) / 4, VEC>(a.rope_sin + rope, sn);
+    }
+    // rotated: dims j .. j + 3 and, HALF further, their partners
+    __device__ __forceinline__ void rotate(float (&lo)[4], float (&hi)[4]) const {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const float u = x[e] * c[e] - y[e] * sn[e], v = y[e] * c[e] + x[e] * sn[e];
+            lo[e] = live ? u : 0.f;
+            hi[e] = live ? v : 0.f;
+        }
+    }
+};
+
+// The new rows' keys and values of kv head g (at most SB_MAX_W rows), HD / 64 pairs and HD / 32 values per thread: loaded with everything
 // else a block reads, rotated and rounded once, and left in LDS for the lanes whose keys they are.
-template <int HD>
+template <int HD, bool VEC>
 struct NewRows {
     static constexpr int HALF = HD / 2, NP = HALF / 32, NV = HD / 32;
     float x[NP], y[NP], c[NP], sn[NP], v[NV];
     __device__ __forceinline__ void load(const AttnArgs& a, int g) {
-        const int r = threadIdx.x >> 5, j = threadIdx.x & 31;   // 32 threads per row
-        const float* kp = a.q + (size_t)(r < a.M ? r : 0) * a.qkv_rows + (size_t)(a.n_heads + g) * HD + j;
-        const float* vp = kp + (size_t)a.kv.n_kv_heads * HD;
-        const size_t rope = (size_t)(a.pos0 + (r < a.M ? r : 0)) * HALF + j;
-#pragma unroll
-        for (int i = 0; i < NP; ++i) {
-            x[i] = kp[i * 32]; y[i] = kp[i * 32 + HALF];
-            c[i] = a.rope_cos[rope + i * 32]; sn[i] = a.rope_sin[rope + i * 32];
-        }
-#pragma unroll
-        for (int i = 0; i < NV; ++i) v[i] = vp[i * 32];
+        const int r = threadIdx.x >> 5, i = threadIdx.x & 31;   // 32 threads per row
+        const float* kp = a.q + (size_t)(r < a.M ? r : 0) * a.qkv_rows + (size_t)(a.n_heads + g) * HD;
+        const size_t rope = (size_t)(a.pos0 + (r < a.M ? r : 0)) * HALF + i * NP;
+        load_near<sizeof(x) / 4, VEC>(kp + i * NP, x);
+        load_near<sizeof(y) / 4, VEC>(kp + i * NP + HALF, y);
+        load_near<sizeof(c) / 4, VEC>(a.rope_cos + rope, c);
+        load_near<sizeof(sn) / 4, VEC>(a.rope_sin + rope, sn);
+        load_near<sizeof(v) / 4, VEC>(kp + (size_t)a.kv.n_kv_heads * HD + i * NV, v);
     }
-    template <typename KVT, int LDK>
+    // V_BY_DIM: the values by dim, 16 keys each from key pos0 & ~7 on, else by row
+    template <typename KVT, int LDK, bool V_BY_DIM>
     __device__ __forceinline__ void store(const AttnArgs& a, KVT* k_s, KVT* v_s) const {
-        const int r = threadIdx.x >> 5, j = threadIdx.x & 31;
+        const int r = threadIdx.x >> 5, i = threadIdx.x & 31;
         if (r >= a.M) return;
+        KVT lo[NP], hi[NP], w[NV];
 #pragma unroll
-        for (int i = 0; i < NP; ++i) {
-            k_s[r * LDK + j + i * 32] = kv_round<KVT>(rope_lo(x[i], y[i], c[i], sn[i]));
-            k_s[r * LDK + j + i * 32 + HALF] = kv_round<KVT>(rope_hi(x[i], y[i], c[i], sn[i]));
+        for (int k = 0; k < NP; ++k) {
+            lo[k] = kv_round<KVT>(rope_lo(x[k], y[k], c[k], sn[k]));
+            hi[k] = kv_round<KVT>(rope_hi(x[k], y[k], c[k], sn[k]));
         }
 #pragma unroll
-        for (int i = 0; i < NV; ++i) v_s[r * HD + j + i * 32] = kv_round<KVT>(v[i]);
+        for (int k = 0; k < NV; ++k) w[k] = kv_round<KVT>(v[k]);
+        store_near(k_s + r * LDK + i * NP, lo);
+        store_near(k_s + r * LDK + i * NP + HALF, hi);
+        if constexpr (V_BY_DIM) {
+#pragma unroll
+            for (int k = 0; k < NV; ++k) v_s[(i * NV + k) * 16 + (a.pos0 & 7) + r] = w[k];
+        } else {
+            store_near(v_s + r * HD + i * NV, w);
+        }
     }
 };
 
@@ -195,7 +269,7 @@ __global__ __launch_bounds__(256, 4) void attn_kernel(AttnArgs a) {
             qsn[it] = a.rope_sin[(size_t)(a.pos0 + r) * HALF + j];
         }
     }
-    NewRows<HD> nr;
+    NewRows<HD, false> nr;
     if (!MANY && has_new) nr.load(a, g);
     uint4 kreg[NKV];
     // element offset of this thread's K slice inside the K pool of the layer
@@ -217,7 +291,7 @@ __global__ __launch_bounds__(256, 4) void attn_kernel(AttnArgs a) {
         qs[qi * HD + j] = qx[it] * qc[it] - qy[it] * qsn[it];
         qs[qi * HD + j + HALF] = qy[it] * qc[it] + qx[it] * qsn[it];
     }
-    if (!MANY && has_new) nr.template store<KVT, HD>(a, nk_s, nv_s);
+    if (!MANY && has_new) nr.template store<KVT, HD, false>(a, nk_s, nv_s);
     __syncthreads();
     if (LATE_V) {
         __builtin_amdgcn_sched_barrier(0);
@@ -399,8 +473,10 @@ __global__ __launch_bounds__(256, 4) void attn_kernel(AttnArgs a) {
 // What bounds it: the chain page table -> operands -> scores -> soft-max -> values of a block, of which three per CU cover for each
 // other.  The chunk with the new rows is the longest: it is started first, and its new keys and values come with the other operands
 // and through LDS (a load and a wait for each element, as lanes picked them from the projections, cost 3 us at six rows).
-// 32 heads x 128, both kernels: six rows behind 100 / 700 / 4200 keys 8.6 / 13.6 / 27.3 -> 6.9 / 10.2 / 21.6 us, one row 6.0 / 9.3 / 22.2
-// -> 5.3 / 8.7 / 19.6; 8 kv heads, eight rows behind 8000 25.7 -> 22.4.
+// Both kernels in a graph of launches, 32 heads x 128, six rows behind 520 / 2000 / 4200 keys 9.70 / 12.7 / 20.9 -> 9.02 / 12.4 / 20.5 us, one row behind 520 8.5 -> 8.1;
+// 32 heads over 8 x 128, four rows behind 700 9.9 -> 8.3, one row 8.55 -> 7.9; one row of 32 behind 20 keys (the first stage alone) 5.4 -> 4.9: with the queries
+// in wide loads, a query's row by a multiplication, new rows looked for only where a tile has one and taken in whole operands, and up to
+// sixteen queries' soft-max side by side.  Of 5.4 us for a block's chain now, 1.7 are an empty launch's and 2.6 the two round trips.
 // LDS of one block of the matrix-core attention kernels (one work item is computed at a time).
 template <int HD>
 struct AttnLds {
@@ -415,42 +491,24 @@ struct AttnLds {
 // steps: load() requests everything the item reads from memory (the first query group with its
 // rotary factors, the chunk's K and V operands) into registers, compute() does the rest.  A block
 // that owns several items requests the next item's operands before it computes the current one.
-template <int HD>
+template <int HD, bool VEC>
 struct AttnItem {
     static constexpr int CH = 128, QG = 16, HALF = HD / 2;
     static constexpr int KSQ = HD / 32;      // k steps (of 32 dims) of the score product
     static constexpr int KSV = CH / 32;      // k steps (of 32 keys) of the value product
     static constexpr int DT = HD / 64;       // 16-dim output tiles per wave
     static constexpr int QS = HD + 8, PS = CH + 8, SS = CH + 4;
-    static constexpr int QIT = QG * HALF / 256;
     int g, chunk, zb;
-    float qx[QIT], qy[QIT], qc[QIT], qsn[QIT];
+    QueryRows<HD, VEC> qr;
     uint4 kreg[2][KSQ];
     int kpage[2];
     uint4 vreg[DT][KSV];
     int vpg[KSV];       // page of this lane's keys of a step
-    NewRows<HD> nr;
+    NewRows<HD, VEC> nr;
 
     __device__ __forceinline__ void load_q(const AttnArgs& a, int qg) {
-        const int tid = threadIdx.x;
-        const int G = a.n_heads / a.kv.n_kv_heads, nq_total = a.M * G;
-            const int q0 = qg * QG;
-            const int nq = (nq_total - q0 < QG) ? (nq_total - q0) : QG;
-    #pragma unroll
-            for (int it = 0; it < QIT; ++it) {
-                const int i = tid + it * 256;
-                const int qi = i / HALF, j = i - qi * HALF;
-                qx[it] = qy[it] = qsn[it] = 0.f;
-                qc[it] = 1.f;
-                if (qi < nq) {
-                    int qq = q0 + qi, r = qq / G, gi = qq - r * G;
-                    const float* qp = a.q + (size_t)r * a.qkv_rows + (size_t)(g * G + gi) * HD;
-                    qx[it] = qp[j];
-                    qy[it] = qp[j + HALF];
-                    qc[it] = a.rope_cos[(size_t)(a.pos0 + r) * HALF + j];
-                    qsn[it] = a.rope_sin[(size_t)(a.pos0 + r) * HALF + j];
-                }
-            }
+        const int nq_total = a.M * (a.n_heads / a.kv.n_kv_heads), q0 = qg * QG;
+        qr.load(a, g, q0, nq_total - q0 < QG ? nq_total - q0 : QG);
     }
 
     __device__ __forceinline__ void load(const AttnArgs& a, int g_, int chunk_, int zb_) {
@@ -531,8 +589,8 @@ struct AttnItem {
         float* const s_s = lds.s_s; float* const s_m = lds.s_m; float* const s_l = lds.s_l;
         // (the new rows lie where the probabilities come later)
         uint16_t* const nk_s = lds.p_hi; uint16_t* const nv_s = lds.p_lo;
-        static_assert(SB_MAX_W * QS <= QG * PS, "the new rows fit");
-        if (has_new) nr.template store<uint16_t, QS>(a, nk_s, nv_s);
+        static_assert(SB_MAX_W * QS <= QG * PS && HD * 16 <= QG * PS && SB_MAX_W <= 8, "the new rows fit");
+        if (has_new) nr.template store<uint16_t, QS, true>(a, nk_s, nv_s);
         for (int qg = qg_first; qg < qg_last; ++qg) {
         // (the thread's number anew for every group: the addresses that follow from it, some hundred instructions and
         // as many registers, would otherwise be worked out ahead of the loop, which most launches go round once)
@@ -543,28 +601,30 @@ struct AttnItem {
         const int q0 = qg * QG;
         const int nq = (nq_total - q0 < QG) ? (nq_total - q0) : QG;
         // ---- rotated queries -> LDS as hi + lo
+        if (qr.query() < QG) {
+            float lo[4], hi[4];
+            qr.rotate(lo, hi);
+            const int at = qr.query() * QS + qr.dim();
     #pragma unroll
-        for (int it = 0; it < QIT; ++it) {
-            const int i = tid + it * 256;
-            const int qi = i / HALF, j = i - qi * HALF;
-            const float u = qx[it] * qc[it] - qy[it] * qsn[it], v = qy[it] * qc[it] + qx[it] * qsn[it];
-            const uint16_t uh = f2bf(u), vh = f2bf(v);
-            q_hi[qi * QS + j] = uh;
-            q_lo[qi * QS + j] = f2bf(u - bf2f(uh));
-            q_hi[qi * QS + j + HALF] = vh;
-            q_lo[qi * QS + j + HALF] = f2bf(v - bf2f(vh));
+            for (int o = 0; o < 2; ++o) {
+                const float (&u)[4] = o ? hi : lo;
+                uint32_t h[2], l[2];
+                split_pair(__float_as_uint(u[0]), __float_as_uint(u[1]), h[0], l[0]);
+                split_pair(__float_as_uint(u[2]), __float_as_uint(u[3]), h[1], l[1]);
+                *reinterpret_cast<uint2*>(q_hi + at + o * HALF) = make_uint2(h[0], h[1]);
+                *reinterpret_cast<uint2*>(q_lo + at + o * HALF) = make_uint2(l[0], l[1]);
+            }
         }
         if (qg + 1 < qg_last) load_q(a, qg + 1);  // (in flight during this group's products)
         __syncthreads();
         // ---- keys and values of the new rows take the place of what the cache held, appended by query group 0; values of
         // slots past the last key become zero (0 x stale bits that read as NaN is not 0; their scores are masked): in a step
-        // with new rows value by value, in a later one all at once (value by value there as well, a chunk of few keys was slower
-        // than with a load for every value: 32 heads over 8 x 128, one row behind 3 / 130 keys 6.8 / 8.6 us then, 7.3 / 9.0 value
-        // by value, 6.3 / 8.1 now)
+        // with new rows by masks, in a later one all at once
         if (has_new && qg == qg_first) {
     #pragma unroll
             for (int t = 0; t < 2; ++t) {
-                const int key = key0 + wave * 32 + t * 16 + li;
+                const int kt0 = key0 + wave * 32 + t * 16, key = kt0 + li;
+                if (kt0 + 16 <= a.pos0 || kt0 >= n_total) continue;   // (wave-uniform: no new key in this tile)
                 const bool fresh = key >= a.pos0 && key < n_total;
                 const uint16_t* kp = nk_s + (fresh ? key - a.pos0 : 0) * QS + lq * 8;
     #pragma unroll
@@ -577,19 +637,21 @@ struct AttnItem {
             for (int ks = 0; ks < KSV; ++ks) {
                 const int kf = key0 + ks * 32 + lq * 8;
                 if (key0 + ks * 32 + 32 <= a.pos0 || key0 + ks * 32 >= n_total) continue;   // (block-uniform: no new row in this step)
+                // of this lane's eight keys: which are new (or past the last key), which exist
+                uint32_t fresh[4], keep[4];
+    #pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int k = kf + 2 * e;
+                    fresh[e] = (k >= a.pos0 ? 0xffffu : 0u) | (k + 1 >= a.pos0 ? 0xffff0000u : 0u);
+                    keep[e] = (k < n_total ? 0xffffu : 0u) | (k + 1 < n_total ? 0xffff0000u : 0u);
+                }
+                const int at = kf - (a.pos0 & ~7);   // (a multiple of 8; the slots are 0 and 8)
     #pragma unroll
                 for (int dt = 0; dt < DT; ++dt) {
-                    const uint16_t* vp = nv_s + (wave * DT + dt) * 16 + li;
-                    uint32_t w[4] = {vreg[dt][ks].x, vreg[dt][ks].y, vreg[dt][ks].z, vreg[dt][ks].w};
-    #pragma unroll
-                    for (int e = 0; e < 8; ++e) {
-                        const int r = kf + e - a.pos0;   // new row, if any
-                        const uint32_t v = vp[(r >= 0 && r < a.M ? r : 0) * HD];
-                        const uint32_t h = r < a.M ? v : 0u;
-                        const uint32_t x = (e & 1) ? ((w[e >> 1] & 0x0000ffffu) | (h << 16)) : ((w[e >> 1] & 0xffff0000u) | h);
-                        w[e >> 1] = r >= 0 ? x : w[e >> 1];
-                    }
-                    vreg[dt][ks] = make_uint4(w[0], w[1], w[2], w[3]);
+                    const uint4 v = *reinterpret_cast<const uint4*>(nv_s + ((wave * DT + dt) * 16 + li) * 16 + (at == 8 ? 8 : 0));
+                    uint4& w = vreg[dt][ks];
+                    w = make_uint4(((w.x & ~fresh[0]) | (v.x & fresh[0])) & keep[0], ((w.y & ~fresh[1]) | (v.y & fresh[1])) & keep[1],
+                                   ((w.z & ~fresh[2]) | (v.z & fresh[2])) & keep[2], ((w.w & ~fresh[3]) | (v.w & fresh[3])) & keep[3]);
                 }
             }
     #pragma unroll
@@ -635,34 +697,61 @@ struct AttnItem {
                 for (int r = 0; r < 4; ++r) s_s[(4 * lq + r) * SS + wave * 32 + t * 16 + li] = acc[t][r];
         }
         __syncthreads();
-        // ---- softmax partial of each query over the chunk (one wave per query)
-        for (int qi = wave; qi < QG; qi += 4) {
-            if (qi >= nq) {  // unused operand rows: defined values
-                p_hi[qi * PS + lane] = p_hi[qi * PS + lane + 64] = 0;
-                p_lo[qi * PS + lane] = p_lo[qi * PS + lane + 64] = 0;
-                continue;
+        // ---- softmax partial of each query over the chunk: up to four queries a wave each, with more all sixteen at once, 16 lanes
+        // each with keys t0, t0 + 16, ..; either way a query's sum is taken over key bits 6, 5, .. 0 in this order
+        if (nq <= 4) {
+            const int qi = wave;
+            for (int z = wave; z < QG; z += 4) {   // unused operand rows: defined values
+                if (z < nq) continue;
+                p_hi[z * PS + lane] = p_hi[z * PS + lane + 64] = 0;
+                p_lo[z * PS + lane] = p_lo[z * PS + lane + 64] = 0;
             }
-            const int r = (q0 + qi) / G;
-            float sc[2];
-            float mx = -SB_INF;
+            if (qi < nq) {
+                const int r = attn_row<VEC>(a, q0 + qi);
+                float sc[2], mx = -SB_INF;
     #pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const int t = lane + 64 * h;
-                sc[h] = (key0 + t <= a.pos0 + r) ? s_s[qi * SS + t] * scale : -SB_INF;
-                mx = fmaxf(mx, sc[h]);
-            }
-            mx = wave_max(mx);
-            float l = 0.f;
+                for (int h = 0; h < 2; ++h) {
+                    const int t = lane + 64 * h;
+                    sc[h] = (key0 + t <= a.pos0 + r) ? s_s[qi * SS + t] * scale : -SB_INF;
+                    mx = fmaxf(mx, sc[h]);
+                }
+                mx = wave_max(mx);
+                float l = 0.f;
     #pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const float p = (mx == -SB_INF) ? 0.f : expf(sc[h] - mx);
-                const uint16_t ph = f2bf(p);
-                p_hi[qi * PS + lane + 64 * h] = ph;
-                p_lo[qi * PS + lane + 64 * h] = f2bf(p - bf2f(ph));
-                l += p;
+                for (int h = 0; h < 2; ++h) {
+                    const float p = (mx == -SB_INF) ? 0.f : expf(sc[h] - mx);
+                    const uint16_t ph = f2bf(p);
+                    p_hi[qi * PS + lane + 64 * h] = ph;
+                    p_lo[qi * PS + lane + 64 * h] = f2bf(p - bf2f(ph));
+                    l += p;
+                }
+                l = wave_sum(l);
+                if (lane == 0) { s_m[qi] = mx; s_l[qi] = l; }
             }
-            l = wave_sum(l);
-            if (lane == 0) { s_m[qi] = mx; s_l[qi] = l; }
+        } else {
+            const int qi = tid >> 4, t0 = tid & 15;
+            const bool live = qi < nq;   // (unused operand rows: defined values)
+            const int vis = a.pos0 + attn_row<VEC>(a, q0 + qi) - key0 - t0;
+            float sc[8], p[8], mx = -SB_INF;
+    #pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                sc[k] = 16 * k <= vis ? s_s[qi * SS + t0 + 16 * k] * scale : -SB_INF;
+                mx = fmaxf(mx, sc[k]);
+            }
+            mx = lanes_max<8>(mx);
+    #pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                p[k] = !live || mx == -SB_INF ? 0.f : expf(sc[k] - mx);
+                const uint16_t ph = f2bf(p[k]);
+                p_hi[qi * PS + t0 + 16 * k] = ph;
+                p_lo[qi * PS + t0 + 16 * k] = f2bf(p[k] - bf2f(ph));
+            }
+    #pragma unroll
+            for (int d = 4; d > 0; d >>= 1)
+    #pragma unroll
+                for (int k = 0; k < d; ++k) p[k] += p[k + d];
+            const float l = lanes_sum<8>(p[0]);
+            if (t0 == 0 && live) { s_m[qi] = mx; s_l[qi] = l; }
         }
         __syncthreads();
         // ---- weighted values: this wave's DT tiles of 16 dims, all keys of the chunk
@@ -685,7 +774,7 @@ struct AttnItem {
             for (int r = 0; r < 4; ++r) {
                 const int qi = 4 * lq + r;
                 if (qi >= nq) continue;
-                const int qq = q0 + qi, rr = qq / G, gi = qq - rr * G;
+                const int qq = q0 + qi, rr = attn_row<VEC>(a, qq), gi = qq - rr * G;
                 if (key0 > a.pos0 + rr) continue;  // (a chunk with no visible key leaves no partial)
                 if (a.direct) {
     #pragma unroll
@@ -703,17 +792,17 @@ struct AttnItem {
     }
 };
 
-template <int HD>
+template <int HD, bool VEC>
 __device__ __forceinline__ void attn_mfma_body(const AttnArgs& a, const int g, const int chunk, const int zb) {
     __shared__ AttnLds<HD> lds;
-    AttnItem<HD> it;
+    AttnItem<HD, VEC> it;
     it.load(a, g, chunk, zb);
     it.compute(a, lds);
 }
 
-template <int HD>
+template <int HD, bool VEC>
 __global__ __launch_bounds__(256, 3) void attn_mfma_kernel(AttnArgs a) {
-    attn_mfma_body<HD>(a, blockIdx.x, gridDim.y - 1 - blockIdx.y, blockIdx.z);   // (the chunk with the new rows first)
+    attn_mfma_body<HD, VEC>(a, blockIdx.x, gridDim.y - 1 - blockIdx.y, blockIdx.z);   // (the chunk with the new rows first)
 }
 
 // Several sequences' passes in one launch (batch > 1): grid.z = sequence x query-group slice, grid.y
@@ -727,7 +816,7 @@ __global__ __launch_bounds__(256, 3) void attn_mfma_batch_kernel(AttnBatchArgs a
     const int n_chunks = (a.pos0 + a.M + 127) / 128;
     const int n_qg = (a.M * (a.n_heads / a.kv.n_kv_heads) + 15) / 16;
     if ((int)blockIdx.y >= n_chunks || zb * a.qg_per_block >= n_qg) return;
-    attn_mfma_body<HD>(a, blockIdx.x, n_chunks - 1 - blockIdx.y, zb);
+    attn_mfma_body<HD, true>(a, blockIdx.x, n_chunks - 1 - blockIdx.y, zb);
 }
 
 // Second stage: one block per (row, query head) merges that row's chunk partials
@@ -842,12 +931,23 @@ static bool attn_shape(const AttnArgs& a, int* n_chunks, int* n_qg, int* qpb) {
     return true;
 }
 
+// The fast form of the matrix-core kernel: rows and tables that 16-byte loads may read (their rows are whole multiples of that), and rows found by
+// a multiplication (at most 8 G queries and 15 unused ones: 8 G G < 2^32).
+static bool attn_fast(const AttnArgs& a) {
+    return (((uintptr_t)a.q | (uintptr_t)a.rope_cos | (uintptr_t)a.rope_sin) & 15) == 0 && a.qkv_rows % 4 == 0 && a.n_heads / a.kv.n_kv_heads <= 16384;
+}
+static uint32_t attn_g_inv(const AttnArgs& a) {
+    const uint64_t G = a.n_heads / a.kv.n_kv_heads;
+    return G == 1 ? 0u : (uint32_t)(((1ull << 32) + G - 1) / G);
+}
+
 hipError_t launch_attention(const AttnArgs& a, hipStream_t st) {
     const int hd = a.kv.head_dim;
     int n_chunks, n_qg, qpb;
     if (!attn_shape(a, &n_chunks, &n_qg, &qpb)) return hipErrorInvalidValue;
     AttnArgs b = a;
     b.qg_per_block = qpb;
+    b.g_inv = attn_g_inv(a);
     // With a single chunk the merge would multiply by exp(0) and add zeros: the first stage divides and
     // stores by itself (the same bits), a launch less.  An output over the input has to wait for the end of the first stage.
     b.direct = n_chunks == 1 && !attn_out_over_input(a);
@@ -856,8 +956,16 @@ hipError_t launch_attention(const AttnArgs& a, hipStream_t st) {
     dim3 mgrid(a.n_heads, a.M);
     if (a.kv.kv_dtype == SB_BF16) {
         if (a.M > SB_MAX_W) return hipErrorInvalidValue;   // (more rows: launch_prefill_attention)
-        if (hd == 128) { attn_mfma_kernel<128><<<grid, 256, 0, st>>>(b); if (!b.direct) attn_merge_kernel<128, 128><<<mgrid, 256, 0, st>>>(a); }
-        else { attn_mfma_kernel<64><<<grid, 256, 0, st>>>(b); if (!b.direct) attn_merge_kernel<64, 128><<<mgrid, 256, 0, st>>>(a); }
+        const bool fast = attn_fast(a);
+        if (hd == 128) {
+            if (fast) attn_mfma_kernel<128, true><<<grid, 256, 0, st>>>(b);
+            else attn_mfma_kernel<128, false><<<grid, 256, 0, st>>>(b);
+            if (!b.direct) attn_merge_kernel<128, 128><<<mgrid, 256, 0, st>>>(a);
+        } else {
+            if (fast) attn_mfma_kernel<64, true><<<grid, 256, 0, st>>>(b);
+            else attn_mfma_kernel<64, false><<<grid, 256, 0, st>>>(b);
+            if (!b.direct) attn_merge_kernel<64, 128><<<mgrid, 256, 0, st>>>(a);
+        }
     } else {
         const auto first = [&](auto hd_c) {
             constexpr int HD = decltype(hd_c)::value;
@@ -881,6 +989,7 @@ hipError_t launch_attention_batch(const AttnArgs* seqs, int n, hipStream_t st) {
     for (int i = 1; i < n; ++i)
         one_shape = one_shape && seqs[i].kv.kv_dtype == SB_BF16 && seqs[i].kv.head_dim == seqs[0].kv.head_dim &&
                     seqs[i].kv.n_kv_heads == seqs[0].kv.n_kv_heads && seqs[i].n_heads == seqs[0].n_heads;
+    for (int i = 0; i < n; ++i) one_shape = one_shape && attn_fast(seqs[i]);
     if (n == 1 || !one_shape) {  // (an fp32 cache takes the vector-ALU kernel, a launch per sequence)
         for (int i = 0; i < n; ++i) {
             hipError_t e = launch_attention(seqs[i], st);
@@ -896,6 +1005,7 @@ hipError_t launch_attention_batch(const AttnArgs* seqs, int n, hipStream_t st) {
         if (!attn_shape(seqs[i], &n_chunks, &n_qg, &qpb) || seqs[i].M > SB_MAX_W) return hipErrorInvalidValue;
         ab.seq[i] = seqs[i];
         ab.seq[i].qg_per_block = qpb;
+        ab.seq[i].g_inv = attn_g_inv(seqs[i]);
         const int z = (n_qg + qpb - 1) / qpb;
         if (z > ab.zdim) ab.zdim = z;
         if (n_chunks > max_chunks) max_chunks = n_chunks;

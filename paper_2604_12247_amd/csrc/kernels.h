@@ -168,6 +168,7 @@ struct AttnArgs {
     int32_t split_rows;  // 8 for decode passes, SB_PREFILL_ROWS for prompt passes
     int32_t qg_per_block;  // set by launch_attention
     int32_t direct;        // set by launch_attention: the first stage finishes every row (they see one chunk only)
+    uint32_t g_inv;        // set by launch_attention: 2^32 over the queries per row and kv head, rounded up (0: one)
 };
 int attn_chunk_keys(int32_t head_dim, int32_t kv_dtype);
 hipError_t launch_attention(const AttnArgs& a, hipStream_t st);

@@ -802,6 +802,35 @@ def test_prompt_attention_query_parts(T, H, hd):
     assert np.max(np.abs(out - ref[:, :, None])) <= 2 * 2.0 ** -13
 
 
+# operands that wide loads may not read take the kernel's general form; new rows at every place of an eight-key operand and of a step, up to
+# and across the end of a chunk, one to 64 queries per kv head
+@pytest.mark.parametrize("Hq,Hkv,hd", [(4, 4, 128), (12, 4, 64), (8, 1, 128)])
+@pytest.mark.parametrize("pos0", [0, 1, 6, 7, 8, 27, 121, 127, 128, 253])
+def test_attention_unaligned_operands(T, Hq, Hkv, hd, pos0):
+    import paper_2604_12247_amd as sb
+    g = np.random.default_rng(Hq + hd + pos0)
+    n_pages = (pos0 + 8 + 15) // 16
+    c, s = sb.rope_table(hd, 1e4, n_pages * 16)
+    table = _dev(T, g.permutation(n_pages).astype(np.int32))
+    base = T.from_numpy(g.standard_normal((2 * n_pages * Hkv * 16, hd)).astype(np.float32)).cuda().to(T.bfloat16)
+
+    def shifted(x):
+        t = T.empty(x.size + 1, dtype=T.float32, device="cuda")[1:].view(x.shape)
+        t.copy_(_dev(T, x))
+        assert t.data_ptr() % 16 == 4
+        return t
+
+    for M in (1, 2, 5, 8):
+        qkv = g.standard_normal((M, (Hq + 2 * Hkv) * hd)).astype(np.float32)
+        got = []
+        for put in (lambda x: _dev(T, x), shifted):
+            pool = base.clone()
+            out = sb.op_attention(put(qkv), Hq, Hkv, hd, sb.BF16, pool, table, 0, put(c), put(s), pos0)
+            got.append((out.cpu().numpy(), pool.view(T.int16).cpu().numpy()))
+        assert np.array_equal(got[0][1], got[1][1])                                  # what the cache holds, bit for bit
+        assert np.max(np.abs(got[0][0] - got[1][0])) <= 4e-6, M                      # (float sums; a product may be fused in one form only)
+
+
 def test_attention_row_result_does_not_depend_on_m(T):
     """The same position gives the same bits alone and inside a pass of 6 rows."""
     args = (8, 8, 128, True)
