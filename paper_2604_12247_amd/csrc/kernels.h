@@ -201,6 +201,7 @@ struct GemmArgs {
     const void* Wp;      // packed weights [rows][K]
     int32_t rows, K;
     const uint16_t* xs;
+    const float* x;      // optional, a single pass without the fused SwiGLU: the rows as floats [M][K] (16-byte aligned, less than 4 GiB) instead of xs
     int32_t plane_rows;
     int32_t M;           // live rows over all passes
     int32_t n_pass;      // ceil(M / SB_PREFILL_ROWS)

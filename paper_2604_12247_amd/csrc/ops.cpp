@@ -95,9 +95,15 @@ int32_t sb_op_gemm(const void* Wp, int32_t N, int32_t K, const float* x, float* 
     hipStream_t st = (hipStream_t)stream;
     uint16_t* xs = (uint16_t*)scratch;
     float* part = (float*)((char*)scratch + align_up((size_t)2 * SB_PREFILL_ROWS * K * 2, 256));
-    HIP_TRY(launch_prefill_split(x, xs, SB_PREFILL_ROWS, M, K, st));
     GemmArgs g{};
-    g.Wp = Wp; g.rows = N; g.K = K; g.xs = xs; g.plane_rows = SB_PREFILL_ROWS; g.M = M; g.n_pass = 1;
+    // the GEMM reads float rows by 16-byte loads at 32-bit offsets; any others are split into their two parts first
+    if (((uintptr_t)x & 15) || (size_t)M * K >= 1u << 30) {
+        HIP_TRY(launch_prefill_split(x, xs, SB_PREFILL_ROWS, M, K, st));
+        g.xs = xs;
+    } else {
+        g.x = x;
+    }
+    g.Wp = Wp; g.rows = N; g.K = K; g.plane_rows = SB_PREFILL_ROWS; g.M = M; g.n_pass = 1;
     g.part = part; g.S = gemm_splits(N, K, 1);
     HIP_TRY(launch_prefill_gemm(g, st));
     GemmEpiArgs e{};

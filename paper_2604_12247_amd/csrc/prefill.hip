@@ -172,8 +172,9 @@ __device__ __forceinline__ void gemm_load_a(uint4 (&ar)[RT], const GemmWeights<R
 // lies 32 rows below unit i - 1 (same segment), first in the high plane, then in the low plane.
 // Rows past the live ones are read too, from the planes' unused rows: whatever they hold only
 // reaches result columns that are never stored.
-template <int CT>
+template <int CT, bool RAW>
 struct GemmStage {
+    static constexpr int N = CT, FIRST = CT > 4 ? (CT + 1) / 2 : CT;   // 16-byte registers of a k block; requested at its start, the rest half way
     const char* base;      // the pass's first row in the high plane
     uint32_t off;          // this thread's byte offset at unit 0
     size_t off_mid;        // ... at the unit that holds the last rows of the high and the first of the low plane (odd CT)
@@ -188,8 +189,8 @@ struct GemmStage {
         off_mid = (size_t)(rm < CT * 16 ? rm : lo_off + rm - CT * 16) * row_bytes + seg;
         dst = r * ROWB + seg;
     }
-    template <int I0, int I1, int N>
-    __device__ __forceinline__ void load(u32x4 (&br)[N], int kb) const {
+    template <int I0, int I1, int NR>
+    __device__ __forceinline__ void load(u32x4 (&br)[NR], int kb) const {
         const char* p = base + (size_t)kb * 256;
 #pragma unroll
         for (int i = I0; i < I1; ++i) {
@@ -201,10 +202,56 @@ struct GemmStage {
             }
         }
     }
-    template <int I0, int I1, int N>
-    __device__ __forceinline__ void store(unsigned char* stage, const u32x4 (&br)[N]) const {
+    template <int I0, int I1, int NR>
+    __device__ __forceinline__ void store(unsigned char* stage, const u32x4 (&br)[NR]) const {
 #pragma unroll
         for (int i = I0; i < I1; ++i) *reinterpret_cast<u32x4*>(stage + dst + i * 32 * ROWB) = br[i - I0];
+    }
+};
+// The same from float rows (a single pass): a thread loads eight floats of a row, registers 2 i and 2 i + 1 of the rows 32 i below its first, and
+// makes both parts of them on the way to LDS: the bytes are the same, and a launch that splits the rows first is saved ([15360 x 5120] at
+// 45 rows, whole call 38.7 us, with it 36.0; at 128 rows 55.2 and 48.4, [4096 x 4096] 27.0 and 22.5).  Rows past the live ones read the
+// last of them; it has no others.
+template <int CT>
+struct GemmStage<CT, true> {
+    static constexpr int U = (CT + 1) / 2, N = 2 * U, FIRST = CT > 4 ? (U + 1) / 2 * 2 : N;
+    const char* base;
+    uint32_t off[U];
+    int dst;
+    bool half;             // of the last unit of an odd CT, whose rows are 16: this thread has one
+    __device__ __forceinline__ void init(const GemmArgs& a, const GemmCtx& c, int tid) {
+        base = reinterpret_cast<const char*>(a.x);
+        const int r = tid >> 4, seg = tid & 15;
+#pragma unroll
+        for (int i = 0; i < U; ++i) {
+            const int row = i * 32 + r < c.Mp ? i * 32 + r : c.Mp - 1;
+            off[i] = (uint32_t)row * (uint32_t)(a.K * 4) + seg * 32;
+        }
+        dst = r * ROWB + seg * 16;
+        half = r < 16;
+    }
+    template <int I0, int I1, int NR>
+    __device__ __forceinline__ void load(u32x4 (&br)[NR], int kb) const {
+        const char* p = base + (size_t)kb * 512;
+#pragma unroll
+        for (int i = I0; i < I1; ++i) br[i - I0] = *reinterpret_cast<const u32x4*>(p + off[i / 2] + (i & 1) * 16);
+    }
+    template <int I0, int I1, int NR>
+    __device__ __forceinline__ void store(unsigned char* stage, const u32x4 (&br)[NR]) const {
+#pragma unroll
+        for (int i = I0; i < I1; i += 2) {
+            const u32x4 x = br[i - I0], y = br[i - I0 + 1];
+            uint32_t h[4], l[4];
+            split_pair(x[0], x[1], h[0], l[0]);
+            split_pair(x[2], x[3], h[1], l[1]);
+            split_pair(y[0], y[1], h[2], l[2]);
+            split_pair(y[2], y[3], h[3], l[3]);
+            unsigned char* const d = stage + dst + (i / 2) * 32 * ROWB;
+            if (CT % 2 == 0 || i / 2 < U - 1 || half) {
+                *reinterpret_cast<u32x4*>(d) = u32x4{h[0], h[1], h[2], h[3]};
+                *reinterpret_cast<u32x4*>(d + CT * 16 * ROWB) = u32x4{l[0], l[1], l[2], l[3]};
+            }
+        }
     }
 };
 
@@ -280,11 +327,11 @@ __device__ __forceinline__ void gemm_flush(f32x4 (&acc)[RT][CT], const GemmArgs&
 // throughout, took 819 us there against 739; multiplying all 128 rows of a pass whatever it holds took 82 us on
 // [27648 x 5120] at 45 rows against 55 (5.1 TB/s) with only the live column tiles.  32 x 32 x 16 MFMAs, which the
 // MFMA-only loop prefers by 4 %, were 5 % slower here.
-template <int RT, int CT, int D, int PD, bool STREAM, bool SWI, bool WHOLE>
+template <int RT, int CT, int D, int PD, bool STREAM, bool SWI, bool WHOLE, bool RAW>
 __global__ __launch_bounds__(64 * WPB) void prefill_gemm_kernel(GemmArgs a, int q, int xa) {
     constexpr int STAGE = stage_bytes(CT), UB = D / 4;   // UB: k blocks per turn of the ring
-    // staging units requested at the start of a k block; the rest half way
-    constexpr int H0 = CT > 4 ? (CT + 1) / 2 : CT, H1 = CT > H0 ? CT - H0 : 1;
+    using Stage = GemmStage<CT, RAW>;
+    constexpr int H0 = Stage::FIRST, HN = Stage::N, H1 = HN > H0 ? HN - H0 : 1;
     static_assert(D == 4 || D == 8, "the ring turns over in whole k blocks");
     static_assert(!WHOLE || D == 8, "one k block multiplied, the next requested");
     constexpr int AHEAD = WHOLE ? 4 : D - 1;   // steps requested before the first is multiplied
@@ -320,20 +367,20 @@ __global__ __launch_bounds__(64 * WPB) void prefill_gemm_kernel(GemmArgs a, int 
 #pragma unroll
         for (int ct = 0; ct < CT; ++ct) acc[t][ct] = f32x4{0.f, 0.f, 0.f, 0.f};
     uint4 ar[D][RT];
-    GemmStage<CT> sg;
+    Stage sg;
     sg.init(a, c, tid);
     GemmWeights<RT, SWI> w;  // the pair whose last step (WHOLE: all steps) is requested at the first step of a k block; then the pair after it
     w.init(c, a.Wp, it0);
     int b = w.b, kb = w.kb;  // the pair being multiplied
     {
-        u32x4 br[CT];
-        sg.template load<0, CT>(br, kb);
+        u32x4 br[HN];
+        sg.template load<0, HN>(br, kb);
 #pragma unroll
         for (int s = 0; s < AHEAD; ++s) {
             gemm_load_a<RT, STREAM, SWI>(ar[s], w, s & 3, lane_off);
             if ((s & 3) == 3) w.next(c, a.Wp);
         }
-        sg.template store<0, CT>(bt, br);
+        sg.template store<0, HN>(bt, br);
     }
     float* const s_inv = reinterpret_cast<float*>(bt + 2 * STAGE);
     if (a.fused) {  // 1 / rms of this pass's input rows, from the partial sums of squares their producer left
@@ -365,9 +412,9 @@ __global__ __launch_bounds__(64 * WPB) void prefill_gemm_kernel(GemmArgs a, int 
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             if (u == 0) sg.template load<0, H0>(br0, kbn);
-            if (CT > H0 && u == 2) {
+            if (HN > H0 && u == 2) {
                 sg.template store<0, H0>(dst, br0);
-                sg.template load<H0, CT>(br1, kbn);
+                sg.template load<H0, HN>(br1, kbn);
             }
             if (WHOLE) {
                 if (u == 0) {
@@ -395,7 +442,7 @@ __global__ __launch_bounds__(64 * WPB) void prefill_gemm_kernel(GemmArgs a, int 
             }
         }
         if (it + 1 >= c.it1 || kb + 1 == c.KB) gemm_flush<RT, CT, SWI>(acc, a, c, b, q, s_inv, lane);
-        if (CT > H0) sg.template store<H0, CT>(dst, br1);
+        if (HN > H0) sg.template store<H0, HN>(dst, br1);
         else sg.template store<0, H0>(dst, br0);
         if (++kb == c.KB) { kb = 0; ++b; }
         buf ^= 1;
@@ -409,17 +456,17 @@ __global__ __launch_bounds__(64 * WPB) void prefill_gemm_kernel(GemmArgs a, int 
     if constexpr (UB > 1) if (it < c.it1) k_block(std::integral_constant<int, 0>{}, it);
 }
 
-template <int RT, int CT, int D, int PD, bool STREAM, bool SWI, bool WHOLE>
+template <int RT, int CT, int D, int PD, bool STREAM, bool SWI, bool WHOLE, bool RAW>
 static hipError_t launch_gemm_t(const GemmArgs& a, int q, int xa, int grid, hipStream_t st) {
     constexpr int LDS = lds_bytes(CT);
     static bool attr_set = false;
     if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&prefill_gemm_kernel<RT, CT, D, PD, STREAM, SWI, WHOLE>),
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&prefill_gemm_kernel<RT, CT, D, PD, STREAM, SWI, WHOLE, RAW>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
         if (e != hipSuccess) return e;
         attr_set = true;
     }
-    prefill_gemm_kernel<RT, CT, D, PD, STREAM, SWI, WHOLE><<<grid, 64 * WPB, LDS, st>>>(a, q, xa);
+    prefill_gemm_kernel<RT, CT, D, PD, STREAM, SWI, WHOLE, RAW><<<grid, 64 * WPB, LDS, st>>>(a, q, xa);
     return hipGetLastError();
 }
 // D and PD by measurement (45 and 128 rows, 7B to 13B shapes): one tile per wave keeps seven steps in flight
@@ -436,12 +483,20 @@ static hipError_t launch_gemm_t(const GemmArgs& a, int q, int xa, int grid, hipS
 template <int RT, int CT, bool STREAM>
 static hipError_t launch_gemm_ct(const GemmArgs& a, int q, int xa, int grid, hipStream_t st) {
     constexpr int D = RT == 1 ? 8 : 4, PD = 2;
-    if constexpr (RT == 2 && STREAM)
-        if (q >= 9 && q % 2) return a.fused == 1 + EPI_SWIGLU ? launch_gemm_t<RT, CT, 8, PD, STREAM, true, true>(a, q, xa, grid, st)
-                                                      : launch_gemm_t<RT, CT, 8, PD, STREAM, false, true>(a, q, xa, grid, st);
+    if constexpr (STREAM) {
+        const bool whole = RT == 2 && q >= 9 && q % 2;
+        if (a.x) {
+            if constexpr (RT == 2)
+                if (whole) return launch_gemm_t<RT, CT, 8, PD, STREAM, false, true, true>(a, q, xa, grid, st);
+            return launch_gemm_t<RT, CT, D, PD, STREAM, false, false, true>(a, q, xa, grid, st);
+        }
+        if constexpr (RT == 2)
+            if (whole) return a.fused == 1 + EPI_SWIGLU ? launch_gemm_t<RT, CT, 8, PD, STREAM, true, true, false>(a, q, xa, grid, st)
+                                                        : launch_gemm_t<RT, CT, 8, PD, STREAM, false, true, false>(a, q, xa, grid, st);
+    }
     if constexpr (RT > 1)
-        if (a.fused == 1 + EPI_SWIGLU) return launch_gemm_t<RT, CT, D, PD, STREAM, true, false>(a, q, xa, grid, st);
-    return launch_gemm_t<RT, CT, D, PD, STREAM, false, false>(a, q, xa, grid, st);
+        if (a.fused == 1 + EPI_SWIGLU) return launch_gemm_t<RT, CT, D, PD, STREAM, true, false, false>(a, q, xa, grid, st);
+    return launch_gemm_t<RT, CT, D, PD, STREAM, false, false, false>(a, q, xa, grid, st);
 }
 
 hipError_t launch_prefill_gemm(const GemmArgs& a_, hipStream_t st) {
@@ -449,6 +504,7 @@ hipError_t launch_prefill_gemm(const GemmArgs& a_, hipStream_t st) {
     if (a.rows < 16 || a.rows % 16 || a.K < 128 || a.K % 128 || a.M < 1 || a.n_pass < 1 || a.n_pass > SB_PREFILL_PASSES ||
         a.n_pass != (a.M + PM - 1) / PM || a.plane_rows < a.n_pass * PM)
         return hipErrorInvalidValue;
+    if (a.x ? (a.n_pass != 1 || a.fused == 1 + EPI_SWIGLU || ((uintptr_t)a.x & 15) || (size_t)a.M * a.K >= 1u << 30) : !a.xs) return hipErrorInvalidValue;
     const GemmPlan p = gemm_plan(a.rows, a.K, a.n_pass, a.fused == 1 + EPI_SWIGLU);
     a.pass_rows = gemm_pass_rows(a.M, a.n_pass);
     if (a.S != p.smax || (long)p.nb * (a.K >> 7) > 0x3fffffffL) return hipErrorInvalidValue;

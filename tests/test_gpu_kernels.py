@@ -162,6 +162,26 @@ def test_prompt_pass_gemm_last_columns(T, N, K, M):
     assert float((y - ref).abs().max()) <= 3e-5 * float(ref.abs().max())   # 16-bit activation parts, as in test_prompt_pass_gemm
 
 
+# rows on a 16-byte boundary are split into their two parts inside the GEMM, any others by a launch of their own: the same bits, at every
+# number of column tiles (a last unit of 16 or 32 rows), one and two weight tiles per wave, steps requested singly and whole; no row past
+# the last is read into a result
+@pytest.mark.parametrize("N,K", [(4096, 1024), (20480, 2560), (20480, 6528)])
+@pytest.mark.parametrize("M", [9, 16, 17, 47, 64, 65, 95, 112, 127, 128])
+def test_prompt_pass_gemm_unaligned_rows(T, N, K, M):
+    import paper_2604_12247_amd as sb
+    g = T.Generator(device="cuda")
+    g.manual_seed(N + K + M)
+    Wp = sb.op_repack((T.randn(N, K, generator=g, device="cuda") * 0.02).to(T.bfloat16))
+    buf = T.full((4 + M * K + 1,), float("nan"), device="cuda")
+    buf[4:-1] = T.randn(M * K, generator=g, device="cuda")
+    x = buf[4:-1].view(M, K)
+    off = T.full((M * K + 1,), float("nan"), device="cuda")
+    off[1:] = x.reshape(-1)
+    z = off[1:].view(M, K)
+    assert x.data_ptr() % 16 == 0 and z.data_ptr() % 16 == 4
+    assert T.equal(sb.op_gemm(Wp, x), sb.op_gemm(Wp, z))
+
+
 # a single pass whose thread blocks own 9, 10, 15, 16 and 17 k blocks: odd numbers of weight blocks are requested whole
 @pytest.mark.parametrize("N,K", [(17088, 4096), (7184, 10368), (20480, 6144), (20480, 6528), (20480, 6784)])
 @pytest.mark.parametrize("M", [9, 40, 128])
