@@ -19,10 +19,10 @@ namespace sb {
 // The work inside a block is latency, not bandwidth, so everything is laid out for
 // few dependent steps: K and V go from the cache straight into registers (no LDS
 // tile), each in the mapping its consumer needs, all loads issued up front.
-//   scores   thread = (key, slice of head_dim): partial dot products, slices added in order
+//   scores   four lanes per key, each with every fourth piece of 16 bytes: two exchanges add them up
 //   softmax  wave per query over the chunk's keys
 //   values   thread = (16-byte group of dims, key slot): a few keys each, then a fixed
-//            shuffle tree over the key slots of a wave and the four waves in order
+//            tree over the key slots of a wave
 // Whatever the cache holds in the slots of the new rows (they are loaded with the rest, without
 // a condition) is replaced: the block rotates their keys (half-split pairing, table built on the
 // host in double and held in float) and rounds keys and values from qkv exactly as they are
@@ -183,40 +183,40 @@ struct NewRows {
 };
 
 // Four blocks per CU (one wave of each per SIMD).  MANY: passes of more than SB_MAX_W rows, whose chunks are full of new rows: each thread
-// prepares its own, in the 128 registers that four blocks leave it, with some spilled (in 160, three blocks per CU: prompts of up to 1000
-// rows through two layers of the 7B and 8B shapes the same, 1999 rows 6.1 and 6.4 ms where four take 5.8 and 6.1).  Else the
-// new rows go through LDS.
-// What bounds a decode pass: few keys the chain of round trips (page table, operands, LDS), many the memory.  The page table through
-// the scalar cache and everything else in one go, instead of a table entry, a wait and a load for each of a thread's eight
-// value pieces: 4 heads x 64, 90 keys, one row 6.5 -> 5.2 us, four 9.0 -> 7.4; 32 heads, one row, 2000 keys x 128 24.8 -> 17.6,
-// 9000 x 128 85 -> 63, 9000 x 64 47.5 -> 33.6.
-template <typename KVT, int HD, bool MANY>
+// prepares its own.  Else the new rows go through LDS.  VEC: as in QueryRows.
+// What bounds it: few keys the instructions of one wave in a row, of which each is some six cycles, behind two round trips (page table,
+// operands) and an empty launch's 1.7 us; many keys the memory.  So what a wave can do without is left to a branch of the whole wave (new rows,
+// slots past the last key, dims of dead queries), a query is finished by the lanes of one key slot after the loop over queries, not by all
+// inside it, and four lanes share a key: a load covers 64 bytes of each of 16 keys (a lane with half a key for itself touched 64 lines with
+// each load), and a query's dims come out of LDS once for two keys.  Before and after: 4 heads x 64 behind 60 keys, one / four / eight rows
+// 5.0 / 7.3 / 10.8 -> 3.7 / 4.7 / 6.5 us; 32 heads x 128, one row behind 300 / 2000 / 9000 keys 8.9 / 16.8 / 62.8 -> 8.1 / 16.3 / 62.5, six behind 2000
+// 20.3 -> 19.3; 128 rows of 32 heads x 128 behind none / 4000 31 / 280 -> 20.5 / 259.
+template <typename KVT, int HD, bool MANY, bool VEC>
 __global__ __launch_bounds__(256, 4) void attn_kernel(AttnArgs a) {
     constexpr int CH = (HD * sizeof(KVT) <= 256) ? 128 : 64;  // keys per chunk
     constexpr int EPV = KvVec<KVT>::EPV;                      // elements per 16 bytes
     constexpr int QG = 16;                                    // queries per block
     constexpr int HALF = HD / 2;
-    constexpr int DSPLIT = 256 / CH;                          // score threads per key
-    constexpr int DPT = HD / DSPLIT;                          // dims per score thread
-    constexpr int NKV = DPT / EPV;                            // 16-byte loads per score thread
+    // scores mapping: a wave takes CH / 4 keys, a page at a time; four lanes per key, each with every fourth piece of 16 bytes
+    constexpr int KT = CH / 4 / SB_KV_BLOCK;                  // pages per wave
+    constexpr int NKV = HD / EPV / 4;                         // pieces per key and lane
     // values mapping: each wave owns HD/4 dims and sees every key of the chunk, so the
     // sum over keys ends inside the wave (no cross-wave stage, no LDS buffer for it)
     constexpr int DGW = HD / 4 / EPV;                         // 16-byte dim groups per wave
     constexpr int KS = 64 / DGW;                              // key slots (lanes per dim group)
     constexpr int KPT = CH / KS;                              // keys per value thread
-    // A score thread reads 128 bytes of its key, a piece per load, so a wave's lines have to stay in the L1 over all of its
-    // loads: at head_dim 128 the values are requested behind them (32 heads, one row behind 300 / 2000 / 9000 keys 8.0 / 17.4 / 62.9 us,
-    // together 8.3 / 18.3 / 63.2).
+    // (head_dim 128: the values are requested behind the keys' first use.  32 heads, one row behind 300 / 2000 / 9000 keys 8.0 / 16.2 / 62.5 us, together 7.8 /
+    // 16.9 / 62.3)
     constexpr bool LATE_V = HD * sizeof(KVT) > 256;
-    static_assert(DPT <= HALF && HALF % DPT == 0, "a score thread's dims lie in one rotary half");
-    static_assert(DGW >= 1 && KS * KPT == CH, "value mapping");
+    static_assert(KT >= 1 && NKV % 2 == 0, "a wave's keys are whole pages; a lane has both parts of its rotary pairs");
+    static_assert(DGW >= 1 && KS * KPT == CH && KPT % 4 == 0 && SB_KV_BLOCK % KS == 0, "value mapping: a load's keys lie in one page");
     __shared__ __attribute__((aligned(16))) float qs[QG * HD];
-    __shared__ __attribute__((aligned(16))) float sp[DSPLIT * QG * CH];  // partial scores, then probabilities
+    __shared__ __attribute__((aligned(16))) float sp[QG * CH];  // scores by key, then probabilities by key slot
     __shared__ float s_m[QG], s_l[QG];
     constexpr int NR = MANY ? 1 : SB_MAX_W;
     __shared__ __attribute__((aligned(16))) KVT nk_s[NR * HD], nv_s[NR * HD];   // (!MANY) the new rows' keys and values
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // (the chunk with the new rows, the longest to prepare, first)
     const int g = blockIdx.x, chunk = gridDim.y - 1 - blockIdx.y, qg = blockIdx.z;
     const int Hq = a.n_heads, Hkv = a.kv.n_kv_heads, G = Hq / Hkv;
@@ -228,68 +228,53 @@ __global__ __launch_bounds__(256, 4) void attn_kernel(AttnArgs a) {
     KVT* const kbase = reinterpret_cast<KVT*>(a.kv.pool) + (size_t)(a.layer * 2 + 0) * a.kv.n_pages * page_elems;
     KVT* const vbase = reinterpret_cast<KVT*>(a.kv.pool) + (size_t)(a.layer * 2 + 1) * a.kv.n_pages * page_elems;
 
-    // ---- page-table entries of this thread's keys, all in flight at once; a key past the end takes the last page (what its slot
-    // holds is not used)
+    // ---- page-table entries, all in flight at once; a key past the end takes the last page (what its slot holds is not used)
     const bool has_new = key0 + CH > a.pos0;
-    // scores mapping: key kt, dims [kd0, kd0 + DPT)
-    const int kt = tid % CH, kd0 = (tid / CH) * DPT;
-    const int kkey = key0 + kt;
-    // values mapping: dims [vd0, vd0 + EPV), keys vks + KS * i
-    const int vd0 = wave * (HD / 4) + (lane % DGW) * EPV, vks = lane / DGW;
-    static_assert(SB_KV_BLOCK % KS == 0 && CH % 64 == 0, "a value load's keys lie in one page, a wave's score keys in four");
+    const uint32_t last = (uint32_t)(n_total - 1) / SB_KV_BLOCK;
     auto page_at = [&](int key) {   // (key: the same in all lanes, so through the scalar cache)
-        const int p = key / SB_KV_BLOCK, last = (n_total - 1) / SB_KV_BLOCK;
+        const uint32_t p = (uint32_t)key / SB_KV_BLOCK;
         return a.kv.table[p < last ? p : last];
     };
-    int vpage[KPT];
+    const int kw = key0 + wave * (CH / 4);                     // the wave's first key
+    const int kslot = lane >> 2, kd0 = (lane & 3) * EPV;       // scores: key kw + 16 t + kslot, dims kd0 + 4 EPV i ..
+    const int vd0 = wave * (HD / 4) + (lane % DGW) * EPV, vks = lane / DGW;   // values: dims vd0 .., keys vks + KS * i
+    int kpage[KT], vpage[KPT];
+#pragma unroll
+    for (int t = 0; t < KT; ++t) kpage[t] = page_at(kw + t * SB_KV_BLOCK);
 #pragma unroll
     for (int i = 0; i < KPT; ++i) vpage[i] = page_at(key0 + KS * i);
-    int kpage;   // of this lane's key, from the wave's four (a choice in registers, not of addresses)
-    {
-        const int k0 = __builtin_amdgcn_readfirstlane(key0 + (kt & ~63)), sel = lane / SB_KV_BLOCK;
-        const int p0 = page_at(k0), p1 = page_at(k0 + SB_KV_BLOCK), p2 = page_at(k0 + 2 * SB_KV_BLOCK), p3 = page_at(k0 + 3 * SB_KV_BLOCK);
-        const int lo = p0 + ((p1 - p0) & -(sel & 1)), hi = p2 + ((p3 - p2) & -(sel & 1));
-        kpage = lo + ((hi - lo) & -(sel >> 1));
-    }
     // ---- the other loads: q (+ its rotary factors), the new rows, K, V
-    constexpr int QIT = QG * HALF / 256;
-    float qx[QIT], qy[QIT], qc[QIT], qsn[QIT];
-#pragma unroll
-    for (int it = 0; it < QIT; ++it) {
-        const int i = tid + it * 256;
-        const int qi = i / HALF, j = i - qi * HALF;
-        qx[it] = qy[it] = qsn[it] = 0.f;
-        qc[it] = 1.f;
-        if (qi < nq) {
-            int qq = q0 + qi, r = qq / G, gi = qq - r * G;
-            const float* qp = a.q + (size_t)r * a.qkv_rows + (size_t)(g * G + gi) * HD;
-            qx[it] = qp[j];
-            qy[it] = qp[j + HALF];
-            qc[it] = a.rope_cos[(size_t)(a.pos0 + r) * HALF + j];
-            qsn[it] = a.rope_sin[(size_t)(a.pos0 + r) * HALF + j];
-        }
-    }
-    NewRows<HD, false> nr;
+    QueryRows<HD, VEC> qr;
+    qr.load(a, g, q0, nq);
+    NewRows<HD, VEC> nr;
     if (!MANY && has_new) nr.load(a, g);
-    uint4 kreg[NKV];
-    // element offset of this thread's K slice inside the K pool of the layer
-    const size_t kaddr = (size_t)kpage * page_elems + (uint32_t)((g * SB_KV_BLOCK + (kkey % SB_KV_BLOCK)) * HD + kd0);
+    uint4 kreg[KT][NKV];   // (of a wave without keys: unset and unused)
+    const uint32_t koff = (uint32_t)((g * SB_KV_BLOCK + kslot) * HD + kd0);
+    if (kw < n_total)
 #pragma unroll
-    for (int i = 0; i < NKV; ++i) kreg[i] = *reinterpret_cast<const uint4*>(kbase + kaddr + i * EPV);
+        for (int t = 0; t < KT; ++t)
+#pragma unroll
+            for (int i = 0; i < NKV; ++i) kreg[t][i] = *reinterpret_cast<const uint4*>(kbase + (size_t)kpage[t] * page_elems + koff + i * 4 * EPV);
     uint4 vreg[KPT];
     auto vaddr = [&](int i) { return (size_t)vpage[i] * page_elems + (uint32_t)((g * SB_KV_BLOCK + ((vks + KS * i) % SB_KV_BLOCK)) * HD + vd0); };
     auto load_v = [&]() {
 #pragma unroll
-        for (int i = 0; i < KPT; ++i) vreg[i] = *reinterpret_cast<const uint4*>(vbase + vaddr(i));
+        for (int i = 0; i < KPT; ++i) {
+            vreg[i] = make_uint4(0, 0, 0, 0);   // (slots past the last key: 0 x stale bits that read as NaN is not 0)
+            if (key0 + KS * i < n_total) vreg[i] = *reinterpret_cast<const uint4*>(vbase + vaddr(i));
+        }
     };
     if (!LATE_V) load_v();
     // ---- rotated queries -> LDS, and the new rows' keys and values as they are stored
+    if (qr.live) {
+        float lo[4], hi[4];
 #pragma unroll
-    for (int it = 0; it < QIT; ++it) {
-        const int i = tid + it * 256;
-        const int qi = i / HALF, j = i - qi * HALF;
-        qs[qi * HD + j] = qx[it] * qc[it] - qy[it] * qsn[it];
-        qs[qi * HD + j + HALF] = qy[it] * qc[it] + qx[it] * qsn[it];
+        for (int e = 0; e < 4; ++e) {   // (one rounding for all forms: a row's bits do not depend on the rows beside it)
+            lo[e] = rope_lo(qr.x[e], qr.y[e], qr.c[e], qr.sn[e]);
+            hi[e] = rope_hi(qr.x[e], qr.y[e], qr.c[e], qr.sn[e]);
+        }
+        store_near(qs + qr.query() * HD + qr.dim(), lo);
+        store_near(qs + qr.query() * HD + qr.dim() + HALF, hi);
     }
     if (!MANY && has_new) nr.template store<KVT, HD, false>(a, nk_s, nv_s);
     __syncthreads();
@@ -298,113 +283,106 @@ __global__ __launch_bounds__(256, 4) void attn_kernel(AttnArgs a) {
         load_v();
     }
     // ---- keys (and, below, values) of the new rows take the place of what the cache held, appended by query group 0
-    if (has_new) {
-        if (MANY) {
-            if (kkey >= a.pos0 && kkey < n_total) {
-                const int r = kkey - a.pos0;
-                const float* kp = a.q + (size_t)r * a.qkv_rows + (size_t)(Hq + g) * HD;
-                const bool lo = kd0 < HALF;
-                const int dj = lo ? kd0 : kd0 - HALF;
 #pragma unroll
-                for (int i = 0; i < NKV; ++i) {
-                    float f[EPV];
+    for (int t = 0; t < KT; ++t) {
+        const int k0 = kw + t * SB_KV_BLOCK, key = k0 + kslot;
+        if (k0 + SB_KV_BLOCK <= a.pos0 || k0 >= n_total) continue;
+        if (key >= a.pos0 && key < n_total) {
+            if constexpr (MANY) {
+                const float* kp = a.q + (size_t)(key - a.pos0) * a.qkv_rows + (size_t)(Hq + g) * HD;
+#pragma unroll
+                for (int i = 0; i < NKV / 2; ++i) {
+                    const int j = kd0 + i * 4 * EPV;
+                    float x[EPV], y[EPV], c[EPV], sn[EPV], lo[EPV], hi[EPV];
+                    load_near<EPV, VEC>(kp + j, x);
+                    load_near<EPV, VEC>(kp + j + HALF, y);
+                    load_near<EPV, VEC>(a.rope_cos + (size_t)key * HALF + j, c);
+                    load_near<EPV, VEC>(a.rope_sin + (size_t)key * HALF + j, sn);
 #pragma unroll
                     for (int e = 0; e < EPV; ++e) {
-                        const int j = dj + i * EPV + e;
-                        float c = a.rope_cos[(size_t)kkey * HALF + j], sn = a.rope_sin[(size_t)kkey * HALF + j];
-                        float x = kp[j], y = kp[j + HALF];
-                        f[e] = lo ? rope_lo(x, y, c, sn) : rope_hi(x, y, c, sn);
+                        lo[e] = rope_lo(x[e], y[e], c[e], sn[e]);
+                        hi[e] = rope_hi(x[e], y[e], c[e], sn[e]);
                     }
-                    kreg[i] = KvVec<KVT>::pack(f);
+                    kreg[t][i] = KvVec<KVT>::pack(lo);
+                    kreg[t][i + NKV / 2] = KvVec<KVT>::pack(hi);
                 }
-            }
-        } else {
-            const bool fresh = kkey >= a.pos0 && kkey < n_total;
-            const KVT* kp = &nk_s[(fresh ? kkey - a.pos0 : 0) * HD + kd0];
+            } else {
 #pragma unroll
-            for (int i = 0; i < NKV; ++i) {
-                const uint4 v = *reinterpret_cast<const uint4*>(kp + i * EPV);
-                kreg[i] = pick(fresh, v, kreg[i]);
+                for (int i = 0; i < NKV; ++i) kreg[t][i] = *reinterpret_cast<const uint4*>(&nk_s[(key - a.pos0) * HD + kd0 + i * 4 * EPV]);
             }
+            if (qg == 0)
+#pragma unroll
+                for (int i = 0; i < NKV; ++i) *reinterpret_cast<uint4*>(kbase + (size_t)kpage[t] * page_elems + koff + i * 4 * EPV) = kreg[t][i];
         }
     }
-    auto append_values = [&]() {
-#pragma unroll
-        for (int i = 0; i < KPT; ++i) {
-            const int key = key0 + vks + KS * i;
-            if (key >= a.pos0 && key < n_total) *reinterpret_cast<uint4*>(vbase + vaddr(i)) = vreg[i];
-        }
-    };
-    // values of the new rows; zeros in slots past the last key (0 x stale bits that read as NaN is not 0)
     auto new_values = [&]() {
         if (!has_new) return;
-        if (MANY) {
 #pragma unroll
-            for (int i = 0; i < KPT; ++i) {
-                const int key = key0 + vks + KS * i;
-                if (key >= a.pos0 && key < n_total) {
-                    const float* vp = a.q + (size_t)(key - a.pos0) * a.qkv_rows + (size_t)(Hq + Hkv + g) * HD + vd0;
-                    float f[EPV];
-#pragma unroll
-                    for (int e = 0; e < EPV; ++e) f[e] = vp[e];
-                    vreg[i] = KvVec<KVT>::pack(f);
+        for (int i = 0; i < KPT; ++i) {
+            const int k0 = key0 + KS * i, key = k0 + vks;
+            if (k0 + KS <= a.pos0 || k0 >= n_total) continue;
+            if (key >= a.pos0) {
+                vreg[i] = make_uint4(0, 0, 0, 0);
+                if (key < n_total) {
+                    if constexpr (MANY) {
+                        float f[EPV];
+                        load_near<EPV, VEC>(a.q + (size_t)(key - a.pos0) * a.qkv_rows + (size_t)(Hq + Hkv + g) * HD + vd0, f);
+                        vreg[i] = KvVec<KVT>::pack(f);
+                    } else {
+                        vreg[i] = *reinterpret_cast<const uint4*>(&nv_s[(key - a.pos0) * HD + vd0]);
+                    }
+                    if (qg == 0) *reinterpret_cast<uint4*>(vbase + vaddr(i)) = vreg[i];
                 }
             }
-        } else {
-#pragma unroll
-            for (int i = 0; i < KPT; ++i) {
-                const int key = key0 + vks + KS * i;
-                const uint4 v = *reinterpret_cast<const uint4*>(&nv_s[(key >= a.pos0 && key < n_total ? key - a.pos0 : 0) * HD + vd0]);
-                vreg[i] = pick(key >= a.pos0, v, vreg[i]);
-            }
         }
-#pragma unroll
-        for (int i = 0; i < KPT; ++i) vreg[i] = pick(key0 + vks + KS * i >= n_total, make_uint4(0, 0, 0, 0), vreg[i]);
     };
     if (!LATE_V) new_values();
-    if (has_new && qg == 0) {
-        if (kkey >= a.pos0 && kkey < n_total)
-#pragma unroll
-            for (int i = 0; i < NKV; ++i) *reinterpret_cast<uint4*>(kbase + kaddr + i * EPV) = kreg[i];
-        if (!LATE_V) append_values();
-    }
 
-    // ---- partial scores: this thread's DPT dims of key kt against every live query
-    {
-        float kf[NKV][EPV];
+    // ---- scores of this wave's keys against every live query
+    if (kw < n_total) {
+        float kf[KT][NKV][EPV];
 #pragma unroll
-        for (int i = 0; i < NKV; ++i) KvVec<KVT>::unpack(kreg[i], kf[i]);
+        for (int t = 0; t < KT; ++t)
+#pragma unroll
+            for (int i = 0; i < NKV; ++i) KvVec<KVT>::unpack(kreg[t][i], kf[t][i]);
         for (int qi = 0; qi < nq; ++qi) {
-            const float* qp = &qs[qi * HD + kd0];
-            float4 qv[DPT / 4];   // (all requested before the first is used: one wait, not one per piece)
+            float4 qv[NKV * EPV / 4];   // (all requested before the first is used: one wait, not one per piece)
 #pragma unroll
-            for (int i = 0; i < DPT / 4; ++i) qv[i] = *reinterpret_cast<const float4*>(qp + 4 * i);
+            for (int i = 0; i < NKV; ++i)
+#pragma unroll
+                for (int e = 0; e < EPV; e += 4) qv[(i * EPV + e) / 4] = *reinterpret_cast<const float4*>(&qs[qi * HD + kd0 + i * 4 * EPV + e]);
             __builtin_amdgcn_sched_barrier(0);
-            float s = 0.f;
+            float s[KT];
+#pragma unroll
+            for (int t = 0; t < KT; ++t) s[t] = 0.f;
 #pragma unroll
             for (int i = 0; i < NKV; ++i)
 #pragma unroll
                 for (int e = 0; e < EPV; e += 4) {
                     const float4 v = qv[(i * EPV + e) / 4];
-                    s = fmaf(v.x, kf[i][e], s); s = fmaf(v.y, kf[i][e + 1], s);
-                    s = fmaf(v.z, kf[i][e + 2], s); s = fmaf(v.w, kf[i][e + 3], s);
+#pragma unroll
+                    for (int t = 0; t < KT; ++t) s[t] = fmaf(v.x, kf[t][i][e], s[t]);
+#pragma unroll
+                    for (int t = 0; t < KT; ++t) s[t] = fmaf(v.y, kf[t][i][e + 1], s[t]);
+#pragma unroll
+                    for (int t = 0; t < KT; ++t) s[t] = fmaf(v.z, kf[t][i][e + 2], s[t]);
+#pragma unroll
+                    for (int t = 0; t < KT; ++t) s[t] = fmaf(v.w, kf[t][i][e + 3], s[t]);
                 }
-            sp[((tid / CH) * QG + qi) * CH + kt] = s;
+#pragma unroll
+            for (int t = 0; t < KT; ++t) sp[qi * CH + wave * (CH / 4) + t * SB_KV_BLOCK + kslot] = lanes_sum<2>(s[t]);
         }
     }
     __syncthreads();
     // ---- softmax partial of each live query over the chunk (one wave per query)
     for (int qi = wave; qi < nq; qi += 4) {
-        const int r = (q0 + qi) / G;
+        const int r = attn_row<VEC>(a, q0 + qi);
         float sc[CH / 64];
         float mx = -SB_INF;
 #pragma unroll
         for (int h = 0; h < CH / 64; ++h) {
             const int t = lane + 64 * h;
-            float s = sp[qi * CH + t];
-#pragma unroll
-            for (int ds = 1; ds < DSPLIT; ++ds) s += sp[(ds * QG + qi) * CH + t];
-            sc[h] = (key0 + t <= a.pos0 + r) ? s * scale : -SB_INF;
+            sc[h] = (key0 + t <= a.pos0 + r) ? sp[qi * CH + t] * scale : -SB_INF;
             mx = fmaxf(mx, sc[h]);
         }
         mx = wave_max(mx);
@@ -417,43 +395,61 @@ __global__ __launch_bounds__(256, 4) void attn_kernel(AttnArgs a) {
         }
         l = wave_sum(l);
 #pragma unroll
-        for (int h = 0; h < CH / 64; ++h) sp[qi * CH + lane + 64 * h] = sc[h];
+        for (int h = 0; h < CH / 64; ++h) {
+            const int t = lane + 64 * h;
+            sp[qi * CH + (t % KS) * KPT + t / KS] = sc[h];
+        }
         if (lane == 0) { s_m[qi] = mx; s_l[qi] = l; }
     }
     __syncthreads();
-    if (LATE_V) {
-        new_values();
-        if (has_new && qg == 0) append_values();
-    }
-    // ---- weighted values
+    if (LATE_V) new_values();
+    // ---- weighted values; the lanes of key slot s finish query q1 + s
     {
         float vf[KPT][EPV];
 #pragma unroll
         for (int i = 0; i < KPT; ++i) KvVec<KVT>::unpack(vreg[i], vf[i]);
-        for (int qi = 0; qi < nq; ++qi) {
-            float p[KPT], o[EPV];
+        for (int q1 = 0; q1 < nq; q1 += KS) {
+            float res[EPV];
 #pragma unroll
-            for (int i = 0; i < KPT; ++i) p[i] = sp[qi * CH + vks + KS * i];
+            for (int e = 0; e < EPV; ++e) res[e] = 0.f;
+            const int nk = nq - q1 < KS ? nq - q1 : KS;
+            for (int z = 0; z < nk; ++z) {
+                float p[KPT], o[EPV];
 #pragma unroll
-            for (int e = 0; e < EPV; ++e) o[e] = 0.f;
+                for (int i = 0; i < KPT; i += 4) {
+                    const float4 v = *reinterpret_cast<const float4*>(&sp[(q1 + z) * CH + vks * KPT + i]);
+                    p[i] = v.x; p[i + 1] = v.y; p[i + 2] = v.z; p[i + 3] = v.w;
+                }
 #pragma unroll
-            for (int i = 0; i < KPT; ++i)
+                for (int e = 0; e < EPV; ++e) o[e] = 0.f;
 #pragma unroll
-                for (int e = 0; e < EPV; ++e) o[e] = fmaf(p[i], vf[i][e], o[e]);
-            // sum over the key slots: fixed tree inside the wave
+                for (int i = 0; i < KPT; ++i)
 #pragma unroll
-            for (int e = 0; e < EPV; ++e) o[e] = lanes_sum<32, DGW>(o[e]);
-            const int qq = q0 + qi, r = qq / G, gi = qq - r * G;
-            if (lane < DGW && key0 <= a.pos0 + r) {  // (a chunk with no visible key leaves no partial)
+                    for (int e = 0; e < EPV; ++e) o[e] = fmaf(p[i], vf[i][e], o[e]);
+                // sum over the key slots: fixed tree inside the wave
+#pragma unroll
+                for (int e = 0; e < EPV; ++e) {
+                    const float t = lanes_sum<32, DGW>(o[e]);
+                    res[e] = vks == z ? t : res[e];
+                }
+            }
+            const int qi = q1 + vks, qq = q0 + qi, r = attn_row<VEC>(a, qq), gi = qq - r * G;
+            if (vks < nk && key0 <= a.pos0 + r) {  // (a chunk with no visible key leaves no partial)
                 if (a.direct) {
 #pragma unroll
-                    for (int e = 0; e < EPV; ++e) attn_finish(a, r, (g * G + gi) * HD + vd0 + e, Hq * HD, o[e] / s_l[qi]);
-                    continue;
-                }
-                float* dst = a.partials + ((size_t)(r * Hq + g * G + gi) * a.max_chunks + chunk) * (HD + 2);
+                    for (int e = 0; e < EPV; ++e) res[e] /= s_l[qi];
+                    if (a.out)
 #pragma unroll
-                for (int e = 0; e < EPV; ++e) dst[2 + vd0 + e] = o[e];
-                if (tid == 0) { dst[0] = s_m[qi]; dst[1] = s_l[qi]; }
+                        for (int e = 0; e < EPV; ++e) a.out[(size_t)r * Hq * HD + (g * G + gi) * HD + vd0 + e] = res[e];
+                    if (a.out_split)
+#pragma unroll
+                        for (int e = 0; e < EPV; ++e) split_store_rows(a.out_split, Hq * HD, a.split_rows, r, (g * G + gi) * HD + vd0 + e, res[e]);
+                } else {
+                    float* dst = a.partials + ((size_t)(r * Hq + g * G + gi) * a.max_chunks + chunk) * (HD + 2);
+#pragma unroll
+                    for (int e = 0; e < EPV; ++e) dst[2 + vd0 + e] = res[e];
+                    if (vd0 == 0) { dst[0] = s_m[qi]; dst[1] = s_l[qi]; }
+                }
             }
         }
     }
@@ -969,8 +965,13 @@ hipError_t launch_attention(const AttnArgs& a, hipStream_t st) {
     } else {
         const auto first = [&](auto hd_c) {
             constexpr int HD = decltype(hd_c)::value;
-            if (a.M > SB_MAX_W) attn_kernel<float, HD, true><<<grid1, 256, 0, st>>>(b);
-            else attn_kernel<float, HD, false><<<grid1, 256, 0, st>>>(b);
+            if (a.M > SB_MAX_W) {
+                attn_kernel<float, HD, true, false><<<grid1, 256, 0, st>>>(b);
+            } else if (attn_fast(a)) {
+                attn_kernel<float, HD, false, true><<<grid1, 256, 0, st>>>(b);
+            } else {
+                attn_kernel<float, HD, false, false><<<grid1, 256, 0, st>>>(b);
+            }
         };
         if (hd == 128) {
             first(std::integral_constant<int, 128>{});

@@ -851,6 +851,35 @@ def test_attention_unaligned_operands(T, Hq, Hkv, hd, pos0):
         assert np.max(np.abs(got[0][0] - got[1][0])) <= 4e-6, M                      # (float sums; a product may be fused in one form only)
 
 
+# the fp32 cache's kernel in both forms: the same bits, with new rows in one page of a wave, in two, and across two waves and two chunks,
+# first and last keys of a page, one to 32 queries per kv head (two groups), both chunk lengths
+@pytest.mark.parametrize("Hq,Hkv,hd", [(4, 4, 64), (12, 4, 64), (8, 2, 128), (4, 1, 128)])
+@pytest.mark.parametrize("pos0", [0, 9, 15, 16, 27, 31, 59, 64, 121, 127, 250])
+def test_attention_fp32_unaligned_operands(T, Hq, Hkv, hd, pos0):
+    import paper_2604_12247_amd as sb
+    g = np.random.default_rng(Hq + hd + pos0)
+    n_pages = (pos0 + 8 + 15) // 16
+    c, s = sb.rope_table(hd, 1e4, n_pages * 16)
+    table = _dev(T, g.permutation(n_pages).astype(np.int32))
+    base = _dev(T, g.standard_normal((2 * n_pages * Hkv * 16, hd)).astype(np.float32))
+
+    def shifted(x):
+        t = T.empty(x.size + 1, dtype=T.float32, device="cuda")[1:].view(x.shape)
+        t.copy_(_dev(T, x))
+        return t
+
+    for M in (1, 3, 8):
+        qkv = g.standard_normal((M, (Hq + 2 * Hkv) * hd)).astype(np.float32)
+        got = []
+        for put in (lambda x: _dev(T, x), shifted):
+            pool = base.clone()
+            out = sb.op_attention(put(qkv), Hq, Hkv, hd, sb.FP32, pool, table, 0, put(c), put(s), pos0)
+            got.append((out, pool))
+        assert T.equal(got[0][0], got[1][0]) and T.equal(got[0][1], got[1][1]), M
+        worst, _ = _attention_case(T, Hq, Hkv, hd, False, pos0, M, 1e4, True, seed=pos0 + M)
+        assert worst <= 2e-5, M   # (as in test_new_rows_at_every_place_of_a_chunk)
+
+
 def test_attention_row_result_does_not_depend_on_m(T):
     """The same position gives the same bits alone and inside a pass of 6 rows."""
     args = (8, 8, 128, True)
