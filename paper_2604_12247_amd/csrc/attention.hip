@@ -950,38 +950,22 @@ hipError_t launch_attention(const AttnArgs& a, hipStream_t st) {
     dim3 grid(a.kv.n_kv_heads, n_chunks, (n_qg + qpb - 1) / qpb);
     dim3 grid1(a.kv.n_kv_heads, n_chunks, n_qg);
     dim3 mgrid(a.n_heads, a.M);
-    if (a.kv.kv_dtype == SB_BF16) {
-        if (a.M > SB_MAX_W) return hipErrorInvalidValue;   // (more rows: launch_prefill_attention)
+    const auto go = [&](auto hd_c) {
+        constexpr int HD = decltype(hd_c)::value, CH32 = HD == 128 ? 64 : 128;   // (keys per chunk of an fp32 cache)
         const bool fast = attn_fast(a);
-        if (hd == 128) {
-            if (fast) attn_mfma_kernel<128, true><<<grid, 256, 0, st>>>(b);
-            else attn_mfma_kernel<128, false><<<grid, 256, 0, st>>>(b);
-            if (!b.direct) attn_merge_kernel<128, 128><<<mgrid, 256, 0, st>>>(a);
+        hipError_t e;
+        if (a.kv.kv_dtype == SB_BF16) {
+            if (a.M > SB_MAX_W) return hipErrorInvalidValue;   // (more rows: launch_prefill_attention)
+            e = launch(fast ? &attn_mfma_kernel<HD, true> : &attn_mfma_kernel<HD, false>, grid, 256, st, b);
+        } else if (a.M > SB_MAX_W) {
+            e = launch(&attn_kernel<float, HD, true, false>, grid1, 256, st, b);
         } else {
-            if (fast) attn_mfma_kernel<64, true><<<grid, 256, 0, st>>>(b);
-            else attn_mfma_kernel<64, false><<<grid, 256, 0, st>>>(b);
-            if (!b.direct) attn_merge_kernel<64, 128><<<mgrid, 256, 0, st>>>(a);
+            e = launch(fast ? &attn_kernel<float, HD, false, true> : &attn_kernel<float, HD, false, false>, grid1, 256, st, b);
         }
-    } else {
-        const auto first = [&](auto hd_c) {
-            constexpr int HD = decltype(hd_c)::value;
-            if (a.M > SB_MAX_W) {
-                attn_kernel<float, HD, true, false><<<grid1, 256, 0, st>>>(b);
-            } else if (attn_fast(a)) {
-                attn_kernel<float, HD, false, true><<<grid1, 256, 0, st>>>(b);
-            } else {
-                attn_kernel<float, HD, false, false><<<grid1, 256, 0, st>>>(b);
-            }
-        };
-        if (hd == 128) {
-            first(std::integral_constant<int, 128>{});
-            if (!b.direct) attn_merge_kernel<128, 64><<<mgrid, 256, 0, st>>>(a);
-        } else {
-            first(std::integral_constant<int, 64>{});
-            if (!b.direct) attn_merge_kernel<64, 128><<<mgrid, 256, 0, st>>>(a);
-        }
-    }
-    return hipGetLastError();
+        if (b.direct || e != hipSuccess) return e;
+        return launch(a.kv.kv_dtype == SB_BF16 ? &attn_merge_kernel<HD, 128> : &attn_merge_kernel<HD, CH32>, mgrid, 256, st, a);
+    };
+    return hd == 128 ? go(std::integral_constant<int, 128>{}) : go(std::integral_constant<int, 64>{});
 }
 
 hipError_t launch_attention_batch(const AttnArgs* seqs, int n, hipStream_t st) {
@@ -1015,14 +999,12 @@ hipError_t launch_attention_batch(const AttnArgs* seqs, int n, hipStream_t st) {
     for (int i = 0; i < n; ++i) ab.seq[i].direct = max_chunks == 1;   // (the sessions' own buffers: no output over an input)
     dim3 grid(seqs[0].kv.n_kv_heads, max_chunks, n * ab.zdim);
     dim3 mgrid(seqs[0].n_heads, max_m, n);
-    if (seqs[0].kv.head_dim == 128) {
-        attn_mfma_batch_kernel<128><<<grid, 256, 0, st>>>(ab);
-        if (max_chunks > 1) attn_merge_batch_kernel<128, 128><<<mgrid, 256, 0, st>>>(ab);
-    } else {
-        attn_mfma_batch_kernel<64><<<grid, 256, 0, st>>>(ab);
-        if (max_chunks > 1) attn_merge_batch_kernel<64, 128><<<mgrid, 256, 0, st>>>(ab);
-    }
-    return hipGetLastError();
+    const auto go = [&](auto hd_c) {
+        constexpr int HD = decltype(hd_c)::value;
+        const hipError_t e = launch(&attn_mfma_batch_kernel<HD>, grid, 256, st, ab);
+        return max_chunks == 1 || e != hipSuccess ? e : launch(&attn_merge_batch_kernel<HD, 128>, mgrid, 256, st, ab);
+    };
+    return seqs[0].kv.head_dim == 128 ? go(std::integral_constant<int, 128>{}) : go(std::integral_constant<int, 64>{});
 }
 
 }  // namespace sb

@@ -8,14 +8,58 @@
 
 #include <math.h>
 #include <mutex>
+#include <type_traits>
 
 namespace sb {
+
+// What the kernels read of GemvArgs.  The host writes a launch's arguments across the bus: 32 / 168 / 328 bytes take 2.11 / 2.26 / 2.32 us of it in a
+// process beside the GPU and 2.7 / 3.3 / 4.0 in one on the far socket, and a chain of small launches is bound by that.
+struct HeadOut { float* partials; float* logits; float T; };
+template <int EPI> struct ValuOut { float* y; int32_t ldy; };
+template <> struct ValuOut<EPI_HEAD> : HeadOut {};
+template <int EPI> struct MfmaOut;
+template <> struct MfmaOut<EPI_STORE> { float* y; int32_t ldy; };
+template <> struct MfmaOut<EPI_SWIGLU> { float* y; uint16_t* ys; int32_t ldy; };
+template <> struct MfmaOut<EPI_RESID> { float* y; const float* gainA; uint16_t* nxA; const float* gainB; uint16_t* nxB; float* ssq_out; float* ssq_out2; int32_t ldy; };
+template <> struct MfmaOut<EPI_HEAD> : HeadOut {};
+template <int EPI> struct ValuArgs {
+    const void* W; const float* x; const float* norm_gain;
+    int32_t N, K;
+    float eps;
+    ValuOut<EPI> out;
+};
+template <int EPI> struct MfmaArgs {
+    const void* W; const void* x;   // (x: float rows or their parts)
+    int32_t N, K, M;
+    uint32_t row_mask;
+    const float* ssq_in;
+    int32_t ssq_nb, ssq_ld;
+    float eps;
+    MfmaOut<EPI> out;
+};
+static HeadOut head_out(const HeadArgs& h) { return {h.partials, h.logits, h.T}; }
+template <int EPI>
+static ValuArgs<EPI> valu_args(const GemvArgs& a) {
+    ValuArgs<EPI> v{a.W, a.x, a.norm_gain, a.N, a.K, a.eps, {}};
+    if constexpr (EPI == EPI_HEAD) static_cast<HeadOut&>(v.out) = head_out(a.head);
+    else v.out = {a.y, a.ldy};
+    return v;
+}
+template <int EPI, bool RAW>
+static MfmaArgs<EPI> mfma_args(const GemvArgs& a) {
+    MfmaArgs<EPI> v{a.W, RAW ? (const void*)a.x : (const void*)a.xs, a.N, a.K, a.M, a.row_mask, a.ssq_in, a.ssq_nb, a.ssq_ld, a.eps, {}};
+    if constexpr (EPI == EPI_HEAD) static_cast<HeadOut&>(v.out) = head_out(a.head);
+    else if constexpr (EPI == EPI_STORE) v.out = {a.y, a.ldy};
+    else if constexpr (EPI == EPI_SWIGLU) v.out = {a.y, a.ys, a.ldy};
+    else v.out = {a.y, a.gainA, a.nxA, a.gainB, a.nxB, a.ssq_out, a.ssq_out2, a.ldy};
+    return v;
+}
 
 // Partial (max, arg max, sum exp) of the block's logits zs[i][m], i < ROWS: thread (m, i) holds one
 // logit, the ROWS lanes of a row are reduced with a fixed shuffle tree (ties: the lower index).
 // Every thread of the block calls it (blocks have at least 8 * ROWS threads).
 template <int ROWS>
-__device__ __forceinline__ void head_partial(const HeadArgs& h, float (*zs)[SB_MAX_W], uint32_t rows, int n0, int N, int nb) {
+__device__ __forceinline__ void head_partial(const HeadOut& h, float (*zs)[SB_MAX_W], uint32_t rows, int n0, int N, int nb) {
     static_assert(ROWS == 16 || ROWS == 32, "a row's lanes lie in one wave");
     const int tid = threadIdx.x;
     if (tid >= SB_MAX_W * ROWS) return;   // (whole waves: 8 * ROWS is a multiple of 64)
@@ -50,7 +94,7 @@ __device__ __forceinline__ void head_partial(const HeadArgs& h, float (*zs)[SB_M
 // block, and registers that hold weights through the staging are waves the stream misses: [11008 x 4096] bf16, 8 rows, 52.7 us
 // with the weights first and 24.6 without ([1024 x 1024] fp32, one row, 3.4 us with them first, 4.0 in a loop of load and store).
 template <typename WT, int M, int EPI, bool SHORT, int R>
-__global__ __launch_bounds__(256) void gemv_valu_kernel(GemvArgs a) {
+__global__ __launch_bounds__(256) void gemv_valu_kernel(ValuArgs<EPI> a) {
     static_assert(EPI != EPI_HEAD || R == 4, "a head's partial is taken over 16 logits");
     constexpr int KC = SHORT ? SB_VALU_NORM_K : (M <= 4) ? 2048 : 1024;
     constexpr int RO = (EPI == EPI_SWIGLU) ? R / 2 : R;   // outputs per wave
@@ -103,7 +147,8 @@ __global__ __launch_bounds__(256) void gemv_valu_kernel(GemvArgs a) {
     };
     // (the residual's element is requested with the first weights, not after the last)
     float pre_y = 0.f;
-    if (EPI == EPI_RESID && lane < R * M && n0 + wave * R + lane / M < N) pre_y = a.y[(size_t)(lane % M) * a.ldy + n0 + wave * R + lane / M];
+    if constexpr (EPI == EPI_RESID)
+        if (lane < R * M && n0 + wave * R + lane / M < N) pre_y = a.out.y[(size_t)(lane % M) * a.out.ldy + n0 + wave * R + lane / M];
     for (int k0 = 0; k0 < K; k0 += KC) {   // (SHORT: one chunk)
         const int kc = (K - k0 < KC) ? (K - k0) : KC;
         Piece8<WT> w0[R], w1[R];   // (SHORT)
@@ -176,22 +221,22 @@ __global__ __launch_bounds__(256) void gemv_valu_kernel(GemvArgs a) {
 #pragma unroll
         for (int m = 0; m < M; ++m) acc[r][m] = wave_sum(acc[r][m]);
 
-    if (EPI == EPI_STORE || EPI == EPI_RESID) {
+    if constexpr (EPI == EPI_STORE || EPI == EPI_RESID) {
 #pragma unroll
         for (int r = 0; r < R; ++r)
 #pragma unroll
             for (int m = 0; m < M; ++m)
                 if (lane == r * M + m && outn[r] < N) {
-                    float* yp = a.y + (size_t)m * a.ldy + outn[r];
+                    float* yp = a.out.y + (size_t)m * a.out.ldy + outn[r];
                     *yp = (EPI == EPI_RESID) ? (pre_y + acc[r][m]) : acc[r][m];
                 }
-    } else if (EPI == EPI_SWIGLU) {
+    } else if constexpr (EPI == EPI_SWIGLU) {
 #pragma unroll
         for (int j = 0; j < RO; ++j)
 #pragma unroll
             for (int m = 0; m < M; ++m)
                 if (lane == j * M + m && outn[j] < N)
-                    a.y[(size_t)m * a.ldy + outn[j]] = silu_mul(acc[j][m], acc[RO + j][m]);
+                    a.out.y[(size_t)m * a.out.ldy + outn[j]] = silu_mul(acc[j][m], acc[RO + j][m]);
     } else {  // EPI_HEAD
 #pragma unroll
         for (int r = 0; r < R; ++r)
@@ -199,7 +244,7 @@ __global__ __launch_bounds__(256) void gemv_valu_kernel(GemvArgs a) {
             for (int m = 0; m < M; ++m)
                 if (lane == r * M + m) zs[wave * R + r][m] = acc[r][m];
         __syncthreads();
-        head_partial<16>(a.head, zs, (1u << M) - 1u, n0, N, gridDim.x);
+        head_partial<16>(a.out, zs, (1u << M) - 1u, n0, N, gridDim.x);
     }
 }
 
@@ -217,27 +262,22 @@ template <typename WT, int M, bool SHORT>
 static hipError_t launch_gemv_valu_m(const GemvArgs& a, hipStream_t st) {
     const int n = a.epi == EPI_SWIGLU ? 2 * a.N : a.N;
     const bool few = n < 16 * 256 || (M <= (int)sizeof(WT) && n < 16 * (a.K >= 1024 || a.epi == EPI_SWIGLU ? 1024 : 512));
+    const auto go = [&](auto epi_c, auto r_c) {   // (r: weight rows of a wave)
+        constexpr int EPI = decltype(epi_c)::value, R = decltype(r_c)::value, RB = 4 * (EPI == EPI_SWIGLU ? R / 2 : R);
+        return launch(&gemv_valu_kernel<WT, M, EPI, SHORT, R>, dim3((a.N + RB - 1) / RB), 256, st, valu_args<EPI>(a));
+    };
+    using std::integral_constant;
+    using Four = integral_constant<int, 4>;
     switch (a.epi) {
-        case EPI_STORE:
-            if (few) gemv_valu_kernel<WT, M, EPI_STORE, SHORT, 1><<<(a.N + 3) / 4, 256, 0, st>>>(a);
-            else gemv_valu_kernel<WT, M, EPI_STORE, SHORT, 4><<<(a.N + 15) / 16, 256, 0, st>>>(a);
-            break;
-        case EPI_RESID:
-            if (few) gemv_valu_kernel<WT, M, EPI_RESID, SHORT, 1><<<(a.N + 3) / 4, 256, 0, st>>>(a);
-            else gemv_valu_kernel<WT, M, EPI_RESID, SHORT, 4><<<(a.N + 15) / 16, 256, 0, st>>>(a);
-            break;
-        case EPI_SWIGLU:
-            if (few) gemv_valu_kernel<WT, M, EPI_SWIGLU, SHORT, 2><<<(a.N + 3) / 4, 256, 0, st>>>(a);
-            else gemv_valu_kernel<WT, M, EPI_SWIGLU, SHORT, 4><<<(a.N + 7) / 8, 256, 0, st>>>(a);
-            break;
+        case EPI_STORE: return few ? go(integral_constant<int, EPI_STORE>{}, integral_constant<int, 1>{}) : go(integral_constant<int, EPI_STORE>{}, Four{});
+        case EPI_RESID: return few ? go(integral_constant<int, EPI_RESID>{}, integral_constant<int, 1>{}) : go(integral_constant<int, EPI_RESID>{}, Four{});
+        case EPI_SWIGLU: return few ? go(integral_constant<int, EPI_SWIGLU>{}, integral_constant<int, 2>{}) : go(integral_constant<int, EPI_SWIGLU>{}, Four{});
         case EPI_HEAD: {
-            gemv_valu_kernel<WT, M, EPI_HEAD, SHORT, 4><<<(a.N + 15) / 16, 256, 0, st>>>(a);
-            hipError_t e = hipGetLastError();
-            return e != hipSuccess ? e : launch_head_merge(a.head, M, (a.N + 15) / 16, st);
+            const hipError_t e = go(integral_constant<int, EPI_HEAD>{}, Four{});
+            return e != hipSuccess ? e : launch_head_merge(a.head, M, head_blocks_valu(a.N), st);
         }
         default: return hipErrorInvalidValue;
     }
-    return hipGetLastError();
 }
 template <typename WT>
 static hipError_t launch_gemv_valu_t(const GemvArgs& a, hipStream_t st) {
@@ -297,8 +337,7 @@ __global__ __launch_bounds__(256) void repack_kernel(const uint16_t* __restrict_
 hipError_t launch_repack(const void* W, void* P, int32_t N, int32_t K, hipStream_t st) {
     if (N % 16 || K % 128 || N < 16 || K < 128) return hipErrorInvalidValue;
     const size_t n_units = (size_t)N * K / 8;
-    repack_kernel<<<(unsigned)((n_units + 255) / 256), 256, 0, st>>>((const uint16_t*)W, (uint16_t*)P, N, K);
-    return hipGetLastError();
+    return launch(&repack_kernel, dim3((unsigned)((n_units + 255) / 256)), 256, st, (const uint16_t*)W, (uint16_t*)P, N, K);
 }
 
 // RAW: the rows come as floats and every block makes the two bf16 parts of what it multiplies by itself: the same
@@ -306,7 +345,7 @@ hipError_t launch_repack(const void* W, void* P, int32_t N, int32_t K, hipStream
 // and exchange parts), some 80 vector instructions per k block, and no launch before this one.
 // [6144 x 4096], one row: 13.6 -> 10.6 us with the launch it saves, [27648 x 5120], six rows: 49.4 -> 48.5.
 template <int RT, int EPI, int WPB, int DEPTH, bool PACKED, bool RAW>
-__global__ __launch_bounds__(64 * WPB) void gemv_mfma_kernel(GemvArgs a) {
+__global__ __launch_bounds__(64 * WPB) void gemv_mfma_kernel(MfmaArgs<EPI> a) {
     constexpr int NT = 64 * WPB;
     static_assert(NT >= (EPI == EPI_SWIGLU ? RT / 2 : RT) * 128, "the tails take one element per thread");
     __shared__ __attribute__((aligned(16))) float red[WPB][RT][64][4];
@@ -339,8 +378,8 @@ __global__ __launch_bounds__(64 * WPB) void gemv_mfma_kernel(GemvArgs a) {
     // sequences) the slots of a bit mask.  Lanes whose column is a row that is not there load nothing.
     const uint32_t rows = a.row_mask ? a.row_mask : ((1u << M) - 1u);
     const bool bact = (rows >> (li & 7)) & 1u;
-    const uint16_t* bp = a.xs + (size_t)li * K;
-    const float* xp = a.x + (size_t)(li & 7) * K + (li >> 3) * 4;   // (RAW)
+    const uint16_t* bp = reinterpret_cast<const uint16_t*>(a.x) + (size_t)li * K;
+    const float* xp = reinterpret_cast<const float*>(a.x) + (size_t)(li & 7) * K + (li >> 3) * 4;   // (RAW)
 
     f32x4 acc[RT];
 #pragma unroll
@@ -392,12 +431,14 @@ __global__ __launch_bounds__(64 * WPB) void gemv_mfma_kernel(GemvArgs a) {
     // What the residual tail needs from memory (the element this thread finishes, its norm gains)
     // is requested now, behind the first weight loads, instead of at the end of the k loop.
     float pre_y = 0.f, pre_gA = 0.f, pre_gB = 0.f;
-    if (EPI == EPI_RESID && tid < RT * 16 * 8) {
-        const int t = tid >> 7, m = (tid >> 4) & 7, i = tid & 15, n = n0 + t * 16 + i;
-        if (((rows >> m) & 1u) && n < N) {
-            pre_y = a.y[(size_t)m * a.ldy + n];
-            if (a.nxA) pre_gA = a.gainA[n];
-            if (a.nxB) pre_gB = a.gainB[n];
+    if constexpr (EPI == EPI_RESID) {
+        if (tid < RT * 16 * 8) {
+            const int t = tid >> 7, m = (tid >> 4) & 7, i = tid & 15, n = n0 + t * 16 + i;
+            if (((rows >> m) & 1u) && n < N) {
+                pre_y = a.out.y[(size_t)m * a.out.ldy + n];
+                if (a.out.nxA) pre_gA = a.out.gainA[n];
+                if (a.out.nxB) pre_gB = a.out.gainB[n];
+            }
         }
     }
     // RMSNorm scale of each row from the partial sums of squares its producer left
@@ -437,37 +478,39 @@ __global__ __launch_bounds__(64 * WPB) void gemv_mfma_kernel(GemvArgs a) {
     }
     __syncthreads();
 
-    if (EPI == EPI_STORE || EPI == EPI_RESID) {
+    if constexpr (EPI == EPI_STORE || EPI == EPI_RESID) {
         for (int e = tid; e < RT * 16 * 8; e += NT) {
             int t = e >> 7, m = (e >> 4) & 7, i = e & 15;
             int n = n0 + t * 16 + i;
             float sq = 0.f;
             if (((rows >> m) & 1u) && n < N) {
                 float v = (cs[t][i][m] + cs[t][i][m + 8]) * s_inv[m];
-                float* yp = a.y + (size_t)m * a.ldy + n;
+                float* yp = a.out.y + (size_t)m * a.out.ldy + n;
                 if (EPI == EPI_RESID) v += pre_y;   // (e == tid: a block has at least RT * 128 threads)
                 *yp = v;
-                if (EPI == EPI_RESID) {
-                    if (a.nxA) split_store(a.nxA, a.ldy, m, n, v * pre_gA);
-                    if (a.nxB) split_store(a.nxB, a.ldy, m, n, v * pre_gB);
+                if constexpr (EPI == EPI_RESID) {
+                    if (a.out.nxA) split_store(a.out.nxA, a.out.ldy, m, n, v * pre_gA);
+                    if (a.out.nxB) split_store(a.out.nxB, a.out.ldy, m, n, v * pre_gB);
                     sq = v * v;
                 }
             }
             if (EPI == EPI_RESID) zs[t * 16 + i][m] = sq;
         }
-        if (EPI == EPI_RESID && a.ssq_out) {  // sum of squares of each 16-row tile, rows in index order
-            __syncthreads();
-            if (tid < RT * 8) {
-                int t = tid >> 3, m = tid & 7;
-                if (((rows >> m) & 1u) && n0 + t * 16 < N) {
-                    float sum = 0.f;
-                    for (int i = 0; i < 16; ++i) sum += zs[t * 16 + i][m];
-                    a.ssq_out[(size_t)m * a.ssq_ld + blockIdx.x * RT + t] = sum;
-                    if (a.ssq_out2) a.ssq_out2[(size_t)m * a.ssq_ld + blockIdx.x * RT + t] = sum;
+        if constexpr (EPI == EPI_RESID) {
+            if (a.out.ssq_out) {  // sum of squares of each 16-row tile, rows in index order
+                __syncthreads();
+                if (tid < RT * 8) {
+                    int t = tid >> 3, m = tid & 7;
+                    if (((rows >> m) & 1u) && n0 + t * 16 < N) {
+                        float sum = 0.f;
+                        for (int i = 0; i < 16; ++i) sum += zs[t * 16 + i][m];
+                        a.out.ssq_out[(size_t)m * a.ssq_ld + blockIdx.x * RT + t] = sum;
+                        if (a.out.ssq_out2) a.out.ssq_out2[(size_t)m * a.ssq_ld + blockIdx.x * RT + t] = sum;
+                    }
                 }
             }
         }
-    } else if (EPI == EPI_SWIGLU) {
+    } else if constexpr (EPI == EPI_SWIGLU) {
         if (tid < OT * 128) {
             int t = tid >> 7, m = (tid >> 4) & 7, i = tid & 15;
             int n = n0 + t * 16 + i;
@@ -475,8 +518,8 @@ __global__ __launch_bounds__(64 * WPB) void gemv_mfma_kernel(GemvArgs a) {
                 float g = (cs[t][i][m] + cs[t][i][m + 8]) * s_inv[m];
                 float u = (cs[OT + t][i][m] + cs[OT + t][i][m + 8]) * s_inv[m];
                 float v = silu_mul(g, u);
-                if (a.y) a.y[(size_t)m * a.ldy + n] = v;
-                if (a.ys) split_store(a.ys, a.ldy, m, n, v);
+                if (a.out.y) a.out.y[(size_t)m * a.out.ldy + n] = v;
+                if (a.out.ys) split_store(a.out.ys, a.out.ldy, m, n, v);
             }
         }
     } else if constexpr (EPI == EPI_HEAD) {
@@ -485,7 +528,7 @@ __global__ __launch_bounds__(64 * WPB) void gemv_mfma_kernel(GemvArgs a) {
             zs[t * 16 + i][m] = (cs[t][i][m] + cs[t][i][m + 8]) * (((rows >> m) & 1u) ? s_inv[m] : 0.f);
         }
         __syncthreads();
-        head_partial<16 * RT>(a.head, zs, rows, n0, N, gridDim.x);
+        head_partial<16 * RT>(a.out, zs, rows, n0, N, gridDim.x);
     }
 }
 
@@ -519,9 +562,10 @@ static int mfma_waves(int32_t N) { return N <= 4096 ? 8 : 4; }
 int head_blocks_mfma(int32_t N) { return (N + 16 * mfma_row_tiles(N) - 1) / (16 * mfma_row_tiles(N)); }
 
 template <int EPI, bool PACKED, bool RAW = false>
-static void launch_gemv_mfma_e(const GemvArgs& a, hipStream_t st) {
+static hipError_t launch_gemv_mfma_e(const GemvArgs& a, hipStream_t st) {
     if constexpr (!RAW && EPI != EPI_RESID)
         if (!a.xs) return launch_gemv_mfma_e<EPI, PACKED, true>(a, st);
+    const MfmaArgs<EPI> m = mfma_args<EPI, RAW>(a);
     if constexpr (EPI == EPI_SWIGLU) {
         const int pairs = a.N / 16;
         // Four tiles (two pairs) read the rows half as often; two blocks of them fit on a CU, so up to 1024 pairs, and only where
@@ -530,17 +574,15 @@ static void launch_gemv_mfma_e(const GemvArgs& a, hipStream_t st) {
         // 47.0, 51.6 / 48.2; 864 49.2 / 45.6, 50.6 / 46.5, 52.8 / 47.5, one row 45.5 and 46.4; 1024 52.8 / 52.3, 54.4 / 53.5, 56.5 / 52.8;
         // 1040, six rows 61.0 / 65.5. K = 4096: 896 pairs, three rows 38.9 and 39.5, row-major weights 47.4 and 50.4.
         if constexpr (PACKED)
-            if (a.K > 4096 && mfma_rows(a) >= 3 && pairs > 768 && pairs <= 1024) {
-                gemv_mfma_kernel<4, EPI, 4, 2, PACKED, RAW><<<(pairs + 1) / 2, 256, 0, st>>>(a);
-                return;
-            }
-        gemv_mfma_kernel<2, EPI, 4, 3, PACKED, RAW><<<pairs, 256, 0, st>>>(a);
+            if (a.K > 4096 && mfma_rows(a) >= 3 && pairs > 768 && pairs <= 1024)
+                return launch(&gemv_mfma_kernel<4, EPI, 4, 2, PACKED, RAW>, dim3((pairs + 1) / 2), 256, st, m);
+        return launch(&gemv_mfma_kernel<2, EPI, 4, 3, PACKED, RAW>, dim3(pairs), 256, st, m);
     } else {
         const MfmaShape sh = EPI == EPI_HEAD ? MfmaShape{mfma_row_tiles(a.N), mfma_waves(a.N)} : mfma_shape(a);
         const int one = a.N / 16, two = (a.N + 31) / 32;
-        if (sh.rt == 1 && sh.wpb == 8) gemv_mfma_kernel<1, EPI, 8, 2, PACKED, RAW><<<one, 512, 0, st>>>(a);
-        else if (sh.rt == 1) gemv_mfma_kernel<1, EPI, 4, 3, PACKED, RAW><<<one, 256, 0, st>>>(a);
-        else gemv_mfma_kernel<2, EPI, 4, 3, PACKED, RAW><<<two, 256, 0, st>>>(a);
+        if (sh.rt == 1 && sh.wpb == 8) return launch(&gemv_mfma_kernel<1, EPI, 8, 2, PACKED, RAW>, dim3(one), 512, st, m);
+        if (sh.rt == 1) return launch(&gemv_mfma_kernel<1, EPI, 4, 3, PACKED, RAW>, dim3(one), 256, st, m);
+        return launch(&gemv_mfma_kernel<2, EPI, 4, 3, PACKED, RAW>, dim3(two), 256, st, m);
     }
 }
 
@@ -548,18 +590,16 @@ hipError_t launch_gemv_mfma(const GemvArgs& a, hipStream_t st) {
     if (a.w_dtype != SB_BF16 || a.K % 128 != 0 || a.N % 16 != 0 || a.M < 1 || a.M > 8 || (!a.xs && (!a.x || a.epi == EPI_RESID)))
         return hipErrorInvalidValue;
     switch (a.epi) {
-        case EPI_STORE: a.packed ? launch_gemv_mfma_e<EPI_STORE, true>(a, st) : launch_gemv_mfma_e<EPI_STORE, false>(a, st); break;
-        case EPI_RESID: a.packed ? launch_gemv_mfma_e<EPI_RESID, true>(a, st) : launch_gemv_mfma_e<EPI_RESID, false>(a, st); break;
-        case EPI_SWIGLU: a.packed ? launch_gemv_mfma_e<EPI_SWIGLU, true>(a, st) : launch_gemv_mfma_e<EPI_SWIGLU, false>(a, st); break;
+        case EPI_STORE: return a.packed ? launch_gemv_mfma_e<EPI_STORE, true>(a, st) : launch_gemv_mfma_e<EPI_STORE, false>(a, st);
+        case EPI_RESID: return a.packed ? launch_gemv_mfma_e<EPI_RESID, true>(a, st) : launch_gemv_mfma_e<EPI_RESID, false>(a, st);
+        case EPI_SWIGLU: return a.packed ? launch_gemv_mfma_e<EPI_SWIGLU, true>(a, st) : launch_gemv_mfma_e<EPI_SWIGLU, false>(a, st);
         case EPI_HEAD: {
-            a.packed ? launch_gemv_mfma_e<EPI_HEAD, true>(a, st) : launch_gemv_mfma_e<EPI_HEAD, false>(a, st);
-            hipError_t e = hipGetLastError();
+            const hipError_t e = a.packed ? launch_gemv_mfma_e<EPI_HEAD, true>(a, st) : launch_gemv_mfma_e<EPI_HEAD, false>(a, st);
             if (e != hipSuccess || a.head.skip_merge) return e;
             return launch_head_merge(a.head, a.M, head_blocks_mfma(a.N), st);
         }
         default: return hipErrorInvalidValue;
     }
-    return hipGetLastError();
 }
 
 // ---------------------------------------------------------------- head evaluation without a workspace

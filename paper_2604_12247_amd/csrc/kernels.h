@@ -45,6 +45,17 @@ struct EmbedNorm { const float* gain; uint16_t* nx; float* ssq_out; int32_t ssq_
 enum Epilogue { EPI_STORE = 0, EPI_RESID = 1, EPI_SWIGLU = 2, EPI_HEAD = 3 };
 enum HeadPost { POST_NONE = 0, POST_EXIT = 1, POST_ACCEPT = 2 };
 
+// A launch without the push and the pop of a configuration that the <<< >>> form does around it (2.40 -> 2.26 us of host time); an error is
+// returned and not left for the caller's next call.
+template <typename T> struct as_given { using type = T; };
+template <typename... P>
+inline hipError_t launch(void (*kernel)(P...), dim3 grid, unsigned threads, hipStream_t st, typename as_given<P>::type... a) {
+    void* args[] = {&a...};
+    const hipError_t e = hipLaunchKernel(reinterpret_cast<const void*>(kernel), grid, dim3(threads), args, 0, st);
+    if (e != hipSuccess) (void)hipGetLastError();
+    return e;
+}
+
 // What the merge stage of a head evaluation does once the arg max / confidence
 // of all rows are known.
 struct HeadArgs {

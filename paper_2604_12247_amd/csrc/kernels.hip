@@ -83,11 +83,8 @@ __global__ __launch_bounds__(256) void embed_kernel(const WT* __restrict__ E, in
 
 hipError_t launch_embed(const void* E, int32_t w_dtype, int32_t vocab, int32_t d, float* H, int32_t M,
                         RowToks toks, const int32_t* slot_tok, int32_t* clear_flag, EmbedNorm en, hipStream_t st) {
-    if (w_dtype == SB_BF16)
-        embed_kernel<uint16_t><<<M, 256, 0, st>>>((const uint16_t*)E, vocab, d, H, toks, slot_tok, clear_flag, en);
-    else
-        embed_kernel<float><<<M, 256, 0, st>>>((const float*)E, vocab, d, H, toks, slot_tok, clear_flag, en);
-    return hipGetLastError();
+    if (w_dtype == SB_BF16) return launch(&embed_kernel<uint16_t>, dim3(M), 256, st, (const uint16_t*)E, vocab, d, H, toks, slot_tok, clear_flag, en);
+    return launch(&embed_kernel<float>, dim3(M), 256, st, (const float*)E, vocab, d, H, toks, slot_tok, clear_flag, en);
 }
 
 // The same for one row each of n sequences.
@@ -101,9 +98,8 @@ __global__ __launch_bounds__(256) void embed_batch_kernel(const WT* __restrict__
 }
 hipError_t launch_embed_batch(const void* E, int32_t w_dtype, int32_t vocab, int32_t d, const EmbedBatch& eb, int32_t n, hipStream_t st) {
     if (n < 1 || n > SB_MAX_W) return hipErrorInvalidValue;
-    if (w_dtype == SB_BF16) embed_batch_kernel<uint16_t><<<n, 256, 0, st>>>((const uint16_t*)E, vocab, d, eb);
-    else embed_batch_kernel<float><<<n, 256, 0, st>>>((const float*)E, vocab, d, eb);
-    return hipGetLastError();
+    if (w_dtype == SB_BF16) return launch(&embed_batch_kernel<uint16_t>, dim3(n), 256, st, (const uint16_t*)E, vocab, d, eb);
+    return launch(&embed_batch_kernel<float>, dim3(n), 256, st, (const float*)E, vocab, d, eb);
 }
 
 // ---------------------------------------------------------------- RMSNorm
@@ -160,8 +156,7 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(const float* __restrict__ 
 
 hipError_t launch_rmsnorm(const float* x, const float* gain, float* out, uint16_t* out_split, int32_t ld_split,
                           int32_t M, int32_t d, float eps, hipStream_t st) {
-    rmsnorm_kernel<<<M, 256, 0, st>>>(x, gain, out, out_split, ld_split, d, eps);
-    return hipGetLastError();
+    return launch(&rmsnorm_kernel, dim3(M), 256, st, x, gain, out, out_split, ld_split, d, eps);
 }
 
 __global__ void split_kernel(const float* __restrict__ x, uint16_t* __restrict__ xs, int K) {
@@ -170,8 +165,7 @@ __global__ void split_kernel(const float* __restrict__ x, uint16_t* __restrict__
     if (i < K) split_store(xs, K, m, i, x[(size_t)m * K + i]);
 }
 hipError_t launch_split(const float* x, uint16_t* xs, int32_t M, int32_t K, hipStream_t st) {
-    split_kernel<<<dim3((K + 255) / 256, M), 256, 0, st>>>(x, xs, K);
-    return hipGetLastError();
+    return launch(&split_kernel, dim3((K + 255) / 256, M), 256, st, x, xs, K);
 }
 
 __global__ void fill_u32_kernel(uint32_t* p, size_t n, uint32_t v) {
@@ -362,15 +356,13 @@ __global__ __launch_bounds__(MERGE_T) void head_merge_batch_kernel(HeadMergeBatc
 }
 
 hipError_t launch_head_merge(const HeadArgs& h, int32_t M, int32_t nb, hipStream_t st) {
-    head_merge_kernel<<<1, MERGE_T, 0, st>>>(h, M, nb);
-    return hipGetLastError();
+    return launch(&head_merge_kernel, dim3(1), MERGE_T, st, h, M, nb);
 }
 
 hipError_t launch_head_merge_batch(const HeadMergeBatch& hb, int32_t n, int32_t nb, hipStream_t st) {
     if (n < 1 || n > SB_MAX_W) return hipErrorInvalidValue;
     if (n == 1) return launch_head_merge(hb.h[0], hb.M[0], nb, st);
-    head_merge_batch_kernel<<<n, MERGE_T, 0, st>>>(hb, nb);
-    return hipGetLastError();
+    return launch(&head_merge_batch_kernel, dim3(n), MERGE_T, st, hb, nb);
 }
 
 // ---------------------------------------------------------------- sampling-mode acceptance
