@@ -85,23 +85,33 @@ int gemm_splits(int32_t rows, int32_t K, int32_t n_pass, bool gate_up) { return 
 // Rows of a pass: the super-pass in n_pass equal parts, rounded up to whole column tiles.
 static int gemm_pass_rows(int32_t M, int32_t n_pass) { return ((M + n_pass - 1) / n_pass + 15) / 16 * 16; }
 
-// Of the n values at p (16-byte aligned, readable up to the next multiple of four) this thread's share, four at a time: thread i of LANES. U
-// loads in flight together (a loop of load and add would be a round trip for each, single values four times the requests).
+// Of the n values at p (16-byte aligned, readable up to the next multiple of four) the share of thread i of LANES, four at a time: the first U
+// fours are requested together (a loop of load and add would be a round trip for each, single values four times the requests),
+// and added up where the caller has other loads on their way as well.
 template <int LANES, int U>
-__device__ __forceinline__ float sum_share(const float* p, int i, int n) {
-    float t = 0.f;
-    for (int j0 = i * 4; j0 < n; j0 += LANES * 4 * U) {
-        float4 q[U];
-#pragma unroll
-        for (int k = 0; k < U; ++k) q[k] = *reinterpret_cast<const float4*>(p + (j0 + k * LANES * 4 < n ? j0 + k * LANES * 4 : 0));
+struct SumShare {
+    float4 q[U];
+    __device__ __forceinline__ void load(const float* p, int i, int n, int j0 = 0) {
 #pragma unroll
         for (int k = 0; k < U; ++k) {
-            const int j = j0 + k * LANES * 4;
-            t += ((j < n ? q[k].x : 0.f) + (j + 1 < n ? q[k].y : 0.f)) + ((j + 2 < n ? q[k].z : 0.f) + (j + 3 < n ? q[k].w : 0.f));
+            const int j = j0 + (i + k * LANES) * 4;
+            q[k] = *reinterpret_cast<const float4*>(p + (j < n ? j : 0));
         }
     }
-    return t;
-}
+    __device__ __forceinline__ float sum(const float* p, int i, int n) {
+        float t = 0.f;
+        for (int j0 = 0;;) {
+#pragma unroll
+            for (int k = 0; k < U; ++k) {
+                const int j = j0 + (i + k * LANES) * 4;
+                t += ((j < n ? q[k].x : 0.f) + (j + 1 < n ? q[k].y : 0.f)) + ((j + 2 < n ? q[k].z : 0.f) + (j + 3 < n ? q[k].w : 0.f));
+            }
+            j0 += LANES * 4 * U;
+            if (j0 >= n) return t;   // (the same for all lanes)
+            load(p, i, n, j0);
+        }
+    }
+};
 
 // ---- pieces of the GEMM kernel (all inlined; register arrays are passed by reference) ----
 struct GemmCtx {
@@ -255,11 +265,15 @@ struct GemmStage<CT, true> {
     }
 };
 
+// Where a lane's four values lie in a piece whose first row is followed by `live` - 1 live ones (in floats).
+__device__ __forceinline__ int piece_offset(int lane, int live) { return live < 16 ? (lane & 15) * 16 + (lane >> 4) * 4 : lane * 4; }
+
 // Partial sum of row block b, or the finished tail where the row block's whole k range was this thread
 // block's; then zero for the next row block.  C layout: register r of lane l is weight row 4 (l / 16) + r
 // of the tile, activation row l % 16.  A partial sum is left as the registers hold it, 1 KB per weight tile and column tile, lane l's four
 // values at 16 l: as rows of the result, 64 bytes of each of 16 rows per store, the launches took 4 to 6 % longer
-// ([22016 x 4096] at 512 rows 154 us, now 144; without any partial sums 132).
+// ([22016 x 4096] at 512 rows 154 us, now 144; without any partial sums 132).  Of a column tile that is not full only the live rows are left, 64
+// neighbouring bytes each ([28672 x 4096] at 17 rows 42.6 us, with all 32 rows 44.9, with the live lanes at 16 l 43.8).
 template <int RT, int CT, bool SWI>
 __device__ __forceinline__ void gemm_flush(f32x4 (&acc)[RT][CT], const GemmArgs& a, const GemmCtx& c, int b, int q,
                                            const float* s_inv, int lane) {
@@ -301,13 +315,15 @@ __device__ __forceinline__ void gemm_flush(f32x4 (&acc)[RT][CT], const GemmArgs&
             }
         }
     } else {
-        float* const p = a.part + (size_t)(c.pass * a.S + c.cid - first) * a.pass_rows * a.rows + lane * 4;
+        float* const p = a.part + (size_t)(c.pass * a.S + c.cid - first) * a.pass_rows * a.rows;
 #pragma unroll
         for (int t = 0; t < RT; ++t) {
             const int tile = gemm_tile<RT, SWI>(c, b, t);
             if (tile < 0) continue;
 #pragma unroll
-            for (int ct = 0; ct < CT; ++ct) *reinterpret_cast<f32x4*>(p + ((size_t)tile * CT + ct) * 256) = acc[t][ct];
+            for (int ct = 0; ct < CT; ++ct)
+                if (ct * 16 + li < c.Mp)
+                    *reinterpret_cast<f32x4*>(p + ((size_t)tile * CT + ct) * 256 + piece_offset(lane, c.Mp - ct * 16)) = acc[t][ct];
         }
     }
 #pragma unroll
@@ -386,7 +402,12 @@ __global__ __launch_bounds__(64 * WPB) void prefill_gemm_kernel(GemmArgs a, int 
     if (a.fused) {  // 1 / rms of this pass's input rows, from the partial sums of squares their producer left
         const int m = tid >> 2, part = tid & 3;
         float t = 0.f;
-        if (a.ssq_in) t = sum_share<4, 6>(a.ssq_in + (size_t)(c.row0 + (m < c.Mp ? m : 0)) * a.ssq_ld, part, a.ssq_nb);
+        if (a.ssq_in && m < c.Mp) {
+            const float* const p = a.ssq_in + (size_t)(c.row0 + m) * a.ssq_ld;
+            SumShare<4, 5> ss;
+            ss.load(p, part, a.ssq_nb);
+            t = ss.sum(p, part, a.ssq_nb);
+        }
         t += __shfl_xor(t, 1, 64);
         t += __shfl_xor(t, 2, 64);
         if (part == 0) s_inv[m] = a.ssq_in ? 1.0f / sqrtf(t / (float)a.K + a.eps) : 1.0f;
@@ -587,16 +608,18 @@ __global__ __launch_bounds__(256) void prefill_epilogue_kernel(GemmEpiArgs a, Ge
     // ([28672 x 4096] at 1999 rows, where the GEMM finishes six row blocks in seven, took 46 us with every wave adding up its rows' sums
     // of squares first, 29 without)
     if (fused && __syncthreads_and(skip)) return;
-    if (a.ssq_in) {   // scales of the rows
-        const int r = tid >> 4, i = tid & 15;
-        const float t = lanes_sum<8>(sum_share<16, 2>(a.ssq_in + (size_t)(m0 + (r < rows ? r : 0)) * a.ssq_ld, i, a.ssq_nb));
-        if (i == 0) s_inv[r] = 1.0f / sqrtf(t / (float)a.K + a.eps);
-    }
     const int li = lane & 15, lq = lane >> 4;
+    // Scales of the rows, requested before the sums and added up behind them.  A wave that keeps its registers' layout works out its own
+    // (four lanes per row), else sixteen threads a row's for the block.
+    constexpr bool OWN = TN == 1 && EPI != EPI_RESID;
+    const int sr = OWN ? li : tid >> 4, si = OWN ? lq : tid & 15;
+    const float* const ssp = a.ssq_in + (size_t)(m0 + (sr < rows ? sr : 0)) * a.ssq_ld;
+    SumShare<OWN ? 4 : 16, OWN ? 5 : 2> ss;
+    if (a.ssq_in) ss.load(ssp, si, a.ssq_nb);
     f32x4 v[TN], u[TN];
-    if (!skip) {
+    if (!skip && li < rows) {
         const size_t plane = (size_t)mp.pass_rows * a.rows, tstride = (size_t)CT * 256;
-        const float* const p0 = a.part + (size_t)pass * a.S * plane + (size_t)lane * 4;
+        const float* const p0 = a.part + (size_t)pass * a.S * plane + piece_offset(lane, rows);
         const int sp = splits_of(mp, nt);
         const bool full = nt + TN * 16 <= a.N;
         const auto sum = [&](f32x4 (&x)[TN], int c0, int splits) {
@@ -612,13 +635,26 @@ __global__ __launch_bounds__(256) void prefill_epilogue_kernel(GemmEpiArgs a, Ge
                         x[t] = one[0];
                     }
         };
-        sum(v, nt, sp);
-        if (EPI == EPI_SWIGLU) sum(u, a.N + nt, sp);   // (a row block holds gate and up tiles side by side)
+        // (a row block holds gate and up tiles side by side)
+        if constexpr (EPI == EPI_SWIGLU && TN == 1) {
+            f32x4 x[2];
+            sum_splits<2, 4>(x, p0 + ((size_t)(nt / 16) * CT + ct) * 256, (size_t)(a.N / 16) * CT * 256, plane, sp);
+            v[0] = x[0];
+            u[0] = x[1];
+        } else {
+            sum(v, nt, sp);
+            if (EPI == EPI_SWIGLU) sum(u, a.N + nt, sp);
+        }
     }
-    if constexpr (TN == 1 && EPI != EPI_RESID) {   // (as the registers hold them: a short launch gains more by a barrier less)
-        if (a.ssq_in) __syncthreads();
+    float inv_own = 1.0f;
+    if (a.ssq_in) {
+        const float t = ss.sum(ssp, si, a.ssq_nb), sum = OWN ? lanes_sum<32, 16>(t) : lanes_sum<8>(t);
+        inv_own = 1.0f / sqrtf(sum / (float)a.K + a.eps);
+        if (!OWN && si == 0) s_inv[sr] = inv_own;
+    }
+    if constexpr (OWN) {   // (as the registers hold them: a short launch gains more by a barrier less)
         if (skip || li >= rows) return;
-        const float inv = a.ssq_in ? s_inv[li] : 1.0f;
+        const float inv = inv_own;
         const int m = m0 + li, n = nt + lq * 4;
         if (EPI == EPI_SWIGLU)
             split_store4(a.ys, a.N, a.plane_rows, m, n, make_float4(silu_mul(v[0][0] * inv, u[0][0] * inv), silu_mul(v[0][1] * inv, u[0][1] * inv),
