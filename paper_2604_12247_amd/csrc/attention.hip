@@ -108,7 +108,7 @@ __device__ __forceinline__ void store_near(T* p, const T (&v)[N]) {
 template <bool VEC>
 __device__ __forceinline__ int attn_row(const AttnArgs& a, int qq) {
     if constexpr (VEC) return a.g_inv ? (int)__umulhi((uint32_t)qq, a.g_inv) : qq;   // (0: one query per row and kv head)
-    else return qq / (a.n_heads / a.kv.n_kv_heads);
+    else return qq / a.group;
 }
 
 // The queries of a block with their rotary factors, four pairs per thread.  VEC: four loads of 16 bytes each instead of sixteen.
@@ -121,7 +121,7 @@ struct QueryRows {
     static __device__ __forceinline__ int dim() { return threadIdx.x % TPQ * 4; }
     // queries q0 .. q0 + nq - 1 of kv head g; the others read the first one and count as zeros
     __device__ __forceinline__ void load(const AttnArgs& a, int g, int q0, int nq) {
-        const int G = a.n_heads / a.kv.n_kv_heads, qi = query(), j = dim();
+        const int G = a.group, qi = query(), j = dim();
         live = qi < nq;
         const int qq = q0 + (live ? qi : 0), r = attn_row<VEC>(a, qq), gi = qq - r * G;
         const float* qp = a.q + (size_t)r * a.qkv_rows + (size_t)(g * G + gi) * HD + j;
@@ -219,7 +219,7 @@ __global__ __launch_bounds__(256, 4) void attn_kernel(AttnArgs a) {
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // (the chunk with the new rows, the longest to prepare, first)
     const int g = blockIdx.x, chunk = gridDim.y - 1 - blockIdx.y, qg = blockIdx.z;
-    const int Hq = a.n_heads, Hkv = a.kv.n_kv_heads, G = Hq / Hkv;
+    const int Hq = a.n_heads, Hkv = a.kv.n_kv_heads, G = a.group;
     const int nq_total = a.M * G, q0 = qg * QG;
     const int nq = (nq_total - q0 < QG) ? (nq_total - q0) : QG;
     const int key0 = chunk * CH, n_total = a.pos0 + a.M;
@@ -469,10 +469,13 @@ __global__ __launch_bounds__(256, 4) void attn_kernel(AttnArgs a) {
 // What bounds it: the chain page table -> operands -> scores -> soft-max -> values of a block, of which three per CU cover for each
 // other.  The chunk with the new rows is the longest: it is started first, and its new keys and values come with the other operands
 // and through LDS (a load and a wait for each element, as lanes picked them from the projections, cost 3 us at six rows).
-// Both kernels in a graph of launches, 32 heads x 128, six rows behind 520 / 2000 / 4200 keys 9.70 / 12.7 / 20.9 -> 9.02 / 12.4 / 20.5 us, one row behind 520 8.5 -> 8.1;
-// 32 heads over 8 x 128, four rows behind 700 9.9 -> 8.3, one row 8.55 -> 7.9; one row of 32 behind 20 keys (the first stage alone) 5.4 -> 4.9: with the queries
-// in wide loads, a query's row by a multiplication, new rows looked for only where a tile has one and taken in whole operands, and up to
-// sixteen queries' soft-max side by side.  Of 5.4 us for a block's chain now, 1.7 are an empty launch's and 2.6 the two round trips.
+// Both kernels in a graph of launches, 32 heads x 128, one row behind 520 / 1000 keys 8.5 / 9.4 -> 7.75 / 8.7 us, six behind 520 / 2000 / 4200 9.70 / 12.7 /
+// 20.9 -> 8.75 / 12.2 / 20.3; 32 heads over 8 x 128, one / four rows behind 700 8.55 / 9.9 -> 7.5 / 8.1; one row of 32 behind 20 keys (the first stage alone)
+// 5.4 -> 4.6.  What that took: the queries in wide loads, a query's row by a multiplication, the group's size from the host, new rows looked for only
+// where a tile has one and taken under a branch, up to sixteen queries' soft-max side by side with their probabilities split in pairs, nothing
+// written for queries that are not there, a partial's maximum and sum stored where they are found, its address in 32 bits.  Of some
+// 8500 cycles of a block's chain (one row) the page table takes 500, the operands 3000, the new rows 1400, the queries 850, scores 500,
+// soft-max 850, values and stores 1000.
 // LDS of one block of the matrix-core attention kernels (one work item is computed at a time).
 template <int HD>
 struct AttnLds {
@@ -480,7 +483,7 @@ struct AttnLds {
     __attribute__((aligned(16))) uint16_t q_hi[QG * QS], q_lo[QG * QS];
     __attribute__((aligned(16))) uint16_t p_hi[QG * PS], p_lo[QG * PS];
     __attribute__((aligned(16))) float s_s[QG * SS];
-    float s_m[QG], s_l[QG];
+    float s_l[QG];
 };
 
 // One work item of the kernel -- (kv head g, key chunk, slice zb of the query groups) -- in two
@@ -503,7 +506,7 @@ struct AttnItem {
     NewRows<HD, VEC> nr;
 
     __device__ __forceinline__ void load_q(const AttnArgs& a, int qg) {
-        const int nq_total = a.M * (a.n_heads / a.kv.n_kv_heads), q0 = qg * QG;
+        const int nq_total = a.M * a.group, q0 = qg * QG;
         qr.load(a, g, q0, nq_total - q0 < QG ? nq_total - q0 : QG);
     }
 
@@ -511,7 +514,7 @@ struct AttnItem {
         g = g_; chunk = chunk_; zb = zb_;
         const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
         const int li = lane & 15, lq = lane >> 4;
-        const int Hq = a.n_heads, Hkv = a.kv.n_kv_heads, G = Hq / Hkv;
+        const int Hkv = a.kv.n_kv_heads, G = a.group;
         const int nq_total = a.M * G;
         // this block's query groups (16 queries each), handled one after the other with the
         // chunk's K and V held in registers
@@ -565,7 +568,7 @@ struct AttnItem {
     __device__ __forceinline__ void compute(const AttnArgs& a, AttnLds<HD>& lds) {
         const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
         const int li = lane & 15, lq = lane >> 4;
-        const int Hq = a.n_heads, Hkv = a.kv.n_kv_heads, G = Hq / Hkv;
+        const int Hq = a.n_heads, Hkv = a.kv.n_kv_heads, G = a.group;
         const int nq_total = a.M * G;
         // this block's query groups (16 queries each), handled one after the other with the
         // chunk's K and V held in registers
@@ -582,7 +585,7 @@ struct AttnItem {
         (void)kbase; (void)vbase; (void)has_new; (void)page_elems; (void)nq_total;
         uint16_t* const q_hi = lds.q_hi; uint16_t* const q_lo = lds.q_lo;
         uint16_t* const p_hi = lds.p_hi; uint16_t* const p_lo = lds.p_lo;
-        float* const s_s = lds.s_s; float* const s_m = lds.s_m; float* const s_l = lds.s_l;
+        float* const s_s = lds.s_s; float* const s_l = lds.s_l;
         // (the new rows lie where the probabilities come later)
         uint16_t* const nk_s = lds.p_hi; uint16_t* const nv_s = lds.p_lo;
         static_assert(SB_MAX_W * QS <= QG * PS && HD * 16 <= QG * PS && SB_MAX_W <= 8, "the new rows fit");
@@ -621,18 +624,25 @@ struct AttnItem {
             for (int t = 0; t < 2; ++t) {
                 const int kt0 = key0 + wave * 32 + t * 16, key = kt0 + li;
                 if (kt0 + 16 <= a.pos0 || kt0 >= n_total) continue;   // (wave-uniform: no new key in this tile)
-                const bool fresh = key >= a.pos0 && key < n_total;
-                const uint16_t* kp = nk_s + (fresh ? key - a.pos0 : 0) * QS + lq * 8;
+                if (key >= a.pos0 && key < n_total) {
+                    uint16_t* const at = kbase + (size_t)kpage[t] * page_elems + (uint32_t)((g * SB_KV_BLOCK + li) * HD + lq * 8);
     #pragma unroll
-                for (int ks = 0; ks < KSQ; ++ks) {
-                    const uint4 v = *reinterpret_cast<const uint4*>(kp + ks * 32);
-                    kreg[t][ks] = pick(fresh, v, kreg[t][ks]);
+                    for (int ks = 0; ks < KSQ; ++ks) {
+                        kreg[t][ks] = *reinterpret_cast<const uint4*>(nk_s + (key - a.pos0) * QS + lq * 8 + ks * 32);
+                        if (zb == 0) *reinterpret_cast<uint4*>(at + ks * 32) = kreg[t][ks];
+                    }
                 }
             }
     #pragma unroll
             for (int ks = 0; ks < KSV; ++ks) {
                 const int kf = key0 + ks * 32 + lq * 8;
-                if (key0 + ks * 32 + 32 <= a.pos0 || key0 + ks * 32 >= n_total) continue;   // (block-uniform: no new row in this step)
+                // (block-uniform: no new row in this step, or no row at all)
+                if (key0 + ks * 32 + 32 <= a.pos0) continue;
+                if (key0 + ks * 32 >= n_total) {
+    #pragma unroll
+                    for (int dt = 0; dt < DT; ++dt) vreg[dt][ks] = make_uint4(0, 0, 0, 0);
+                    continue;
+                }
                 // of this lane's eight keys: which are new (or past the last key), which exist
                 uint32_t fresh[4], keep[4];
     #pragma unroll
@@ -649,26 +659,9 @@ struct AttnItem {
                     w = make_uint4(((w.x & ~fresh[0]) | (v.x & fresh[0])) & keep[0], ((w.y & ~fresh[1]) | (v.y & fresh[1])) & keep[1],
                                    ((w.z & ~fresh[2]) | (v.z & fresh[2])) & keep[2], ((w.w & ~fresh[3]) | (v.w & fresh[3])) & keep[3]);
                 }
-            }
+                if (zb == 0 && kf + 8 > a.pos0 && kf < n_total)
     #pragma unroll
-            for (int ks = 1; ks < KSV; ++ks)   // (the first step holds a key)
-    #pragma unroll
-                for (int dt = 0; dt < DT; ++dt) vreg[dt][ks] = pick(key0 + ks * 32 >= n_total, make_uint4(0, 0, 0, 0), vreg[dt][ks]);
-            if (zb == 0) {
-    #pragma unroll
-                for (int t = 0; t < 2; ++t) {
-                    const int key = key0 + wave * 32 + t * 16 + li;
-                    if (key >= a.pos0 && key < n_total)
-    #pragma unroll
-                        for (int ks = 0; ks < KSQ; ++ks) *reinterpret_cast<uint4*>(kbase + (size_t)kpage[t] * page_elems + (uint32_t)((g * SB_KV_BLOCK + li) * HD + lq * 8) + ks * 32) = kreg[t][ks];
-                }
-    #pragma unroll
-                for (int ks = 0; ks < KSV; ++ks) {
-                    const int kf = key0 + ks * 32 + lq * 8;
-                    if (kf + 8 > a.pos0 && kf < n_total)
-    #pragma unroll
-                        for (int dt = 0; dt < DT; ++dt) *reinterpret_cast<uint4*>(vbase + (size_t)vpg[ks] * page_elems + (uint32_t)((g * HD + (wave * DT + dt) * 16 + li) * SB_KV_BLOCK + (lq & 1) * 8)) = vreg[dt][ks];
-                }
+                    for (int dt = 0; dt < DT; ++dt) *reinterpret_cast<uint4*>(vbase + (size_t)vpg[ks] * page_elems + (uint32_t)((g * HD + (wave * DT + dt) * 16 + li) * SB_KV_BLOCK + (lq & 1) * 8)) = vreg[dt][ks];
             }
         }
 
@@ -695,13 +688,23 @@ struct AttnItem {
         __syncthreads();
         // ---- softmax partial of each query over the chunk: up to four queries a wave each, with more all sixteen at once, 16 lanes
         // each with keys t0, t0 + 16, ..; either way a query's sum is taken over key bits 6, 5, .. 0 in this order
+        // (what lies in the operand rows of queries that are not there reaches their own result rows only)
+        const auto put_pair = [&](int at, int step, float x, float y) {   // two probabilities as high and low parts
+            uint32_t h, l;
+            split_pair(__float_as_uint(x), __float_as_uint(y), h, l);
+            p_hi[at] = (uint16_t)h; p_hi[at + step] = (uint16_t)(h >> 16);
+            p_lo[at] = (uint16_t)l; p_lo[at + step] = (uint16_t)(l >> 16);
+        };
+        const auto partial = [&](int qq, int r) {   // of query qq, a query of row r (the head's number is g G + qq - r G)
+            const uint32_t at = (uint32_t)(r * (Hq - G) + g * G + qq) * (uint32_t)a.max_chunks + (uint32_t)chunk;
+            return a.partials + (size_t)at * (HD + 2);
+        };
+        const auto put_sum = [&](int qi, int r, float mx, float l) {
+            if (a.direct) s_l[qi] = l;
+            else if (key0 <= a.pos0 + r) *reinterpret_cast<float2*>(partial(q0 + qi, r)) = make_float2(mx, l);
+        };
         if (nq <= 4) {
             const int qi = wave;
-            for (int z = wave; z < QG; z += 4) {   // unused operand rows: defined values
-                if (z < nq) continue;
-                p_hi[z * PS + lane] = p_hi[z * PS + lane + 64] = 0;
-                p_lo[z * PS + lane] = p_lo[z * PS + lane + 64] = 0;
-            }
             if (qi < nq) {
                 const int r = attn_row<VEC>(a, q0 + qi);
                 float sc[2], mx = -SB_INF;
@@ -712,22 +715,17 @@ struct AttnItem {
                     mx = fmaxf(mx, sc[h]);
                 }
                 mx = wave_max(mx);
-                float l = 0.f;
+                float p[2];
     #pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    const float p = (mx == -SB_INF) ? 0.f : expf(sc[h] - mx);
-                    const uint16_t ph = f2bf(p);
-                    p_hi[qi * PS + lane + 64 * h] = ph;
-                    p_lo[qi * PS + lane + 64 * h] = f2bf(p - bf2f(ph));
-                    l += p;
-                }
-                l = wave_sum(l);
-                if (lane == 0) { s_m[qi] = mx; s_l[qi] = l; }
+                for (int h = 0; h < 2; ++h) p[h] = (mx == -SB_INF) ? 0.f : expf(sc[h] - mx);
+                put_pair(qi * PS + lane, 64, p[0], p[1]);
+                const float l = wave_sum(p[0] + p[1]);
+                if (lane == 0) put_sum(qi, r, mx, l);
             }
         } else {
             const int qi = tid >> 4, t0 = tid & 15;
             const bool live = qi < nq;   // (unused operand rows: defined values)
-            const int vis = a.pos0 + attn_row<VEC>(a, q0 + qi) - key0 - t0;
+            const int r = attn_row<VEC>(a, q0 + qi), vis = a.pos0 + r - key0 - t0;
             float sc[8], p[8], mx = -SB_INF;
     #pragma unroll
             for (int k = 0; k < 8; ++k) {
@@ -736,18 +734,15 @@ struct AttnItem {
             }
             mx = lanes_max<8>(mx);
     #pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                p[k] = !live || mx == -SB_INF ? 0.f : expf(sc[k] - mx);
-                const uint16_t ph = f2bf(p[k]);
-                p_hi[qi * PS + t0 + 16 * k] = ph;
-                p_lo[qi * PS + t0 + 16 * k] = f2bf(p[k] - bf2f(ph));
-            }
+            for (int k = 0; k < 8; ++k) p[k] = !live || mx == -SB_INF ? 0.f : expf(sc[k] - mx);
+    #pragma unroll
+            for (int k = 0; k < 8; k += 2) put_pair(qi * PS + t0 + 16 * k, 16, p[k], p[k + 1]);
     #pragma unroll
             for (int d = 4; d > 0; d >>= 1)
     #pragma unroll
                 for (int k = 0; k < d; ++k) p[k] += p[k + d];
             const float l = lanes_sum<8>(p[0]);
-            if (t0 == 0 && live) { s_m[qi] = mx; s_l[qi] = l; }
+            if (t0 == 0 && live) put_sum(qi, r, mx, l);
         }
         __syncthreads();
         // ---- weighted values: this wave's DT tiles of 16 dims, all keys of the chunk
@@ -770,17 +765,17 @@ struct AttnItem {
             for (int r = 0; r < 4; ++r) {
                 const int qi = 4 * lq + r;
                 if (qi >= nq) continue;
-                const int qq = q0 + qi, rr = attn_row<VEC>(a, qq), gi = qq - rr * G;
+                const int rr = attn_row<VEC>(a, q0 + qi);
                 if (key0 > a.pos0 + rr) continue;  // (a chunk with no visible key leaves no partial)
                 if (a.direct) {
+                    const int gi = q0 + qi - rr * G;
     #pragma unroll
                     for (int dt = 0; dt < DT; ++dt) attn_finish(a, rr, (g * G + gi) * HD + (wave * DT + dt) * 16 + li, Hq * HD, o[dt][r] / s_l[qi]);
                     continue;
                 }
-                float* p = a.partials + ((size_t)(rr * Hq + g * G + gi) * a.max_chunks + chunk) * (HD + 2);
+                float* const p = partial(q0 + qi, rr) + 2 + wave * DT * 16 + li;
     #pragma unroll
-                for (int dt = 0; dt < DT; ++dt) p[2 + (wave * DT + dt) * 16 + li] = o[dt][r];
-                if (wave == 0 && li == 0) { p[0] = s_m[qi]; p[1] = s_l[qi]; }
+                for (int dt = 0; dt < DT; ++dt) p[dt * 16] = o[dt][r];
             }
         }
         __syncthreads();  // the next group overwrites the LDS arrays
@@ -943,6 +938,7 @@ hipError_t launch_attention(const AttnArgs& a, hipStream_t st) {
     if (!attn_shape(a, &n_chunks, &n_qg, &qpb)) return hipErrorInvalidValue;
     AttnArgs b = a;
     b.qg_per_block = qpb;
+    b.group = a.n_heads / a.kv.n_kv_heads;
     b.g_inv = attn_g_inv(a);
     // With a single chunk the merge would multiply by exp(0) and add zeros: the first stage divides and
     // stores by itself (the same bits), a launch less.  An output over the input has to wait for the end of the first stage.
@@ -990,6 +986,7 @@ hipError_t launch_attention_batch(const AttnArgs* seqs, int n, hipStream_t st) {
         if (!attn_shape(seqs[i], &n_chunks, &n_qg, &qpb) || seqs[i].M > SB_MAX_W) return hipErrorInvalidValue;
         ab.seq[i] = seqs[i];
         ab.seq[i].qg_per_block = qpb;
+        ab.seq[i].group = seqs[i].n_heads / seqs[i].kv.n_kv_heads;
         ab.seq[i].g_inv = attn_g_inv(seqs[i]);
         const int z = (n_qg + qpb - 1) / qpb;
         if (z > ab.zdim) ab.zdim = z;

@@ -172,6 +172,7 @@ struct AttnArgs {
     int32_t qkv_rows, n_heads;
     KvLayout kv;
     int32_t layer, pos0, M;
+    int32_t group;       // set by launch_attention: n_heads / n_kv_heads (a division by a number that only the launch knows is some forty instructions)
     float* partials;     // [M*n_heads][max_chunks][head_dim + 2]
     int32_t max_chunks;
     float* out;          // [M][n_heads*head_dim]
