@@ -352,7 +352,7 @@ __global__ __launch_bounds__(64 * WPB) void gemv_mfma_kernel(MfmaArgs<EPI> a) {
     __shared__ float cs[RT][16][17];
     __shared__ float zs[16 * RT][SB_MAX_W];
     __shared__ float s_inv[SB_MAX_W];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int li = lane & 15, lq = lane >> 4;
     const uint16_t* __restrict__ W = reinterpret_cast<const uint16_t*>(a.W);
     const int N = a.N, K = a.K, M = a.M;
@@ -426,6 +426,21 @@ __global__ __launch_bounds__(64 * WPB) void gemv_mfma_kernel(MfmaArgs<EPI> a) {
     };
     const int kb0 = wave;
     const int nkb = KB > wave ? (KB - wave + WPB - 1) / WPB : 0;  // k blocks of this wave
+    // The rows' partial sums of squares are requested before the weights: loads come back in order, and behind them these were waited for with
+    // the ring's three blocks of every wave, 37 MB at the 7B shape's QKV, before the next was asked for ([12288 x 4096], one / six rows 18.25 / 20.3 -> 17.25 / 19.7 us,
+    // [22016 x 4096] gate and up 28.0 / 30.7 -> 27.6 / 30.0, [6144 x 4096] one row 11.6 -> 11.2).
+    constexpr int SQ_ROWS = SB_MAX_W / WPB, SQ_U = 8;   // rows per wave; values per lane up to K = 8192
+    float sq[SQ_ROWS][SQ_U];
+    const auto sq_row = [&](int i) { return wave + i * WPB; };
+    if (a.ssq_in)
+#pragma unroll
+        for (int i = 0; i < SQ_ROWS; ++i)
+            if ((rows >> sq_row(i)) & 1u) {   // (wave-uniform, as the bounds below)
+                const float* const p = a.ssq_in + (size_t)sq_row(i) * a.ssq_ld;
+#pragma unroll
+                for (int u = 0; u < SQ_U; ++u)
+                    if (u * 64 < a.ssq_nb) sq[i][u] = p[u * 64 + lane < a.ssq_nb ? u * 64 + lane : 0];
+            }
 #pragma unroll
     for (int s = 0; s < DEPTH - 1; ++s) load_block(wbuf[s], bbuf[s], kb0 + s * WPB);
     // What the residual tail needs from memory (the element this thread finishes, its norm gains)
@@ -442,12 +457,17 @@ __global__ __launch_bounds__(64 * WPB) void gemv_mfma_kernel(MfmaArgs<EPI> a) {
         }
     }
     // RMSNorm scale of each row from the partial sums of squares its producer left
-    // (added in index order; the first weight loads are already in flight)
+    // (added in index order; the first weight loads are in flight)
     if (a.ssq_in) {
-        for (int m = wave; m < SB_MAX_W; m += WPB) {
-            if (!((rows >> m) & 1u)) continue;   // (wave-uniform)
+#pragma unroll
+        for (int i = 0; i < SQ_ROWS; ++i) {
+            const int m = sq_row(i);
+            if (!((rows >> m) & 1u)) continue;
             float t = 0.f;
-            for (int b = lane; b < a.ssq_nb; b += 64) t += a.ssq_in[(size_t)m * a.ssq_ld + b];
+#pragma unroll
+            for (int u = 0; u < SQ_U; ++u)
+                if (u * 64 < a.ssq_nb) t += u * 64 + lane < a.ssq_nb ? sq[i][u] : 0.f;
+            for (int b = lane + SQ_U * 64; b < a.ssq_nb; b += 64) t += a.ssq_in[(size_t)m * a.ssq_ld + b];
             t = wave_sum(t);
             if (lane == 0) s_inv[m] = 1.0f / sqrtf(t / (float)K + a.eps);
         }
