@@ -656,3 +656,23 @@ def test_failed_launch_abandons_the_round_and_keeps_the_committed_state(sb):
     assert gm2.cfg.max_w == 0
     cfg_small = sb.make_config(shape, 160, max_w=2)
     assert cfg_small.max_w == 2
+
+
+# partial sums of squares of a row, one per 16 columns: a single load of the wave, a second that few lanes have, eight and a loop for the rest
+@pytest.mark.parametrize("d_model", [1024, 1152, 8320])
+@pytest.mark.parametrize("n_prompt", [1, 7])
+def test_row_scales_of_decode_passes(sb, d_model, n_prompt):
+    """Cached keys and values of the second layer, whose rows are scaled by sums that the first layer left, against the oracle."""
+    kw = dict(d_model=d_model, n_heads=2, n_kv_heads=2, head_dim=128, d_ffn=256)
+    shape = si.tiny_shape(n_layers=2, n_exit_heads=1, **dict(_variants(sb)["bf16-mfma-packed"][0], **kw))
+    w = si.make_weights(shape, 79, gain_jitter=0.1)
+    om, gm = Oracle(shape, w, 32), gpu_model(shape, w, 32)
+    prompt = si.make_prompt(shape.vocab, n_prompt, 83)
+    osn, gsn = om.session(), gm.session()
+    osn.prefill(prompt)
+    gsn.prefill(prompt)
+    for pos in range(n_prompt):
+        (ko, vo), (kg, vg) = osn.kv_read(1, pos), gsn.debug_kv(1, pos)
+        # one bf16 unit of the largest value, as in test_prompt_pass_heights
+        assert np.max(np.abs(kg - ko)) <= 2.0 ** -7 * max(1.0, np.max(np.abs(ko))), pos
+        assert np.max(np.abs(vg - vo)) <= 2.0 ** -7 * max(1.0, np.max(np.abs(vo))), pos

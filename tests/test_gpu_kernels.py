@@ -197,6 +197,32 @@ def test_prompt_pass_gemm_long_ranges(T, N, K, M):
     assert float((y - ref).abs().max()) <= 3e-5 * float(ref.abs().max())   # 16-bit activation parts, as in test_prompt_pass_gemm
 
 
+# every number of k blocks that a wave is left with at the end (and waves without any): eight waves and a ring of two, four and a ring of three
+# with one and two tiles, and the gate / up form with two pairs of tiles
+@pytest.mark.parametrize("kb", [1, 2, 3, 4, 5, 7, 8, 9, 11, 13, 16, 17, 20, 23, 24, 25, 29, 33, 41, 47])
+def test_gemv_mfma_last_blocks(T, kb):
+    import paper_2604_12247_amd as sb
+    K = 128 * kb
+    g = T.Generator(device="cuda")
+    g.manual_seed(kb)
+    for N, M in ((528, 1), (528, 8), (4128, 2), (8208, 1), (12320, 6)):
+        W = (T.randn(N, K, generator=g, device="cuda") * 0.02).to(T.bfloat16)
+        x = T.randn(M, K, generator=g, device="cuda")
+        ref = x.double() @ W.double().t().contiguous()
+        y, yp = sb.op_gemv(W, x, sb.PROJ_MFMA), sb.op_gemv(sb.op_repack(W), x, sb.PROJ_MFMA_PACKED)
+        assert T.equal(y, yp)
+        assert float((y.double() - ref).abs().max()) <= 3e-5 * float(ref.abs().max())   # 16-bit activation parts, as in test_prompt_pass_gemm
+    if kb >= 33:   # (K > 4096)
+        N, M = 12320, 3
+        W = (T.randn(2 * N, K, generator=g, device="cuda") * 0.02).to(T.bfloat16)
+        x = T.randn(M, K, generator=g, device="cuda")
+        z = x.double() @ W.double().t().contiguous()
+        ref = T.nn.functional.silu(z[:, :N]) * z[:, N:]
+        y = sb.op_gate_up(sb.op_repack(W), x, sb.PROJ_MFMA_PACKED).double()
+        # the two factors are off by at most 3e-5 of their largest value each; silu's slope is at most 1.1
+        assert float((y - ref).abs().max()) <= 2.1 * 3e-5 * float(z.abs().max()) ** 2
+
+
 # either side of the lines between the block shapes (4096, 6144, 8192 and 12288 output rows, K = 2048, 4096 and 8192, three and five rows)
 @pytest.mark.parametrize("N,K", [(4112, 4096), (4112, 1920), (4112, 8320), (6144, 2048), (6160, 2048), (8176, 256), (8192, 2048), (8208, 4224),
                                  (12288, 384), (12304, 384), (12304, 4224)])
