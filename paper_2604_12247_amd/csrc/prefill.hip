@@ -69,7 +69,7 @@ static GemmPlan gemm_plan_rt(int32_t rows, int32_t K, int32_t n_pass, int rt) {
 // a thread block still gets half a row block's k range or more (measured about even below it: [12288 x 4096] at
 // 512 rows 120 and 126 us with their epilogues, [4096 x 11008] at 1024 rows 183 and 196).  A single pass is bound
 // by the weight stream: small matrices take one tile, so that a thread block's range is long and its partial
-// sums few.  Whole calls with one / two tiles at 16, 64 and 128 rows: [12288 x 4096] (q = 12) 24.8 / 28.8, 32.5 / 38.6,
+// sums few.  Calls that split their rows first, with one / two tiles at 16, 64 and 128 rows: [12288 x 4096] (q = 12) 24.8 / 28.8, 32.5 / 38.6,
 // 46.3 / 53.8 us; [16384 x 4096] (16) 35.0 / 38.8, 39.9 / 47.5, 53.4 / 58.7; [5120 x 13824] (17) 31.6 / 31.6, 42.4 / 42.0,
 // 69.9 / 57.5; [15360 x 5120] (19) 33.2 / 33.5, 44.8 / 41.7, 61.3 / 58.4.
 static GemmPlan gemm_plan(int32_t rows, int32_t K, int32_t n_pass, bool gate_up) {
