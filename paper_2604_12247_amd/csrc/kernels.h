@@ -13,7 +13,7 @@ namespace sb {
 #define SB_PREFILL_ROWS 128
 
 // columns of one partial sum of squares of a prompt row
-#define SB_PREFILL_SSQ 64
+#define SB_PREFILL_SSQ 256
 
 // ---- device-resident record of the current round (read back once per sync) ----
 struct DevRound {

@@ -85,30 +85,30 @@ int gemm_splits(int32_t rows, int32_t K, int32_t n_pass, bool gate_up) { return 
 // Rows of a pass: the super-pass in n_pass equal parts, rounded up to whole column tiles.
 static int gemm_pass_rows(int32_t M, int32_t n_pass) { return ((M + n_pass - 1) / n_pass + 15) / 16 * 16; }
 
-// Of the n values at p (16-byte aligned, readable up to the next multiple of four) the share of thread i of LANES, four at a time: the first U
-// fours are requested together (a loop of load and add would be a round trip for each, single values four times the requests),
-// and added up where the caller has other loads on their way as well.
-template <int LANES, int U>
-struct SumShare {
+// The sum of the n values at p (16-byte aligned, readable up to the next multiple of four), added in index order: the first 4 U are requested
+// together (a loop of load and add would be a round trip for each, single values four times the requests), and added
+// up where the caller has other loads on their way as well.
+template <int U>
+struct IndexSum {
     float4 q[U];
-    __device__ __forceinline__ void load(const float* p, int i, int n, int j0 = 0) {
+    __device__ __forceinline__ void load(const float* p, int n, int j0 = 0) {
 #pragma unroll
-        for (int k = 0; k < U; ++k) {
-            const int j = j0 + (i + k * LANES) * 4;
-            q[k] = *reinterpret_cast<const float4*>(p + (j < n ? j : 0));
-        }
+        for (int k = 0; k < U; ++k) q[k] = *reinterpret_cast<const float4*>(p + (j0 + 4 * k < n ? j0 + 4 * k : 0));
     }
-    __device__ __forceinline__ float sum(const float* p, int i, int n) {
+    __device__ __forceinline__ float sum(const float* p, int n) {
         float t = 0.f;
         for (int j0 = 0;;) {
 #pragma unroll
             for (int k = 0; k < U; ++k) {
-                const int j = j0 + (i + k * LANES) * 4;
-                t += ((j < n ? q[k].x : 0.f) + (j + 1 < n ? q[k].y : 0.f)) + ((j + 2 < n ? q[k].z : 0.f) + (j + 3 < n ? q[k].w : 0.f));
+                const int j = j0 + 4 * k;
+                t += j < n ? q[k].x : 0.f;
+                t += j + 1 < n ? q[k].y : 0.f;
+                t += j + 2 < n ? q[k].z : 0.f;
+                t += j + 3 < n ? q[k].w : 0.f;
             }
-            j0 += LANES * 4 * U;
+            j0 += 4 * U;
             if (j0 >= n) return t;   // (the same for all lanes)
-            load(p, i, n, j0);
+            load(p, n, j0);
         }
     }
 };
@@ -265,8 +265,8 @@ struct GemmStage<CT, true> {
     }
 };
 
-// Where a lane's four values lie in a piece whose first row is followed by `live` - 1 live ones (in floats).
-__device__ __forceinline__ int piece_offset(int lane, int live) { return live < 16 ? (lane & 15) * 16 + (lane >> 4) * 4 : lane * 4; }
+// Where columns 4 quad .. 4 quad + 3 of a row lie in a piece whose first row is followed by `live` - 1 live ones (in floats).
+__device__ __forceinline__ int piece_offset(int row, int quad, int live) { return live < 16 ? row * 16 + quad * 4 : (quad * 16 + row) * 4; }
 
 // Partial sum of row block b, or the finished tail where the row block's whole k range was this thread
 // block's; then zero for the next row block.  C layout: register r of lane l is weight row 4 (l / 16) + r
@@ -323,7 +323,7 @@ __device__ __forceinline__ void gemm_flush(f32x4 (&acc)[RT][CT], const GemmArgs&
 #pragma unroll
             for (int ct = 0; ct < CT; ++ct)
                 if (ct * 16 + li < c.Mp)
-                    *reinterpret_cast<f32x4*>(p + ((size_t)tile * CT + ct) * 256 + piece_offset(lane, c.Mp - ct * 16)) = acc[t][ct];
+                    *reinterpret_cast<f32x4*>(p + ((size_t)tile * CT + ct) * 256 + piece_offset(li, lane >> 4, c.Mp - ct * 16)) = acc[t][ct];
         }
     }
 #pragma unroll
@@ -404,9 +404,13 @@ __global__ __launch_bounds__(64 * WPB) void prefill_gemm_kernel(GemmArgs a, int 
         float t = 0.f;
         if (a.ssq_in && m < c.Mp) {
             const float* const p = a.ssq_in + (size_t)(c.row0 + m) * a.ssq_ld;
-            SumShare<4, 5> ss;
-            ss.load(p, part, a.ssq_nb);
-            t = ss.sum(p, part, a.ssq_nb);
+            for (int i0 = part; i0 < a.ssq_nb; i0 += 20) {   // (five loads in flight: all of them up to K = 5120)
+                float x[5];
+#pragma unroll
+                for (int k = 0; k < 5; ++k) x[k] = p[i0 + 4 * k < a.ssq_nb ? i0 + 4 * k : 0];
+#pragma unroll
+                for (int k = 0; k < 5; ++k) t += i0 + 4 * k < a.ssq_nb ? x[k] : 0.f;
+            }
         }
         t += __shfl_xor(t, 1, 64);
         t += __shfl_xor(t, 2, 64);
@@ -591,36 +595,38 @@ __device__ __forceinline__ void sum_splits(f32x4 (&v)[TN], const float* p, size_
 // grid (ceil(N / (64 TN)), column tiles of all passes), 256 threads: a block takes 16 rows and 64 TN columns.  The sums are read as the
 // GEMM left them, a 1 KB piece per load, a wave TN weight tiles, and turned in LDS: then 16 TN lanes have a row's neighbouring
 // columns, and what is loaded and stored is whole cache lines (1999 rows, N = 6144: launch and GEMM 179 -> 169 us, of which 24 -> 20 here, with
-// rows of float4 read from row-major partial sums before).  The sums of squares are left per 64 columns.
-template <int EPI, int TN>
+// rows of float4 read from row-major partial sums before).
+// The residual takes 256 columns, so that a wave has those of one partial sum of squares; FEW: four rows of them, a wave four weight tiles.
+// A row's scale is the same in all forms: its partial sums of squares are added in index order.
+template <int EPI, int TN, bool FEW>
 __global__ __launch_bounds__(256) void prefill_epilogue_kernel(GemmEpiArgs a, GemmSplitMap mp) {
-    constexpr int COLS = 64 * TN, LD = COLS + 4, U = TN == 1 ? 8 : 2;   // (LDS rows four banks apart)
-    __shared__ __attribute__((aligned(16))) float turn[16 * LD];
-    __shared__ float s_inv[16];
+    static_assert(EPI == EPI_RESID ? TN == (FEW ? 1 : 4) : !FEW, "a residual's block has 256 columns");
+    constexpr int ROWS = FEW ? 4 : 16, WT = FEW ? 4 : TN;               // rows of a block, weight tiles of a wave
+    constexpr int COLS = 64 * WT, LD = COLS + 4, U = TN == 1 ? 8 : 2;   // (LDS rows four banks apart)
+    __shared__ __attribute__((aligned(16))) float turn[ROWS * LD];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int CT = mp.pass_rows / 16, pass = blockIdx.y / CT, ct = blockIdx.y - pass * CT;
-    const int m0 = pass * mp.pass_rows + ct * 16;   // first row, in the super-pass
-    const int rows = a.M - m0;                      // live rows from there (a pass before the last is full)
+    const int CT = mp.pass_rows / 16, tile = FEW ? blockIdx.y >> 2 : blockIdx.y, pass = tile / CT, ct = tile - pass * CT;
+    const int r1 = FEW ? (blockIdx.y & 3) * 4 : 0;  // the block's first row in the column tile
+    const int m0 = pass * mp.pass_rows + ct * 16;   // the tile's first row, in the super-pass
+    const int live = a.M - m0, rows = live - r1;    // live rows from there (a pass before the last is full)
     if (rows <= 0) return;
     const bool fused = (EPI == EPI_SWIGLU || EPI == EPI_STORE) && a.fused;
-    const int nb0 = blockIdx.x * COLS, nt = nb0 + wave * TN * 16;   // the block's first column, this wave's (its tiles lie in one row block)
-    const bool skip = nt >= a.N || (fused && splits_of(mp, nt) == 1);   // (past the end, or finished by the GEMM)
+    const int nb0 = blockIdx.x * COLS, nw = nb0 + wave * WT * 16;   // the block's first column, this wave's (its tiles lie in one row block)
+    // this lane's row of the block, quad of columns and (FEW: a lane has one of the wave's tiles) first column
+    const int li = lane & (ROWS - 1), lq = (FEW ? lane >> 2 : lane >> 4) & 3, nt = FEW ? nw + (lane >> 4) * 16 : nw;
+    const bool skip = nt >= a.N || (fused && splits_of(mp, nw) == 1);   // (past the end, or finished by the GEMM)
     // ([28672 x 4096] at 1999 rows, where the GEMM finishes six row blocks in seven, took 46 us with every wave adding up its rows' sums
     // of squares first, 29 without)
     if (fused && __syncthreads_and(skip)) return;
-    const int li = lane & 15, lq = lane >> 4;
-    // Scales of the rows, requested before the sums and added up behind them.  A wave that keeps its registers' layout works out its own
-    // (four lanes per row), else sixteen threads a row's for the block.
-    constexpr bool OWN = TN == 1 && EPI != EPI_RESID;
-    const int sr = OWN ? li : tid >> 4, si = OWN ? lq : tid & 15;
-    const float* const ssp = a.ssq_in + (size_t)(m0 + (sr < rows ? sr : 0)) * a.ssq_ld;
-    SumShare<OWN ? 4 : 16, OWN ? 5 : 2> ss;
-    if (a.ssq_in) ss.load(ssp, si, a.ssq_nb);
+    // Scale of the lane's row, requested before the sums and added up behind them.
+    const float* const ssp = a.ssq_in + (size_t)(m0 + r1 + (li < rows ? li : 0)) * a.ssq_ld;
+    IndexSum<5> ss;
+    if (a.ssq_in) ss.load(ssp, a.ssq_nb);
     f32x4 v[TN], u[TN];
     if (!skip && li < rows) {
         const size_t plane = (size_t)mp.pass_rows * a.rows, tstride = (size_t)CT * 256;
-        const float* const p0 = a.part + (size_t)pass * a.S * plane + piece_offset(lane, rows);
-        const int sp = splits_of(mp, nt);
+        const float* const p0 = a.part + (size_t)pass * a.S * plane + piece_offset(r1 + li, lq, live);
+        const int sp = splits_of(mp, nw);
         const bool full = nt + TN * 16 <= a.N;
         const auto sum = [&](f32x4 (&x)[TN], int c0, int splits) {
             const float* p = p0 + ((size_t)(c0 / 16) * CT + ct) * 256;
@@ -646,15 +652,10 @@ __global__ __launch_bounds__(256) void prefill_epilogue_kernel(GemmEpiArgs a, Ge
             if (EPI == EPI_SWIGLU) sum(u, a.N + nt, sp);
         }
     }
-    float inv_own = 1.0f;
-    if (a.ssq_in) {
-        const float t = ss.sum(ssp, si, a.ssq_nb), sum = OWN ? lanes_sum<32, 16>(t) : lanes_sum<8>(t);
-        inv_own = 1.0f / sqrtf(sum / (float)a.K + a.eps);
-        if (!OWN && si == 0) s_inv[sr] = inv_own;
-    }
-    if constexpr (OWN) {   // (as the registers hold them: a short launch gains more by a barrier less)
+    float inv = 1.0f;
+    if (a.ssq_in) inv = 1.0f / sqrtf(ss.sum(ssp, a.ssq_nb) / (float)a.K + a.eps);
+    if constexpr (TN == 1 && EPI != EPI_RESID) {   // (as the registers hold them: a short launch gains more by a barrier less)
         if (skip || li >= rows) return;
-        const float inv = inv_own;
         const int m = m0 + li, n = nt + lq * 4;
         if (EPI == EPI_SWIGLU)
             split_store4(a.ys, a.N, a.plane_rows, m, n, make_float4(silu_mul(v[0][0] * inv, u[0][0] * inv), silu_mul(v[0][1] * inv, u[0][1] * inv),
@@ -663,33 +664,32 @@ __global__ __launch_bounds__(256) void prefill_epilogue_kernel(GemmEpiArgs a, Ge
             *reinterpret_cast<float4*>(a.y + (size_t)m * a.ldy + n) = make_float4(v[0][0] * inv, v[0][1] * inv, v[0][2] * inv, v[0][3] * inv);
         return;
     }
-    // this thread's four columns, the same for all of its TN rows; what the residual needs of them is on its way while the block turns its tiles
-    const int c4 = (tid % (16 * TN)) * 4, n = nb0 + c4, r0 = tid / (16 * TN);
+    // this thread's four columns, the same for all of its TN rows (a wave takes a row's 256); what the residual needs of them is on its way while
+    // the block turns its tiles
+    const int c4 = lane * 4, n = nb0 + c4, m1 = m0 + r1;
     const bool mine = n < a.N && !(fused && splits_of(mp, n) == 1);
     float4 gn = make_float4(0.f, 0.f, 0.f, 0.f), y0[TN];
     if (EPI == EPI_RESID && mine) {
         if (a.nx) gn = *reinterpret_cast<const float4*>(a.gain + n);
 #pragma unroll
         for (int k = 0; k < TN; ++k) {
-            const int r = r0 + k * (16 / TN);
-            y0[k] = *reinterpret_cast<const float4*>(a.y + (size_t)(m0 + (r < rows ? r : 0)) * a.ldy + n);
+            const int r = wave + k * 4;
+            y0[k] = *reinterpret_cast<const float4*>(a.y + (size_t)(m1 + (r < rows ? r : 0)) * a.ldy + n);
         }
     }
-    if (a.ssq_in) __syncthreads();
     if (!skip) {
-        const float inv = a.ssq_in ? s_inv[li] : 1.0f;
 #pragma unroll
         for (int t = 0; t < TN; ++t) {
             f32x4 x;
 #pragma unroll
             for (int r = 0; r < 4; ++r) x[r] = EPI == EPI_SWIGLU ? silu_mul(v[t][r] * inv, u[t][r] * inv) : v[t][r] * inv;
-            *reinterpret_cast<f32x4*>(turn + li * LD + (wave * TN + t) * 16 + lq * 4) = x;
+            *reinterpret_cast<f32x4*>(turn + li * LD + nt - nb0 + t * 16 + lq * 4) = x;
         }
     }
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < TN; ++k) {
-        const int r = r0 + k * (16 / TN), m = m0 + r;
+        const int r = wave + k * 4, m = m1 + r;
         float sq = 0.f;
         if (mine && r < rows) {
             float4 x = *reinterpret_cast<const float4*>(turn + r * LD + c4);
@@ -705,15 +705,17 @@ __global__ __launch_bounds__(256) void prefill_epilogue_kernel(GemmEpiArgs a, Ge
             }
         }
         if (EPI == EPI_RESID && a.ssq_out) {
-            sq = lanes_sum<8>(sq);
-            if ((lane & 15) == 0 && mine && r < rows) a.ssq_out[(size_t)m * a.ssq_ld + n / SB_PREFILL_SSQ] = sq;
+            static_assert(SB_PREFILL_SSQ == 256, "a wave of four columns each");
+            sq = wave_sum(sq);
+            if (lane == 0 && r < rows) a.ssq_out[(size_t)m * a.ssq_ld + blockIdx.x] = sq;
         }
     }
 }
-template <int EPI, int TN>
+template <int EPI, int TN, bool FEW = false>
 static void launch_epilogue_t(const GemmEpiArgs& a, const GemmSplitMap& mp, hipStream_t st) {
-    const dim3 grid((a.N + 64 * TN - 1) / (64 * TN), a.n_pass * (mp.pass_rows / 16));
-    prefill_epilogue_kernel<EPI, TN><<<grid, 256, 0, st>>>(a, mp);
+    constexpr int COLS = FEW ? 256 : 64 * TN;
+    const dim3 grid((a.N + COLS - 1) / COLS, a.n_pass * (mp.pass_rows / 16) * (FEW ? 4 : 1));
+    prefill_epilogue_kernel<EPI, TN, FEW><<<grid, 256, 0, st>>>(a, mp);
 }
 
 hipError_t launch_prefill_epilogue(const GemmEpiArgs& a, hipStream_t st) {
@@ -729,17 +731,19 @@ hipError_t launch_prefill_epilogue(const GemmEpiArgs& a, hipStream_t st) {
                           gemm_pass_rows(a.M, a.n_pass)};
     if (a.epi != EPI_STORE && a.epi != EPI_RESID && a.epi != EPI_SWIGLU) return hipErrorInvalidValue;
     // A wave with four weight tiles stores whole rows of 1 KB; with one there are four times the blocks, which a launch of few
-    // needs and a residual, bound by what it reads, takes throughout. GEMM and epilogue, four / one, us: STORE [12288 x 4096] at 512 rows (1536 blocks) 100.4 / 104.5, 128 rows
+    // needs. GEMM and epilogue, four / one, us: STORE [12288 x 4096] at 512 rows (1536 blocks) 100.4 / 104.5, 128 rows
     // (384) 44.1 / 44.3, [15360 x 5120] at 45 rows (180) 38.1 / 36.9; SwiGLU [22016 x 4096] at 512 rows (1376) 163.5 / 164.7, [27648 x 5120] at 1000 rows 436 / 448, at 128
-    // rows (432) 90.0 / 89.5, 45 rows (162) 62.8 / 61.8; residual [4096 x 4096] at 512 rows 41.7 / 40.8, [5120 x 13824] at 45 rows 35.0 / 32.2, at 1999 rows the same.
+    // rows (432) 90.0 / 89.5, 45 rows (162) 62.8 / 61.8. The residual's blocks have 256 columns either way, of 16 rows or of four: three
+    // layers, whole prompt, 16 / four, us: 8B shape at 17 / 64 / 128 / 200 rows (32 to 208 blocks) 555 / 536, 656 / 643, 798 / 784, 923 / 917, 13B at 200 / 300 / 512
+    // (260 to 640) 1110 / 1119, 2032 / 2047, 1992 / 2018, 7B at 1999 (2000) 4257 / 4298.
     const long wide_blocks = (long)((a.N + 255) / 256) * a.n_pass * (mp.pass_rows / 16);
-    if (a.epi == EPI_RESID) launch_epilogue_t<EPI_RESID, 1>(a, mp, st);
+    if (a.epi == EPI_RESID) wide_blocks >= 256 ? launch_epilogue_t<EPI_RESID, 4>(a, mp, st) : launch_epilogue_t<EPI_RESID, 1, true>(a, mp, st);
     else if (a.epi == EPI_STORE) wide_blocks >= 512 ? launch_epilogue_t<EPI_STORE, 4>(a, mp, st) : launch_epilogue_t<EPI_STORE, 1>(a, mp, st);
     else wide_blocks >= 512 ? launch_epilogue_t<EPI_SWIGLU, 4>(a, mp, st) : launch_epilogue_t<EPI_SWIGLU, 1>(a, mp, st);
     return hipGetLastError();
 }
 
-// grid (ceil(d / 2048), M), d % 8 == 0: a thread takes eight neighbouring columns, eight lanes the 64
+// grid (ceil(d / 2048), M), d % 8 == 0: a thread takes eight neighbouring columns, the 32 lanes of half a wave the 256
 // columns of one partial sum of squares (16-byte stores throughout: 1999 rows of 4096 took 37 us with two-byte ones)
 template <typename WT>
 __global__ __launch_bounds__(256) void prefill_embed_kernel(const WT* __restrict__ E, int vocab, int d,
@@ -759,9 +763,9 @@ __global__ __launch_bounds__(256) void prefill_embed_kernel(const WT* __restrict
         for (int k = 0; k < 8; ++k) sq += v[k] * v[k];
     }
     if (ssq_out) {
-        static_assert(SB_PREFILL_SSQ == 64, "eight lanes of eight columns");
-        sq = lanes_sum<4>(sq);
-        if ((tid & 7) == 0 && n < d) ssq_out[(size_t)m * ssq_ld + n / SB_PREFILL_SSQ] = sq;
+        static_assert(SB_PREFILL_SSQ == 256, "32 lanes of eight columns");
+        sq = lanes_sum<16>(sq);
+        if ((tid & 31) == 0 && n < d) ssq_out[(size_t)m * ssq_ld + n / SB_PREFILL_SSQ] = sq;
     }
 }
 

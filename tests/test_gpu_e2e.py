@@ -676,3 +676,59 @@ def test_row_scales_of_decode_passes(sb, d_model, n_prompt):
         # one bf16 unit of the largest value, as in test_prompt_pass_heights
         assert np.max(np.abs(kg - ko)) <= 2.0 ** -7 * max(1.0, np.max(np.abs(ko))), pos
         assert np.max(np.abs(vg - vo)) <= 2.0 ** -7 * max(1.0, np.max(np.abs(vo))), pos
+
+
+def _prompt_rows(gm, layer, prompt):
+    """Cached keys and values of a prompt's positions, [2][position][kv heads x head_dim]."""
+    s = gm.session()
+    s.prefill(prompt)
+    return np.stack([np.stack(s.debug_kv(layer, p)) for p in range(len(prompt))], 1)
+
+
+# epilogues of one and of four weight tiles per wave (from 337 rows on at this width), one to three passes
+@pytest.mark.parametrize("n_prompt", [45, 150, 337])
+def test_prompt_row_scales_order_of_additions(sb, n_prompt):
+    """The scales of a prompt's rows, bit for bit: a partial sum of squares per 256 columns, by the fixed tree of the 32 lanes (embedding:
+    eight columns in a row each) or 64 lanes (residual: four each, as two pairs) that hold them, the partial sums in index order, or, where
+    the GEMM finishes the row, in two pairs.  Values are the rows themselves times the scale: V weights are the identity, W_o and W_down zero."""
+    shape = si.tiny_shape(n_layers=2, n_exit_heads=1, weight_dtype=si.configs.BF16, d_model=1024, n_heads=32, n_kv_heads=8, head_dim=128, d_ffn=256)
+    w = dict(si.make_weights(shape, 69))
+    d = shape.d_model
+    eye = (np.eye(d, dtype=np.float32).view(np.uint32) >> 16).astype(np.uint16)
+    for l in range(2):
+        w[f"w_qkv.{l}"] = np.concatenate([w[f"w_qkv.{l}"][:-d], eye])
+        w[f"w_o.{l}"], w[f"w_down.{l}"] = np.zeros_like(w[f"w_o.{l}"]), np.zeros_like(w[f"w_down.{l}"])
+    gm = gpu_model(shape, w, 352)
+    prompt = si.make_prompt(shape.vocab, n_prompt, 75)
+    h = (w["embed"][prompt].astype(np.uint32) << 16).view(np.float32)
+    q = h * h                                                  # (bf16 squares: exact)
+
+    def tree(a):
+        while a.shape[-1] > 1:
+            a = a[..., :a.shape[-1] // 2] + a[..., a.shape[-1] // 2:]
+        return a[..., 0]
+
+    lanes8 = q.reshape(n_prompt, 4, 32, 8)
+    emb = lanes8[..., 0]
+    for k in range(1, 8):
+        emb = emb + lanes8[..., k]
+    lanes4 = q.reshape(n_prompt, 4, 64, 4)
+    res = (lanes4[..., 0] + lanes4[..., 1]) + (lanes4[..., 2] + lanes4[..., 3])
+    for l, part in enumerate((tree(emb), tree(res))):
+        v = _prompt_rows(gm, l, prompt)[1]
+        same = np.zeros(n_prompt, dtype=bool)
+        for t in (((part[:, 0] + part[:, 1]) + part[:, 2]) + part[:, 3], (part[:, 0] + part[:, 1]) + (part[:, 2] + part[:, 3])):
+            inv = np.float32(1) / np.sqrt(t / np.float32(d) + np.float32(shape.rms_eps))
+            assert inv.dtype == np.float32
+            same |= np.all(v == h * inv[:, None], axis=1)
+        assert same.all(), (l, np.flatnonzero(~same)[:8])
+
+
+# prompts of as many passes on either side of the line between the epilogue's forms
+@pytest.mark.parametrize("n_heads,n_kv_heads,short,long", [(32, 8, 336, 337), (32, 32, 150, 170)])
+def test_prompt_row_does_not_depend_on_the_rows_after_it(sb, n_heads, n_kv_heads, short, long):
+    shape = si.tiny_shape(n_layers=1, n_exit_heads=1, weight_dtype=si.configs.BF16, d_model=4096, n_heads=n_heads, n_kv_heads=n_kv_heads,
+                          head_dim=128, d_ffn=256)
+    gm = gpu_model(shape, si.make_weights(shape, 70, gain_jitter=0.1), 352)
+    prompt = si.make_prompt(shape.vocab, long, 76)
+    assert np.array_equal(_prompt_rows(gm, 0, prompt[:short]), _prompt_rows(gm, 0, prompt)[:, :short])
