@@ -265,6 +265,23 @@ struct GemmStage<CT, true> {
     }
 };
 
+// Four outputs silu(g inv) * (u inv) as their two bf16 parts, {high, low} of two neighbours each.  The low part is what the unrounded product has
+// beyond the high one, spelled out: left to the compiler it is that only where the product is at hand, and a row's bits would depend on the form.
+__device__ __forceinline__ uint4 silu_parts4(f32x4 g, f32x4 u, float inv) {
+    uint32_t h[4], l[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const float x = g[i] * inv, y = u[i] * inv, s = x / (1.0f + expf(-x));
+        h[i] = f2bf(s * y);
+        l[i] = f2bf(fmaf(s, y, -bf2f((uint16_t)h[i])));
+    }
+    return make_uint4(h[0] | (h[1] << 16), h[2] | (h[3] << 16), l[0] | (l[1] << 16), l[2] | (l[3] << 16));
+}
+__device__ __forceinline__ void store_parts4(uint16_t* xs, int ld, int lo_rows, int m, int n, uint4 p) {
+    *reinterpret_cast<uint2*>(xs + (size_t)m * ld + n) = make_uint2(p.x, p.y);
+    *reinterpret_cast<uint2*>(xs + (size_t)(lo_rows + m) * ld + n) = make_uint2(p.z, p.w);
+}
+
 // Where columns 4 quad .. 4 quad + 3 of a row lie in a piece whose first row is followed by `live` - 1 live ones (in floats).
 __device__ __forceinline__ int piece_offset(int row, int quad, int live) { return live < 16 ? row * 16 + quad * 4 : (quad * 16 + row) * 4; }
 
@@ -293,9 +310,7 @@ __device__ __forceinline__ void gemm_flush(f32x4 (&acc)[RT][CT], const GemmArgs&
                 if (j >= 0 && m < c.Mp) {
                     const float inv = s_inv[m];
                     const f32x4 g = acc[t][ct], u = acc[RT / 2 + t][ct];
-                    split_store4(a.ys, a.N, a.plane_rows, c.row0 + m, j * 16 + sub,
-                                 make_float4(silu_mul(g[0] * inv, u[0] * inv), silu_mul(g[1] * inv, u[1] * inv),
-                                             silu_mul(g[2] * inv, u[2] * inv), silu_mul(g[3] * inv, u[3] * inv)));
+                    store_parts4(a.ys, a.N, a.plane_rows, c.row0 + m, j * 16 + sub, silu_parts4(g, u, inv));
                 }
             }
         }
@@ -658,8 +673,7 @@ __global__ __launch_bounds__(256) void prefill_epilogue_kernel(GemmEpiArgs a, Ge
         if (skip || li >= rows) return;
         const int m = m0 + li, n = nt + lq * 4;
         if (EPI == EPI_SWIGLU)
-            split_store4(a.ys, a.N, a.plane_rows, m, n, make_float4(silu_mul(v[0][0] * inv, u[0][0] * inv), silu_mul(v[0][1] * inv, u[0][1] * inv),
-                                                                    silu_mul(v[0][2] * inv, u[0][2] * inv), silu_mul(v[0][3] * inv, u[0][3] * inv)));
+            store_parts4(a.ys, a.N, a.plane_rows, m, n, silu_parts4(v[0], u[0], inv));
         else
             *reinterpret_cast<float4*>(a.y + (size_t)m * a.ldy + n) = make_float4(v[0][0] * inv, v[0][1] * inv, v[0][2] * inv, v[0][3] * inv);
         return;
@@ -680,9 +694,9 @@ __global__ __launch_bounds__(256) void prefill_epilogue_kernel(GemmEpiArgs a, Ge
     if (!skip) {
 #pragma unroll
         for (int t = 0; t < TN; ++t) {
-            f32x4 x;
-#pragma unroll
-            for (int r = 0; r < 4; ++r) x[r] = EPI == EPI_SWIGLU ? silu_mul(v[t][r] * inv, u[t][r] * inv) : v[t][r] * inv;
+            f32x4 x;   // (gate / up: the parts, so that they are made of the same unrounded products as in the other forms)
+            if constexpr (EPI == EPI_SWIGLU) x = __builtin_bit_cast(f32x4, silu_parts4(v[t], u[t], inv));
+            else x = v[t] * inv;
             *reinterpret_cast<f32x4*>(turn + li * LD + nt - nb0 + t * 16 + lq * 4) = x;
         }
     }
@@ -694,7 +708,7 @@ __global__ __launch_bounds__(256) void prefill_epilogue_kernel(GemmEpiArgs a, Ge
         if (mine && r < rows) {
             float4 x = *reinterpret_cast<const float4*>(turn + r * LD + c4);
             if (EPI == EPI_SWIGLU) {
-                split_store4(a.ys, a.N, a.plane_rows, m, n, x);
+                store_parts4(a.ys, a.N, a.plane_rows, m, n, __builtin_bit_cast(uint4, x));
             } else {
                 if (EPI == EPI_RESID) {
                     x.x += y0[k].x; x.y += y0[k].y; x.z += y0[k].z; x.w += y0[k].w;

@@ -732,3 +732,21 @@ def test_prompt_row_does_not_depend_on_the_rows_after_it(sb, n_heads, n_kv_heads
     gm = gpu_model(shape, si.make_weights(shape, 70, gain_jitter=0.1), 352)
     prompt = si.make_prompt(shape.vocab, long, 76)
     assert np.array_equal(_prompt_rows(gm, 0, prompt[:short]), _prompt_rows(gm, 0, prompt)[:, :short])
+
+
+# gate / up of as many passes with one and with two pairs of weight tiles per wave of the epilogue; 33152: blocks of it with a row block that
+# the GEMM has finished and one that it has not
+@pytest.mark.parametrize("d_ffn,short,long", [(11008, 160, 161), (33152, 48, 60)])
+def test_prompt_gate_up_forms_give_the_same_rows(sb, d_ffn, short, long):
+    """Keys and values of the second layer: the same bits for a common prefix, and the oracle's values."""
+    shape = si.tiny_shape(n_layers=2, n_exit_heads=1, weight_dtype=si.configs.BF16, d_model=512, n_heads=4, n_kv_heads=4, head_dim=128, d_ffn=d_ffn)
+    w = si.make_weights(shape, 71, gain_jitter=0.1)
+    om, gm = Oracle(shape, w, 176), gpu_model(shape, w, 176)
+    prompt = si.make_prompt(shape.vocab, long, 77)
+    got = _prompt_rows(gm, 1, prompt)
+    assert np.array_equal(_prompt_rows(gm, 1, prompt[:short]), got[:, :short])
+    osn = om.session()
+    osn.prefill(prompt)
+    for pos in range(long):
+        for o, g in zip(osn.kv_read(1, pos), got[:, pos]):
+            assert np.max(np.abs(g - o)) <= 1.5e-4 * np.max(np.abs(o)), pos      # as in test_prompt_pass_heights_fp32_cache
