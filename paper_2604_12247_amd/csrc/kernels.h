@@ -207,7 +207,8 @@ int prefill_attention_block_queries(int32_t n_heads, int32_t head_dim, int32_t M
 // that the passes' thread blocks meet on the same weights in the caches.  Activations
 // come as bf16 planes xs [2][plane_rows][K] (high parts, then low parts; row r of pass p
 // is row p * pass_rows + r); the product is left as k-split partial sums
-// part [n_pass][S][rows / 16][pass_rows / 16][64 lanes][4] for the epilogue that follows (16 x 16 tiles as the matrix cores leave them).
+// part [n_pass][S][rows / 16][pass_rows / 16][256] for the epilogue that follows (tiles of 16 weight rows and 16 rows, in the order that
+// piece_offset gives).
 #define SB_PREFILL_PASSES 16
 struct GemmArgs {
     const void* Wp;      // packed weights [rows][K]

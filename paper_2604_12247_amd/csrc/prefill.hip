@@ -265,7 +265,7 @@ struct GemmStage<CT, true> {
     }
 };
 
-// Four outputs silu(g inv) * (u inv) as their two bf16 parts, {high, low} of two neighbours each.  The low part is what the unrounded product has
+// Four outputs silu(g inv) (u inv) as their two bf16 parts, {high, low} of two neighbours each.  The low part is what the unrounded product has
 // beyond the high one, spelled out: left to the compiler it is that only where the product is at hand, and a row's bits would depend on the form.
 __device__ __forceinline__ uint4 silu_parts4(f32x4 g, f32x4 u, float inv) {
     uint32_t h[4], l[4];
@@ -282,14 +282,16 @@ __device__ __forceinline__ void store_parts4(uint16_t* xs, int ld, int lo_rows, 
     *reinterpret_cast<uint2*>(xs + (size_t)(lo_rows + m) * ld + n) = make_uint2(p.z, p.w);
 }
 
-// Where columns 4 quad .. 4 quad + 3 of a row lie in a piece whose first row is followed by `live` - 1 live ones (in floats).
-__device__ __forceinline__ int piece_offset(int row, int quad, int live) { return live < 16 ? row * 16 + quad * 4 : (quad * 16 + row) * 4; }
+// Where columns 4 quad .. 4 quad + 3 of a row lie in a piece (in floats): row by row, or as the registers hold it.
+__device__ __forceinline__ int piece_offset(int row, int quad, bool by_row) { return by_row ? row * 16 + quad * 4 : (quad * 16 + row) * 4; }
 
 // Partial sum of row block b, or the finished tail where the row block's whole k range was this thread
 // block's; then zero for the next row block.  C layout: register r of lane l is weight row 4 (l / 16) + r
-// of the tile, activation row l % 16.  A partial sum is left as the registers hold it, 1 KB per weight tile and column tile, lane l's four
-// values at 16 l: as rows of the result, 64 bytes of each of 16 rows per store, the launches took 4 to 6 % longer
-// ([22016 x 4096] at 512 rows 154 us, now 144; without any partial sums 132).  Of a column tile that is not full only the live rows are left, 64
+// of the tile, activation row l % 16.  A partial sum is left in 1 KB pieces, one per weight tile and column tile: of several passes as the registers
+// hold it, lane l's four values at 16 l (as rows of the result, 64 bytes of each of 16 rows per store, the launches took 4 to 6 % longer:
+// [22016 x 4096] at 512 rows 154 us, now 144; without any partial sums 132); of a single pass row by row, so that four rows of
+// it are 256 bytes in one place for the epilogue (13B shape, three layers at 45 / 64 rows 596 / 641 us as the registers hold it, 588 / 628 so;
+// at 200 / 512 rows, two and four passes, 1078 / 1985 and 1089 / 1990).  Of a column tile that is not full only the live rows are left, 64
 // neighbouring bytes each ([28672 x 4096] at 17 rows 42.6 us, with all 32 rows 44.9, with the live lanes at 16 l 43.8).
 template <int RT, int CT, bool SWI>
 __device__ __forceinline__ void gemm_flush(f32x4 (&acc)[RT][CT], const GemmArgs& a, const GemmCtx& c, int b, int q,
@@ -338,7 +340,7 @@ __device__ __forceinline__ void gemm_flush(f32x4 (&acc)[RT][CT], const GemmArgs&
 #pragma unroll
             for (int ct = 0; ct < CT; ++ct)
                 if (ct * 16 + li < c.Mp)
-                    *reinterpret_cast<f32x4*>(p + ((size_t)tile * CT + ct) * 256 + piece_offset(li, lane >> 4, c.Mp - ct * 16)) = acc[t][ct];
+                    *reinterpret_cast<f32x4*>(p + ((size_t)tile * CT + ct) * 256 + piece_offset(li, lane >> 4, a.n_pass == 1 || c.Mp - ct * 16 < 16)) = acc[t][ct];
         }
     }
 #pragma unroll
@@ -607,18 +609,18 @@ __device__ __forceinline__ void sum_splits(f32x4 (&v)[TN], const float* p, size_
             for (int t = 0; t < TN; ++t) v[t] += x[i][t];
     }
 }
-// grid (ceil(N / (64 TN)), column tiles of all passes), 256 threads: a block takes 16 rows and 64 TN columns.  The sums are read as the
-// GEMM left them, a 1 KB piece per load, a wave TN weight tiles, and turned in LDS: then 16 TN lanes have a row's neighbouring
-// columns, and what is loaded and stored is whole cache lines (1999 rows, N = 6144: launch and GEMM 179 -> 169 us, of which 24 -> 20 here, with
-// rows of float4 read from row-major partial sums before).
-// The residual takes 256 columns, so that a wave has those of one partial sum of squares; FEW: four rows of them, a wave four weight tiles.
-// A row's scale is the same in all forms: its partial sums of squares are added in index order.
-template <int EPI, int TN, bool FEW>
+// grid (ceil(N / 256), column tiles of all passes, of FEW quarters of them), 256 threads: a block takes 256 columns of 16 rows, or, FEW, of four, a
+// wave four weight tiles of them.  The sums are read as the GEMM left them, a 1 KB piece per load (FEW: 256 bytes of each of four), and what is
+// loaded and stored besides is whole cache lines: 16 rows are turned in LDS so that a wave has a row's 256 columns, of
+// four rows a wave has 64 neighbouring columns each (1999 rows, N = 6144: launch and GEMM 179 -> 169 us, of which 24 -> 20 here, with rows
+// of float4 read from row-major partial sums before).  The residual turns four rows as well: its sums of squares are per 256 columns.
+// A row's scale is the same in both forms: its partial sums of squares are added in index order.
+template <int EPI, bool FEW>
 __global__ __launch_bounds__(256) void prefill_epilogue_kernel(GemmEpiArgs a, GemmSplitMap mp) {
-    static_assert(EPI == EPI_RESID ? TN == (FEW ? 1 : 4) : !FEW, "a residual's block has 256 columns");
-    constexpr int ROWS = FEW ? 4 : 16, WT = FEW ? 4 : TN;               // rows of a block, weight tiles of a wave
-    constexpr int COLS = 64 * WT, LD = COLS + 4, U = TN == 1 ? 8 : 2;   // (LDS rows four banks apart)
-    __shared__ __attribute__((aligned(16))) float turn[ROWS * LD];
+    constexpr int ROWS = FEW ? 4 : 16, TN = FEW ? 1 : 4;   // rows of a block, weight tiles of a lane
+    constexpr int LD = 260, U = FEW ? 8 : 2;               // (LDS rows four banks apart)
+    constexpr bool TURN = !FEW || EPI == EPI_RESID;
+    __shared__ __attribute__((aligned(16))) float turn[TURN ? ROWS * LD : 1];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int CT = mp.pass_rows / 16, tile = FEW ? blockIdx.y >> 2 : blockIdx.y, pass = tile / CT, ct = tile - pass * CT;
     const int r1 = FEW ? (blockIdx.y & 3) * 4 : 0;  // the block's first row in the column tile
@@ -626,9 +628,10 @@ __global__ __launch_bounds__(256) void prefill_epilogue_kernel(GemmEpiArgs a, Ge
     const int live = a.M - m0, rows = live - r1;    // live rows from there (a pass before the last is full)
     if (rows <= 0) return;
     const bool fused = (EPI == EPI_SWIGLU || EPI == EPI_STORE) && a.fused;
-    const int nb0 = blockIdx.x * COLS, nw = nb0 + wave * WT * 16;   // the block's first column, this wave's (its tiles lie in one row block)
+    const int nb0 = blockIdx.x * 256, nw = nb0 + wave * 64;   // the block's first column, this wave's (its tiles lie in one row block)
     // this lane's row of the block, quad of columns and (FEW: a lane has one of the wave's tiles) first column
-    const int li = lane & (ROWS - 1), lq = (FEW ? lane >> 2 : lane >> 4) & 3, nt = FEW ? nw + (lane >> 4) * 16 : nw;
+    const bool by_row = a.n_pass == 1;              // (a lane's place in a full piece follows the piece's order)
+    const int li = (by_row ? lane >> 2 : lane) & (ROWS - 1), lq = (by_row ? lane : FEW ? lane >> 2 : lane >> 4) & 3, nt = FEW ? nw + (lane >> 4) * 16 : nw;
     const bool skip = nt >= a.N || (fused && splits_of(mp, nw) == 1);   // (past the end, or finished by the GEMM)
     // ([28672 x 4096] at 1999 rows, where the GEMM finishes six row blocks in seven, took 46 us with every wave adding up its rows' sums
     // of squares first, 29 without)
@@ -640,7 +643,7 @@ __global__ __launch_bounds__(256) void prefill_epilogue_kernel(GemmEpiArgs a, Ge
     f32x4 v[TN], u[TN];
     if (!skip && li < rows) {
         const size_t plane = (size_t)mp.pass_rows * a.rows, tstride = (size_t)CT * 256;
-        const float* const p0 = a.part + (size_t)pass * a.S * plane + piece_offset(r1 + li, lq, live);
+        const float* const p0 = a.part + (size_t)pass * a.S * plane + piece_offset(r1 + li, lq, by_row || live < 16);
         const int sp = splits_of(mp, nw);
         const bool full = nt + TN * 16 <= a.N;
         const auto sum = [&](f32x4 (&x)[TN], int c0, int splits) {
@@ -657,7 +660,7 @@ __global__ __launch_bounds__(256) void prefill_epilogue_kernel(GemmEpiArgs a, Ge
                     }
         };
         // (a row block holds gate and up tiles side by side)
-        if constexpr (EPI == EPI_SWIGLU && TN == 1) {
+        if constexpr (EPI == EPI_SWIGLU && FEW) {
             f32x4 x[2];
             sum_splits<2, 4>(x, p0 + ((size_t)(nt / 16) * CT + ct) * 256, (size_t)(a.N / 16) * CT * 256, plane, sp);
             v[0] = x[0];
@@ -669,9 +672,9 @@ __global__ __launch_bounds__(256) void prefill_epilogue_kernel(GemmEpiArgs a, Ge
     }
     float inv = 1.0f;
     if (a.ssq_in) inv = 1.0f / sqrtf(ss.sum(ssp, a.ssq_nb) / (float)a.K + a.eps);
-    if constexpr (TN == 1 && EPI != EPI_RESID) {   // (as the registers hold them: a short launch gains more by a barrier less)
+    if constexpr (!TURN) {
         if (skip || li >= rows) return;
-        const int m = m0 + li, n = nt + lq * 4;
+        const int m = m0 + r1 + li, n = nt + lq * 4;
         if (EPI == EPI_SWIGLU)
             store_parts4(a.ys, a.N, a.plane_rows, m, n, silu_parts4(v[0], u[0], inv));
         else
@@ -725,11 +728,10 @@ __global__ __launch_bounds__(256) void prefill_epilogue_kernel(GemmEpiArgs a, Ge
         }
     }
 }
-template <int EPI, int TN, bool FEW = false>
+template <int EPI, bool FEW>
 static void launch_epilogue_t(const GemmEpiArgs& a, const GemmSplitMap& mp, hipStream_t st) {
-    constexpr int COLS = FEW ? 256 : 64 * TN;
-    const dim3 grid((a.N + COLS - 1) / COLS, a.n_pass * (mp.pass_rows / 16) * (FEW ? 4 : 1));
-    prefill_epilogue_kernel<EPI, TN, FEW><<<grid, 256, 0, st>>>(a, mp);
+    const dim3 grid((a.N + 255) / 256, a.n_pass * (mp.pass_rows / 16) * (FEW ? 4 : 1));
+    prefill_epilogue_kernel<EPI, FEW><<<grid, 256, 0, st>>>(a, mp);
 }
 
 hipError_t launch_prefill_epilogue(const GemmEpiArgs& a, hipStream_t st) {
@@ -744,16 +746,17 @@ hipError_t launch_prefill_epilogue(const GemmEpiArgs& a, hipStream_t st) {
     const GemmSplitMap mp{a.epi == EPI_SWIGLU ? pl.block_rows / 2 : pl.block_rows, a.K >> 7, pl.q,
                           gemm_pass_rows(a.M, a.n_pass)};
     if (a.epi != EPI_STORE && a.epi != EPI_RESID && a.epi != EPI_SWIGLU) return hipErrorInvalidValue;
-    // A wave with four weight tiles stores whole rows of 1 KB; with one there are four times the blocks, which a launch of few
-    // needs. GEMM and epilogue, four / one, us: STORE [12288 x 4096] at 512 rows (1536 blocks) 100.4 / 104.5, 128 rows
-    // (384) 44.1 / 44.3, [15360 x 5120] at 45 rows (180) 38.1 / 36.9; SwiGLU [22016 x 4096] at 512 rows (1376) 163.5 / 164.7, [27648 x 5120] at 1000 rows 436 / 448, at 128
-    // rows (432) 90.0 / 89.5, 45 rows (162) 62.8 / 61.8. The residual's blocks have 256 columns either way, of 16 rows or of four: three
-    // layers, whole prompt, 16 / four, us: 8B shape at 17 / 64 / 128 / 200 rows (32 to 208 blocks) 555 / 536, 656 / 643, 798 / 784, 923 / 917, 13B at 200 / 300 / 512
-    // (260 to 640) 1110 / 1119, 2032 / 2047, 1992 / 2018, 7B at 1999 (2000) 4257 / 4298.
+    // Blocks of 16 rows read whole pieces and have four tiles' loads on their way in a lane; of four rows there are four times as many, which a
+    // launch of few needs.  Several passes leave pieces as the registers hold them, of which four rows are half lines, so the line is lower
+    // there.  Four rows / 16, us: GEMM and epilogue [4096 x 4096] at 45 rows (48 blocks of 16) 13.8 / 15.2, [5120 x 13824] 31.2 / 33.4, [22016 x 4096] at
+    // 64 rows (344) 44.4 / 45.6, [27648 x 5120] (432) 63.5 / 63.9, [32000 x 1024] at 64 / 128 rows (500 / 1000) 25.2 / 24.4, 36.2 / 33.8; three layers, whole prompt, 8B
+    // shape at 17 / 45 / 90 rows (residual 32 / 48 / 96 blocks) 541 / 566, 597 / 617, 724 / 735, 200 (208) 919 / 921, 13B at 200 / 300 / 512 (260 / 420 / 640) 1101 / 1084,
+    // 2067 / 2052, 2091 / 2006.
     const long wide_blocks = (long)((a.N + 255) / 256) * a.n_pass * (mp.pass_rows / 16);
-    if (a.epi == EPI_RESID) wide_blocks >= 256 ? launch_epilogue_t<EPI_RESID, 4>(a, mp, st) : launch_epilogue_t<EPI_RESID, 1, true>(a, mp, st);
-    else if (a.epi == EPI_STORE) wide_blocks >= 512 ? launch_epilogue_t<EPI_STORE, 4>(a, mp, st) : launch_epilogue_t<EPI_STORE, 1>(a, mp, st);
-    else wide_blocks >= 512 ? launch_epilogue_t<EPI_SWIGLU, 4>(a, mp, st) : launch_epilogue_t<EPI_SWIGLU, 1>(a, mp, st);
+    const bool few = wide_blocks < (a.n_pass == 1 ? 512 : 256);
+    if (a.epi == EPI_RESID) few ? launch_epilogue_t<EPI_RESID, true>(a, mp, st) : launch_epilogue_t<EPI_RESID, false>(a, mp, st);
+    else if (a.epi == EPI_STORE) few ? launch_epilogue_t<EPI_STORE, true>(a, mp, st) : launch_epilogue_t<EPI_STORE, false>(a, mp, st);
+    else few ? launch_epilogue_t<EPI_SWIGLU, true>(a, mp, st) : launch_epilogue_t<EPI_SWIGLU, false>(a, mp, st);
     return hipGetLastError();
 }
 

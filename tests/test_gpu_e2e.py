@@ -685,7 +685,7 @@ def _prompt_rows(gm, layer, prompt):
     return np.stack([np.stack(s.debug_kv(layer, p)) for p in range(len(prompt))], 1)
 
 
-# epilogues of one and of four weight tiles per wave (from 337 rows on at this width), one to three passes
+# epilogues of four and of 16 rows per block (161 rows and more at this width), one to three passes
 @pytest.mark.parametrize("n_prompt", [45, 150, 337])
 def test_prompt_row_scales_order_of_additions(sb, n_prompt):
     """The scales of a prompt's rows, bit for bit: a partial sum of squares per 256 columns, by the fixed tree of the 32 lanes (embedding:
@@ -725,7 +725,7 @@ def test_prompt_row_scales_order_of_additions(sb, n_prompt):
 
 
 # prompts of as many passes on either side of the line between the epilogue's forms
-@pytest.mark.parametrize("n_heads,n_kv_heads,short,long", [(32, 8, 336, 337), (32, 32, 150, 170)])
+@pytest.mark.parametrize("n_heads,n_kv_heads,short,long", [(32, 8, 336, 337), (32, 32, 150, 170), (32, 8, 160, 161)])
 def test_prompt_row_does_not_depend_on_the_rows_after_it(sb, n_heads, n_kv_heads, short, long):
     shape = si.tiny_shape(n_layers=1, n_exit_heads=1, weight_dtype=si.configs.BF16, d_model=4096, n_heads=n_heads, n_kv_heads=n_kv_heads,
                           head_dim=128, d_ffn=256)
@@ -734,9 +734,9 @@ def test_prompt_row_does_not_depend_on_the_rows_after_it(sb, n_heads, n_kv_heads
     assert np.array_equal(_prompt_rows(gm, 0, prompt[:short]), _prompt_rows(gm, 0, prompt)[:, :short])
 
 
-# gate / up of as many passes with one and with two pairs of weight tiles per wave of the epilogue; 33152: blocks of it with a row block that
-# the GEMM has finished and one that it has not
-@pytest.mark.parametrize("d_ffn,short,long", [(11008, 160, 161), (33152, 48, 60)])
+# gate / up of as many passes on either side of the line between the epilogue's forms; 33152: blocks of it with a row block that the GEMM
+# has finished and one that it has not
+@pytest.mark.parametrize("d_ffn,short,long", [(11008, 160, 161), (5632, 160, 161), (33152, 48, 60)])
 def test_prompt_gate_up_forms_give_the_same_rows(sb, d_ffn, short, long):
     """Keys and values of the second layer: the same bits for a common prefix, and the oracle's values."""
     shape = si.tiny_shape(n_layers=2, n_exit_heads=1, weight_dtype=si.configs.BF16, d_model=512, n_heads=4, n_kv_heads=4, head_dim=128, d_ffn=d_ffn)
