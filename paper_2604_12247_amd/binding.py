@@ -501,13 +501,16 @@ def op_gemm(Wp, x, scratch=None):
     return y
 
 
-def _unused_scratch(torch, x, y):
-    """The scratch area of a decode projection of x into y.  The library writes to it only where y lies over x, which a
-    newly made y does not: y itself stands in for it (an allocation less).  Rows that are not dense get an area, as the
-    range that the library takes them to fill is not theirs alone."""
-    if x.is_contiguous():
-        return y
-    return torch.empty(max(lib().sb_op_gemv_scratch_bytes(x.shape[0], x.shape[1]), 256), dtype=torch.uint8, device=x.device)
+def _unused_scratch(torch, x, K, y):
+    """The scratch area of a decode projection of x [M, K] into y.  The library writes to it only where y lies over the 4 M K bytes that it
+    takes x to fill, which a newly made y does not if they are x's own: y itself stands in for it (an allocation less).  Rows that are not
+    dense get an area, as the range is not theirs alone; an x of fewer bytes is refused."""
+    M = x.shape[0]
+    if not x.is_contiguous():
+        return torch.empty(max(lib().sb_op_gemv_scratch_bytes(M, K), 256), dtype=torch.uint8, device=x.device)
+    if x.numel() * x.element_size() < 4 * M * K:
+        raise ValueError(f"expected float32 rows of {K}, not {tuple(x.shape)} of {x.dtype}")
+    return y
 
 
 def op_gemv(W, x, kernel: int = PROJ_VALU):
@@ -517,7 +520,7 @@ def op_gemv(W, x, kernel: int = PROJ_VALU):
     N, K = W.shape
     M = x.shape[0]
     y = torch.empty((M, N), dtype=torch.float32, device=x.device)
-    scratch = _unused_scratch(torch, x, y)
+    scratch = _unused_scratch(torch, x, K, y)
     check(lib().sb_op_gemv(W.data_ptr(), _wdtype(W), N, K, x.data_ptr(), y.data_ptr(), M, kernel,
                            scratch.data_ptr(), _stream_ptr(torch, x)))
     return y
@@ -530,7 +533,7 @@ def op_gate_up(W, x, kernel: int = PROJ_VALU):
     N, K = W.shape[0] // 2, W.shape[1]
     M = x.shape[0]
     u = torch.empty((M, N), dtype=torch.float32, device=x.device)
-    scratch = _unused_scratch(torch, x, u)
+    scratch = _unused_scratch(torch, x, K, u)
     check(lib().sb_op_gate_up(W.data_ptr(), _wdtype(W), N, K, x.data_ptr(), u.data_ptr(), M, kernel,
                               scratch.data_ptr(), _stream_ptr(torch, x)))
     return u

@@ -161,3 +161,13 @@ def test_single_kernel_calls_refuse_host_tensors():
                  lambda: sb.op_rmsnorm(x, x[0], 1e-6), lambda: sb.op_copy(x, x.clone())):
         with pytest.raises(ValueError):
             call()
+
+
+def test_projections_refuse_rows_that_do_not_fill_their_range():
+    """The output stands in for the scratch area, so the range that the library takes x to fill has to be x's own."""
+    import torch
+    W = torch.zeros(32, 256, dtype=torch.bfloat16)
+    for x in (torch.zeros(2, 256, dtype=torch.bfloat16), torch.zeros(2, 128), torch.zeros(2, 256, dtype=torch.float16)):
+        for call in (sb.op_gemv, sb.op_gate_up):
+            with pytest.raises(ValueError, match="expected float32 rows of 256"):
+                call(W, x, sb.PROJ_MFMA)
