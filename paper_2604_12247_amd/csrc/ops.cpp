@@ -96,8 +96,10 @@ int32_t sb_op_gemm(const void* Wp, int32_t N, int32_t K, const float* x, float* 
     uint16_t* xs = (uint16_t*)scratch;
     float* part = (float*)((char*)scratch + align_up((size_t)2 * SB_PREFILL_ROWS * K * 2, 256));
     GemmArgs g{};
-    // the GEMM reads float rows by 16-byte loads at 32-bit offsets; any others are split into their two parts first
-    if (((uintptr_t)x & 15) || (size_t)M * K >= 1u << 30) {
+    // the GEMM reads float rows by 16-byte loads at 32-bit offsets, and its blocks leave partial sums while others read; rows that
+    // do not suit that are split into their two parts first
+    if (((uintptr_t)x & 15) || (size_t)M * K >= 1u << 30 ||
+        overlaps(x, (size_t)M * K * 4, part, (size_t)gemm_splits(N, K, 1) * SB_PREFILL_ROWS * N * 4)) {
         HIP_TRY(launch_prefill_split(x, xs, SB_PREFILL_ROWS, M, K, st));
         g.xs = xs;
     } else {

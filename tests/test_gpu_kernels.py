@@ -182,6 +182,23 @@ def test_prompt_pass_gemm_unaligned_rows(T, N, K, M):
     assert T.equal(sb.op_gemm(Wp, x), sb.op_gemm(Wp, z))
 
 
+# rows that the caller left where the partial sums come: they are read whole before the first is written (65536: thread blocks of two row
+# blocks, of which the first's sums are stored while all blocks have half the rows' products before them)
+@pytest.mark.parametrize("N,K,M", [(4096, 4096, 100), (65536, 512, 128)])
+def test_prompt_pass_gemm_rows_in_the_scratch_area(T, N, K, M):
+    import paper_2604_12247_amd as sb
+    g = T.Generator(device="cuda")
+    g.manual_seed(N + K + M)
+    Wp = sb.op_repack((T.randn(N, K, generator=g, device="cuda") * 0.02).to(T.bfloat16))
+    x = T.randn(M, K, generator=g, device="cuda")
+    y = sb.op_gemm(Wp, x)
+    planes = 2 * 128 * K * 2                                    # the rows' two parts come first, then the partial sums
+    scratch = T.empty(sb.lib().sb_op_gemm_scratch_bytes(N, K), dtype=T.uint8, device="cuda")
+    inside = scratch[planes:planes + 4 * M * K].view(T.float32).view(M, K)
+    inside.copy_(x)
+    assert T.equal(sb.op_gemm(Wp, inside, scratch), y)
+
+
 # a single pass whose thread blocks own 9, 10, 15, 16 and 17 k blocks: odd numbers of weight blocks are requested whole
 @pytest.mark.parametrize("N,K", [(17088, 4096), (7184, 10368), (20480, 6144), (20480, 6528), (20480, 6784)])
 @pytest.mark.parametrize("M", [9, 40, 128])
