@@ -28,29 +28,13 @@ namespace sb {
 // host in double and held in float) and rounds keys and values from qkv exactly as they are
 // stored, and the block of query group 0 also writes them into the cache (KV append).  A row's result depends on its own
 // position and keys only.
-template <typename KVT> struct KvVec;
-template <> struct KvVec<uint16_t> {
-    static constexpr int EPV = 8;
-    static __device__ __forceinline__ void unpack(uint4 v, float* f) {
-        f[0] = __uint_as_float(v.x << 16); f[1] = __uint_as_float(v.x & 0xffff0000u);
-        f[2] = __uint_as_float(v.y << 16); f[3] = __uint_as_float(v.y & 0xffff0000u);
-        f[4] = __uint_as_float(v.z << 16); f[5] = __uint_as_float(v.z & 0xffff0000u);
-        f[6] = __uint_as_float(v.w << 16); f[7] = __uint_as_float(v.w & 0xffff0000u);
-    }
-    static __device__ __forceinline__ uint4 pack(const float* f) {
-        return make_uint4((uint32_t)f2bf(f[0]) | ((uint32_t)f2bf(f[1]) << 16), (uint32_t)f2bf(f[2]) | ((uint32_t)f2bf(f[3]) << 16),
-                          (uint32_t)f2bf(f[4]) | ((uint32_t)f2bf(f[5]) << 16), (uint32_t)f2bf(f[6]) | ((uint32_t)f2bf(f[7]) << 16));
-    }
-};
-template <> struct KvVec<float> {
-    static constexpr int EPV = 4;
-    static __device__ __forceinline__ void unpack(uint4 v, float* f) {
-        f[0] = __uint_as_float(v.x); f[1] = __uint_as_float(v.y); f[2] = __uint_as_float(v.z); f[3] = __uint_as_float(v.w);
-    }
-    static __device__ __forceinline__ uint4 pack(const float* f) {
-        return make_uint4(__float_as_uint(f[0]), __float_as_uint(f[1]), __float_as_uint(f[2]), __float_as_uint(f[3]));
-    }
-};
+// Four values of an fp32 cache.
+__device__ __forceinline__ void unpack4(uint4 v, float* f) {
+    f[0] = __uint_as_float(v.x); f[1] = __uint_as_float(v.y); f[2] = __uint_as_float(v.z); f[3] = __uint_as_float(v.w);
+}
+__device__ __forceinline__ uint4 pack4(const float* f) {
+    return make_uint4(__float_as_uint(f[0]), __float_as_uint(f[1]), __float_as_uint(f[2]), __float_as_uint(f[3]));
+}
 
 // A value as the cache holds it.
 template <typename KVT>
@@ -68,11 +52,6 @@ __device__ __forceinline__ float rope_hi(float x, float y, float c, float sn) { 
 __device__ __forceinline__ void attn_finish(const AttnArgs& a, int r, int col, int ld, float v) {
     if (a.out) a.out[(size_t)r * ld + col] = v;
     if (a.out_split) split_store_rows(a.out_split, ld, a.split_rows, r, col, v);
-}
-
-// (by value: `c ? a : b` on two arrays' elements is a choice of addresses, which would keep the arrays in memory)
-__device__ __forceinline__ uint4 pick(bool c, uint4 a, uint4 b) {
-    return make_uint4(c ? a.x : b.x, c ? a.y : b.y, c ? a.z : b.z, c ? a.w : b.w);
 }
 
 // N neighbouring floats: one load where the operands are 16-byte aligned (VEC), else N.
@@ -191,10 +170,10 @@ struct NewRows {
 // each load), and a query's dims come out of LDS once for two keys.  Before and after: 4 heads x 64 behind 60 keys, one / four / eight rows
 // 5.0 / 7.3 / 10.8 -> 3.7 / 4.7 / 6.5 us; 32 heads x 128, one row behind 300 / 2000 / 9000 keys 8.9 / 16.8 / 62.8 -> 8.1 / 16.3 / 62.5, six behind 2000
 // 20.3 -> 19.3; 128 rows of 32 heads x 128 behind none / 4000 31 / 280 -> 20.5 / 259.
-template <typename KVT, int HD, bool MANY, bool VEC>
+template <int HD, bool MANY, bool VEC>
 __global__ __launch_bounds__(256, 4) void attn_kernel(AttnArgs a) {
-    constexpr int CH = (HD * sizeof(KVT) <= 256) ? 128 : 64;  // keys per chunk
-    constexpr int EPV = KvVec<KVT>::EPV;                      // elements per 16 bytes
+    constexpr int CH = HD <= 64 ? 128 : 64;                   // keys per chunk
+    constexpr int EPV = 4;                                    // elements per 16 bytes
     constexpr int QG = 16;                                    // queries per block
     constexpr int HALF = HD / 2;
     // scores mapping: a wave takes CH / 4 keys, a page at a time; four lanes per key, each with every fourth piece of 16 bytes
@@ -207,14 +186,14 @@ __global__ __launch_bounds__(256, 4) void attn_kernel(AttnArgs a) {
     constexpr int KPT = CH / KS;                              // keys per value thread
     // (head_dim 128: the values are requested behind the keys' first use.  32 heads, one row behind 300 / 2000 / 9000 keys 8.0 / 16.2 / 62.5 us, together 7.8 /
     // 16.9 / 62.3)
-    constexpr bool LATE_V = HD * sizeof(KVT) > 256;
+    constexpr bool LATE_V = HD > 64;
     static_assert(KT >= 1 && NKV % 2 == 0, "a wave's keys are whole pages; a lane has both parts of its rotary pairs");
     static_assert(DGW >= 1 && KS * KPT == CH && KPT % 4 == 0 && SB_KV_BLOCK % KS == 0, "value mapping: a load's keys lie in one page");
     __shared__ __attribute__((aligned(16))) float qs[QG * HD];
     __shared__ __attribute__((aligned(16))) float sp[QG * CH];  // scores by key, then probabilities by key slot
     __shared__ float s_m[QG], s_l[QG];
     constexpr int NR = MANY ? 1 : SB_MAX_W;
-    __shared__ __attribute__((aligned(16))) KVT nk_s[NR * HD], nv_s[NR * HD];   // (!MANY) the new rows' keys and values
+    __shared__ __attribute__((aligned(16))) float nk_s[NR * HD], nv_s[NR * HD];   // (!MANY) the new rows' keys and values
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // (the chunk with the new rows, the longest to prepare, first)
@@ -225,8 +204,8 @@ __global__ __launch_bounds__(256, 4) void attn_kernel(AttnArgs a) {
     const int key0 = chunk * CH, n_total = a.pos0 + a.M;
     const float scale = 1.0f / sqrtf((float)HD);
     const size_t page_elems = (size_t)Hkv * SB_KV_BLOCK * HD;
-    KVT* const kbase = reinterpret_cast<KVT*>(a.kv.pool) + (size_t)(a.layer * 2 + 0) * a.kv.n_pages * page_elems;
-    KVT* const vbase = reinterpret_cast<KVT*>(a.kv.pool) + (size_t)(a.layer * 2 + 1) * a.kv.n_pages * page_elems;
+    float* const kbase = reinterpret_cast<float*>(a.kv.pool) + (size_t)(a.layer * 2 + 0) * a.kv.n_pages * page_elems;
+    float* const vbase = reinterpret_cast<float*>(a.kv.pool) + (size_t)(a.layer * 2 + 1) * a.kv.n_pages * page_elems;
 
     // ---- page-table entries, all in flight at once; a key past the end takes the last page (what its slot holds is not used)
     const bool has_new = key0 + CH > a.pos0;
@@ -276,7 +255,7 @@ __global__ __launch_bounds__(256, 4) void attn_kernel(AttnArgs a) {
         store_near(qs + qr.query() * HD + qr.dim(), lo);
         store_near(qs + qr.query() * HD + qr.dim() + HALF, hi);
     }
-    if (!MANY && has_new) nr.template store<KVT, HD, false>(a, nk_s, nv_s);
+    if (!MANY && has_new) nr.template store<float, HD, false>(a, nk_s, nv_s);
     __syncthreads();
     if (LATE_V) {
         __builtin_amdgcn_sched_barrier(0);
@@ -303,8 +282,8 @@ __global__ __launch_bounds__(256, 4) void attn_kernel(AttnArgs a) {
                         lo[e] = rope_lo(x[e], y[e], c[e], sn[e]);
                         hi[e] = rope_hi(x[e], y[e], c[e], sn[e]);
                     }
-                    kreg[t][i] = KvVec<KVT>::pack(lo);
-                    kreg[t][i + NKV / 2] = KvVec<KVT>::pack(hi);
+                    kreg[t][i] = pack4(lo);
+                    kreg[t][i + NKV / 2] = pack4(hi);
                 }
             } else {
 #pragma unroll
@@ -327,7 +306,7 @@ __global__ __launch_bounds__(256, 4) void attn_kernel(AttnArgs a) {
                     if constexpr (MANY) {
                         float f[EPV];
                         load_near<EPV, VEC>(a.q + (size_t)(key - a.pos0) * a.qkv_rows + (size_t)(Hq + Hkv + g) * HD + vd0, f);
-                        vreg[i] = KvVec<KVT>::pack(f);
+                        vreg[i] = pack4(f);
                     } else {
                         vreg[i] = *reinterpret_cast<const uint4*>(&nv_s[(key - a.pos0) * HD + vd0]);
                     }
@@ -344,7 +323,7 @@ __global__ __launch_bounds__(256, 4) void attn_kernel(AttnArgs a) {
 #pragma unroll
         for (int t = 0; t < KT; ++t)
 #pragma unroll
-            for (int i = 0; i < NKV; ++i) KvVec<KVT>::unpack(kreg[t][i], kf[t][i]);
+            for (int i = 0; i < NKV; ++i) unpack4(kreg[t][i], kf[t][i]);
         for (int qi = 0; qi < nq; ++qi) {
             float4 qv[NKV * EPV / 4];   // (all requested before the first is used: one wait, not one per piece)
 #pragma unroll
@@ -407,7 +386,7 @@ __global__ __launch_bounds__(256, 4) void attn_kernel(AttnArgs a) {
     {
         float vf[KPT][EPV];
 #pragma unroll
-        for (int i = 0; i < KPT; ++i) KvVec<KVT>::unpack(vreg[i], vf[i]);
+        for (int i = 0; i < KPT; ++i) unpack4(vreg[i], vf[i]);
         for (int q1 = 0; q1 < nq; q1 += KS) {
             float res[EPV];
 #pragma unroll
@@ -466,8 +445,8 @@ __global__ __launch_bounds__(256, 4) void attn_kernel(AttnArgs a) {
 //            and a wave's loads cover whole pages.  A wave owns HD/4 output dims.
 // Every output row of an MFMA depends on its own operand row only, so a query's
 // partial does not depend on which other queries share the block.
-// What bounds it: the chain page table -> operands -> scores -> soft-max -> values of a block, of which three per CU cover for each
-// other.  The chunk with the new rows is the longest: it is started first, and its new keys and values come with the other operands
+// What bounds it: the chain page table -> operands -> scores -> soft-max -> values of a block, of which four per CU cover for each
+// other (126 registers at head_dim 128, 98 at 64, 26 and 22 KB of LDS).  The chunk with the new rows is the longest: it is started first, and its new keys and values come with the other operands
 // and through LDS (a load and a wait for each element, as lanes picked them from the projections, cost 3 us at six rows).
 // Both kernels in a graph of launches, 32 heads x 128, one row behind 520 / 1000 keys 8.5 / 9.4 -> 7.75 / 8.7 us, six behind 520 / 2000 / 4200 9.70 / 12.7 /
 // 20.9 -> 8.75 / 12.2 / 20.3; 32 heads over 8 x 128, one / four rows behind 700 8.55 / 9.9 -> 7.5 / 8.1; one row of 32 behind 20 keys (the first stage alone)
@@ -476,7 +455,7 @@ __global__ __launch_bounds__(256, 4) void attn_kernel(AttnArgs a) {
 // written for queries that are not there, a partial's maximum and sum stored where they are found, its address in 32 bits.  Of some
 // 8500 cycles of a block's chain (one row) the page table takes 500, the operands 3000, the new rows 1400, the queries 850, scores 500,
 // soft-max 850, values and stores 1000.
-// LDS of one block of the matrix-core attention kernels (one work item is computed at a time).
+// LDS of one block of the matrix-core attention kernels.
 template <int HD>
 struct AttnLds {
     static constexpr int CH = 128, QG = 16, QS = HD + 8, PS = CH + 8, SS = CH + 4;   // padded row strides
@@ -486,10 +465,8 @@ struct AttnLds {
     float s_l[QG];
 };
 
-// One work item of the kernel -- (kv head g, key chunk, slice zb of the query groups) -- in two
-// steps: load() requests everything the item reads from memory (the first query group with its
-// rotary factors, the chunk's K and V operands) into registers, compute() does the rest.  A block
-// that owns several items requests the next item's operands before it computes the current one.
+// A block's work -- (kv head g, key chunk, slice zb of the query groups) -- in two steps: load() requests everything that it
+// reads from memory (the first query group with its rotary factors, the chunk's K and V operands) into registers, compute() does the rest.
 template <int HD, bool VEC>
 struct AttnItem {
     static constexpr int CH = 128, QG = 16, HALF = HD / 2;
@@ -514,21 +491,10 @@ struct AttnItem {
         g = g_; chunk = chunk_; zb = zb_;
         const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
         const int li = lane & 15, lq = lane >> 4;
-        const int Hkv = a.kv.n_kv_heads, G = a.group;
-        const int nq_total = a.M * G;
-        // this block's query groups (16 queries each), handled one after the other with the
-        // chunk's K and V held in registers
-        const int n_qg = (nq_total + QG - 1) / QG;
-        const int qg_first = zb * a.qg_per_block;
-        const int qg_last = (qg_first + a.qg_per_block < n_qg) ? qg_first + a.qg_per_block : n_qg;
         const int key0 = chunk * CH, n_total = a.pos0 + a.M;
-        const float scale = 1.0f / sqrtf((float)HD);
-        const size_t page_elems = (size_t)Hkv * SB_KV_BLOCK * HD;
-        uint16_t* const kbase = reinterpret_cast<uint16_t*>(a.kv.pool) + (size_t)(a.layer * 2 + 0) * a.kv.n_pages * page_elems;
-        uint16_t* const vbase = reinterpret_cast<uint16_t*>(a.kv.pool) + (size_t)(a.layer * 2 + 1) * a.kv.n_pages * page_elems;
-        const bool has_new = key0 + CH > a.pos0;  // the chunk holds keys of the new rows
-        (void)lane; (void)wave; (void)li; (void)lq; (void)n_qg; (void)qg_first; (void)qg_last; (void)n_total; (void)scale;
-        (void)kbase; (void)vbase; (void)has_new; (void)page_elems; (void)nq_total;
+        const size_t page_elems = (size_t)a.kv.n_kv_heads * SB_KV_BLOCK * HD;
+        const uint16_t* const kbase = reinterpret_cast<const uint16_t*>(a.kv.pool) + (size_t)(a.layer * 2 + 0) * a.kv.n_pages * page_elems;
+        const uint16_t* const vbase = reinterpret_cast<const uint16_t*>(a.kv.pool) + (size_t)(a.layer * 2 + 1) * a.kv.n_pages * page_elems;
         // ---- page-table entries of the chunk, all in flight at once, through the scalar cache; a page past the end is the
         // last one (what its slots hold is masked or replaced)
         const int last_page = (n_total - 1) / SB_KV_BLOCK;
@@ -544,8 +510,8 @@ struct AttnItem {
             kpage[t] = a.kv.table[p < last_page ? p : last_page];
         }
         // ---- every other load of the item: q (+ its rotary factors) of the first group, the new rows, K, V
-        load_q(a, qg_first);
-        if (has_new) nr.load(a, g);
+        load_q(a, zb * a.qg_per_block);
+        if (key0 + CH > a.pos0) nr.load(a, g);   // (the chunk holds keys of the new rows)
         // K operands: tile t of this wave = keys key0 + wave*32 + t*16 + li (one page), dims ks*32 + lq*8 ..
     #pragma unroll
         for (int t = 0; t < 2; ++t) {
@@ -566,9 +532,7 @@ struct AttnItem {
     }
 
     __device__ __forceinline__ void compute(const AttnArgs& a, AttnLds<HD>& lds) {
-        const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-        const int li = lane & 15, lq = lane >> 4;
-        const int Hq = a.n_heads, Hkv = a.kv.n_kv_heads, G = a.group;
+        const int Hq = a.n_heads, G = a.group;
         const int nq_total = a.M * G;
         // this block's query groups (16 queries each), handled one after the other with the
         // chunk's K and V held in registers
@@ -577,12 +541,10 @@ struct AttnItem {
         const int qg_last = (qg_first + a.qg_per_block < n_qg) ? qg_first + a.qg_per_block : n_qg;
         const int key0 = chunk * CH, n_total = a.pos0 + a.M;
         const float scale = 1.0f / sqrtf((float)HD);
-        const size_t page_elems = (size_t)Hkv * SB_KV_BLOCK * HD;
+        const size_t page_elems = (size_t)a.kv.n_kv_heads * SB_KV_BLOCK * HD;
         uint16_t* const kbase = reinterpret_cast<uint16_t*>(a.kv.pool) + (size_t)(a.layer * 2 + 0) * a.kv.n_pages * page_elems;
         uint16_t* const vbase = reinterpret_cast<uint16_t*>(a.kv.pool) + (size_t)(a.layer * 2 + 1) * a.kv.n_pages * page_elems;
         const bool has_new = key0 + CH > a.pos0;  // the chunk holds keys of the new rows
-        (void)lane; (void)wave; (void)li; (void)lq; (void)n_qg; (void)qg_first; (void)qg_last; (void)n_total; (void)scale;
-        (void)kbase; (void)vbase; (void)has_new; (void)page_elems; (void)nq_total;
         uint16_t* const q_hi = lds.q_hi; uint16_t* const q_lo = lds.q_lo;
         uint16_t* const p_hi = lds.p_hi; uint16_t* const p_lo = lds.p_lo;
         float* const s_s = lds.s_s; float* const s_l = lds.s_l;
@@ -954,9 +916,9 @@ hipError_t launch_attention(const AttnArgs& a, hipStream_t st) {
             if (a.M > SB_MAX_W) return hipErrorInvalidValue;   // (more rows: launch_prefill_attention)
             e = launch(fast ? &attn_mfma_kernel<HD, true> : &attn_mfma_kernel<HD, false>, grid, 256, st, b);
         } else if (a.M > SB_MAX_W) {
-            e = launch(&attn_kernel<float, HD, true, false>, grid1, 256, st, b);
+            e = launch(&attn_kernel<HD, true, false>, grid1, 256, st, b);
         } else {
-            e = launch(fast ? &attn_kernel<float, HD, false, true> : &attn_kernel<float, HD, false, false>, grid1, 256, st, b);
+            e = launch(fast ? &attn_kernel<HD, false, true> : &attn_kernel<HD, false, false>, grid1, 256, st, b);
         }
         if (b.direct || e != hipSuccess) return e;
         return launch(a.kv.kv_dtype == SB_BF16 ? &attn_merge_kernel<HD, 128> : &attn_merge_kernel<HD, CH32>, mgrid, 256, st, a);

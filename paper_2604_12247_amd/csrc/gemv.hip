@@ -427,7 +427,7 @@ __global__ __launch_bounds__(64 * WPB) void gemv_mfma_kernel(MfmaArgs<EPI> a) {
     const int kb0 = wave;
     const int nkb = KB > wave ? (KB - wave + WPB - 1) / WPB : 0;  // k blocks of this wave
     // The rows' partial sums of squares are requested before the weights: loads come back in order, and behind them these were waited for with
-    // the ring's three blocks of every wave, 37 MB at the 7B shape's QKV, before the next was asked for ([12288 x 4096], one / six rows 18.25 / 20.3 -> 17.25 / 19.7 us,
+    // the ring's first two blocks of every wave, 25 MB at the 7B shape's QKV, before the next was asked for ([12288 x 4096], one / six rows 18.25 / 20.3 -> 17.25 / 19.7 us,
     // [22016 x 4096] gate and up 28.0 / 30.7 -> 27.6 / 30.0, [6144 x 4096] one row 11.6 -> 11.2).
     constexpr int SQ_ROWS = SB_MAX_W / WPB, SQ_U = 8;   // rows per wave; values per lane up to K = 8192
     float sq[SQ_ROWS][SQ_U];
